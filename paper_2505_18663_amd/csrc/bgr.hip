@@ -4,16 +4,33 @@
 // round, and keeps the grid with the smallest row error: either as Alg. 1 prints it (starts
 // i = 1, 2, ..., a start's result is the grid of its last round) or as a superset search (i = 0,
 // plain MinMax, is a start too and every grid evaluated competes).  Runs once per layer, off the
-// inference path; everything is fp64 so that its decisions (roundings, comparisons) match a
-// plain fp64 implementation up to summation order.
+// inference path; everything that decides is fp64, so that its decisions (roundings, comparisons)
+// match a plain fp64 implementation up to summation order.
 //
-// One workgroup per row.  The row lives in LDS as fp32; one "evaluation" of a grid
-// (Delta, z) is a pass over the row that quantizes every weight and accumulates, in fp64,
-//   e2  = sum (w - Delta (q - z))^2        the squared row error
-//   num = sum (q - z) w,  den = sum (q - z)^2,  sq = sum q
-// i.e. also the sums the NEXT refinement round needs, so the codes are never stored until
-// the best grid is known.  All threads then run the same scalar search logic on the reduced
-// sums (uniform control flow, no divergence in the barriers).
+// One workgroup per row.  A row is evaluated on several hundred grids (Delta, z), and what an evaluation needs of
+// it are only four sums over c = clamp(rint(w / Delta) + z, 0, 15), d = c - z:
+//   e2 = sum (w - Delta d)^2,  num = sum d w,  den = sum d^2,  sq = sum c.
+// c takes 16 values, and it is monotone in w: on the SORTED row an evaluation is 15 positions
+//   pos_j = #{w : rint(w / Delta) <= j - z},  j = 0 .. 14,
+// and, with P(p) the sum of the p smallest weights, Abel summation gives
+//   sq  = 15 K - sum_j pos_j
+//   den = (15 - z)^2 K - sum_j (2 (j - z) + 1) pos_j          (both exact integers)
+//   num = (15 - z) P(K) - sum_j P(pos_j)
+//   e2  = sum w^2 - 2 Delta num + Delta^2 den                 (taken from the row itself where this would cancel)
+// So the row is sorted once, its prefix sums are kept, and an evaluation costs 15 lookups instead of a pass over
+// the row with a division per weight.  A lookup is three dependent LDS reads (the cell of values the threshold falls
+// in, the block of 4 .. 16 weights there, its weights and prefix sum).  The division survives only where it decides:
+// for a float that sits on a threshold to within fp64 rounding, so every weight is classified by exactly the quotient
+// and rounding of the definition.  The starts of the search are independent of each other: 8 lanes take one start (two
+// positions per lane; with one position per lane the divisions and the square root of a round, which are the same in
+// all lanes of a start, weigh twice as much), with no barrier inside the search.
+//
+// Cost.  1536 rows of 8960 weights, 100 steps, 10 rounds: 0.14 ms; a pass over the row per evaluation, one workgroup of
+// 256 threads per row, took 8.7 ms.  Bound by latencies, not by memory (62 MB) nor by vector issue: of the 95 K clocks a
+// row is in work (two rows per compute unit) 10 K are the load, 22 K the two dealing passes with the counts between them
+// (LDS atomics and barriers), 14 K the windows, 4 K the prefix sums, 45 K the search (eleven rounds of 4 K, a chain of
+// three divisions, a square root and five LDS reads).  8 lanes per start instead of 16 took 0.06 ms off, windows in
+// place of counting every weight's rank among its cell's 0.04 ms.
 #include "dvdq_internal.h"
 
 #pragma clang fp contract(off)   // every product and sum rounded on its own, like a plain C loop
@@ -21,12 +38,31 @@
 namespace dvdq {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / 64;
-constexpr double kQmax = 15.0;   // INT4
-constexpr size_t kMaxK = 32768;  // longest row (the row is kept in LDS); the C ABI checks it
+constexpr double kQmax = 15.0;           // INT4
+constexpr int kLanes = 8;        // lanes per start of the search
+constexpr int kCellLimit = 1024; // fullest cell that is sorted in windows (see the kernel)
 
-struct Sums { double e2, num, den, sq; };
+// Sums over 8 neighbouring lanes: two quad permutes and a half-row mirror; every lane ends with the same bits.
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true); }
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)dpp_i<CTRL>((int)(uint32_t)u), hi = (uint32_t)dpp_i<CTRL>((int)(uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double sum8(double v) {
+    v += dpp_d<0xB1>(v);    // quad_perm:[1,0,3,2]
+    v += dpp_d<0x4E>(v);    // quad_perm:[2,3,0,1]
+    v += dpp_d<0x141>(v);   // row_half_mirror
+    return v;
+}
+__device__ __forceinline__ int sum8(int v) {
+    v += dpp_i<0xB1>(v);
+    v += dpp_i<0x4E>(v);
+    v += dpp_i<0x141>(v);
+    return v;
+}
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -34,135 +70,479 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// sum of `v` over the workgroup, returned to every thread; `slots` holds kWaves doubles
-__device__ __forceinline__ double block_sum(double v, double *slots) {
-    v = wave_sum(v);
-    __syncthreads();   // the previous use of the slots is over
-    if ((threadIdx.x & 63) == 0) slots[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i) s += slots[i];
-    return s;
-}
-
 __device__ __forceinline__ double clamp_d(double v, double lo, double hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// quantize the row on the grid (delta, z) and reduce the four sums
-__device__ __forceinline__ Sums evaluate(const float *row, int K, double delta, double z, double *slots) {
-    Sums s = {0.0, 0.0, 0.0, 0.0};
-    for (int k = threadIdx.x; k < K; k += kThreads) {
-        const double w = (double)row[k];
-        const double c = clamp_d(rint(w / delta) + z, 0.0, kQmax);   // rint: ties to even
-        const double d = c - z;
-        const double r = w - delta * d;
-        s.e2 += r * r;
-        s.num += d * w;
-        s.den += d * d;
-        s.sq += c;
+// the float right after v (toward +inf)
+__device__ __forceinline__ float next_up(float v) {
+    const uint32_t u = __float_as_uint(v);
+    return __uint_as_float(v == 0.f ? 1u : (u & 0x80000000u) ? u - 1u : u + 1u);
+}
+
+// Value cells: `cells` equal parts of the row's range; monotone in v (every step rounds monotonically).
+struct CellMap {
+    float lo, inv;
+    int last;
+    __device__ __forceinline__ int operator()(float v) const { return max((int)fminf((v - lo) * inv, (float)last), 0); }
+};
+
+struct Sums { double e2, num, den, sq; };
+
+// What a start of the search looks the row up in (LDS).
+template <int BLK>
+struct Row {
+    const float *sorted;      // the weights, ascending, then +infinity up to a multiple of BLK (at least one)
+    const double *prefix;     // prefix[b] = sum of the first b * BLK of them
+    const uint32_t *cells;    // cells[c] = number of weights in the cells before c
+    CellMap cell;
+    int K;
+    double sw, sw2;           // sum of the weights, sum of their squares
+};
+
+// The four sums on the grid (delta, z), by the 8 lanes of a group (j = lane % 8 takes positions j and j + 8): every
+// lane gets all of them.
+template <int BLK>
+__device__ __forceinline__ Sums evaluate(const Row<BLK> &r, int j, double delta, double z) {
+    float bound[2];      // pos_j = #{w < bound}
+    int lo[2], hi[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        // With t the threshold (j - z + 1/2) Delta and c the float nearest to it, every smaller float is below t and
+        // every larger one above it by at least a quarter of a float's ulp, which the roundings of t and of a
+        // quotient (fp64) cannot bridge.  So is c itself unless it equals t to within a few of those roundings:
+        // then its own quotient decides.
+        const double u = (double)(j + i * kLanes) - z, t = (u + 0.5) * delta;
+        const float c = (float)t;
+        const double off = (double)c - t;
+        bool below = off < 0.0;
+        if (fabs(off) <= fabs(t) * 0x1p-48) below = rint((double)c / delta) <= u;
+        bound[i] = below ? next_up(c) : c;
+        const int cb = r.cell(bound[i]);
+        const int first = (int)r.cells[cb], past = (int)r.cells[cb + 1];
+        lo[i] = first / BLK;
+        hi[i] = max(past - 1, first) / BLK;
     }
-    s.e2 = block_sum(s.e2, slots);
-    s.num = block_sum(s.num, slots);
-    s.den = block_sum(s.den, slots);
-    s.sq = block_sum(s.sq, slots);
+    // the last block of each cell that starts below the bound (or the cell's first)
+    while (lo[0] < hi[0] || lo[1] < hi[1]) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int mid = (lo[i] + hi[i] + 1) >> 1;
+            const bool up = r.sorted[mid * BLK] < bound[i] || lo[i] >= hi[i];
+            lo[i] = up ? mid : lo[i];   // (mid = lo where the range is a single block)
+            hi[i] = up ? hi[i] : mid - 1;
+        }
+    }
+    double p[2];
+    int pos[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        p[i] = r.prefix[lo[i]];
+        pos[i] = lo[i] * BLK;
+        const float4 *blk = reinterpret_cast<const float4 *>(r.sorted + lo[i] * BLK);
+#pragma unroll
+        for (int b = 0; b < BLK / 4; ++b) {
+            const float4 v = blk[b];
+            const float q[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const bool in = q[h] < bound[i];
+                pos[i] += in ? 1 : 0;
+                p[i] += (double)(in ? q[h] : 0.f);
+            }
+        }
+    }
+    if (j == kLanes - 1) { pos[1] = 0; p[1] = 0.0; }   // (15 positions)
+    const int zi = (int)z;
+    Sums s;
+    s.num = (15.0 - z) * r.sw - sum8(p[0] + p[1]);
+    s.den = (double)((15 - zi) * (15 - zi) * r.K - sum8((2 * (j - zi) + 1) * pos[0] + (2 * (j + kLanes - zi) + 1) * pos[1]));
+    s.sq = (double)(15 * r.K - sum8(pos[0] + pos[1]));
+    s.e2 = r.sw2 - 2.0 * delta * s.num + delta * delta * s.den;
+    // A (nearly) exact fit: the difference has lost too many digits (relative error 2^-53 sw2 / e2), take the
+    // sum over the row instead, as slow as it is.
+    if (!(s.e2 > 1e-4 * r.sw2)) {
+        double e2 = 0.0;
+        for (int k = j; k < r.K; k += kLanes) {
+            const double w = (double)r.sorted[k];
+            const double d = w - delta * (clamp_d(rint(w / delta) + z, 0.0, kQmax) - z);
+            e2 += d * d;
+        }
+        s.e2 = sum8(e2);
+    }
     return s;
 }
 
-__global__ __launch_bounds__(kThreads) void bgr_kernel(const float *__restrict__ w, int K, int n_steps, int max_refine,
-                                                       double eps, int search, uint8_t *__restrict__ w_packed,
-                                                       float *__restrict__ w_scale, int8_t *__restrict__ w_zero,
-                                                       double *__restrict__ row_error) {
-    extern __shared__ __align__(16) uint8_t smem_raw[];
-    double *slots = reinterpret_cast<double *>(smem_raw);            // kWaves doubles
-    float *row = reinterpret_cast<float *>(smem_raw + kWaves * sizeof(double));
-    const int64_t n = blockIdx.x;
-    const float *src = w + n * K;
+// ---- sorting
+// Order-preserving integers for floats (and back: the map is its own inverse), so that a comparator is one integer
+// minimum and one maximum.
+__device__ __forceinline__ int order_key(float v) { const int u = __float_as_int(v); return u ^ ((u >> 31) & 0x7FFFFFFF); }
+__device__ __forceinline__ float from_key(int k) { return __int_as_float(k ^ ((k >> 31) & 0x7FFFFFFF)); }
 
-    // the row into LDS; its minimum, maximum and sum
-    double lo0 = INFINITY, hi0 = -INFINITY, sw = 0.0;
-    for (int k = threadIdx.x; k < K; k += kThreads) {
-        const float v = src[k];
-        row[k] = v;
-        lo0 = fmin(lo0, (double)v);
-        hi0 = fmax(hi0, (double)v);
-        sw += (double)v;
+// Bitonic network over 32 registers whose comparators all put the smaller value first (the first step of a merge pairs
+// mirrored positions).  FROM = 2: a full sort; FROM = 32: merges two sorted halves.
+template <int FROM>
+__device__ __forceinline__ void network32(int (&k)[32]) {
+#pragma unroll
+    for (int span = FROM; span <= 32; span *= 2)
+#pragma unroll
+        for (int dist = span / 2; dist >= 1; dist /= 2)
+#pragma unroll
+            for (int i = 0; i < 32; ++i) {
+                const int l = dist == span / 2 ? i ^ (span - 1) : i ^ dist;
+                if (l > i) {
+                    const int a = min(k[i], k[l]), b = max(k[i], k[l]);
+                    k[i] = a;
+                    k[l] = b;
+                }
+            }
+}
+
+// Sorts or merges the 32 floats at `a` (16-byte aligned), in one thread.
+template <int FROM>
+__device__ __forceinline__ void window32(float *a) {
+    int k[32];
+    float4 *q = reinterpret_cast<float4 *>(a);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float4 v = q[i];
+        k[4 * i] = order_key(v.x);
+        k[4 * i + 1] = order_key(v.y);
+        k[4 * i + 2] = order_key(v.z);
+        k[4 * i + 3] = order_key(v.w);
     }
+    network32<FROM>(k);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        q[i] = make_float4(from_key(k[4 * i]), from_key(k[4 * i + 1]), from_key(k[4 * i + 2]), from_key(k[4 * i + 3]));
+}
+
+// floats the row takes in LDS: up to a whole window and one more, of which the last K .. are +infinity
+__host__ __device__ constexpr int row_floats(int K) { return (K / 32 + 2) * 32; }
+
+// Sorts a[0 .. n): the same network in LDS, where positions past n act as +infinity without being there.
+template <int T>
+__device__ void bitonic_sort(float *a, int n) {
+    int span = 2;
+    for (;; span <<= 1) {
+        for (int dist = span >> 1; dist >= 1; dist >>= 1) {
+            const bool mirror = dist == span >> 1;
+            for (int t = threadIdx.x;; t += T) {
+                const int i = ((t & ~(dist - 1)) << 1) | (t & (dist - 1));
+                if (i >= n) break;
+                const int l = mirror ? i ^ (span - 1) : i + dist;
+                if (l < n) {
+                    const float x = a[i], y = a[l];
+                    if (y < x) { a[i] = y; a[l] = x; }
+                }
+            }
+            __syncthreads();
+        }
+        if (span >= n) break;
+    }
+}
+
+// T threads, a prefix sum every BLK weights.  HELD > 0: the threads hold the row in registers, HELD pairs of weights
+// each (K <= 2 HELD T); 0: it is read again for every step that needs it in its own order.
+// (16 waves per compute unit in every case: one workgroup of 1024 threads or two of 512, 128 registers per lane.)
+template <int T, int BLK, int HELD>
+__global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, int K, int cells, int n_steps, int max_refine,
+                                                double eps, int search, uint8_t *__restrict__ w_packed,
+                                                float *__restrict__ w_scale, int8_t *__restrict__ w_zero,
+                                                double *__restrict__ row_error) {
+    constexpr bool REGS = HELD > 0;   // the row is held
+    constexpr int WAVES = T / 64, PAIRS = REGS ? HELD : 4;
+    // LDS: the row fp32 [row_floats(K)], prefix sums fp64 [blocks], the cells uint32 [cells + 1]
+    extern __shared__ __align__(16) uint8_t smem_raw[];
+    const int blocks = K / BLK + 1;
+    float *row = reinterpret_cast<float *>(smem_raw);
+    double *prefix = reinterpret_cast<double *>(row + row_floats(K));
+    uint32_t *first = reinterpret_cast<uint32_t *>(prefix + blocks);   // first[c]: weights before cell c
+    __shared__ double s_a[WAVES], s_b[WAVES], s_c[WAVES];
+    __shared__ int s_i[WAVES], s_max[WAVES];
+    __shared__ double s_best[3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t n = blockIdx.x;
+    const float2 *src = reinterpret_cast<const float2 *>(w + n * K);   // (K is even, w 16-byte aligned)
+    const int pairs = K / 2;
+
+    // f(pair number, pair) for this thread's pairs; the loads of PAIRS pairs are in flight together
+    float2 held[PAIRS];
+    auto load = [&] __device__(int base) {
+#pragma unroll
+        for (int i = 0; i < PAIRS; ++i)
+            if (base + i * T < pairs) held[i] = src[base + i * T];
+    };
+    auto for_row = [&] __device__(auto f) {
+        for (int base = tid;; base += PAIRS * T) {
+            if (!REGS) load(base);
+#pragma unroll
+            for (int i = 0; i < PAIRS; ++i)
+                if (base + i * T < pairs) f(base + i * T, held[i]);
+            if (REGS || base + PAIRS * T >= pairs) break;
+        }
+    };
+    if (REGS) load(tid);
+
+    // ---- minimum, maximum, sum and sum of squares
+    float lo_f = INFINITY, hi_f = -INFINITY;
+    double sw = 0.0, sw2 = 0.0;
+    for (int c = tid; c <= cells; c += T) first[c] = 0u;
+    for_row([&] __device__(int, float2 v) {
+        lo_f = fminf(lo_f, fminf(v.x, v.y));
+        hi_f = fmaxf(hi_f, fmaxf(v.x, v.y));
+        const double a = (double)v.x, b = (double)v.y;
+        sw += a;
+        sw += b;
+        sw2 += a * a;
+        sw2 += b * b;
+    });
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) {
-        lo0 = fmin(lo0, __shfl_xor(lo0, m, 64));
-        hi0 = fmax(hi0, __shfl_xor(hi0, m, 64));
+        lo_f = fminf(lo_f, __shfl_xor(lo_f, m, 64));
+        hi_f = fmaxf(hi_f, __shfl_xor(hi_f, m, 64));
     }
-    __shared__ double s_lo[kWaves], s_hi[kWaves];
-    if ((threadIdx.x & 63) == 0) { s_lo[threadIdx.x >> 6] = lo0; s_hi[threadIdx.x >> 6] = hi0; }
-    sw = block_sum(sw, slots);   // (its barriers also publish s_lo / s_hi and the row)
+    sw = wave_sum(sw);
+    sw2 = wave_sum(sw2);
+    if (lane == 0) {
+        s_a[wave] = sw;
+        s_b[wave] = sw2;
+        s_c[wave] = __builtin_bit_cast(double, make_float2(lo_f, hi_f));
+    }
+    __syncthreads();
+    sw = sw2 = 0.0;
 #pragma unroll
-    for (int i = 0; i < kWaves; ++i) { lo0 = fmin(lo0, s_lo[i]); hi0 = fmax(hi0, s_hi[i]); }
+    for (int i = 0; i < WAVES; ++i) {
+        sw += s_a[i];
+        sw2 += s_b[i];
+        const float2 r = __builtin_bit_cast(float2, s_c[i]);
+        lo_f = fminf(lo_f, r.x);
+        hi_f = fmaxf(hi_f, r.y);
+    }
+    const double lo0 = (double)lo_f, hi0 = (double)hi_f;
+    const bool constant = !(hi0 > lo0);
 
-    double best = INFINITY, best_delta = 1.0, best_z = 0.0;
-    if (!(hi0 > lo0)) {
-        // constant row c, represented exactly: Delta = |c| (1 if c = 0), z = (c < 0), q = (c > 0)
-        best = 0.0;
-        best_delta = lo0 == 0.0 ? 1.0 : fabs(lo0);
-        best_z = lo0 < 0.0 ? 1.0 : 0.0;
-    } else {
-        const double step = (hi0 - lo0) / (double)n_steps;
+    // constant row c, represented exactly: Delta = |c| (1 if c = 0), z = (c < 0), q = (c > 0)
+    double best = 0.0;
+    double best_delta = lo0 == 0.0 ? 1.0 : fabs(lo0);
+    double best_z = lo0 < 0.0 ? 1.0 : 0.0;
+
+    if (!constant) {   // (the whole workgroup takes the same side: every thread has the same range)
+        // ---- sort.  The row is dealt into cells of equal width (counting with LDS atomics, whose order decides
+        // nothing in the end), which leaves every weight within a cell's length of its place.  Windows of 32 then
+        // put it there, one thread each: sorted once where they are aligned, then merged alternately half a window
+        // further on and aligned again, an odd-even transposition over blocks of 16 (a cell of m weights lies in
+        // (m - 2) / 16 + 2 of them at most and needs as many passes).  Rows whose weights crowd into few cells
+        // (many equal weights, one enormous outlier) take a bitonic sort instead.
+        const CellMap cell = {lo_f, (float)cells / (hi_f - lo_f), cells - 1};
+        for_row([&] __device__(int, float2 v) {
+            atomicAdd(&first[1 + cell(v.x)], 1u);
+            atomicAdd(&first[1 + cell(v.y)], 1u);
+        });
+        __syncthreads();
+        uint32_t *mine = first + 1 + tid * (cells / T);   // this thread's consecutive cells
+        int count = 0, fullest = 0;
+        for (int i = 0; i < cells / T; ++i) {
+            count += (int)mine[i];
+            fullest = max(fullest, (int)mine[i]);
+        }
+        int upto = count;   // inclusive scan over the threads
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+            const int o = __shfl_up(upto, m, 64);
+            if (lane >= m) upto += o;
+            fullest = max(fullest, __shfl_xor(fullest, m, 64));
+        }
+        if (lane == 63) s_i[wave] = upto;
+        if (lane == 0) s_max[wave] = fullest;
+        __syncthreads();
+        int before = upto - count;
+        fullest = 0;
+#pragma unroll
+        for (int i = 0; i < WAVES; ++i) {
+            if (i < wave) before += s_i[i];
+            fullest = max(fullest, s_max[i]);
+        }
+        const bool by_cells = fullest <= kCellLimit;
+        // by cells: the first position of each cell, which the scatter below turns into its end; else the end
+        for (int i = 0; i < cells / T; ++i) {
+            const int c = (int)mine[i];
+            mine[i] = (uint32_t)(by_cells ? before : before + c);
+            before += c;
+        }
+        for (int k = K + tid; k < row_floats(K); k += T) row[k] = INFINITY;
+        if (by_cells) {
+            __syncthreads();
+            for_row([&] __device__(int, float2 v) {
+                row[atomicAdd(&first[1 + cell(v.x)], 1u)] = v.x;
+                row[atomicAdd(&first[1 + cell(v.y)], 1u)] = v.y;
+            });
+            __syncthreads();
+            for (int i = tid * 32; i < K; i += T * 32) window32<2>(row + i);
+            __syncthreads();
+            for (int pass = 1; pass <= (fullest + 14) / 16; ++pass) {
+                for (int i = tid * 32 + (pass & 1) * 16; i < K; i += T * 32) window32<32>(row + i);
+                __syncthreads();
+            }
+        } else {
+            for_row([&] __device__(int p, float2 v) {
+                row[2 * p] = v.x;
+                row[2 * p + 1] = v.y;
+            });
+            __syncthreads();
+            bitonic_sort<T>(row, K);
+        }
+
+        // ---- prefix sums, one every BLK weights
+        {
+            const int full = K / BLK, nb = (full + T - 1) / T;   // whole blocks, consecutive ones of this thread
+            const int b0 = min(tid * nb, full), b1 = min(b0 + nb, full);
+            auto block_sum = [&] __device__(int b) {
+                const float4 *blk = reinterpret_cast<const float4 *>(row + b * BLK);
+                double s = 0.0;
+#pragma unroll
+                for (int i = 0; i < BLK / 4; ++i) {
+                    const float4 v = blk[i];
+                    s += (double)v.x;
+                    s += (double)v.y;
+                    s += (double)v.z;
+                    s += (double)v.w;
+                }
+                return s;
+            };
+            double s = 0.0;
+            for (int b = b0; b < b1; ++b) {
+                prefix[b + 1] = s;   // (for now: within the thread's blocks, before block b)
+                s += block_sum(b);
+            }
+            double incl = s;
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) {
+                const double o = __shfl_up(incl, m, 64);
+                if (lane >= m) incl += o;
+            }
+            if (lane == 63) s_a[wave] = incl;
+            __syncthreads();
+            double run = __shfl_up(incl, 1, 64);   // (every lane takes part: the lanes before this one)
+            if (lane == 0) run = 0.0;
+            for (int i = 0; i < wave; ++i) run += s_a[i];
+            for (int b = b0; b < b1; ++b) prefix[b + 1] = run + (b + 1 < b1 ? prefix[b + 2] : s);   // up to block b's end
+            if (tid == 0) prefix[0] = 0.0;
+            __syncthreads();
+        }
+
+        // ---- search: 8 lanes per start, no barrier
+        const Row<BLK> r = {row, prefix, first, cell, K, sw, sw2};
+        const int j = lane & (kLanes - 1);
         const bool all = search == DVDQ_BGR_BEST_OF_ALL;
-        for (int i = all ? 0 : 1; i <= n_steps; ++i) {
+        const double step = (hi0 - lo0) / (double)n_steps;
+        const double mean = sw / (double)K;
+        int best_i = 0x7FFFFFFF;
+        best = INFINITY;
+        best_delta = 1.0;
+        best_z = 0.0;
+        for (int64_t i = (all ? 0 : 1) + tid / kLanes; i <= n_steps; i += T / kLanes) {
             const double lo = lo0 + (double)i * step, hi = hi0 - (double)i * step;
             if (!(lo < hi)) break;   // the range has collapsed (from i = n_steps / 2 on)
             // clipped MinMax start
             double delta = (hi - lo) / kQmax;
             double z = clamp_d(rint(-(lo / delta)), 0.0, kQmax);
-            Sums s = evaluate(row, K, delta, z, slots);
+            Sums s = evaluate(r, j, delta, z);
             double e = sqrt(s.e2);
-            if (all && e < best) { best = e; best_delta = delta; best_z = z; }
-            for (int j = 0; j < max_refine; ++j) {
+            if (all && e < best) { best = e; best_delta = delta; best_z = z; best_i = (int)i; }
+            for (int round = 0; round < max_refine; ++round) {
                 if (s.den == 0.0) break;
                 const double dn = s.num / s.den;
                 if (!(dn > 0.0)) break;
-                const double zn = clamp_d(rint(s.sq / (double)K - (sw / (double)K) / dn), 0.0, kQmax);
-                s = evaluate(row, K, dn, zn, slots);
+                const double zn = clamp_d(rint(s.sq / (double)K - mean / dn), 0.0, kQmax);
+                if (dn == delta && zn == z) break;   // a fixed point: every further round is this grid again
+                s = evaluate(r, j, dn, zn);
                 const double en = sqrt(s.e2);
-                if (all && en < best) { best = en; best_delta = dn; best_z = zn; }
+                if (all && en < best) { best = en; best_delta = dn; best_z = zn; best_i = (int)i; }
                 const double gain = e - en;
-                e = en; delta = dn; z = zn;   // the start's current (last) grid
+                e = en;
+                delta = dn;
+                z = zn;   // the start's current (last) grid
                 if (gain < eps) break;
             }
             // as printed in Alg. 1: only the grid of the start's last round competes
-            if (!all && e < best) { best = e; best_delta = delta; best_z = z; }
+            if (!all && e < best) { best = e; best_delta = delta; best_z = z; best_i = (int)i; }
         }
+        // ---- the smallest error, ties to the earliest start: across the wave's groups, then the waves
+#pragma unroll
+        for (int m = kLanes; m <= 32; m <<= 1) {
+            const double oe = __shfl_xor(best, m, 64), od = __shfl_xor(best_delta, m, 64), oz = __shfl_xor(best_z, m, 64);
+            const int oi = __shfl_xor(best_i, m, 64);
+            if (oe < best || (oe == best && oi < best_i)) { best = oe; best_delta = od; best_z = oz; best_i = oi; }
+        }
+        if (lane == 0) { s_a[wave] = best; s_b[wave] = best_delta; s_c[wave] = best_z; s_i[wave] = best_i; }
+        __syncthreads();
+        if (tid == 0) {
+            for (int i = 1; i < WAVES; ++i)
+                if (s_a[i] < best || (s_a[i] == best && s_i[i] < best_i)) {
+                    best = s_a[i];
+                    best_delta = s_b[i];
+                    best_z = s_c[i];
+                    best_i = s_i[i];
+                }
+            s_best[0] = best;
+            s_best[1] = best_delta;
+            s_best[2] = best_z;
+        }
+        if (REGS) load(tid);   // (again, from the L2: kept through the search they would cost registers)
+        __syncthreads();
+        best = s_best[0];
+        best_delta = s_best[1];
+        best_z = s_best[2];
     }
 
-    // the codes on the best grid, as signed nibbles (unsigned code - 8), two per byte
-    const bool constant = !(hi0 > lo0);
-    for (int p = threadIdx.x; p < K / 2; p += kThreads) {
+    // ---- the codes on the best grid, as signed nibbles (unsigned code - 8), two per byte
+    for_row([&] __device__(int p, float2 v) {
         int c[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const double wv = (double)row[2 * p + h];
+            const double wv = (double)(h ? v.y : v.x);
             const double q = constant ? (lo0 > 0.0 ? 1.0 : 0.0) : clamp_d(rint(wv / best_delta) + best_z, 0.0, kQmax);
             c[h] = (int)q - 8;
         }
-        w_packed[n * (K / 2) + p] = (uint8_t)((c[0] & 0xF) | ((c[1] & 0xF) << 4));
-    }
-    if (threadIdx.x == 0) {
+        w_packed[n * pairs + p] = (uint8_t)((c[0] & 0xF) | ((c[1] & 0xF) << 4));
+    });
+    if (tid == 0) {
         w_scale[n] = (float)best_delta;
         w_zero[n] = (int8_t)((int)best_z - 8);
         if (row_error) row_error[n] = best;
     }
 }
 
+size_t lds_bytes(int64_t K, int blk, int cells) {
+    return row_floats((int)K) * sizeof(float) + (size_t)(K / blk + 1) * sizeof(double) + (size_t)(cells + 1) * sizeof(uint32_t);
+}
+
+template <int T, int BLK, int HELD>
+int launch(const float *w, int64_t N, int K, int cells, int n_steps, int max_refine, double eps, int search,
+           uint8_t *w_packed, float *w_scale, int8_t *w_zero, double *row_error, hipStream_t stream) {
+    auto k = bgr_kernel<T, BLK, HELD>;
+    static std::atomic<uint64_t> configured{0};   // one per template instantiation
+    allow_dynamic_lds(reinterpret_cast<const void *>(k), 158 * 1024, configured);
+    hipLaunchKernelGGL(k, dim3((unsigned)N), dim3(T), lds_bytes(K, BLK, cells), stream, w, K, cells, n_steps, max_refine, eps,
+                       search, w_packed, w_scale, w_zero, row_error);
+    return check_launch();
+}
+
 }  // namespace
 
 int launch_bgr(const float *w, int64_t N, int64_t K, int n_steps, int max_refine, double eps, int search,
                uint8_t *w_packed, float *w_scale, int8_t *w_zero, double *row_error, hipStream_t stream) {
-    const size_t smem = kWaves * sizeof(double) + (size_t)K * sizeof(float);
-    static std::atomic<uint64_t> configured{0};
-    allow_dynamic_lds(reinterpret_cast<const void *>(bgr_kernel), kWaves * sizeof(double) + kMaxK * sizeof(float),
-                      configured);   // the limit for the longest row the API admits
-    hipLaunchKernelGGL(bgr_kernel, dim3((unsigned)N), dim3(kThreads), smem, stream, w, (int)K, n_steps, max_refine, eps,
-                       search, w_packed, w_scale, w_zero, row_error);
-    return check_launch();
+#define DVDQ_BGR_ARGS(CELLS) \
+    w, N, (int)K, CELLS, n_steps, max_refine, eps, search, w_packed, w_scale, w_zero, row_error, stream
+    // A few weights per cell: 1024 .. 4096 cells.  Two rows at a time per compute unit, as workgroups of 512 threads,
+    // while their LDS allows (half of 160 KB each; longer rows with coarser prefix sums and cells): 0.20 ms against 0.25
+    // as workgroups of 1024 for 1536 rows of 8960.  A workgroup of 1024 threads where there is no second row to put
+    // beside it: with no more rows than compute units (32 rows of 8960: 0.044 ms against 0.056), and from 14 K weights on.
+    const int cells = K <= 2048 ? 1024 : (K <= 4096 ? 2048 : 4096);
+    if (K > 16384) return launch<1024, 16, 0>(DVDQ_BGR_ARGS(2048));
+    if (N > 256 && K <= 10240) return launch<512, 4, 10>(DVDQ_BGR_ARGS(cells));
+    if (N > 256 && K <= 14336) return launch<512, 8, 14>(DVDQ_BGR_ARGS(2048));
+    return launch<1024, 4, 8>(DVDQ_BGR_ARGS(cells));
+#undef DVDQ_BGR_ARGS
 }
 
 }  // namespace dvdq

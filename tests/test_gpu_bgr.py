@@ -101,3 +101,27 @@ def test_bgr_weights_through_the_layer():
     err_bgr = np.linalg.norm(y.float().cpu().numpy().astype(np.float64) - y_float)
     err_mm = np.linalg.norm(xr @ w_mm.T - y_float)
     assert err_bgr < err_mm
+
+
+# One row length on each side of every change of the kernel's launch shape (rows in registers, prefix-sum spacing, number of
+# value cells) and the shortest and longest rows; more rows than compute units where that decides as well.
+@pytest.mark.parametrize("N,K", [(3, 2), (5, 30), (9, 1026), (300, 2048), (300, 2050), (9, 4098), (260, 10240), (258, 10242),
+                                 (257, 14336), (257, 14338), (4, 16384), (4, 16386)])
+@pytest.mark.parametrize("search", [dvdq.BGR_LISTING, dvdq.BGR_BEST_OF_ALL])
+def test_bgr_row_lengths_around_the_launch_shapes(N, K, search):
+    rng = np.random.default_rng(N + K)
+    w = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    print(compare(w, f"N{N} K{K} search{search}", n_steps=9, max_refine=3, search=search))
+
+
+@pytest.mark.parametrize("K", [512, 4096, 20000])
+@pytest.mark.parametrize("search", [dvdq.BGR_LISTING, dvdq.BGR_BEST_OF_ALL])
+def test_bgr_crowded_rows(K, search):
+    """Rows whose weights crowd into few value cells (the sorted row then comes from another network), weights that sit
+    exactly on thresholds, and rows that a grid fits almost exactly (the expanded squared error would cancel)."""
+    rng = np.random.default_rng(K)
+    g = rng.standard_normal(K)
+    rows = [np.where(rng.random(K) < 0.9, 0.0, g), g * 0.02 + np.eye(1, K, 7)[0] * 1e6, 5.0 + 1e-3 * g, -3.0 + 1e-6 * g,
+            np.round(g * 4) / 8, 0.25 * (rng.integers(0, 16, K) - 6) + 1e-7 * g, np.sign(g) * np.abs(g) ** 5,
+            np.where(np.arange(K) < 2, [[-1.0], [1.0]][0] + 2.0 * (np.arange(K) == 1), 1e-4 * g), g * 1e-30, np.exp(3 * g)]
+    print(compare(np.stack(rows).astype(np.float32), f"K{K} search{search}", n_steps=30, max_refine=6, search=search))
