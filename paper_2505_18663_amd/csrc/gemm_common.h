@@ -117,8 +117,11 @@ static __device__ __forceinline__ void tile_origin(int t, int tiles_m, int tiles
 // ---- tile numbers of a persistent launch
 // Workgroup ids are dealt round-robin to the 8 XCDs, and the workgroups of one XCD work on one contiguous
 // run of tile numbers at a time.
-//   ctr != nullptr: XCD x owns tile numbers [x total / 8, (x + 1) total / 8) and its workgroups draw from them
-//     in order through one counter word (an atomic add).  The word is zero when the kernel starts: whatever
+//   ctr != nullptr: XCD x owns tile numbers [x total / 8, (x + 1) total / 8).  Its i-th workgroup starts with the
+//     i-th of them; the others are drawn in order through one counter word (an atomic add).  (A workgroup has to
+//     know its second tile when it starts.  When it drew both, the workgroups that started first took two tiles
+//     each and, with fewer than two tiles per workgroup, left none to the last ones: 732 tiles on 512 workgroups
+//     took 65.7 us instead of 52.9, 125 tiles on 128 workgroups 39 instead of 21.)  The word is zero when the kernel starts: whatever
 //     runs on the stream right before the GEMM clears the slot (the quantizer kernel, if that is what the
 //     library enqueued last on the stream, else a one-wave kernel the GEMM's launcher puts in front), so no
 //     launch depends on what an earlier one -- finished or not -- left behind, and nothing has to be put back
@@ -126,7 +129,7 @@ static __device__ __forceinline__ void tile_origin(int t, int tiles_m, int tiles
 //   ctr == nullptr: fixed shares, the j-th tile of workgroup b is number j * grid + (b % 8) * (grid / 8) + b / 8.
 struct TileSource {
     int total, grid, xcd, first_tile, run_lo;
-    unsigned run_len;
+    unsigned run_len, started;   // tiles of this XCD; how many of them its workgroups start with
     unsigned *ctr;   // this XCD's counter
 
     __device__ __forceinline__ TileSource(int tiles_m, int tiles_n, unsigned *sched) {
@@ -136,11 +139,12 @@ struct TileSource {
         first_tile = xcd * (grid / 8) + blockIdx.x / 8;
         run_lo = (int)((int64_t)xcd * total / 8);
         run_len = (unsigned)((int64_t)(xcd + 1) * total / 8) - (unsigned)run_lo;
+        started = min(run_len, gridDim.x / 8);
         ctr = sched ? sched + xcd : nullptr;
     }
     // the tile a draw's reply stands for (drawn mode), or the workgroup's ordinal-th tile (fixed shares); -1: none left
     __device__ __forceinline__ int tile(unsigned reply, int ordinal) const {
-        if (ctr) return reply < run_len ? run_lo + (int)reply : -1;
+        if (ctr) return reply < run_len - started ? run_lo + (int)(started + reply) : -1;
         const int t = first_tile + ordinal * grid;
         return t < total ? t : -1;
     }
@@ -148,9 +152,13 @@ struct TileSource {
     __device__ __forceinline__ unsigned draw() const { return atomicAdd(ctr, 1u); }
     // the workgroup's first two tiles (one lane; either mode)
     __device__ __forceinline__ void first_two(int &t0, int &t1) const {
-        const unsigned v = ctr ? atomicAdd(ctr, 2u) : 0u;
-        t0 = tile(v, 0);
-        t1 = tile(v + 1u, 1);
+        if (ctr) {
+            t0 = blockIdx.x / 8 < run_len ? run_lo + (int)(blockIdx.x / 8) : -1;
+            t1 = started < run_len ? tile(draw(), 1) : -1;
+        } else {
+            t0 = tile(0u, 0);
+            t1 = tile(0u, 1);
+        }
     }
 };
 

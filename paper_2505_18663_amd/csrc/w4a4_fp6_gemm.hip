@@ -365,7 +365,8 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
     static std::atomic<uint64_t> configured{0};
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
     bool is_clear = false;
-    unsigned *sched = sched_slot(stream, &is_clear);
+    // (a tile per workgroup at most: nothing to draw, no counter to clear)
+    unsigned *sched = total > grid ? sched_slot(stream, &is_clear) : nullptr;
     if (sched && !is_clear && clear_sched_slot(sched, stream) != DVDQ_OK) return DVDQ_ERR_HIP;
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * WAVES_M * WAVES_N), smem, stream, codes, x_scale, w, w_scale,
                        w_zero, code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, group_n, sched);

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
         }
         draw_pending = false;
     };
-    // the first two tiles are drawn together
+    // the first tile follows from the workgroup's number, the second is drawn now
     if (wave == 0 && lane == 0) {
         int t0, t1;
         tiles.first_two(t0, t1);
@@ -554,7 +554,8 @@ int launch_native(const int8_t *codes, const float *x_scale, const uint8_t *w, c
     static std::atomic<uint64_t> configured{0};   // one per template instantiation
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
     bool is_clear = false;
-    unsigned *sched = sched_slot(stream, &is_clear);
+    // (a tile per workgroup at most: nothing to draw, no counter to clear)
+    unsigned *sched = total > grid ? sched_slot(stream, &is_clear) : nullptr;
     if (sched && !is_clear && clear_sched_slot(sched, stream) != DVDQ_OK) return DVDQ_ERR_HIP;
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * WAVES_M * WAVES_N), smem, stream, codes, x_scale, w,
                        w_scale, w_zero, code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, group_n, sched);
