@@ -584,7 +584,8 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     const int m = (int)M, n = (int)N, k = (int)K;
 #define DVDQ_GEMM_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, m, n, k, y, acc_out, stream
     // Tile variants: {tile M, tile N, K slice, waves M x N, ring depth, workgroups per compute unit}.
-    // Variant 2 is the default of the two-wave kernels for every shape: two independent 4-wave workgroups per compute unit,
+    // Outputs of few tiles go to w4ax_gemm_small.hip (small_gemm_shape).  Variant 2 is the default of the two-wave kernels
+    // for every other shape: two independent 4-wave workgroups per compute unit,
     // each owning a 128 x 256 tile (64 x 128 per wave) with K slices of 128 through two buffers.  In
     // interleaved sweeps over the DiT shapes (K = 1536 ... 13824) it was fastest or within 1 % of the
     // fastest: while one workgroup converts and stores its tile the other keeps the matrix cores busy,
@@ -592,6 +593,10 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     // fewer K slices than a variant's ring needs falls back to variant 2, which always qualifies.
     const int forced = gemm_variant();
     int v = forced < 0 ? 2 : forced;
+    const int shape = forced < 0 ? small_gemm_shape(M, N, K) : forced - kFirstSmallVariant;
+    if (shape >= 0)
+        return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, w_zero, code_rowsum,
+                                      bias, M, N, K, codes_format, shape, y, acc_out, stream);
     if (codes_format == DVDQ_CODES_PACKED4) {
         if ((v == 1 && k / 128 < 2) || (v > 2 && k / 128 < 3)) v = 2;
         switch (v) {

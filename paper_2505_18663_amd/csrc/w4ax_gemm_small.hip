@@ -1,0 +1,362 @@
+// W4Ax GEMM for outputs too small to fill the chip with the tiles of w4ax_gemm.hip and w4a4_fp6_gemm.hip
+// (Sec. 3.2: Y = X^ Lambda W^^T; Sec. 3.1 DeQuant, optional zero-points): few tokens, or few output channels.
+//
+// What bounds such a product is neither the matrix cores nor HBM but the chain of K slices a workgroup walks: with
+// one 128 x 256 tile per workgroup and 12 to 108 slices in series, each slice costs a round trip to the L2 or to
+// memory while most compute units have no tile at all.  So here the tile is small (32 x 32 to 64 x 128), the K
+// slices are dealt to the waves of the workgroup, each wave accumulates the WHOLE tile over its share, and the
+// shares are added up through LDS at the end (integers, or fp32 sums that are exact integers: any order gives the
+// same bits).  The waves run independently: no barrier before the reduction.
+//
+//   weights: straight from the native layouts into registers; a fragment load is one contiguous run per wave.
+//   codes:   FP6 likewise.  The row-major containers are loaded as whole lines (rows of a slice: 128 or 64 bytes) and
+//            turned into fragments through the wave's own LDS; fetched as fragments directly, a load instruction
+//            would touch 32 lines.
+//   K tails, rows past M: loads past the end of a buffer descriptor return zeros (zero codes add nothing).
+//
+// Measured (back-to-back launches, int8 codes, before -> now): 2 x 1536 x 9216 (tokens x K x channels): 22.6 -> 4.4 us;
+// 512 x 3072 x 3072: 28.0 -> 11.2; 1 x 13824 x 5120: 104 -> 10.5; 3121 x 1152 x 1160: 27.7 -> 10.8.  Towards the upper
+// end of the range the operand traffic out of the L2s is the limit (14 to 20 TB/s), which is why the tile grows with
+// the output.  A second slice in flight per wave costs registers and
+// resident waves: 10 % slower at 512 x 3072 x 3072, at best 5 % faster (1560 x 3072 x 3072).
+#include <type_traits>
+
+#include "gemm_common.h"
+
+namespace dvdq {
+namespace {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f_t __attribute__((ext_vector_type(4)));
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+constexpr int kFp6Block = kGroup * kBK * 6 / 8;   // 3072: 32 rows of one K slice as E2M3 patterns
+enum { FMT_INT8 = 0, FMT_PACKED4 = 1, FMT_FP6 = 2 };
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const uint8_t *p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p), 0, bytes, 0x00020000);
+}
+
+// two packed dwords (16 codes) -> int8 lanes of 16 * code, channel order (see w4ax_gemm.hip)
+__device__ __forceinline__ v4i widen16(uint32_t lo, uint32_t hi) {
+    v4i f;
+    f[0] = (int)((lo << 4) & 0xF0F0F0F0u);
+    f[1] = (int)(lo & 0xF0F0F0F0u);
+    f[2] = (int)((hi << 4) & 0xF0F0F0F0u);
+    f[3] = (int)(hi & 0xF0F0F0F0u);
+    return f;
+}
+
+// three 16-byte chunks of a row's half slice -> operand of the h-th 64-channel MFMA
+template <int H>
+__device__ __forceinline__ v8i fp6_fragment(v4u c0, v4u c1, v4u c2) {
+    return H == 0 ? v8i{(int)c0[0], (int)c0[1], (int)c0[2], (int)c0[3], (int)c1[0], (int)c1[1], 0, 0}
+                  : v8i{(int)c1[2], (int)c1[3], (int)c2[0], (int)c2[1], (int)c2[2], (int)c2[3], 0, 0};
+}
+
+// what a wave loads of one K slice of 128 channels
+template <int FMT, int TM, int TN>
+struct Slice {
+    static constexpr int A_LOADS = TM * (FMT == FMT_INT8 ? 4 : FMT == FMT_PACKED4 ? 2 : 3);   // 16 bytes per lane each
+    v4u a[A_LOADS];
+    v2u w[FMT == FMT_FP6 ? 1 : TN * 4];
+    v4u w6[FMT == FMT_FP6 ? TN * 3 : 1];
+};
+
+template <int FMT, int TM, int TN, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
+    const uint8_t *__restrict__ codes, const float *__restrict__ x_scale, const uint8_t *__restrict__ w,
+    const float *__restrict__ w_scale, const int8_t *__restrict__ w_zero, const int32_t *__restrict__ code_rowsum,
+    const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out,
+    int tiles_m, int tiles_n, int m_fastest) {
+    constexpr bool FP6 = FMT == FMT_FP6;
+    constexpr int BM = 32 * TM, BN = 32 * TN;
+    constexpr int A_ROW = FMT == FMT_INT8 ? kBK : kBK / 2;     // bytes of a code row per slice (row-major containers)
+    constexpr int PHASES = TN > 2 ? 2 : 1, PN = TN / PHASES;   // the reduction takes PN columns of MFMA tiles at a time
+    constexpr int NG = TM * PN * 4;                            // groups of 4 accumulator registers per phase
+    constexpr int GROUP_STRIDE = 1024 + 32;                    // LDS bytes of one group (see the reduction)
+    constexpr int WAVE_LDS = NG * GROUP_STRIDE;
+    constexpr int CV = (BN + 63) / 64;                         // values per lane of a channel vector
+    static_assert(TM <= 2 && TN <= 4 && TN % PHASES == 0, "token vectors are one value per lane");
+    typedef typename std::conditional<FP6, AccF32x64, AccI32<FMT == FMT_INT8 ? 4 : 8>>::type P;
+    typedef typename P::vec Acc;
+
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int KT = K / kBK;
+    const int G = ((N + kNPad - 1) / kNPad) * (kNPad / kGroup);
+
+    // consecutive workgroups go to different XCDs: each XCD gets a contiguous run of tiles
+    const int total = tiles_m * tiles_n;
+    int tile = blockIdx.x;
+    const int per_xcd = total / 8;
+    if (tile < per_xcd * 8) tile = (tile % 8) * per_xcd + tile / 8;
+    const int slow = tile / (m_fastest ? tiles_m : tiles_n), fast = tile - slow * (m_fastest ? tiles_m : tiles_n);
+    const int m0 = (m_fastest ? fast : slow) * BM, n0 = (m_fastest ? slow : fast) * BN;
+    const int rows = min(BM, M - m0);
+
+    // The tile's token and channel vectors, one value per lane, requested before everything else and put into LDS
+    // after the K loop.  (Always loaded, from some vector that exists: a branch would wait for them here.)
+    const int vm = min(m0 + lane, M - 1);
+    const float v_xs = x_scale[vm];
+    const int v_rs = (w_zero ? code_rowsum : reinterpret_cast<const int32_t *>(x_scale))[vm];
+    float v_ws[CV];
+    uint16_t v_bias[CV];
+    int8_t v_z[CV];
+#pragma unroll
+    for (int i = 0; i < CV; ++i) {
+        const int vn = min(n0 + i * 64 + lane, N - 1);
+        v_ws[i] = w_scale[vn];
+        v_bias[i] = (bias ? bias : reinterpret_cast<const uint16_t *>(w_scale))[vn];
+        v_z[i] = (w_zero ? w_zero : reinterpret_cast<const int8_t *>(w_scale))[vn];
+    }
+
+    const int row_bytes = FMT == FMT_INT8 ? K : K / 2;
+    const uint8_t *a_tile = FP6 ? codes + (int64_t)(m0 / 32) * KT * kFp6Block : codes + (int64_t)m0 * row_bytes;
+    const int a_bytes = FP6 ? (rows + 31) / 32 * KT * kFp6Block : rows * row_bytes;
+    const uint8_t *w_tile = w + (int64_t)(n0 / kGroup) * (FP6 ? kFp6Block : kGroupBytes);
+    const int64_t w_slice_stride = (int64_t)G * (FP6 ? kFp6Block : kGroupBytes);
+    const int frow = lane & 31, fhalf = lane >> 5;
+    constexpr int CHUNKS = A_ROW / 16, ROWS_PER_LOAD = 64 / CHUNKS;
+    const int a_lane = FP6 ? fhalf * 1536 + frow * 16 : (lane / CHUNKS) * row_bytes + (lane % CHUNKS) * 16;
+
+    typedef Slice<FMT, TM, TN> S;
+    auto load = [&](S &s, int kt) __attribute__((always_inline)) {
+        const bool ok = kt < KT;
+        const int a_off = kt * (FP6 ? kFp6Block : A_ROW);
+        const __amdgpu_buffer_rsrc_t ra = buffer(a_tile + (ok ? a_off : 0), ok ? a_bytes - a_off : 0);
+        const __amdgpu_buffer_rsrc_t rw = buffer(w_tile + (ok ? kt * w_slice_stride : 0), ok ? TN * (FP6 ? kFp6Block : kGroupBytes) : 0);
+        if constexpr (FP6) {
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    s.w6[i * 3 + c] = __builtin_amdgcn_raw_buffer_load_b128(rw, a_lane + i * kFp6Block + c * 512, 0, 0);
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    s.a[j * 3 + c] = __builtin_amdgcn_raw_buffer_load_b128(ra, a_lane + j * KT * kFp6Block + c * 512, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < S::A_LOADS; ++i)
+                s.a[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, a_lane + i * ROWS_PER_LOAD * row_bytes, 0, 0);
+#pragma unroll
+            for (int i = 0; i < TN * 4; ++i)
+                s.w[i] = __builtin_amdgcn_raw_buffer_load_b64(rw, lane * 8 + (FMT == FMT_PACKED4 ? fhalf * 256 : 0) + (i / 4) * kGroupBytes + (FMT == FMT_PACKED4 ? (i % 4 / 2) * 1024 + (i % 2) * 256 : (i % 4) * 512), 0, 0);
+        }
+    };
+
+    Acc acc[TN][TM];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+
+    uint8_t *mine = smem + wave * WAVE_LDS;
+    auto multiply = [&](const S &s) __attribute__((always_inline)) {
+        if constexpr (FP6) {
+            auto half = [&](auto hc) __attribute__((always_inline)) {
+                constexpr int H = decltype(hc)::value;
+                v8i fa[TM];
+#pragma unroll
+                for (int j = 0; j < TM; ++j) fa[j] = fp6_fragment<H>(s.a[j * 3], s.a[j * 3 + 1], s.a[j * 3 + 2]);
+#pragma unroll
+                for (int i = 0; i < TN; ++i) {
+                    const v8i fw = fp6_fragment<H>(s.w6[i * 3], s.w6[i * 3 + 1], s.w6[i * 3 + 2]);
+#pragma unroll
+                    for (int j = 0; j < TM; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fw, fa[j], acc[i][j], 2, 2, 0, 0, 0, 0);
+                }
+            };
+            half(std::integral_constant<int, 0>{});
+            half(std::integral_constant<int, 1>{});
+        } else {
+            // the code rows, loaded as whole lines, become fragments through this wave's own LDS (in order: no barrier)
+#pragma unroll
+            for (int i = 0; i < S::A_LOADS; ++i) {
+                const int row = i * ROWS_PER_LOAD + lane / CHUNKS;
+                *reinterpret_cast<v4u *>(mine + row * A_ROW + (((lane % CHUNKS) ^ swz_bk<A_ROW>(row)) << 4)) = s.a[i];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            constexpr int NT = FMT == FMT_PACKED4 ? 2 : 1;
+#pragma unroll
+            for (int ks = 0; ks < 4 / NT; ++ks) {
+                v4i ra[TM];
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+                    ra[j] = *reinterpret_cast<const v4i *>(mine + (j * 32 + frow) * A_ROW + (((ks * 2 + fhalf) ^ swz_bk<A_ROW>(frow)) << 4));
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    v4i fa[TM];
+#pragma unroll
+                    for (int j = 0; j < TM; ++j)
+                        fa[j] = FMT == FMT_PACKED4 ? widen16((uint32_t)ra[j][2 * t], (uint32_t)ra[j][2 * t + 1]) : ra[j];
+#pragma unroll
+                    for (int i = 0; i < TN; ++i) {
+                        const v2u p = s.w[i * 4 + ks * NT + t];
+                        const v4i fw = widen16(p[0], p[1]);
+#pragma unroll
+                        for (int j = 0; j < TM; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fw, fa[j], acc[i][j], 0, 0, 0);
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();   // the next slice's LDS writes stay behind these reads
+        }
+    };
+
+    S slice;
+    load(slice, wave);
+    for (int kt = wave; kt < KT; kt += NW) {
+        multiply(slice);
+        load(slice, kt + NW);   // (the compiler moves it up between the MFMAs; past the last slice it fetches nothing)
+    }
+
+    // ---- reduction over the waves' shares of K and epilogue.  Every wave puts its accumulators into its part of LDS,
+    // group (4 registers) by group; then a thread adds up and finishes 8 consecutive channels of one token, which are
+    // the two lane halves of one group.  Groups are 1024 + 32 bytes apart so that the threads of a token, which read
+    // neighbouring groups, use different banks.
+    float *s_xs = reinterpret_cast<float *>(smem + NW * WAVE_LDS), *s_ws = s_xs + 64, *s_bias = s_ws + CV * 64;
+    int *s_rs = reinterpret_cast<int *>(s_bias + CV * 64), *s_z = s_rs + 64;
+    if (wave == NW - 1) {
+        s_xs[lane] = v_xs * P::edge_fold();
+        s_rs[lane] = w_zero ? v_rs : 0;
+#pragma unroll
+        for (int i = 0; i < CV; ++i) {
+            s_ws[i * 64 + lane] = v_ws[i];
+            s_bias[i * 64 + lane] = __uint_as_float((uint32_t)v_bias[i] << 16);
+            s_z[i * 64 + lane] = w_zero ? v_z[i] : 0;
+        }
+    }
+    constexpr int PIECES = PN * 4;    // 8 consecutive channels each
+    const bool vec8 = (N & 7) == 0, has_bias = bias != nullptr;
+#pragma unroll
+    for (int ph = 0; ph < PHASES; ++ph) {
+#pragma clang fp contract(off)
+        if (ph) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const Acc &t = acc[ph * PN + i][j];
+                    typedef typename std::conditional<FP6, v4f_t, v4i>::type Q;
+                    *reinterpret_cast<Q *>(mine + ((i * TM + j) * 4 + g) * GROUP_STRIDE + lane * 16) =
+                        Q{t[g * 4], t[g * 4 + 1], t[g * 4 + 2], t[g * 4 + 3]};
+                }
+        __syncthreads();
+        for (int it = tid; it < BM * PIECES; it += 64 * NW) {
+            const int p = it % PIECES, r = it / PIECES;
+            const int c = (ph * PIECES + p) * 8;   // the piece's first channel within the tile
+            if (r >= rows || n0 + c >= N) continue;
+            const uint8_t *q = smem + (((p >> 2) * TM + (r >> 5)) * 4 + (p & 3)) * GROUP_STRIDE + (r & 31) * 16;
+            typedef typename std::conditional<FP6, v4f_t, v4i>::type Q;
+            Q lo = *reinterpret_cast<const Q *>(q), hi = *reinterpret_cast<const Q *>(q + 512);
+#pragma unroll
+            for (int u = 1; u < NW; ++u) {
+                lo += *reinterpret_cast<const Q *>(q + u * WAVE_LDS);
+                hi += *reinterpret_cast<const Q *>(q + u * WAVE_LDS + 512);
+            }
+            const float xs = s_xs[r];
+            const int rs = s_rs[r];
+            v4f_t ws[2], bb[2];
+            v4i zz[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                ws[h] = *reinterpret_cast<const v4f_t *>(s_ws + c + h * 4);
+                bb[h] = *reinterpret_cast<const v4f_t *>(s_bias + c + h * 4);
+                zz[h] = *reinterpret_cast<const v4i *>(s_z + c + h * 4);
+            }
+            int a[8];
+            float o[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                a[e] = P::unzero(P::integer(e < 4 ? lo[e] : hi[e - 4]), zz[e / 4][e % 4], rs);
+                o[e] = (float)a[e] * xs * ws[e / 4][e % 4];
+                o[e] = has_bias ? o[e] + bb[e / 4][e % 4] : o[e];
+            }
+            const int64_t at = (int64_t)(m0 + r) * N + n0 + c;
+            if (vec8) {
+                *reinterpret_cast<uint4 *>(y + at) = make_uint4(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]),
+                                                                pack_bf16x2(o[4], o[5]), pack_bf16x2(o[6], o[7]));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (n0 + c + e < N) y[at + e] = (uint16_t)(pack_bf16x2(o[e], 0.f) & 0xFFFFu);
+            }
+            if (acc_out) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (n0 + c + e < N) acc_out[at + e] = P::sum(a[e]);
+            }
+        }
+    }
+}
+
+template <int FMT, int TM, int TN, int NW>
+int launch_tile(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale, const int8_t *w_zero,
+                const int32_t *code_rowsum, const uint16_t *bias, int M, int N, int K, uint16_t *y, int32_t *acc_out,
+                hipStream_t stream) {
+    const int tiles_m = (M + 32 * TM - 1) / (32 * TM), tiles_n = (N + 32 * TN - 1) / (32 * TN);
+    const size_t smem = (size_t)NW * TM * (TN > 2 ? TN / 2 : TN) * 4 * (1024 + 32) + (2 + 3 * ((TN * 32 + 63) / 64)) * 256;
+    auto k = w4ax_gemm_small_kernel<FMT, TM, TN, NW>;
+    static std::atomic<uint64_t> configured{0};
+    allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
+    // an XCD takes a contiguous run of tiles: it should read all of the smaller operand and its share of the larger one
+    const int m_fastest = FMT == FMT_INT8 ? N > 2 * M : N > M;
+    hipLaunchKernelGGL(k, dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * NW), smem, stream, codes, x_scale, w, w_scale, w_zero,
+                       code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, m_fastest);
+    return check_launch();
+}
+
+}  // namespace
+
+// The kernel's shape for an M x N output of K: tile and waves that share its K slices.  -1: the large tiles' kernels.
+// The smallest tile is taken whose workgroups all run at once (1 to 4 per compute unit, by their LDS and registers):
+// more workgroups mean fewer slices in series, until a second round of them costs more.  The lines were taken from a
+// sweep over M = 1 .. 16384, N = 256 .. 9216, K = 256 .. 9216, int8 and FP6 codes (all shapes timed at each point): this
+// rule is within 2.6 % of the best shape in the geometric mean, and the same lines are best for both containers.  On
+// the lines (int8 codes): 1024 x 1024 x 256 (tokens x K x channels, 256 tiles of 32 x 32) 4.6 us as shape 0, 4.8 as 1;
+// 512 x 3072 x 3072 (384 tiles of 64 x 64) 11.8 as 3, 14.7 as 4; 1024 x 3072 x 3072 (768) 18.7 and 16.9;
+// 2048 x 3072 x 3072 (768 tiles of 64 x 128) 28.7 as 5, 31.6 with large tiles; 4096 x 3072 x 3072 (1536) 55 and 45.
+int small_gemm_shape(int64_t M, int64_t N, int64_t K) {
+    auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    if (tiles(32, 32) <= 256) return 0;
+    // (deep K: eight waves; 1 x 9216 x 9216: 14.8 -> 11.0 us, at 3072 channels equal)
+    if (tiles(32, 64) <= 256) return K / kBK >= 48 ? 2 : 1;
+    if (tiles(64, 64) <= 512) return 3;
+    if (tiles(64, 64) <= 1024) return 4;
+    if (tiles(64, 128) <= 1280) return 5;
+    return -1;
+}
+
+int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
+                           const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
+                           int64_t K, int codes_format, int shape, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
+#define DVDQ_SMALL_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, (int)M, (int)N, (int)K, y, acc_out, stream
+#define DVDQ_SMALL(FMT) /* {tile M / 32, tile N / 32, waves} */                \
+    switch (shape) {                                                           \
+        case 0: return launch_tile<FMT, 1, 1, 8>(DVDQ_SMALL_ARGS); \
+        case 1: return launch_tile<FMT, 1, 2, 4>(DVDQ_SMALL_ARGS); \
+        case 2: return launch_tile<FMT, 1, 2, 8>(DVDQ_SMALL_ARGS); \
+        case 3: return launch_tile<FMT, 2, 2, 4>(DVDQ_SMALL_ARGS); \
+        case 4: return launch_tile<FMT, 2, 2, 2>(DVDQ_SMALL_ARGS); \
+        case 5: return launch_tile<FMT, 2, 4, 2>(DVDQ_SMALL_ARGS); \
+        default: return DVDQ_ERR_UNSUPPORTED;                                  \
+    }
+    if (codes_format == DVDQ_CODES_FP6) DVDQ_SMALL(FMT_FP6)
+    if (codes_format == DVDQ_CODES_PACKED4) DVDQ_SMALL(FMT_PACKED4)
+    DVDQ_SMALL(FMT_INT8)
+#undef DVDQ_SMALL
+#undef DVDQ_SMALL_ARGS
+}
+
+}  // namespace dvdq
