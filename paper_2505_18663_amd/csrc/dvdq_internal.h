@@ -19,10 +19,6 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
                      const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
                      int64_t K, int codes_format, int w_layout, uint16_t *y, int32_t *acc_out, hipStream_t stream);
 
-int launch_w4ax_gemm_canonical(const int8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
-                               const uint16_t *bias, int64_t M, int64_t N, int64_t K, uint16_t *y, int32_t *acc_out,
-                               hipStream_t stream);
-
 // W4A4 on the FP6 matrix path (w4a4_fp6_gemm.hip): codes and weights in the FP6 block-slice layouts
 int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                          const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
@@ -32,13 +28,14 @@ int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8
 int launch_w4ax_gemm_wide(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                           const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
                           int64_t K, bool fp6, uint16_t *y, int32_t *acc_out, hipStream_t stream);
-// Small outputs (w4ax_gemm_small.hip): any container of codes with its native weight layout.  small_gemm_shape: the
+// Small outputs, any container of codes with its native weight layout, and int8 codes with canonical weights of any
+// size (w4ax_gemm_small.hip).  small_gemm_shape: the
 // shape of tile and waves for a size, or -1 (not a small output)
 int small_gemm_shape(int64_t M, int64_t N, int64_t K);
-constexpr int kSmallVariants = 6, kFirstSmallVariant = 10;   // benchmark hook: tile variant 10 + shape forces a shape
+constexpr int kSmallVariants = 7, kFirstSmallVariant = 10;   // benchmark hook: tile variant 10 + shape forces a shape
 int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                            const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
-                           int64_t K, int codes_format, int shape, uint16_t *y, int32_t *acc_out, hipStream_t stream);
+                           int64_t K, int codes_format, int w_layout, int shape, uint16_t *y, int32_t *acc_out, hipStream_t stream);
 size_t w4_native_fp6_bytes(int64_t N, int64_t K);
 size_t codes_fp6_bytes(int64_t M, int64_t K);
 int launch_w4_prepack_fp6(const uint8_t *w_canonical, int64_t N, int64_t K, uint8_t *w_native, hipStream_t stream);

@@ -395,7 +395,7 @@ int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8
     int v = gemm_variant();
     const int shape = v < 0 ? small_gemm_shape(M, N, K) : v - kFirstSmallVariant;   // outputs of few tiles
     if (shape >= 0 && shape < kSmallVariants)
-        return launch_w4ax_gemm_small(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, DVDQ_CODES_FP6, shape, y,
+        return launch_w4ax_gemm_small(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, DVDQ_CODES_FP6, DVDQ_W_NATIVE_FP6, shape, y,
                                       acc_out, stream);
     const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
     if (v != 1 && v != 2 && v != 3) v = big_tiles >= 512 ? (K / kBK >= 10 ? 3 : 2) : 1;

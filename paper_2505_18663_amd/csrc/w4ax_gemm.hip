@@ -579,7 +579,10 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
                      int64_t K, int codes_format, int w_layout, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
     if (w_layout == DVDQ_W_CANONICAL) {
         if (codes_format != DVDQ_CODES_INT8 || w_zero) return DVDQ_ERR_UNSUPPORTED;
-        return launch_w4ax_gemm_canonical(codes, x_scale, w, w_scale, bias, M, N, K, y, acc_out, stream);
+        const int v = gemm_variant();
+        return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, nullptr, nullptr, bias, M, N,
+                                      K, codes_format, w_layout, v >= kFirstSmallVariant ? v - kFirstSmallVariant : small_gemm_shape(M, N, K),
+                                      y, acc_out, stream);
     }
     const int m = (int)M, n = (int)N, k = (int)K;
 #define DVDQ_GEMM_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, m, n, k, y, acc_out, stream
@@ -596,7 +599,7 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     const int shape = forced < 0 ? small_gemm_shape(M, N, K) : forced - kFirstSmallVariant;
     if (shape >= 0)
         return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, w_zero, code_rowsum,
-                                      bias, M, N, K, codes_format, shape, y, acc_out, stream);
+                                      bias, M, N, K, codes_format, w_layout, shape, y, acc_out, stream);
     if (codes_format == DVDQ_CODES_PACKED4) {
         if ((v == 1 && k / 128 < 2) || (v > 2 && k / 128 < 3)) v = 2;
         switch (v) {

@@ -12,6 +12,8 @@
 //   codes:   FP6 likewise.  The row-major containers are loaded as whole lines (rows of a slice: 128 or 64 bytes) and
 //            turned into fragments through the wave's own LDS; fetched as fragments directly, a load instruction
 //            would touch 32 lines.
+//            Canonical weights ([N, K/2] as an offline quantizer
+//            hands them over, K any multiple of 32) take the same way, for outputs of every size.
 //   K tails, rows past M: loads past the end of a buffer descriptor return zeros (zero codes add nothing).
 //
 // Measured (back-to-back launches, int8 codes, before -> now): 2 x 1536 x 9216 (tokens x K x channels): 22.6 -> 4.4 us;
@@ -32,7 +34,7 @@ typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kFp6Block = kGroup * kBK * 6 / 8;   // 3072: 32 rows of one K slice as E2M3 patterns
-enum { FMT_INT8 = 0, FMT_PACKED4 = 1, FMT_FP6 = 2 };
+enum { FMT_INT8 = 0, FMT_PACKED4 = 1, FMT_FP6 = 2, FMT_CANONICAL = 3 };   // (CANONICAL: int8 codes, weights [N, K/2])
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const uint8_t *p, int bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p), 0, bytes, 0x00020000);
@@ -48,6 +50,18 @@ __device__ __forceinline__ v4i widen16(uint32_t lo, uint32_t hi) {
     return f;
 }
 
+// the same for two dwords in the canonical nibble order (nibble i = channel i): the bytes of the even and the odd
+// nibbles are interleaved
+__device__ __forceinline__ v4i widen16_canonical(uint32_t lo, uint32_t hi) {
+    const v4i f = widen16(lo, hi);   // even, odd channels of each dword
+    v4i r;
+    r[0] = (int)__builtin_amdgcn_perm((uint32_t)f[1], (uint32_t)f[0], 0x05010400u);
+    r[1] = (int)__builtin_amdgcn_perm((uint32_t)f[1], (uint32_t)f[0], 0x07030602u);
+    r[2] = (int)__builtin_amdgcn_perm((uint32_t)f[3], (uint32_t)f[2], 0x05010400u);
+    r[3] = (int)__builtin_amdgcn_perm((uint32_t)f[3], (uint32_t)f[2], 0x07030602u);
+    return r;
+}
+
 // three 16-byte chunks of a row's half slice -> operand of the h-th 64-channel MFMA
 template <int H>
 __device__ __forceinline__ v8i fp6_fragment(v4u c0, v4u c1, v4u c2) {
@@ -58,11 +72,21 @@ __device__ __forceinline__ v8i fp6_fragment(v4u c0, v4u c1, v4u c2) {
 // what a wave loads of one K slice of 128 channels
 template <int FMT, int TM, int TN>
 struct Slice {
-    static constexpr int A_LOADS = TM * (FMT == FMT_INT8 ? 4 : FMT == FMT_PACKED4 ? 2 : 3);   // 16 bytes per lane each
+    static constexpr int A_LOADS = TM * (FMT == FMT_PACKED4 ? 2 : FMT == FMT_FP6 ? 3 : 4);   // 16 bytes per lane each
     v4u a[A_LOADS];
-    v2u w[FMT == FMT_FP6 ? 1 : TN * 4];
-    v4u w6[FMT == FMT_FP6 ? TN * 3 : 1];
+    v2u w[FMT == FMT_INT8 || FMT == FMT_PACKED4 ? TN * 4 : 1];
+    v4u w16[FMT == FMT_FP6 ? TN * 3 : FMT == FMT_CANONICAL ? TN * 2 : 1];
 };
+
+constexpr int kGroupStride = 1024 + 32;   // LDS bytes of one group of 4 accumulator registers (see the reduction)
+
+// LDS bytes of one wave: its part in the reduction, or its operand slice where that is larger
+template <int FMT, int TM, int TN>
+constexpr int wave_lds() {
+    const int reduction = TM * (TN > 2 ? TN / 2 : TN) * 4 * kGroupStride;
+    const int slice = FMT == FMT_FP6 ? 0 : TM * 32 * (FMT == FMT_PACKED4 ? 64 : 128) + (FMT == FMT_CANONICAL ? TN * 32 * 64 : 0);
+    return reduction > slice ? reduction : slice;
+}
 
 template <int FMT, int TM, int TN, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
@@ -70,22 +94,24 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
     const float *__restrict__ w_scale, const int8_t *__restrict__ w_zero, const int32_t *__restrict__ code_rowsum,
     const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out,
     int tiles_m, int tiles_n, int m_fastest) {
-    constexpr bool FP6 = FMT == FMT_FP6;
+    constexpr bool FP6 = FMT == FMT_FP6, CANONICAL = FMT == FMT_CANONICAL;
     constexpr int BM = 32 * TM, BN = 32 * TN;
-    constexpr int A_ROW = FMT == FMT_INT8 ? kBK : kBK / 2;     // bytes of a code row per slice (row-major containers)
+    constexpr int A_ROW = FMT == FMT_PACKED4 ? kBK / 2 : kBK;    // bytes of a code row per slice (row-major containers)
     constexpr int PHASES = TN > 2 ? 2 : 1, PN = TN / PHASES;   // the reduction takes PN columns of MFMA tiles at a time
     constexpr int NG = TM * PN * 4;                            // groups of 4 accumulator registers per phase
-    constexpr int GROUP_STRIDE = 1024 + 32;                    // LDS bytes of one group (see the reduction)
-    constexpr int WAVE_LDS = NG * GROUP_STRIDE;
+    constexpr int GROUP_STRIDE = kGroupStride;
+    constexpr int A_STAGE = FP6 ? 0 : BM * A_ROW, W_STAGE = CANONICAL ? BN * (kBK / 2) : 0;   // a wave's own slice in LDS
+    constexpr int WAVE_LDS = wave_lds<FMT, TM, TN>();
+    static_assert(NG * GROUP_STRIDE <= WAVE_LDS && A_STAGE + W_STAGE <= WAVE_LDS, "per-wave LDS");
     constexpr int CV = (BN + 63) / 64;                         // values per lane of a channel vector
     static_assert(TM <= 2 && TN <= 4 && TN % PHASES == 0, "token vectors are one value per lane");
-    typedef typename std::conditional<FP6, AccF32x64, AccI32<FMT == FMT_INT8 ? 4 : 8>>::type P;
+    typedef typename std::conditional<FP6, AccF32x64, AccI32<FMT == FMT_PACKED4 ? 8 : 4>>::type P;
     typedef typename P::vec Acc;
 
     extern __shared__ __align__(16) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int KT = K / kBK;
+    const int KT = (K + kBK - 1) / kBK;   // (CANONICAL: K % 32 == 0 only, the last slice may be a part of one)
     const int G = ((N + kNPad - 1) / kNPad) * (kNPad / kGroup);
 
     // consecutive workgroups go to different XCDs: each XCD gets a contiguous run of tiles
@@ -113,10 +139,10 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
         v_z[i] = (w_zero ? w_zero : reinterpret_cast<const int8_t *>(w_scale))[vn];
     }
 
-    const int row_bytes = FMT == FMT_INT8 ? K : K / 2;
+    const int row_bytes = FMT == FMT_PACKED4 ? K / 2 : K;
     const uint8_t *a_tile = FP6 ? codes + (int64_t)(m0 / 32) * KT * kFp6Block : codes + (int64_t)m0 * row_bytes;
     const int a_bytes = FP6 ? (rows + 31) / 32 * KT * kFp6Block : rows * row_bytes;
-    const uint8_t *w_tile = w + (int64_t)(n0 / kGroup) * (FP6 ? kFp6Block : kGroupBytes);
+    const uint8_t *w_tile = CANONICAL ? w + (int64_t)n0 * (K / 2) : w + (int64_t)(n0 / kGroup) * (FP6 ? kFp6Block : kGroupBytes);
     const int64_t w_slice_stride = (int64_t)G * (FP6 ? kFp6Block : kGroupBytes);
     const int frow = lane & 31, fhalf = lane >> 5;
     constexpr int CHUNKS = A_ROW / 16, ROWS_PER_LOAD = 64 / CHUNKS;
@@ -127,18 +153,31 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
         const bool ok = kt < KT;
         const int a_off = kt * (FP6 ? kFp6Block : A_ROW);
         const __amdgpu_buffer_rsrc_t ra = buffer(a_tile + (ok ? a_off : 0), ok ? a_bytes - a_off : 0);
-        const __amdgpu_buffer_rsrc_t rw = buffer(w_tile + (ok ? kt * w_slice_stride : 0), ok ? TN * (FP6 ? kFp6Block : kGroupBytes) : 0);
+        const int64_t w_off = CANONICAL ? kt * (kBK / 2) : kt * w_slice_stride;
+        const int w_bytes = CANONICAL ? min(BN, N - n0) * (K / 2) - (int)w_off : TN * (FP6 ? kFp6Block : kGroupBytes);
+        const __amdgpu_buffer_rsrc_t rw = buffer(w_tile + (ok ? w_off : 0), ok ? w_bytes : 0);
         if constexpr (FP6) {
 #pragma unroll
             for (int i = 0; i < TN; ++i)
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
-                    s.w6[i * 3 + c] = __builtin_amdgcn_raw_buffer_load_b128(rw, a_lane + i * kFp6Block + c * 512, 0, 0);
+                    s.w16[i * 3 + c] = __builtin_amdgcn_raw_buffer_load_b128(rw, a_lane + i * kFp6Block + c * 512, 0, 0);
 #pragma unroll
             for (int j = 0; j < TM; ++j)
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
                     s.a[j * 3 + c] = __builtin_amdgcn_raw_buffer_load_b128(ra, a_lane + j * KT * kFp6Block + c * 512, 0, 0);
+        } else if constexpr (CANONICAL) {
+            // a lane whose channels lie past K (in a last part of a slice) reads past the descriptor instead
+            const int k_left = K - kt * kBK, beyond = 0x7FFFFFF0;
+            const int a_at = (lane % CHUNKS) * 16 < k_left ? a_lane : beyond;
+            const int w_at = (lane % 4) * 32 < k_left ? (lane / 4) * (K / 2) + (lane % 4) * 16 : beyond;
+#pragma unroll
+            for (int i = 0; i < S::A_LOADS; ++i)
+                s.a[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, a_at == beyond ? beyond : a_at + i * ROWS_PER_LOAD * row_bytes, 0, 0);
+#pragma unroll
+            for (int i = 0; i < TN * 2; ++i)
+                s.w16[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, w_at == beyond ? beyond : w_at + i * 16 * (K / 2), 0, 0);
         } else {
 #pragma unroll
             for (int i = 0; i < S::A_LOADS; ++i)
@@ -167,7 +206,7 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
                 for (int j = 0; j < TM; ++j) fa[j] = fp6_fragment<H>(s.a[j * 3], s.a[j * 3 + 1], s.a[j * 3 + 2]);
 #pragma unroll
                 for (int i = 0; i < TN; ++i) {
-                    const v8i fw = fp6_fragment<H>(s.w6[i * 3], s.w6[i * 3 + 1], s.w6[i * 3 + 2]);
+                    const v8i fw = fp6_fragment<H>(s.w16[i * 3], s.w16[i * 3 + 1], s.w16[i * 3 + 2]);
 #pragma unroll
                     for (int j = 0; j < TM; ++j)
                         acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fw, fa[j], acc[i][j], 2, 2, 0, 0, 0, 0);
@@ -181,6 +220,17 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
             for (int i = 0; i < S::A_LOADS; ++i) {
                 const int row = i * ROWS_PER_LOAD + lane / CHUNKS;
                 *reinterpret_cast<v4u *>(mine + row * A_ROW + (((lane % CHUNKS) ^ swz_bk<A_ROW>(row)) << 4)) = s.a[i];
+            }
+            if constexpr (CANONICAL) {
+                // packed weight rows of 64 bytes.  A fragment is 8 bytes: the halves of a 16-byte chunk are swapped in
+                // every second group of 16 rows, so that the 32 rows a read serves at a time use all 64 banks
+#pragma unroll
+                for (int i = 0; i < TN * 2; ++i) {
+                    const int row = i * 16 + lane / 4;
+                    const v4u q = s.w16[i];
+                    *reinterpret_cast<v4u *>(mine + A_STAGE + row * 64 + (((lane % 4) ^ swz_bk<64>(row)) << 4)) =
+                        (i & 1) ? v4u{q[2], q[3], q[0], q[1]} : q;
+                }
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -200,8 +250,15 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
                         fa[j] = FMT == FMT_PACKED4 ? widen16((uint32_t)ra[j][2 * t], (uint32_t)ra[j][2 * t + 1]) : ra[j];
 #pragma unroll
                     for (int i = 0; i < TN; ++i) {
-                        const v2u p = s.w[i * 4 + ks * NT + t];
-                        const v4i fw = widen16(p[0], p[1]);
+                        v4i fw;
+                        if constexpr (CANONICAL) {
+                            const v2u p = *reinterpret_cast<const v2u *>(mine + A_STAGE + (i * 32 + frow) * 64 +
+                                                                         ((ks ^ swz_bk<64>(frow)) << 4) + ((fhalf ^ (frow >> 4)) << 3));
+                            fw = widen16_canonical(p[0], p[1]);
+                        } else {
+                            const v2u p = s.w[i * 4 + ks * NT + t];
+                            fw = widen16(p[0], p[1]);
+                        }
 #pragma unroll
                         for (int j = 0; j < TM; ++j)
                             acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fw, fa[j], acc[i][j], 0, 0, 0);
@@ -306,12 +363,12 @@ int launch_tile(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
                 const int32_t *code_rowsum, const uint16_t *bias, int M, int N, int K, uint16_t *y, int32_t *acc_out,
                 hipStream_t stream) {
     const int tiles_m = (M + 32 * TM - 1) / (32 * TM), tiles_n = (N + 32 * TN - 1) / (32 * TN);
-    const size_t smem = (size_t)NW * TM * (TN > 2 ? TN / 2 : TN) * 4 * (1024 + 32) + (2 + 3 * ((TN * 32 + 63) / 64)) * 256;
+    const size_t smem = (size_t)NW * wave_lds<FMT, TM, TN>() + (2 + 3 * ((TN * 32 + 63) / 64)) * 256;
     auto k = w4ax_gemm_small_kernel<FMT, TM, TN, NW>;
     static std::atomic<uint64_t> configured{0};
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
     // an XCD takes a contiguous run of tiles: it should read all of the smaller operand and its share of the larger one
-    const int m_fastest = FMT == FMT_INT8 ? N > 2 * M : N > M;
+    const int m_fastest = FMT == FMT_INT8 || FMT == FMT_CANONICAL ? N > 2 * M : N > M;
     hipLaunchKernelGGL(k, dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * NW), smem, stream, codes, x_scale, w, w_scale, w_zero,
                        code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, m_fastest);
     return check_launch();
@@ -340,7 +397,7 @@ int small_gemm_shape(int64_t M, int64_t N, int64_t K) {
 
 int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                            const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
-                           int64_t K, int codes_format, int shape, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
+                           int64_t K, int codes_format, int w_layout, int shape, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
 #define DVDQ_SMALL_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, (int)M, (int)N, (int)K, y, acc_out, stream
 #define DVDQ_SMALL(FMT) /* {tile M / 32, tile N / 32, waves} */                \
     switch (shape) {                                                           \
@@ -350,10 +407,18 @@ int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uin
         case 3: return launch_tile<FMT, 2, 2, 4>(DVDQ_SMALL_ARGS); \
         case 4: return launch_tile<FMT, 2, 2, 2>(DVDQ_SMALL_ARGS); \
         case 5: return launch_tile<FMT, 2, 4, 2>(DVDQ_SMALL_ARGS); \
+        case 6: return launch_tile<FMT, 2, 4, 1>(DVDQ_SMALL_ARGS);             \
         default: return DVDQ_ERR_UNSUPPORTED;                                  \
     }
+    // Canonical weights have no other kernel: outputs beyond the lines above take a wave per 64 x 128 tile, all of K in
+    // one wave.  (Codes and weights come in rows of K and K / 2 bytes; a slice of a weight row is half a cache line, and
+    // that traffic out of the L2 is the limit.  7800 x 1440 x 1440: 61.7 us with 256 x 256 tiles shared by four waves,
+    // 43.9 as shape 5, 40.0 as 6; 512 x 3072 x 3072: 83.4 -> 15.5 as 3; 32760 x 1536 x 4608: 543 -> 349 as 6;
+    // 32760 x 13824 x 5120: 2792 -> 2749.)
+    if (w_layout == DVDQ_W_CANONICAL && shape < 0) shape = 6;
     if (codes_format == DVDQ_CODES_FP6) DVDQ_SMALL(FMT_FP6)
     if (codes_format == DVDQ_CODES_PACKED4) DVDQ_SMALL(FMT_PACKED4)
+    if (w_layout == DVDQ_W_CANONICAL) DVDQ_SMALL(FMT_CANONICAL)
     DVDQ_SMALL(FMT_INT8)
 #undef DVDQ_SMALL
 #undef DVDQ_SMALL_ARGS

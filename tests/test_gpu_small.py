@@ -7,6 +7,7 @@ import torch
 
 import oracle
 import paper_2505_18663_amd as dvdq
+from parity import check_y
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -64,7 +65,27 @@ def test_every_shape_is_exact_and_equal_to_the_large_tiles(M, K, N, fmt):
             return y, acc
 
         y_large, _ = run(1 if fmt == "fp6" else 2)
-        for variant in (-1, 10, 11, 12, 13, 14, 15):
+        for variant in (-1, 10, 11, 12, 13, 14, 15, 16):
             y, acc = run(variant)
             assert np.array_equal(acc.cpu().numpy().astype(np.int64), acc_ref), f"variant {variant} zero {zero}"
             assert torch.equal(y.view(torch.int16), y_large.view(torch.int16)), f"variant {variant} zero {zero}"
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 32, 1), (33, 96, 40), (65, 1440, 331), (64, 128, 128), (130, 2080, 264), (1100, 224, 2056)])
+def test_canonical_weights_every_shape_exact(M, K, N):
+    """K a multiple of 32: last slices of 32, 64 and 96 channels, a single part of a slice"""
+    rng = np.random.default_rng(M + K + N)
+    codes = rng.integers(-127, 128, (M, K)).astype(np.int8)
+    wc = rng.integers(-8, 8, (N, K)).astype(np.int8)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    xs, ws = (rng.random(M) + 0.01).astype(np.float32), (rng.random(N) * 0.01 + 1e-3).astype(np.float32)
+    bias = d(rng.standard_normal(N).astype(np.float32)).to(torch.bfloat16)
+    bias_bits = bias.cpu().view(torch.int16).numpy().view(np.uint16)
+    y_ref, acc_ref = oracle.w4ax_gemm(codes, xs, oracle.pack_w4(wc), ws, bias_bits, return_acc=True)
+    for variant in (-1, 10, 11, 12, 13, 14, 15, 16):
+        print(f"canonical M{M} K{K} N{N} variant {variant}", flush=True)
+        dvdq.bench_set_gemm_variant(variant)
+        y, acc = dvdq.w4ax_gemm(d(codes), d(xs), d(oracle.pack_w4(wc)), d(ws), 8, dvdq.W_CANONICAL, bias=bias, want_acc=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(acc.cpu().numpy().astype(np.int64), acc_ref), f"variant {variant}"
+        check_y(y.cpu().view(torch.int16).numpy().view(np.uint16), y_ref, f"canonical variant {variant}", bias_bits)
