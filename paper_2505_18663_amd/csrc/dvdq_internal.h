@@ -46,10 +46,10 @@ void set_gemm_schedule(int v); // benchmark only; 0 = fixed tile shares, -1 = dr
 void set_gemm_grid_limit(int v); // benchmark only; 0 = persistent grids fill the chip, else at most v workgroups
 int limited_grid(int grid);
 // the stream's tile-counter slot (16 words; nullptr: fixed tile shares): for a GEMM, with whether the kernel enqueued last
-// on the stream zeroes it; for a quantizer, the words to zero and the note that it does (w4ax_gemm.hip)
+// on the stream zeroes it; for a quantizer, the words to zero, noted as zeroed unless taken back (w4ax_gemm.hip)
 unsigned *sched_slot(hipStream_t stream, bool *is_clear);
 unsigned *sched_slot_to_clear(hipStream_t stream);
-void sched_slot_cleared(hipStream_t stream);
+void sched_slot_not_cleared(hipStream_t stream);
 void release_sched_slot(hipStream_t stream);               // forget a stream's tile-counter slot (host bookkeeping only)
 int fill_sched_slots(uint32_t value, hipStream_t stream);  // robustness tests only: overwrite every tile counter
 

@@ -489,17 +489,19 @@ unsigned *sched_slot(hipStream_t stream, bool *is_clear) {
     return slot;
 }
 
-// For a quantizer about to be enqueued on `stream`: the 16 words it should zero (or nullptr), and, once it
-// is enqueued, the note that it does.
+// For a quantizer about to be enqueued on `stream`: the 16 words it should zero (or nullptr), noted as zeroed by it;
+// if it could not be enqueued, the note is taken back.
 unsigned *sched_slot_to_clear(hipStream_t stream) {
     std::lock_guard<std::mutex> lock(g_sched_mu);
     int dev = 0, index = 0;
-    return slot_of_stream(stream, &dev, &index);
+    unsigned *slot = slot_of_stream(stream, &dev, &index);
+    if (slot) g_sched_table[dev].clear[index] = true;
+    return slot;
 }
-void sched_slot_cleared(hipStream_t stream) {
+void sched_slot_not_cleared(hipStream_t stream) {
     std::lock_guard<std::mutex> lock(g_sched_mu);
     int dev = 0, index = 0;
-    if (slot_of_stream(stream, &dev, &index)) g_sched_table[dev].clear[index] = true;
+    if (slot_of_stream(stream, &dev, &index)) g_sched_table[dev].clear[index] = false;
 }
 
 int clear_sched_slot(unsigned *slot, hipStream_t stream) {
