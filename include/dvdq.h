@@ -285,7 +285,7 @@ int dvdq_bgr_quantize(const float *w, int64_t N, int64_t K, int n_steps, int max
  * or bits = b_high and sum = 0 once it reaches `delta` (the B_{t_i} case equation).
  * A zero denominator gives +inf (or 0 when the numerator is zero too).
  * `workspace`: device, at least dvdq_gbs_workspace_bytes() bytes, scratch.
- * delta >= 0; b_low <= b_high, each 4, 6 or 8.  Results are bit-reproducible (no atomics).
+ * delta >= 0; b_low <= b_high, each 4, 6 or 8.  Results are bit-reproducible (fixed order of summation).
  */
 size_t dvdq_gbs_workspace_bytes(void);
 int dvdq_gbs_reset(void *state, int initial_bits, void *hip_stream);
