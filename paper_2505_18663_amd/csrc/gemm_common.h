@@ -23,14 +23,25 @@ static __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
     return __builtin_bit_cast(uint32_t, p);
 }
 
-// 16-byte store of output the kernel never reads again.  Non-temporal: with whole 128-byte lines
-// per instruction (the staged epilogue) the output stream then bypasses the L2 instead of evicting
-// code and weight panels and leaving dirty lines to flush at the kernel's end.  (For partial-line
+// 16-byte store of output the kernel never reads again, at byte `off` of the tile's buffer (output_tile below).
+// Non-temporal: with whole 128-byte lines per instruction (the staged epilogue) the output stream then bypasses the L2
+// instead of evicting code and weight panels and leaving dirty lines to flush at the kernel's end.  (For partial-line
 // stores the same hint is much slower than write-back caching.)
-static __device__ __forceinline__ void store_streaming16(uint16_t *p, uint4 v) {
+static __device__ __forceinline__ void store_streaming16(__amdgpu_buffer_rsrc_t tile, uint32_t off, uint4 v) {
     typedef uint32_t v4u __attribute__((ext_vector_type(4)));
     const v4u vv = {v.x, v.y, v.z, v.w};
-    __builtin_nontemporal_store(vv, reinterpret_cast<v4u *>(p));
+    __builtin_amdgcn_raw_buffer_store_b128(vv, tile, (int)off, 0, 2 /* nt */);
+}
+
+// Buffer of the output rows from m0 on, starting at channel n0, at most bm of them: what lies past row M is past the
+// buffer's end, so that a tile at the lower edge of the output is stored by the same instructions as any other (lanes
+// past the end are dropped).  Channels past N are the caller's to drop: kPastTile as the offset of a column group does,
+// whatever row offset is added to it.  Offsets are 32 bits: N below kMaxTileN.
+constexpr int64_t kMaxTileN = (int64_t)1 << 22;
+constexpr uint32_t kPastTile = 0x80000000u;
+static __device__ __forceinline__ __amdgpu_buffer_rsrc_t output_tile(uint16_t *y, int m0, int n0, int M, int N, int bm) {
+    const int rows = min(bm, M - m0);
+    return __builtin_amdgcn_make_buffer_rsrc(y + (int64_t)m0 * N + n0, 0, (rows * N - n0) * 2, 0x00020000);
 }
 
 // vmcnt-only wait (leave expcnt / lgkmcnt alone): gfx9 encoding, vmcnt = {imm[15:14], imm[3:0]}
@@ -211,9 +222,11 @@ struct TileVectors {
     static constexpr int BYTES = OFF_ZERO + BN;
 };
 
-// Interior tile (whole tile inside M x N, N a multiple of 8; specialized on zero-points and, where the caller
-// can afford the code, on bias: a run-time test inside the unrolled loops costs a branch per register group): no predicates, every vector the epilogue needs
-// comes from LDS, one row pointer per lane.  The bf16 tile goes through LDS so that every store instruction
+// Any tile of an output with N a multiple of 8 (below kMaxTileN; tiles at the edges included: see output_tile; specialized on zero-points and, where the caller
+// can afford the code, on bias: a run-time test inside the unrolled loops costs a branch per register group): no predicates, every
+// vector the epilogue needs comes from LDS, one row offset per lane.  (Edge tiles used to go through epilogue_edge, per
+// element with a global load per zero-point; on outputs whose token count is no multiple of the tile the last tiles of a
+// launch then ran several times as long as the others: 5000 x 512 x 3072 with zero-points 27.7 us, now 17.5 (int8 codes).)  The bf16 tile goes through LDS so that every store instruction
 // writes whole 128-byte lines: in the accumulator layout a lane owns one token and 8 consecutive channels per
 // register group, so a direct store touches 32 token rows with 32 bytes each.  32 tokens x 64 channels at a
 // time are staged in `stg` (this wave's 4 KB of the ring buffer whose slice was consumed last: after the
@@ -227,7 +240,7 @@ struct TileVectors {
 template <class P, int BM, int BN, int TM, int TN, bool ZP, int BIAS>
 static __device__ __forceinline__ void epilogue_interior(typename P::vec (&acc)[TN][TM], const uint8_t *s_tile, bool has_bias,
                                                          int lane, int wm, int wn, uint8_t *stg, uint16_t *y, int m0,
-                                                         int n0, int N) {
+                                                         int n0, int M, int N) {
     // (scale, then add the bias, each rounded: a fused multiply-add would differ from the per-element path in the last bit)
 #pragma clang fp contract(off)
     if constexpr (BIAS >= 0) has_bias = BIAS != 0;
@@ -246,6 +259,8 @@ static __device__ __forceinline__ void epilogue_interior(typename P::vec (&acc)[
         rsum[j] = ZP ? s_rsum[wm + j * 32 + frow] : 0;
     }
     const int rd_row = lane >> 3, rd_piece = lane & 7;
+    const __amdgpu_buffer_rsrc_t tile = output_tile(y, m0, n0, M, N, BM);
+    const uint32_t lane_off = ((wm + rd_row) * N + wn + rd_piece * 8) * 2;
     struct ChannelVec { float4 ws; uint2 bb; uint32_t zq; };
     auto fetch = [&] __device__(ChannelVec &cv, int i, int g) {
         const int c = i * 32 + g * 8;
@@ -310,7 +325,7 @@ static __device__ __forceinline__ void epilogue_interior(typename P::vec (&acc)[
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            uint16_t *yb = y + (int64_t)(m0 + wm + j * 32 + rd_row) * N + (n0 + wn + ip * 64 + rd_piece * 8);
+            const uint32_t off = n0 + wn + ip * 64 + rd_piece * 8 < N ? lane_off + (j * 32 * N + ip * 64) * 2 : kPastTile;
             uint4 v[4];
 #pragma unroll
             for (int pass = 0; pass < 4; ++pass) {
@@ -318,13 +333,13 @@ static __device__ __forceinline__ void epilogue_interior(typename P::vec (&acc)[
                 v[pass] = *reinterpret_cast<const uint4 *>(stg + row * 128 + ((rd_piece ^ (row & 7)) << 4));
             }
 #pragma unroll
-            for (int pass = 0; pass < 4; ++pass) store_streaming16(yb + (int64_t)pass * 8 * N, v[pass]);
+            for (int pass = 0; pass < 4; ++pass) store_streaming16(tile, off + pass * 16 * N, v[pass]);
             __builtin_amdgcn_wave_barrier();   // the next chunk's LDS writes stay behind these reads
         }
     }
 }
 
-// Edge tiles, N not a multiple of 8, or the accumulator hook: predicated per element, through the integer
+// N not a multiple of 8 (or kMaxTileN and more), or the accumulator hook: predicated per element, through the integer
 // accumulator (same values and rounding order as the interior path).  The accumulators are left at zero.
 template <class P, int BM, int BN, int TM, int TN>
 static __device__ __forceinline__ void epilogue_edge(typename P::vec (&acc)[TN][TM], const uint8_t *s_tile, const uint16_t *bias,

@@ -141,22 +141,24 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4a4_fp6_gemm_ker
                 else
                     lds_direct_load4(w_scale, (uint32_t)min(n0 + (j - BM / 64) * 64 + lane, N - 1) * 4, sc + j * 256);
             }
-            if (bias && n0 + BN <= N) {
+            // (bias and zero-points go to LDS, pairs and fours of channels at a time, where N is a multiple of 8; else the
+            // epilogue reads them from memory)
+            if (bias && (N & 7) == 0) {
 #pragma unroll
                 for (int j = 0; j < BN / 128; ++j)
                     if (j % NW == wave)
-                        lds_direct_load4(bias + n0, (uint32_t)(j * 64 + lane) * 4, sc + OFF_BIAS + j * 256);
+                        lds_direct_load4(bias, (uint32_t)min(n0 / 2 + j * 64 + lane, N / 2 - 1) * 4, sc + OFF_BIAS + j * 256);
             }
             if (w_zero) {
 #pragma unroll
                 for (int j = 0; j < BM / 64; ++j)
                     if (j % NW == wave)
                         lds_direct_load4(code_rowsum, (uint32_t)min(m0 + j * 64 + lane, M - 1) * 4, sc + OFF_RSUM + j * 256);
-                if (n0 + BN <= N) {
+                if ((N & 7) == 0) {
 #pragma unroll
                     for (int j = 0; j < BN / 256; ++j)
                         if (j % NW == wave)
-                            lds_direct_load4(w_zero + n0, (uint32_t)(j * 64 + lane) * 4, sc + OFF_ZERO + j * 256);
+                            lds_direct_load4(w_zero, (uint32_t)min(n0 / 4 + j * 64 + lane, N / 4 - 1) * 4, sc + OFF_ZERO + j * 256);
                 }
             }
         }
@@ -284,16 +286,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4a4_fp6_gemm_ker
         // back: computed here once per tile instead of being kept (and spilled) across the K loop.
         int lane_e = lane;
         asm volatile("" : "+v"(lane_e));
-        if ((N & 7) == 0 && !acc_out && m0 + BM <= M && n0 + BN <= N) {
+        if ((N & 7) == 0 && !acc_out && N < kMaxTileN) {
             if (KT >= STAGES) store_credit = STAGES - 1;
             uint8_t *stg = smem + (q % STAGES) * STAGE + wave * 4096;
             __builtin_amdgcn_s_barrier();   // every wave is done reading the last slice: its buffer stages the tile
             if (w_zero) {
-                if (bias) epilogue_interior<AccF32x64, BM, BN, TM, TN, true, 1>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, N);
-                else epilogue_interior<AccF32x64, BM, BN, TM, TN, true, 0>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, N);
+                if (bias) epilogue_interior<AccF32x64, BM, BN, TM, TN, true, 1>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
+                else epilogue_interior<AccF32x64, BM, BN, TM, TN, true, 0>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
             } else {
-                if (bias) epilogue_interior<AccF32x64, BM, BN, TM, TN, false, 1>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, N);
-                else epilogue_interior<AccF32x64, BM, BN, TM, TN, false, 0>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, N);
+                if (bias) epilogue_interior<AccF32x64, BM, BN, TM, TN, false, 1>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
+                else epilogue_interior<AccF32x64, BM, BN, TM, TN, false, 0>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
             }
         } else {
             epilogue_edge<AccF32x64, BM, BN, TM, TN>(acc, s_tile, bias, w_zero, lane_e, wm, wn, y, acc_out, m0, n0, M, N);

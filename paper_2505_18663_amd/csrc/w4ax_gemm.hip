@@ -176,23 +176,24 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
                 else
                     lds_direct_load4(w_scale, (uint32_t)min(n0 + (j - BM / 64) * 64 + lane, N - 1) * 4, sc + j * 256);
             }
-            // bias of a tile that lies fully inside N (the only case in which the epilogue reads it from LDS)
-            if (bias && n0 + BN <= N) {
+            // (bias and zero-points go to LDS, pairs and fours of channels at a time, where N is a multiple of 8; else the
+            // epilogue reads them from memory)
+            if (bias && (N & 7) == 0) {
 #pragma unroll
                 for (int j = 0; j < BN / 128; ++j)
                     if (j % NW == wave)
-                        lds_direct_load4(bias + n0, (uint32_t)(j * 64 + lane) * 4, sc + OFF_BIAS + j * 256);
+                        lds_direct_load4(bias, (uint32_t)min(n0 / 2 + j * 64 + lane, N / 2 - 1) * 4, sc + OFF_BIAS + j * 256);
             }
             if (w_zero) {
 #pragma unroll
                 for (int j = 0; j < BM / 64; ++j)
                     if (j % NW == wave)
                         lds_direct_load4(code_rowsum, (uint32_t)min(m0 + j * 64 + lane, M - 1) * 4, sc + OFF_RSUM + j * 256);
-                if (n0 + BN <= N) {
+                if ((N & 7) == 0) {
 #pragma unroll
                     for (int j = 0; j < BN / 256; ++j)
                         if (j % NW == wave)
-                            lds_direct_load4(w_zero + n0, (uint32_t)(j * 64 + lane) * 4, sc + OFF_ZERO + j * 256);
+                            lds_direct_load4(w_zero, (uint32_t)min(n0 / 4 + j * 64 + lane, N / 4 - 1) * 4, sc + OFF_ZERO + j * 256);
                 }
             }
         }
@@ -357,18 +358,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
         comp_tile = __builtin_amdgcn_readfirstlane(s_tiles[tile_j & 7]);   // the next one (its loads are under way)
         const uint8_t *s_tile = smem + STAGES * STAGE + ((tile_j - 1) & 1) * SCALES;
         typedef AccI32<SHIFT> Acc;
-        if ((N & 7) == 0 && !acc_out && m0 + BM <= M && n0 + BN <= N) {
-            // Interior tile: every lane of every wave stores all its values, so the number of stores is exact
-            // (see the store-aware wait above).
+        int lane_e = lane;   // (keeps the epilogue's lane-dependent addresses out of the K loop's registers)
+        asm volatile("" : "+v"(lane_e));
+        if ((N & 7) == 0 && !acc_out && N < kMaxTileN) {
+            // Every wave issues the same number of stores, whatever its tile (see the store-aware wait above).
             if (KT >= STAGES) store_credit = STAGES - 1 - AHEAD;
             uint8_t *stg = smem + (q % STAGES) * STAGE + wave * 4096;
             __builtin_amdgcn_s_barrier();   // every wave is done reading the last slice: its buffer stages the tile
             // Two specializations, with and without weight zero-points, chosen once per tile (with four, bias as
             // well, this kernel spills).
-            if (w_zero) epilogue_interior<Acc, BM, BN, TM, TN, true, -1>(acc, s_tile, bias != nullptr, lane, wm, wn, stg, y, m0, n0, N);
-            else epilogue_interior<Acc, BM, BN, TM, TN, false, -1>(acc, s_tile, bias != nullptr, lane, wm, wn, stg, y, m0, n0, N);
+            if (w_zero) epilogue_interior<Acc, BM, BN, TM, TN, true, -1>(acc, s_tile, bias != nullptr, lane_e, wm, wn, stg, y, m0, n0, M, N);
+            else epilogue_interior<Acc, BM, BN, TM, TN, false, -1>(acc, s_tile, bias != nullptr, lane_e, wm, wn, stg, y, m0, n0, M, N);
         } else {
-            epilogue_edge<Acc, BM, BN, TM, TN>(acc, s_tile, bias, w_zero, lane, wm, wn, y, acc_out, m0, n0, M, N);
+            epilogue_edge<Acc, BM, BN, TM, TN>(acc, s_tile, bias, w_zero, lane_e, wm, wn, y, acc_out, m0, n0, M, N);
         }
         if (comp_tile < 0) break;
     }

@@ -218,22 +218,24 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                 else
                     lds_direct_load4(w_scale, (uint32_t)min(n0 + (j - BM / 64) * 64 + lane, N - 1) * 4, sc + j * 256);
             }
-            if (bias && n0 + BN <= N) {
+            // (bias and zero-points go to LDS, pairs and fours of channels at a time, where N is a multiple of 8; else the
+            // epilogue reads them from memory)
+            if (bias && (N & 7) == 0) {
 #pragma unroll
                 for (int j = 0; j < BN / 128; ++j)
                     if (j % NW == wave)
-                        lds_direct_load4(bias + n0, (uint32_t)(j * 64 + lane) * 4, sc + OFF_BIAS + j * 256);
+                        lds_direct_load4(bias, (uint32_t)min(n0 / 2 + j * 64 + lane, N / 2 - 1) * 4, sc + OFF_BIAS + j * 256);
             }
             if (w_zero) {
 #pragma unroll
                 for (int j = 0; j < BM / 64; ++j)
                     if (j % NW == wave)
                         lds_direct_load4(code_rowsum, (uint32_t)min(m0 + j * 64 + lane, M - 1) * 4, sc + OFF_RSUM + j * 256);
-                if (n0 + BN <= N) {
+                if ((N & 7) == 0) {
 #pragma unroll
                     for (int j = 0; j < BN / 256; ++j)
                         if (j % NW == wave)
-                            lds_direct_load4(w_zero + n0, (uint32_t)(j * 64 + lane) * 4, sc + OFF_ZERO + j * 256);
+                            lds_direct_load4(w_zero, (uint32_t)min(n0 / 4 + j * 64 + lane, N / 4 - 1) * 4, sc + OFF_ZERO + j * 256);
                 }
             }
         }
@@ -529,8 +531,8 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
         // staging: 4 KB per wave in the weight half of the buffer of the slice consumed last (next to be filled; on
         // the FP6 path its code half is already being filled with the next tile's slice 2 while the epilogue runs)
         uint8_t *stg = smem + fill_off + A_STAGE + wave * 4096;
-        if (vec8 && !acc_out && m0 + BM <= M && n0 + BN <= N) {
-            // ---- interior tile: no predicates; channel vectors fetched one register group ahead; the bf16 tile
+        if (vec8 && !acc_out && N < kMaxTileN) {
+            // ---- N a multiple of 8, tiles at the edges included (see output_tile): no predicates; channel vectors fetched one register group ahead; the bf16 tile
             // is transposed through LDS, 32 tokens x 64 channels at a time, into whole-line streaming stores
             if (KT >= 2) store_credit = 1;
             // Four specializations (zero-points, bias), chosen once per tile: inside the unrolled units a run-time
@@ -569,7 +571,8 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                 ChannelVec cv[8];
                 uint32_t pk[2][2];
                 uint4 pend[4];            // a staged chunk on its way back from LDS, and where it goes
-                uint16_t *pend_y = y;
+                uint32_t pend_off = 0, col_off = 0;   // byte offsets within the tile: of that chunk; of this lane's channels
+                const __amdgpu_buffer_rsrc_t tile = output_tile(y, m0, n0, M, N, BM);
                 // 64 units of 4 values: unit u = ((ip * TM + j) * 2 + ii) * 4 + (g + h), MFMA tile column i = 2 ip + ii,
                 // token block j, accumulator registers 4 (g + h) .. + 3; 8 units make a 32-token x 64-channel chunk
                 static_for<(TN / 2) * TM * 8>([&](auto u_c) __attribute__((always_inline)) {
@@ -578,6 +581,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                     if constexpr (U % (8 * TM) == 0) {
 #pragma unroll
                         for (int v = 0; v < 8; ++v) fetch(cv[v], 2 * ip + (v >> 2), v & 3);
+                        col_off = n0 + wn + ip * 64 + rd_piece * 8 < N ? ((wm + rd_row) * N + wn + ip * 64 + rd_piece * 8) * 2 : kPastTile;
                     }
                     const ChannelVec &c = cv[ii * 4 + q];
                     const v4i raw = read_acc4<i * TM + j, q>();
@@ -624,14 +628,14 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                     if constexpr (U == 11) publish_draw();
                     if constexpr ((U & 7) == 3 && U > 8) {
 #pragma unroll
-                        for (int pass = 0; pass < 4; ++pass) store_streaming16(pend_y + (int64_t)pass * 8 * N, pend[pass]);
+                        for (int pass = 0; pass < 4; ++pass) store_streaming16(tile, pend_off + pass * 16 * N, pend[pass]);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     if constexpr ((U & 7) == 7) {   // the chunk is staged: whole rows back, 8 lanes per 128-byte row
                         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                         __builtin_amdgcn_wave_barrier();
                         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        pend_y = y + (int64_t)(m0 + wm + j * 32 + rd_row) * N + (n0 + wn + ip * 64 + rd_piece * 8);
+                        pend_off = col_off + j * 64 * N;
                         const uint8_t *sg = stg;
 #pragma unroll
                         for (int pass = 0; pass < 4; ++pass) {
@@ -643,7 +647,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                     }
                 });
 #pragma unroll
-                for (int pass = 0; pass < 4; ++pass) store_streaming16(pend_y + (int64_t)pass * 8 * N, pend[pass]);   // the last chunk
+                for (int pass = 0; pass < 4; ++pass) store_streaming16(tile, pend_off + pass * 16 * N, pend[pass]);   // the last chunk
             };
             if (w_zero) {
                 if (bias) interior(std::true_type{}, std::true_type{});
@@ -653,7 +657,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                 else interior(std::false_type{}, std::false_type{});
             }
         } else {
-            // ---- edge tiles, N not a multiple of 8, or the accumulator hook: predicated per element, through the
+            // ---- N not a multiple of 8 (or kMaxTileN and more), or the accumulator hook: predicated per element, through the
             // integer accumulator (same values and rounding order as the interior path)
             int lane_s = lane;
             asm volatile("" : "+v"(lane_s));
