@@ -39,7 +39,7 @@ int dvdq_bench_mfma_fp6(int iters, int data, int32_t *sink, double *ops_out, voi
 
 /* Tile-configuration sweeps: force the native-layout GEMMs to use tile variant `variant`
  * (INT8 matrix path: 1..4, see the dispatch tables in w4ax_gemm.hip, one per code container; shapes too
- * shallow in K for a variant's ring fall back to variant 2.  FP6 matrix path: 1..2, see w4a4_fp6_gemm.hip,
+ * shallow in K for a variant's ring fall back to variant 2.  FP6 matrix path: 1 and 3, see w4a4_fp6_gemm.hip,
  * other values mean its own choice; either path: 10..16 force a shape of the small-output kernel, see
  * w4ax_gemm_small.hip); -1 restores the library's own choice.  Process-wide (an atomic
  * that every launch reads once), meant for benchmarking only. */

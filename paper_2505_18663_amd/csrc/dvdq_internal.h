@@ -31,7 +31,7 @@ int launch_w4ax_gemm_wide(const uint8_t *codes, const float *x_scale, const uint
 // Small outputs, any container of codes with its native weight layout, and int8 codes with canonical weights of any
 // size (w4ax_gemm_small.hip).  small_gemm_shape: the
 // shape of tile and waves for a size, or -1 (not a small output)
-int small_gemm_shape(int64_t M, int64_t N, int64_t K);
+int small_gemm_shape(int64_t M, int64_t N, int64_t K, bool fp6);
 constexpr int kSmallVariants = 7, kFirstSmallVariant = 10;   // benchmark hook: tile variant 10 + shape forces a shape
 int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                            const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,

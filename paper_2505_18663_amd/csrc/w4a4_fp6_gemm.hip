@@ -381,29 +381,22 @@ int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8
                          const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
                          int64_t K, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
 #define DVDQ_FP6_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, (int)M, (int)N, (int)K, y, acc_out, stream
-    // Tile variants {tile M, tile N, waves M x N, ring depth, workgroups per compute unit}:
+    // Outputs of few tiles go to w4ax_gemm_small.hip (small_gemm_shape).  Tile variants of the others:
     //   1: two independent 4-wave workgroups per compute unit, 128 x 256 tiles, two buffers: while one
     //      converts and stores a tile the other multiplies;
-    //   2: one 8-wave workgroup, 256 x 256 tiles, three buffers: a third fewer LDS-direct bytes per MFMA and
-    //      one more slice of prefetch distance, which is what this kernel is short of (it is bound by the
-    //      path from L2 / HBM into LDS, not by the matrix cores); 3-11 % faster on the DiT shapes although
-    //      no second workgroup hides its epilogue.  Taken when there are at least two rounds of such tiles
-    //      and K is deep enough for the ring; the benchmark hook can force either.
     //   3: the wide kernel of w4ax_gemm_wide.hip: one 4-wave workgroup, 256 x 256 tiles, 128 x 128 wave tiles with
-    //      the accumulators in AGPRs: a third fewer LDS fragment bytes per MFMA and a K slice in 60 % of
-    //      variant 2's time, but a larger fixed cost per tile (nothing hides its epilogue), so it pays from
-    //      ten K slices on (whole layer steps on a 32760 x 4608 output, variant 3 against variant 2: 14 %
-    //      slower at K = 512, 5 % at 768, equal at 1024, 3 % faster at 1280, 7 % at 1536, 8 % at 2048).
+    //      the accumulators in AGPRs: a third fewer LDS fragment bytes per MFMA, but a larger fixed cost per tile
+    //      (nothing hides its epilogue), so it pays from six K slices on (GEMM alone, 32760 x 4608 output, variants 1
+    //      and 3: 79 and 84 us at K = 512, 101 and 94 at 768, 118 and 109 at 1024, 134 and 116 at 1280; 8192 x 4608:
+    //      29.4 and 28.9, 35.1 and 33.1, 40.9 and 39.6, 46.4 and 41.7; 6144 x 1536: 12.7 and 12.1, 14.0 and 13.3).
+    // (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind one of these at every K from 256 to 1280.)
     int v = gemm_variant();
-    const int shape = v < 0 ? small_gemm_shape(M, N, K) : v - kFirstSmallVariant;   // outputs of few tiles
+    const int shape = v < 0 ? small_gemm_shape(M, N, K, true) : v - kFirstSmallVariant;   // outputs of few tiles
     if (shape >= 0 && shape < kSmallVariants)
         return launch_w4ax_gemm_small(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, DVDQ_CODES_FP6, DVDQ_W_NATIVE_FP6, shape, y,
                                       acc_out, stream);
-    const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
-    if (v != 1 && v != 2 && v != 3) v = big_tiles >= 512 ? (K / kBK >= 10 ? 3 : 2) : 1;
-    if (K / kBK < 2 && v == 2) v = 1;
+    if (v != 1 && v != 3) v = K / kBK >= 6 ? 3 : 1;
     if (v == 3) return launch_w4ax_gemm_wide(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, true, y, acc_out, stream);
-    if (v == 2) return launch_fp6<256, 256, 4, 2, 3, 1>(DVDQ_FP6_ARGS);
     return launch_fp6<128, 256, 2, 2, 2, 2>(DVDQ_FP6_ARGS);
 #undef DVDQ_FP6_ARGS
 }

@@ -585,7 +585,7 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
         if (codes_format != DVDQ_CODES_INT8 || w_zero) return DVDQ_ERR_UNSUPPORTED;
         const int v = gemm_variant();
         return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, nullptr, nullptr, bias, M, N,
-                                      K, codes_format, w_layout, v >= kFirstSmallVariant ? v - kFirstSmallVariant : small_gemm_shape(M, N, K),
+                                      K, codes_format, w_layout, v >= kFirstSmallVariant ? v - kFirstSmallVariant : small_gemm_shape(M, N, K, false),
                                       y, acc_out, stream);
     }
     const int m = (int)M, n = (int)N, k = (int)K;
@@ -600,7 +600,7 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     // fewer K slices than a variant's ring needs falls back to variant 2, which always qualifies.
     const int forced = gemm_variant();
     int v = forced < 0 ? 2 : forced;
-    const int shape = forced < 0 ? small_gemm_shape(M, N, K) : forced - kFirstSmallVariant;
+    const int shape = forced < 0 ? small_gemm_shape(M, N, K, false) : forced - kFirstSmallVariant;
     if (shape >= 0)
         return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, w_zero, code_rowsum,
                                       bias, M, N, K, codes_format, w_layout, shape, y, acc_out, stream);
@@ -614,11 +614,12 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
             default: return DVDQ_ERR_UNSUPPORTED;
         }
     }
-    // Variant 5 is the wide kernel of w4ax_gemm_wide.hip (int8 codes only).  Measured on the DiT shapes it is 2 %
-    // (K = 1536) to 6 % (K = 3072) faster than variant 2 and level with it at K = 13824; it is taken by itself when
-    // a tile has at least 12 K slices and there are at least two rounds of 256 x 256 tiles (fewer tiles are dealt
-    // out more evenly in variant 2's 128 x 256 pieces).
-    if (forced < 0 && codes_format == DVDQ_CODES_INT8 && k / 128 >= 12 && ((M + 255) / 256) * ((N + 255) / 256) >= 512) v = 5;
+    // Variant 5 is the wide kernel of w4ax_gemm_wide.hip (int8 codes only), taken by itself when a tile has at least 12 K
+    // slices.  Against variant 2 (GEMM alone, outputs of 144 to 2304 tiles of 256 x 256): K = 640 up to 7 % slower;
+    // 1280 level where channels are a multiple of 256, up to 7 % slower at 1160; 1536 level without zero-points, 1-6 %
+    // faster with them (15600 x 1536 x 1536: 55.6 -> 52.7 us); 3072 and 9216 mostly 3-10 % faster (4096 x 3072 x 3072: 43.8
+    // -> 40.9).
+    if (forced < 0 && codes_format == DVDQ_CODES_INT8 && k / 128 >= 12) v = 5;
     if (v == 5)
         return launch_w4ax_gemm_wide(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, w_zero, code_rowsum, bias,
                                      M, N, K, false, y, acc_out, stream);

@@ -383,15 +383,18 @@ int launch_tile(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
 // rule is within 2.6 % of the best shape in the geometric mean, and the same lines are best for both containers.  On
 // the lines (int8 codes): 1024 x 1024 x 256 (tokens x K x channels, 256 tiles of 32 x 32) 4.6 us as shape 0, 4.8 as 1;
 // 512 x 3072 x 3072 (384 tiles of 64 x 64) 11.8 as 3, 14.7 as 4; 1024 x 3072 x 3072 (768) 18.7 and 16.9;
-// 2048 x 3072 x 3072 (768 tiles of 64 x 128) 28.7 as 5, 31.6 with large tiles; 4096 x 3072 x 3072 (1536) 55 and 45.
-int small_gemm_shape(int64_t M, int64_t N, int64_t K) {
+// 2048 x 3072 x 3072 (768 tiles of 64 x 128) 29.0 as 5, 31.1 with large tiles; 3072 x 3072 x 3072 (1152) 45.5 and 40.0.
+// FP6 codes halve the large tiles' time per slice, not the operand traffic of the small ones: there the large tiles
+// win as soon as 96 of them (256 x 256) are at work: 1536 x 3072 x 3072 (72) 20.4 as 5 and 24.0, 2048 x 3072 x 3072 (96)
+// 22.9 and 21.9, 5120 x 9216 x 1160 (100) 55 and 47.7, 2048 x 640 x 3072 (96) 13.0 and 10.6.
+int small_gemm_shape(int64_t M, int64_t N, int64_t K, bool fp6) {
     auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     if (tiles(32, 32) <= 256) return 0;
     // (deep K: eight waves; 1 x 9216 x 9216: 14.8 -> 11.0 us, at 3072 channels equal)
     if (tiles(32, 64) <= 256) return K / kBK >= 48 ? 2 : 1;
     if (tiles(64, 64) <= 512) return 3;
     if (tiles(64, 64) <= 1024) return 4;
-    if (tiles(64, 128) <= 1280) return 5;
+    if (tiles(64, 128) <= 1024 && !(fp6 && tiles(256, 256) >= 96)) return 5;
     return -1;
 }
 
