@@ -4,8 +4,8 @@
 // round, and keeps the grid with the smallest row error: either as Alg. 1 prints it (starts
 // i = 1, 2, ..., a start's result is the grid of its last round) or as a superset search (i = 0,
 // plain MinMax, is a start too and every grid evaluated competes).  Runs once per layer, off the
-// inference path; everything that decides is fp64, so that its decisions (roundings, comparisons)
-// match a plain fp64 implementation up to summation order.
+// inference path; everything that decides is fp64 or better, so that its decisions (roundings, comparisons)
+// match a plain fp64 implementation up to the rounding of that one's sums.
 //
 // One workgroup per row.  A row is evaluated on several hundred grids (Delta, z), and what an evaluation needs of
 // it are only four sums over c = clamp(rint(w / Delta) + z, 0, 15), d = c - z:
@@ -16,7 +16,13 @@
 //   sq  = 15 K - sum_j pos_j
 //   den = (15 - z)^2 K - sum_j (2 (j - z) + 1) pos_j          (both exact integers)
 //   num = (15 - z) P(K) - sum_j P(pos_j)
-//   e2  = sum w^2 - 2 Delta num + Delta^2 den                 (taken from the row itself where this would cancel)
+//   e2  = sum w^2 - 2 Delta num + Delta^2 den
+// The last two are differences of larger numbers: for rows quantized well, several digits of e2 cancel.  So nothing
+// in them is rounded before the end.  The prefix sums are 64-bit integers, the weights in units of 2^-43 .. 2^-47 of
+// the row's largest (FixedPoint below): a weight is exact in them unless it is more than 2^20 times smaller than the
+// largest, and then d is 0 on every grid that does not clip the largest away.  sum w^2 is held in two doubles and the
+// expression evaluated in two.  One rounding to fp64 remains (the row error is within 1.3e-16 of what
+// sums in 80 bits give).  Below 2^-40 sum w^2, where the two doubles would run out, e2 is taken from the row.
 // So the row is sorted once, its prefix sums are kept, and an evaluation costs 15 lookups instead of a pass over
 // the row with a division per weight.  A lookup is three dependent LDS reads (the cell of values the threshold falls
 // in, the block of 4 .. 16 weights there, its weights and prefix sum).  The division survives only where it decides:
@@ -25,13 +31,15 @@
 // positions per lane; with one position per lane the divisions and the square root of a round, which are the same in
 // all lanes of a start, weigh twice as much), with no barrier inside the search.
 //
-// Cost.  1536 rows of 8960 weights, 100 steps, 10 rounds: 0.14 ms; a pass over the row per evaluation, one workgroup of
-// 256 threads per row, took 8.7 ms.  Bound by latencies, not by memory (62 MB) nor by vector issue: of the 95 K clocks a
-// row is in work (two rows per compute unit) 10 K are the load, 22 K the two dealing passes with the counts between them
-// (LDS atomics and barriers), 14 K the windows, 4 K the prefix sums, 45 K the search (eleven rounds of 4 K, a chain of
-// three divisions, a square root and five LDS reads).  8 lanes per start instead of 16 took 0.06 ms off, windows in
-// place of counting every weight's rank among its cell's 0.04 ms.
+// Cost.  1536 rows of 8960 weights, 100 steps, 10 rounds: 0.148 ms; a pass over the row per evaluation, one workgroup of
+// 256 threads per row, took 8.7 ms.  Bound by latencies, not by memory (62 MB) nor by vector issue: of the 103 K clocks a
+// row is in work (two rows per compute unit) 18 K are the load and its sums, 17 K the two dealing passes with the counts
+// between them (LDS atomics and barriers), 14 K the windows, 4 K the prefix sums, 46 K the search (eleven rounds of 4 K, a
+// chain of three divisions, a square root and five LDS reads), 6 K the codes.  The sums that are not rounded cost 7 K in
+// the load and 2 K in the search: with sums in fp64, 0.138 ms (8960 rows of 1536: 0.524, now 0.583) and a squared error
+// off by 1e-14, up to 1e-12 where a grid fits a row to a hundredth.
 #include "dvdq_internal.h"
+#include "wave_reduce.h"
 
 #pragma clang fp contract(off)   // every product and sum rounded on its own, like a plain C loop
 
@@ -42,33 +50,55 @@ constexpr double kQmax = 15.0;           // INT4
 constexpr int kLanes = 8;        // lanes per start of the search
 constexpr int kCellLimit = 1024; // fullest cell that is sorted in windows (see the kernel)
 
-// Sums over 8 neighbouring lanes: two quad permutes and a half-row mirror; every lane ends with the same bits.
-template <int CTRL>
-__device__ __forceinline__ int dpp_i(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true); }
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double v) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)dpp_i<CTRL>((int)(uint32_t)u), hi = (uint32_t)dpp_i<CTRL>((int)(uint32_t)(u >> 32));
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double sum8(double v) {
-    v += dpp_d<0xB1>(v);    // quad_perm:[1,0,3,2]
-    v += dpp_d<0x4E>(v);    // quad_perm:[2,3,0,1]
-    v += dpp_d<0x141>(v);   // row_half_mirror
-    return v;
-}
-__device__ __forceinline__ int sum8(int v) {
-    v += dpp_i<0xB1>(v);
-    v += dpp_i<0x4E>(v);
-    v += dpp_i<0x141>(v);
+// Sum over 8 neighbouring lanes of an integer; every lane gets it.
+template <typename T>
+__device__ __forceinline__ T sum8(T v) {
+    v += dpp<DPP_XOR1>(v);
+    v += dpp<DPP_XOR2>(v);
+    v += dpp<DPP_HALF_MIRROR>(v);
     return v;
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-    return v;
+// A sum held in two doubles: hi + lo.
+struct TwoDoubles { double hi, lo; };
+// a + b without an error: hi = a + b rounded, lo the rest (the same bits for b + a)
+__device__ __forceinline__ TwoDoubles two_sum(double a, double b) {
+    const double s = a + b, t = s - a;
+    return {s, (a - (s - t)) + (b - t)};
 }
+// the same for |a| >= |b|
+__device__ __forceinline__ TwoDoubles fast_two_sum(double a, double b) {
+    const double s = a + b;
+    return {s, b - (s - a)};
+}
+__device__ __forceinline__ TwoDoubles operator+(TwoDoubles a, TwoDoubles b) {
+    const TwoDoubles s = two_sum(a.hi, b.hi);
+    return {s.hi, (a.lo + b.lo) + s.lo};
+}
+
+// sum over 16 neighbouring lanes, over the wave; the same in every lane
+template <int CTRL>
+__device__ __forceinline__ TwoDoubles dpp_sum(TwoDoubles v) { return v + TwoDoubles{dpp<CTRL>(v.hi), dpp<CTRL>(v.lo)}; }
+template <bool ROWS32>
+__device__ __forceinline__ TwoDoubles rows_sum(TwoDoubles v) {
+    const Both<double> hi = both_rows<ROWS32>(v.hi), lo = both_rows<ROWS32>(v.lo);
+    return TwoDoubles{hi.a, lo.a} + TwoDoubles{hi.b, lo.b};
+}
+__device__ __forceinline__ TwoDoubles sum16(TwoDoubles v) {
+    return dpp_sum<DPP_MIRROR>(dpp_sum<DPP_HALF_MIRROR>(dpp_sum<DPP_XOR2>(dpp_sum<DPP_XOR1>(v))));
+}
+__device__ __forceinline__ TwoDoubles sum64(TwoDoubles v) { return rows_sum<true>(rows_sum<false>(sum16(v))); }
+
+// Weights as multiples of `unit` = 2^e, summed in 64-bit integers.  A running sum of a few weights is kept as a double
+// near `bias` = 1.5 * 2^52 units, where neighbouring doubles are one unit apart: every addition rounds the weight added
+// to whole units, and the sum's bits less the bias's bits are the integer.  (The weights of a block are always added
+// in the same order from its first one, so that each has one rounded value, whatever position the sum ends at.)
+struct FixedPoint {
+    double bias, unit;
+    __device__ __forceinline__ int64_t integer(double sum) const {
+        return __builtin_bit_cast(int64_t, sum) - __builtin_bit_cast(int64_t, bias);
+    }
+};
 
 __device__ __forceinline__ double clamp_d(double v, double lo, double hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
@@ -91,11 +121,13 @@ struct Sums { double e2, num, den, sq; };
 template <int BLK>
 struct Row {
     const float *sorted;      // the weights, ascending, then +infinity up to a multiple of BLK (at least one)
-    const double *prefix;     // prefix[b] = sum of the first b * BLK of them
+    const int64_t *prefix;    // prefix[b] = sum of the first b * BLK of them, in units
     const uint32_t *cells;    // cells[c] = number of weights in the cells before c
     CellMap cell;
     int K;
-    double sw, sw2;           // sum of the weights, sum of their squares
+    FixedPoint fixed;
+    int64_t sum;              // of all weights, in units
+    TwoDoubles sw2;           // sum of their squares
 };
 
 // The four sums on the grid (delta, z), by the 8 lanes of a group (j = lane % 8 takes positions j and j + 8): every
@@ -131,11 +163,11 @@ __device__ __forceinline__ Sums evaluate(const Row<BLK> &r, int j, double delta,
             hi[i] = up ? hi[i] : mid - 1;
         }
     }
-    double p[2];
+    int64_t p[2];
     int pos[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        p[i] = r.prefix[lo[i]];
+        double run = r.fixed.bias;
         pos[i] = lo[i] * BLK;
         const float4 *blk = reinterpret_cast<const float4 *>(r.sorted + lo[i] * BLK);
 #pragma unroll
@@ -146,20 +178,31 @@ __device__ __forceinline__ Sums evaluate(const Row<BLK> &r, int j, double delta,
             for (int h = 0; h < 4; ++h) {
                 const bool in = q[h] < bound[i];
                 pos[i] += in ? 1 : 0;
-                p[i] += (double)(in ? q[h] : 0.f);
+                run += (double)(in ? q[h] : 0.f);
             }
         }
+        p[i] = r.prefix[lo[i]] + r.fixed.integer(run);
     }
-    if (j == kLanes - 1) { pos[1] = 0; p[1] = 0.0; }   // (15 positions)
+    if (j == kLanes - 1) { pos[1] = 0; p[1] = 0; }   // (15 positions)
     const int zi = (int)z;
     Sums s;
-    s.num = (15.0 - z) * r.sw - sum8(p[0] + p[1]);
+    const int64_t num = (15 - zi) * r.sum - sum8(p[0] + p[1]);
     s.den = (double)((15 - zi) * (15 - zi) * r.K - sum8((2 * (j - zi) + 1) * pos[0] + (2 * (j + kLanes - zi) + 1) * pos[1]));
     s.sq = (double)(15 * r.K - sum8(pos[0] + pos[1]));
-    s.e2 = r.sw2 - 2.0 * delta * s.num + delta * delta * s.den;
-    // A (nearly) exact fit: the difference has lost too many digits (relative error 2^-53 sw2 / e2), take the
-    // sum over the row instead, as slow as it is.
-    if (!(s.e2 > 1e-4 * r.sw2)) {
+    // num in two doubles: its upper and lower 32 bits are exact (and the upper ones, if any, are the larger)
+    const double upper = (double)(int32_t)(num >> 32) * (0x1p32 * r.fixed.unit), lower = (double)(uint32_t)num * r.fixed.unit;
+    s.num = upper + lower;
+    const double num_lo = (upper - s.num) + lower;
+    // e2 = sum w^2 + Delta (Delta den - 2 num), both sums from the larger term on (where it is not the larger one, no
+    // digits cancel: such a grid is worse than no grid at all)
+    const double q = delta * s.den, q_lo = __builtin_fma(delta, s.den, -q);
+    const TwoDoubles t = fast_two_sum(-2.0 * s.num, q);
+    const double t_lo = t.lo + (q_lo - 2.0 * num_lo);
+    const double u = delta * t.hi, u_lo = __builtin_fma(delta, t.hi, -u) + delta * t_lo;
+    const TwoDoubles e = fast_two_sum(r.sw2.hi, u);
+    s.e2 = e.hi + (e.lo + (u_lo + r.sw2.lo));
+    // A (nearly) exact fit: the sum over the row instead, as slow as it is.
+    if (!(s.e2 > 0x1p-40 * r.sw2.hi)) {
         double e2 = 0.0;
         for (int k = j; k < r.K; k += kLanes) {
             const double w = (double)r.sorted[k];
@@ -250,13 +293,14 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
                                                 double *__restrict__ row_error) {
     constexpr bool REGS = HELD > 0;   // the row is held
     constexpr int WAVES = T / 64, PAIRS = REGS ? HELD : 4;
-    // LDS: the row fp32 [row_floats(K)], prefix sums fp64 [blocks], the cells uint32 [cells + 1]
+    // LDS: the row fp32 [row_floats(K)], prefix sums int64 [blocks], the cells uint32 [cells + 1]
     extern __shared__ __align__(16) uint8_t smem_raw[];
     const int blocks = K / BLK + 1;
     float *row = reinterpret_cast<float *>(smem_raw);
-    double *prefix = reinterpret_cast<double *>(row + row_floats(K));
+    int64_t *prefix = reinterpret_cast<int64_t *>(row + row_floats(K));
     uint32_t *first = reinterpret_cast<uint32_t *>(prefix + blocks);   // first[c]: weights before cell c
-    __shared__ double s_a[WAVES], s_b[WAVES], s_c[WAVES];
+    __shared__ double s_a[WAVES], s_b[WAVES], s_c[WAVES], s_d[WAVES];
+    __shared__ int64_t s_sum[WAVES];
     __shared__ int s_i[WAVES], s_max[WAVES];
     __shared__ double s_best[3];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -284,7 +328,8 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
 
     // ---- minimum, maximum, sum and sum of squares
     float lo_f = INFINITY, hi_f = -INFINITY;
-    double sw = 0.0, sw2 = 0.0;
+    double sw = 0.0;
+    TwoDoubles sw2 = {0.0, 0.0};
     for (int c = tid; c <= cells; c += T) first[c] = 0u;
     for_row([&] __device__(int, float2 v) {
         lo_f = fminf(lo_f, fminf(v.x, v.y));
@@ -292,8 +337,8 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
         const double a = (double)v.x, b = (double)v.y;
         sw += a;
         sw += b;
-        sw2 += a * a;
-        sw2 += b * b;
+        const TwoDoubles s1 = two_sum(sw2.hi, a * a), s2 = two_sum(s1.hi, b * b);   // (the square of a float is exact)
+        sw2 = {s2.hi, sw2.lo + (s1.lo + s2.lo)};
     });
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) {
@@ -301,22 +346,24 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
         hi_f = fmaxf(hi_f, __shfl_xor(hi_f, m, 64));
     }
     sw = wave_sum(sw);
-    sw2 = wave_sum(sw2);
+    sw2 = sum64(sw2);
     if (lane == 0) {
         s_a[wave] = sw;
-        s_b[wave] = sw2;
+        s_b[wave] = sw2.hi;
+        s_d[wave] = sw2.lo;
         s_c[wave] = __builtin_bit_cast(double, make_float2(lo_f, hi_f));
     }
     __syncthreads();
-    sw = sw2 = 0.0;
+    sw = 0.0;
 #pragma unroll
     for (int i = 0; i < WAVES; ++i) {
         sw += s_a[i];
-        sw2 += s_b[i];
         const float2 r = __builtin_bit_cast(float2, s_c[i]);
         lo_f = fminf(lo_f, r.x);
         hi_f = fmaxf(hi_f, r.y);
     }
+    const int slot = lane & 15;
+    sw2 = sum16(slot < WAVES ? TwoDoubles{s_b[slot], s_d[slot]} : TwoDoubles{0.0, 0.0});
     const double lo0 = (double)lo_f, hi0 = (double)hi_f;
     const bool constant = !(hi0 > lo0);
 
@@ -391,13 +438,18 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
             bitonic_sort<T>(row, K);
         }
 
-        // ---- prefix sums, one every BLK weights
+        // ---- prefix sums, one every BLK weights.  A unit is 2^-bits of the power of two above the largest weight: the
+        // sums of up to BLK weights stay below 2^51 units, those of 15 prefix sums of K weights below 2^63.
+        const int bits = min(47, 59 - (32 - __builtin_clz(K)));
+        const double unit = ldexp(1.0, __builtin_amdgcn_frexp_expf(fmaxf(fabsf(lo_f), fabsf(hi_f))) - bits);
+        const FixedPoint fixed = {0x1.8p52 * unit, unit};
+        int64_t total;   // all K weights
         {
             const int full = K / BLK, nb = (full + T - 1) / T;   // whole blocks, consecutive ones of this thread
             const int b0 = min(tid * nb, full), b1 = min(b0 + nb, full);
             auto block_sum = [&] __device__(int b) {
                 const float4 *blk = reinterpret_cast<const float4 *>(row + b * BLK);
-                double s = 0.0;
+                double s = fixed.bias;
 #pragma unroll
                 for (int i = 0; i < BLK / 4; ++i) {
                     const float4 v = blk[i];
@@ -406,31 +458,33 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
                     s += (double)v.z;
                     s += (double)v.w;
                 }
-                return s;
+                return fixed.integer(s);
             };
-            double s = 0.0;
+            int64_t s = 0;
             for (int b = b0; b < b1; ++b) {
                 prefix[b + 1] = s;   // (for now: within the thread's blocks, before block b)
                 s += block_sum(b);
             }
-            double incl = s;
+            int64_t incl = s;
 #pragma unroll
             for (int m = 1; m < 64; m <<= 1) {
-                const double o = __shfl_up(incl, m, 64);
+                const int64_t o = __shfl_up((long long)incl, m, 64);
                 if (lane >= m) incl += o;
             }
-            if (lane == 63) s_a[wave] = incl;
+            if (lane == 63) s_sum[wave] = incl;
             __syncthreads();
-            double run = __shfl_up(incl, 1, 64);   // (every lane takes part: the lanes before this one)
-            if (lane == 0) run = 0.0;
-            for (int i = 0; i < wave; ++i) run += s_a[i];
+            int64_t run = incl - s;   // the lanes before this one, then the waves before
+            for (int i = 0; i < wave; ++i) run += s_sum[i];
             for (int b = b0; b < b1; ++b) prefix[b + 1] = run + (b + 1 < b1 ? prefix[b + 2] : s);   // up to block b's end
-            if (tid == 0) prefix[0] = 0.0;
+            if (tid == 0) prefix[0] = 0;
             __syncthreads();
+            double rest = fixed.bias;
+            for (int k = full * BLK; k < K; ++k) rest += (double)row[k];
+            total = prefix[full] + fixed.integer(rest);
         }
 
         // ---- search: 8 lanes per start, no barrier
-        const Row<BLK> r = {row, prefix, first, cell, K, sw, sw2};
+        const Row<BLK> r = {row, prefix, first, cell, K, fixed, total, sw2};
         const int j = lane & (kLanes - 1);
         const bool all = search == DVDQ_BGR_BEST_OF_ALL;
         const double step = (hi0 - lo0) / (double)n_steps;
@@ -449,7 +503,7 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
             double e = sqrt(s.e2);
             if (all && e < best) { best = e; best_delta = delta; best_z = z; best_i = (int)i; }
             for (int round = 0; round < max_refine; ++round) {
-                if (s.den == 0.0) break;
+                if (s.den == 0.0 || e != e) break;   // (e: a NaN among the weights)
                 const double dn = s.num / s.den;
                 if (!(dn > 0.0)) break;
                 const double zn = clamp_d(rint(s.sq / (double)K - mean / dn), 0.0, kQmax);
@@ -513,7 +567,7 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
 }
 
 size_t lds_bytes(int64_t K, int blk, int cells) {
-    return row_floats((int)K) * sizeof(float) + (size_t)(K / blk + 1) * sizeof(double) + (size_t)(cells + 1) * sizeof(uint32_t);
+    return row_floats((int)K) * sizeof(float) + (size_t)(K / blk + 1) * sizeof(int64_t) + (size_t)(cells + 1) * sizeof(uint32_t);
 }
 
 template <int T, int BLK, int HELD>
@@ -534,9 +588,10 @@ int launch_bgr(const float *w, int64_t N, int64_t K, int n_steps, int max_refine
 #define DVDQ_BGR_ARGS(CELLS) \
     w, N, (int)K, CELLS, n_steps, max_refine, eps, search, w_packed, w_scale, w_zero, row_error, stream
     // A few weights per cell: 1024 .. 4096 cells.  Two rows at a time per compute unit, as workgroups of 512 threads,
-    // while their LDS allows (half of 160 KB each; longer rows with coarser prefix sums and cells): 0.20 ms against 0.25
+    // while their LDS allows (half of 160 KB each; longer rows with coarser prefix sums and cells): 0.148 ms against 0.201
     // as workgroups of 1024 for 1536 rows of 8960.  A workgroup of 1024 threads where there is no second row to put
-    // beside it: with no more rows than compute units (32 rows of 8960: 0.044 ms against 0.056), and from 14 K weights on.
+    // beside it: with no more rows than compute units (32 rows of 8960: level at 100 steps, 46.7 us against 50.8 at 200;
+    // 200 rows of 13824: 41.7 against 46.0), and from 14 K weights on.
     const int cells = K <= 2048 ? 1024 : (K <= 4096 ? 2048 : 4096);
     if (K > 16384) return launch<1024, 16, 0>(DVDQ_BGR_ARGS(2048));
     if (N > 256 && K <= 10240) return launch<512, 4, 10>(DVDQ_BGR_ARGS(cells));

@@ -125,3 +125,51 @@ def test_bgr_crowded_rows(K, search):
             np.round(g * 4) / 8, 0.25 * (rng.integers(0, 16, K) - 6) + 1e-7 * g, np.sign(g) * np.abs(g) ** 5,
             np.where(np.arange(K) < 2, [[-1.0], [1.0]][0] + 2.0 * (np.arange(K) == 1), 1e-4 * g), g * 1e-30, np.exp(3 * g)]
     print(compare(np.stack(rows).astype(np.float32), f"K{K} search{search}", n_steps=30, max_refine=6, search=search))
+
+
+def _exact_listing_error(w, n_steps, refine):
+    """The error of the listing's best grid for one row with every sum in 80-bit arithmetic: starts i = 1, 2, ..., at
+    most one refinement round each.  Grids are computed as the definition says, in fp64, from the sums rounded once."""
+    L = np.longdouble
+    wl, K = w.astype(L), len(w)
+    w = w.astype(np.float64)
+    lo0, hi0 = w.min(), w.max()
+    step, mean, best = (hi0 - lo0) / n_steps, float(wl.sum()) / K, np.inf
+
+    def sums(delta, z):
+        c = np.clip(np.rint(w / delta) + z, 0, 15)
+        d = (c - z).astype(L)
+        r = wl - L(delta) * d
+        return np.sqrt((r * r).sum()), float((d * wl).sum()), float((d * d).sum()), c.sum()
+
+    for i in range(1, n_steps + 1):
+        lo, hi = lo0 + i * step, hi0 - i * step
+        if not lo < hi:
+            break
+        delta = (hi - lo) / 15
+        e, num, den, sq = sums(delta, np.clip(np.rint(-(lo / delta)), 0, 15))
+        if refine and den > 0 and num / den > 0:
+            delta = num / den
+            e = sums(delta, np.clip(np.rint(sq / K - mean / delta), 0, 15))[0]
+        best = min(best, e)
+    return best
+
+
+@pytest.mark.parametrize("refine", [0, 1])
+@pytest.mark.parametrize("K", [6, 1536, 8960, 20000])
+def test_bgr_row_error_is_rounded_once(K, refine):
+    """row_error is sqrt of a squared error whose sums are not rounded on the way (2^-53), then rounded itself (2^-53):
+    1.5 * 2^-53 = 1.7e-16 together, and the yardstick's own K additions of 2^-64 (sqrt(K) of them: 1e-17)."""
+    rng = np.random.default_rng(K + refine)
+    g = rng.standard_normal(K)
+    rows = [g * 0.02, 3.0 + 0.1 * g, -1.0 + g, np.sign(g) * np.abs(g) ** 3, np.exp(2 * g), g * 1e-30, g * 1e30,
+            0.25 * (rng.integers(0, 16, K) - 6) + 5e-3 * g, 0.25 * (rng.integers(0, 16, K) - 6) + 2e-2 * g,
+            np.where(np.arange(K) < 3, 200.0 * g, 0.01 * g)]
+    w = np.stack(rows).astype(np.float32)
+    _, _, _, err = dvdq.bgr_quantize(torch.from_numpy(w).to(DEV), n_steps=20, max_refine=refine, eps=0.0, want_error=True,
+                                     search=dvdq.BGR_LISTING)
+    torch.cuda.synchronize()
+    err = err.cpu().numpy()
+    rel = [abs(float((np.longdouble(e) - x) / x)) for e, x in zip(err, (_exact_listing_error(r, 20, refine) for r in w))]
+    print(f"K{K} refine{refine}:", " ".join(f"{r:.1e}" for r in rel))
+    assert max(rel) <= 2e-16, rel
