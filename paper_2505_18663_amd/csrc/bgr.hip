@@ -576,9 +576,16 @@ int launch(const float *w, int64_t N, int K, int cells, int n_steps, int max_ref
     auto k = bgr_kernel<T, BLK, HELD>;
     static std::atomic<uint64_t> configured{0};   // one per template instantiation
     allow_dynamic_lds(reinterpret_cast<const void *>(k), 158 * 1024, configured);
-    hipLaunchKernelGGL(k, dim3((unsigned)N), dim3(T), lds_bytes(K, BLK, cells), stream, w, K, cells, n_steps, max_refine, eps,
-                       search, w_packed, w_scale, w_zero, row_error);
-    return check_launch();
+    // (a launch has fewer than 2^32 threads: more rows than that in several)
+    constexpr int64_t kRows = ((int64_t)1 << 32) / T / 2;
+    for (int64_t n = 0; n < N; n += kRows) {
+        const unsigned rows = (unsigned)(N - n < kRows ? N - n : kRows);
+        hipLaunchKernelGGL(k, dim3(rows), dim3(T), lds_bytes(K, BLK, cells), stream, w + n * K, K, cells, n_steps, max_refine, eps,
+                           search, w_packed + n * (K / 2), w_scale + n, w_zero + n, row_error ? row_error + n : nullptr);
+        const int rc = check_launch();
+        if (rc != DVDQ_OK) return rc;
+    }
+    return DVDQ_OK;
 }
 
 }  // namespace

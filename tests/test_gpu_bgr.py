@@ -173,3 +173,21 @@ def test_bgr_row_error_is_rounded_once(K, refine):
     rel = [abs(float((np.longdouble(e) - x) / x)) for e, x in zip(err, (_exact_listing_error(r, 20, refine) for r in w))]
     print(f"K{K} refine{refine}:", " ".join(f"{r:.1e}" for r in rel))
     assert max(rel) <= 2e-16, rel
+
+
+def test_bgr_more_rows_than_one_launch_takes():
+    """2^23 + 5 rows of two weights: at 512 threads a row, a launch of 2^32 threads, the grid limit, is full before that.
+    Constant rows, whose grid is known, and one that has to be searched at the end."""
+    N = 2 ** 23 + 5
+    w = torch.randint(-3, 4, (N, 1), device=DEV).float().expand(N, 2).contiguous()
+    w[-1] = torch.tensor([-0.3, 0.7], device=DEV)
+    wp, ws, wz, err = dvdq.bgr_quantize(w, n_steps=5, max_refine=2, want_error=True)
+    torch.cuda.synchronize()
+    c = w[:-1, 0]
+    assert torch.equal(ws[:-1], torch.where(c == 0, torch.ones_like(c), c.abs()))
+    assert torch.equal(wz[:-1], (c < 0).to(torch.int8) - 8) and not err[:-1].any()
+    q = (c > 0).to(torch.uint8)
+    assert torch.equal(wp[:-1, 0], ((q + 8) & 15) * 17)
+    q_r, d_r, z_r, e_r = oracle.bgr(w[-1:].cpu().numpy(), n_steps=5, max_refine=2)
+    assert float(ws[-1]) == np.float32(d_r[0]) and int(wz[-1]) + 8 == z_r[0] and abs(float(err[-1]) - e_r[0]) <= 1e-15
+    assert (int(wp[-1, 0]) ^ 0x88) == int(q_r[0, 0]) | int(q_r[0, 1]) << 4
