@@ -284,7 +284,10 @@ int dvdq_bgr_quantize(const float *w, int64_t N, int64_t K, int n_steps, int max
  * adds it to the running sum, and sets bits = b_low while the sum stays below `delta`,
  * or bits = b_high and sum = 0 once it reaches `delta` (the B_{t_i} case equation).
  * A zero denominator gives +inf (or 0 when the numerator is zero too).
- * `workspace`: device, at least dvdq_gbs_workspace_bytes() bytes, scratch.
+ * `workspace`: device, at least dvdq_gbs_workspace_bytes() bytes, scratch.  Steps that may run at the same time (two
+ * controllers on two streams) need a workspace each, as they need a state each: a step whose partial sums are
+ * overwritten waits ten seconds for them and then leaves the running sum as it was, NaN as the change and
+ * bits = b_high.
  * delta >= 0; b_low <= b_high, each 4, 6 or 8.  Results are bit-reproducible (fixed order of summation).
  */
 size_t dvdq_gbs_workspace_bytes(void);

@@ -61,6 +61,11 @@ int dvdq_bench_set_gemm_grid_limit(int workgroups);
  * launched afterwards must still give the right result. */
 int dvdq_bench_fill_tile_counters(uint32_t value, void *hip_stream);
 
+/* Robustness tests: let dvdq_gbs_step (outside stream capture) wait `ticks` (0 .. 10^8) of the 100 MHz device clock for
+ * partial sums that do not come, as if another step had overwritten them; -1 restores the library's behaviour.
+ * Process-wide (an atomic that every launch reads once). */
+int dvdq_bench_set_gbs_wait(int64_t ticks);
+
 #ifdef __cplusplus
 }
 #endif

@@ -28,7 +28,7 @@ EXPORTED_SYMBOLS = (
     "dvdq_rotate_quant", "dvdq_rotate_quant_blockwise", "dvdq_w4ax_gemm", "dvdq_qlinear", "dvdq_qlinear_workspace_bytes",
     "dvdq_qlinear_scale_offset", "dvdq_qlinear_rowsum_offset", "dvdq_qlinear_static", "dvdq_static_workspace_bytes", "dvdq_w4_prepack", "dvdq_w4_native_bytes", "dvdq_w4_prepack_fp6",
     "dvdq_w4_native_fp6_bytes", "dvdq_codes_bytes", "dvdq_status_string",
-    "dvdq_version", "dvdq_gbs_workspace_bytes", "dvdq_gbs_reset", "dvdq_gbs_step", "dvdq_bgr_quantize", "dvdq_bench_copy", "dvdq_bench_mfma_i8", "dvdq_bench_mfma_fp6", "dvdq_bench_set_gemm_variant", "dvdq_bench_set_gemm_schedule", "dvdq_bench_fill_tile_counters", "dvdq_bench_set_gemm_grid_limit", "dvdq_release_stream",
+    "dvdq_version", "dvdq_gbs_workspace_bytes", "dvdq_gbs_reset", "dvdq_gbs_step", "dvdq_bgr_quantize", "dvdq_bench_copy", "dvdq_bench_mfma_i8", "dvdq_bench_mfma_fp6", "dvdq_bench_set_gemm_variant", "dvdq_bench_set_gemm_schedule", "dvdq_bench_fill_tile_counters", "dvdq_bench_set_gemm_grid_limit", "dvdq_bench_set_gbs_wait", "dvdq_release_stream",
 )
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -103,6 +103,8 @@ def lib() -> C.CDLL:
     L.dvdq_bench_fill_tile_counters.restype = i32
     L.dvdq_bench_set_gemm_grid_limit.argtypes = [i32]
     L.dvdq_bench_set_gemm_grid_limit.restype = i32
+    L.dvdq_bench_set_gbs_wait.argtypes = [i64]
+    L.dvdq_bench_set_gbs_wait.restype = i32
     L.dvdq_release_stream.argtypes = [C.c_void_p]
     L.dvdq_release_stream.restype = i32
     for f in ("dvdq_rotate_quant", "dvdq_rotate_quant_blockwise", "dvdq_w4ax_gemm", "dvdq_qlinear", "dvdq_w4_prepack", "dvdq_version",
@@ -477,6 +479,11 @@ def bench_set_gemm_schedule(schedule: int) -> None:
 def bench_set_gemm_grid_limit(workgroups: int) -> None:
     """At most `workgroups` workgroups per persistent GEMM launch (0: fill the chip).  Same results."""
     _check(lib().dvdq_bench_set_gemm_grid_limit(int(workgroups)), "dvdq_bench_set_gemm_grid_limit")
+
+
+def bench_set_gbs_wait(ticks: int) -> None:
+    """Steps of the controller wait `ticks` of the 100 MHz clock for partial sums that do not come (-1: normal steps)."""
+    _check(lib().dvdq_bench_set_gbs_wait(int(ticks)), "dvdq_bench_set_gbs_wait")
 
 
 def bench_fill_tile_counters(value: int, stream=None) -> None:

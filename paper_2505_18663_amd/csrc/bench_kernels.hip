@@ -179,6 +179,12 @@ int dvdq_bench_set_gemm_schedule(int schedule) {
     return DVDQ_OK;
 }
 
+int dvdq_bench_set_gbs_wait(int64_t ticks) {
+    if (ticks < -1 || ticks > 100000000) return DVDQ_ERR_UNSUPPORTED;
+    dvdq::set_gbs_wait(ticks);
+    return DVDQ_OK;
+}
+
 int dvdq_bench_set_gemm_grid_limit(int workgroups) {
     if (workgroups < 0) return DVDQ_ERR_UNSUPPORTED;
     dvdq::set_gemm_grid_limit(workgroups);

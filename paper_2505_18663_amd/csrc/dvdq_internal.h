@@ -56,6 +56,7 @@ int fill_sched_slots(uint32_t value, hipStream_t stream);  // robustness tests o
 int launch_w4_prepack(const uint8_t *w_canonical, int64_t N, int64_t K, uint8_t *w_native, hipStream_t stream);
 
 size_t gbs_workspace_bytes();
+void set_gbs_wait(int64_t ticks);   // tests only
 int launch_gbs_reset(void *state, int bits, hipStream_t stream);
 int launch_gbs_step(const uint16_t *ft, const uint16_t *fp, int64_t n, double delta, int b_low, int b_high,
                     void *state, void *workspace, hipStream_t stream);

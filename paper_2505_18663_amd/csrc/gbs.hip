@@ -72,9 +72,11 @@ __device__ __forceinline__ void update_state(double2 s, double before, double de
 template <bool WHOLE>
 __global__ __launch_bounds__(kThreads) void gbs_partial_kernel(const uint16_t *__restrict__ ft,
                                                                const uint16_t *__restrict__ fp, int64_t n,
-                                                               uint64_t *partial, uint64_t tag, double delta, int b_low,
-                                                               int b_high, GbsState *state) {
+                                                               uint64_t *partial, uint64_t tag, uint64_t wait_tag,
+                                                               uint64_t wait_ticks, double delta, int b_low, int b_high,
+                                                               GbsState *state) {
     __shared__ double s_num[kThreads / 64], s_den[kThreads / 64];
+    __shared__ int s_lost;
     const int64_t nvec = n / 8;
     const uint4 *a = reinterpret_cast<const uint4 *>(ft), *b = reinterpret_cast<const uint4 *>(fp);
     float num = 0.f, den = 0.f;
@@ -99,6 +101,7 @@ __global__ __launch_bounds__(kThreads) void gbs_partial_kernel(const uint16_t *_
     den = wave_sum(den);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) { s_num[wave] = (double)num; s_den[wave] = (double)den; }
+    if (threadIdx.x == 0) s_lost = 0;
     __syncthreads();
     if (threadIdx.x == 0) {
         double dn = 0.0, dd = 0.0;
@@ -118,8 +121,9 @@ __global__ __launch_bounds__(kThreads) void gbs_partial_kernel(const uint16_t *_
         if (blockIdx.x != gridDim.x - 1) return;
         // (Nothing waits for this workgroup: the others finish whatever it does, so the loop below ends.  Two steps at
         // once on one scratch buffer, which it is not for, would overwrite each other's partials: then it ends after
-        // ten seconds of the constant 100 MHz clock, and the change counts as zero.)
-        const uint64_t deadline = wall_clock64() + 1000000000ull;
+        // `wait_ticks` of the constant 100 MHz clock, and the step says that it has no result: NaN as the change, the
+        // running sum as it was, and the higher bit-width, the safe choice.  wait_tag is `tag`; another in the test of this.)
+        const uint64_t deadline = wall_clock64() + wait_ticks;
         const double before = state->acc;
         double2 p = make_double2(0.0, 0.0);
         if (threadIdx.x < gridDim.x) {
@@ -128,9 +132,9 @@ __global__ __launch_bounds__(kThreads) void gbs_partial_kernel(const uint16_t *_
                 a = __hip_atomic_load(partial + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 b = __hip_atomic_load(partial + kMaxBlocks + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 c = __hip_atomic_load(partial + 2 * kMaxBlocks + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (c == tag + kMixNum * a + kMixDen * b) break;
+                if (c == wait_tag + kMixNum * a + kMixDen * b) break;
                 if (wall_clock64() > deadline) {
-                    a = b = 0x7FF8000000000000ull;
+                    s_lost = 1;
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
@@ -138,6 +142,13 @@ __global__ __launch_bounds__(kThreads) void gbs_partial_kernel(const uint16_t *_
             p = make_double2(__builtin_bit_cast(double, a), __builtin_bit_cast(double, b));
         }
         __syncthreads();   // s_num, s_den are read above
+        if (s_lost) {
+            if (threadIdx.x == 0) {
+                state->last_l1 = __builtin_nanf("");
+                state->bits = b_high;
+            }
+            return;
+        }
         p = workgroup_sum(p, s_num, s_den);
         if (threadIdx.x == 0) update_state(p, before, delta, b_low, b_high, state);
     }
@@ -169,7 +180,12 @@ uint64_t next_tag() {
     return tag.fetch_add(1, std::memory_order_relaxed);
 }
 
+constexpr int64_t kWaitTicks = 1000000000;   // ten seconds: longer than any step takes, also on a GPU shared with others
+std::atomic<int64_t> g_wait{-1};             // test hook: wait this long for partials that do not come; -1: off
+
 }  // namespace
+
+void set_gbs_wait(int64_t ticks) { g_wait.store(ticks, std::memory_order_relaxed); }
 
 size_t gbs_workspace_bytes() { return sizeof(double) * 2 * kWorkspaceSlots; }
 
@@ -192,10 +208,14 @@ int launch_gbs_step(const uint16_t *ft, const uint16_t *fp, int64_t n, double de
         cap = hipStreamCaptureStatusActive;
     }
     if (cap == hipStreamCaptureStatusNone) {
-        hipLaunchKernelGGL(gbs_partial_kernel<true>, grid, block, 0, stream, ft, fp, n, partial, next_tag(), delta, b_low, b_high, st);
+        const int64_t hook = g_wait.load(std::memory_order_relaxed);
+        const uint64_t tag = next_tag();
+        hipLaunchKernelGGL(gbs_partial_kernel<true>, grid, block, 0, stream, ft, fp, n, partial, tag, hook < 0 ? tag : ~tag,
+                           (uint64_t)(hook < 0 ? kWaitTicks : hook), delta, b_low, b_high, st);
         return check_launch();
     }
-    hipLaunchKernelGGL(gbs_partial_kernel<false>, grid, block, 0, stream, ft, fp, n, partial, (uint64_t)0, delta, b_low, b_high, st);
+    hipLaunchKernelGGL(gbs_partial_kernel<false>, grid, block, 0, stream, ft, fp, n, partial, (uint64_t)0, (uint64_t)0, (uint64_t)0, delta,
+                       b_low, b_high, st);
     const int rc = check_launch();
     if (rc != DVDQ_OK) return rc;
     hipLaunchKernelGGL(gbs_update_kernel, dim3(1), block, 0, stream, static_cast<const double2 *>(workspace), (int)blocks, delta,

@@ -171,6 +171,8 @@ def test_bench_helpers_argument_errors():
     assert L.dvdq_bench_mfma_fp6(4, -1, FAKE, None, None) == 3
     assert L.dvdq_bench_set_gemm_grid_limit(-8) == 3
     assert L.dvdq_bench_set_gemm_grid_limit(0) == 0
+    assert L.dvdq_bench_set_gbs_wait(-2) == 3 and L.dvdq_bench_set_gbs_wait(10 ** 9) == 3   # bounded waits only
+    assert L.dvdq_bench_set_gbs_wait(-1) == 0
     assert L.dvdq_bench_set_gemm_schedule(2) == 3
 
 

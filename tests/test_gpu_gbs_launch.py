@@ -59,3 +59,23 @@ def test_captured_steps_replay():
         ref.step(cur, prev)
         torch.cuda.synchronize()
         assert ctl.read() == ref.read()
+
+
+@pytest.mark.parametrize("n", [1, 8 * 512 * 512 + 3])
+def test_a_step_without_its_partial_sums_says_so(n):
+    """what happens when another step overwrites the scratch: no number, the higher bit-width, the sum kept; later steps
+    are not affected"""
+    cur, prev = (torch.randn(n, device=DEV).to(torch.bfloat16) for _ in range(2))
+    ctl = dvdq.GbsController(delta=1e9, b_low=4, b_high=6)
+    ctl.step(cur, prev)
+    acc, l1, bits = ctl.read()
+    assert bits == 4 and acc > 0
+    try:
+        dvdq.bench_set_gbs_wait(100000)   # one millisecond
+        ctl.step(cur, prev)
+        lost = ctl.read()
+    finally:
+        dvdq.bench_set_gbs_wait(-1)
+    assert lost[0] == acc and lost[1] != lost[1] and lost[2] == 6
+    ctl.step(cur, prev)
+    assert ctl.read() == (acc + acc, l1, 4)
