@@ -38,12 +38,16 @@ int dvdq_bench_mfma_i8(int iters, int data, int32_t *sink, double *ops_out, void
 int dvdq_bench_mfma_fp6(int iters, int data, int32_t *sink, double *ops_out, void *hip_stream);
 
 /* Tile-configuration sweeps: force the native-layout GEMMs to use tile variant `variant`
- * (INT8 matrix path: 1..4, see the dispatch tables in w4ax_gemm.hip, one per code container; shapes too
+ * (INT8 matrix path: 1..5, see the dispatch tables in w4ax_gemm.hip, one per code container; shapes too
  * shallow in K for a variant's ring fall back to variant 2.  FP6 matrix path: 1 and 3, see w4a4_fp6_gemm.hip,
  * other values mean its own choice; either path: 10..16 force a shape of the small-output kernel, see
  * w4ax_gemm_small.hip); -1 restores the library's own choice.  Process-wide (an atomic
  * that every launch reads once), meant for benchmarking only. */
 int dvdq_bench_set_gemm_variant(int variant);
+
+/* The tile variant the library takes by itself for a product (numbers as above; host only, no GPU needed).  `vectors`:
+ * how many there are of bias and zero-points.  Sizes below 1: minus a dvdq_status code. */
+int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors);
 
 /* How the native-layout GEMM's persistent workgroups get their tiles: 0 = fixed equal shares,
  * -1 = the library's own choice (tiles drawn from per-stream counters, fixed shares while a

@@ -173,6 +173,12 @@ int dvdq_bench_set_gemm_variant(int variant) {
     return DVDQ_OK;
 }
 
+int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors) {
+    if (M < 1 || N < 1 || K < 32) return -DVDQ_ERR_SHAPE;
+    if (w_layout == DVDQ_W_NATIVE_FP6) return dvdq::w4a4_fp6_gemm_choice(M, N, K, vectors);
+    return dvdq::w4ax_gemm_choice(M, N, K, codes_format, w_layout);
+}
+
 int dvdq_bench_set_gemm_schedule(int schedule) {
     if (schedule < -1 || schedule > 0) return DVDQ_ERR_UNSUPPORTED;
     dvdq::set_gemm_schedule(schedule);

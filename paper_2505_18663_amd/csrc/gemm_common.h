@@ -37,7 +37,6 @@ static __device__ __forceinline__ void store_streaming16(__amdgpu_buffer_rsrc_t 
 // buffer's end, so that a tile at the lower edge of the output is stored by the same instructions as any other (lanes
 // past the end are dropped).  Channels past N are the caller's to drop: kPastTile as the offset of a column group does,
 // whatever row offset is added to it.  Offsets are 32 bits: N below kMaxTileN.
-constexpr int64_t kMaxTileN = (int64_t)1 << 22;
 constexpr uint32_t kPastTile = 0x80000000u;
 static __device__ __forceinline__ __amdgpu_buffer_rsrc_t output_tile(uint16_t *y, int m0, int n0, int M, int N, int bm) {
     const int rows = min(bm, M - m0);

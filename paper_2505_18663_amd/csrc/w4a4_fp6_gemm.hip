@@ -377,6 +377,24 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
 
 }  // namespace
 
+// The tile variant for a size (variants 1 and 3 below, 10 + shape: the small-output kernel).  `vectors`: how many there are of bias
+// and zero-points.
+// The wide kernel's fixed cost per tile (nothing hides its epilogue) makes it pay from six K slices on (GEMM alone,
+// 32760 x 4608 output, variants 1 and 3: 79 and 84 us at K = 512, 101 and 94 at 768, 118 and 109 at 1024, 134 and 116 at
+// 1280; 8192 x 4608: 29.4 and 28.9, 35.1 and 33.1, 40.9 and 39.6, 46.4 and 41.7; 6144 x 1536: 12.7 and 12.1, 14.0 and 13.3).
+// (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind one of these at every K from 256 to 1280.)
+// Tiles stored per element (N no multiple of 8) make that cost several times as large, above all where bias or zero-points
+// are fetched per element too: with both it does not pay at any depth (15601 x 1161, variants 1 and 3: 109.4 and 183.9 us at
+// K = 1280, 172.1 and 229.5 at 6144, 273 and 304 at 13824), with one from 96 slices on (with a bias 129.8 and 161.7 at K = 3072,
+// 211 and 221 at 9216, 250.7 and 250.5 at 12288, 271 and 266 at 13824), without from 24 (in the mean of 20 sizes 2 % slower at
+// K = 1280, 1 % faster at 3072, 9 % at 6144).
+int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors) {
+    const int shape = small_gemm_shape(M, N, K, true);
+    if (shape >= 0) return kFirstSmallVariant + shape;
+    if (whole_line_tiles(N)) return K / kBK >= 6 ? 3 : 1;
+    return vectors < 2 && K / kBK >= (vectors ? 96 : 24) ? 3 : 1;
+}
+
 int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                          const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
                          int64_t K, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
@@ -385,17 +403,13 @@ int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8
     //   1: two independent 4-wave workgroups per compute unit, 128 x 256 tiles, two buffers: while one
     //      converts and stores a tile the other multiplies;
     //   3: the wide kernel of w4ax_gemm_wide.hip: one 4-wave workgroup, 256 x 256 tiles, 128 x 128 wave tiles with
-    //      the accumulators in AGPRs: a third fewer LDS fragment bytes per MFMA, but a larger fixed cost per tile
-    //      (nothing hides its epilogue), so it pays from six K slices on (GEMM alone, 32760 x 4608 output, variants 1
-    //      and 3: 79 and 84 us at K = 512, 101 and 94 at 768, 118 and 109 at 1024, 134 and 116 at 1280; 8192 x 4608:
-    //      29.4 and 28.9, 35.1 and 33.1, 40.9 and 39.6, 46.4 and 41.7; 6144 x 1536: 12.7 and 12.1, 14.0 and 13.3).
-    // (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind one of these at every K from 256 to 1280.)
+    //      the accumulators in AGPRs: a third fewer LDS fragment bytes per MFMA, but a larger fixed cost per tile.
     int v = gemm_variant();
-    const int shape = v < 0 ? small_gemm_shape(M, N, K, true) : v - kFirstSmallVariant;   // outputs of few tiles
-    if (shape >= 0 && shape < kSmallVariants)
-        return launch_w4ax_gemm_small(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, DVDQ_CODES_FP6, DVDQ_W_NATIVE_FP6, shape, y,
-                                      acc_out, stream);
-    if (v != 1 && v != 3) v = K / kBK >= 6 ? 3 : 1;
+    if (v != 1 && v != 3 && (v < kFirstSmallVariant || v >= kFirstSmallVariant + kSmallVariants))
+        v = w4a4_fp6_gemm_choice(M, N, K, (bias != nullptr) + (w_zero != nullptr));
+    if (v >= kFirstSmallVariant)
+        return launch_w4ax_gemm_small(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, DVDQ_CODES_FP6,
+                                      DVDQ_W_NATIVE_FP6, v - kFirstSmallVariant, y, acc_out, stream);
     if (v == 3) return launch_w4ax_gemm_wide(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, true, y, acc_out, stream);
     return launch_fp6<128, 256, 2, 2, 2, 2>(DVDQ_FP6_ARGS);
 #undef DVDQ_FP6_ARGS

@@ -578,32 +578,45 @@ int limited_grid(int grid) {
     return limit < 8 ? 8 : limit / 8 * 8;
 }
 
+// The tile variant for a size (variants 2 and 5 below; 10 + shape: the small-output kernel, all that canonical weights have).
+// Variant 5 is the wide kernel of w4ax_gemm_wide.hip (int8 codes only), taken
+//   - from 12 K slices on.  Against variant 2 (GEMM alone, outputs of 144 to 2304 tiles of 256 x 256): K = 640 up to 7 %
+//     slower; 1280 level where channels are a multiple of 256, up to 7 % slower at 1160; 1536 level without zero-points, 1-6 %
+//     faster with them (15600 x 1536 x 1536: 55.6 -> 52.7 us); 3072 and 9216 mostly 3-10 % faster (4096 x 3072 x 3072: 43.8
+//     -> 40.9);
+//   - where its tiles are stored as whole lines.  Stored per element (N no multiple of 8), a tile takes several times as
+//     long, and there is no second workgroup to multiply meanwhile: variant 2 is 4-24 % faster at K = 1536 .. 6144, and
+//     with bias and zero-points 20-53 % (5000 x 4609 with K = 3072: 147.1 -> 118.3 us, with both 234.3 -> 161.7).
+int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout) {
+    const int shape = small_gemm_shape(M, N, K, false);
+    if (w_layout == DVDQ_W_CANONICAL) return kFirstSmallVariant + (shape < 0 ? kLargestSmallShape : shape);
+    if (shape >= 0) return kFirstSmallVariant + shape;
+    return codes_format == DVDQ_CODES_INT8 && K / 128 >= 12 && whole_line_tiles(N) ? 5 : 2;
+}
+
 int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                      const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
                      int64_t K, int codes_format, int w_layout, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
     if (w_layout == DVDQ_W_CANONICAL) {
         if (codes_format != DVDQ_CODES_INT8 || w_zero) return DVDQ_ERR_UNSUPPORTED;
-        const int v = gemm_variant();
+        const int f = gemm_variant(), v = f >= kFirstSmallVariant ? f : w4ax_gemm_choice(M, N, K, codes_format, w_layout);
         return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, nullptr, nullptr, bias, M, N,
-                                      K, codes_format, w_layout, v >= kFirstSmallVariant ? v - kFirstSmallVariant : small_gemm_shape(M, N, K, false),
-                                      y, acc_out, stream);
+                                      K, codes_format, w_layout, v - kFirstSmallVariant, y, acc_out, stream);
     }
     const int m = (int)M, n = (int)N, k = (int)K;
 #define DVDQ_GEMM_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, m, n, k, y, acc_out, stream
     // Tile variants: {tile M, tile N, K slice, waves M x N, ring depth, workgroups per compute unit}.
-    // Outputs of few tiles go to w4ax_gemm_small.hip (small_gemm_shape).  Variant 2 is the default of the two-wave kernels
-    // for every other shape: two independent 4-wave workgroups per compute unit,
+    // Outputs of few tiles go to w4ax_gemm_small.hip (small_gemm_shape).  Variant 2 is the default of the two-wave kernels: two independent 4-wave workgroups per compute unit,
     // each owning a 128 x 256 tile (64 x 128 per wave) with K slices of 128 through two buffers.  In
     // interleaved sweeps over the DiT shapes (K = 1536 ... 13824) it was fastest or within 1 % of the
     // fastest: while one workgroup converts and stores its tile the other keeps the matrix cores busy,
     // which the one-workgroup 256 x 256 variants cannot do.  The others remain for sweeps; a shape with
     // fewer K slices than a variant's ring needs falls back to variant 2, which always qualifies.
     const int forced = gemm_variant();
-    int v = forced < 0 ? 2 : forced;
-    const int shape = forced < 0 ? small_gemm_shape(M, N, K, false) : forced - kFirstSmallVariant;
-    if (shape >= 0)
+    int v = forced < 0 ? w4ax_gemm_choice(M, N, K, codes_format, w_layout) : forced;
+    if (v >= kFirstSmallVariant)
         return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, w_zero, code_rowsum,
-                                      bias, M, N, K, codes_format, w_layout, shape, y, acc_out, stream);
+                                      bias, M, N, K, codes_format, w_layout, v - kFirstSmallVariant, y, acc_out, stream);
     if (codes_format == DVDQ_CODES_PACKED4) {
         if ((v == 1 && k / 128 < 2) || (v > 2 && k / 128 < 3)) v = 2;
         switch (v) {
@@ -614,12 +627,6 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
             default: return DVDQ_ERR_UNSUPPORTED;
         }
     }
-    // Variant 5 is the wide kernel of w4ax_gemm_wide.hip (int8 codes only), taken by itself when a tile has at least 12 K
-    // slices.  Against variant 2 (GEMM alone, outputs of 144 to 2304 tiles of 256 x 256): K = 640 up to 7 % slower;
-    // 1280 level where channels are a multiple of 256, up to 7 % slower at 1160; 1536 level without zero-points, 1-6 %
-    // faster with them (15600 x 1536 x 1536: 55.6 -> 52.7 us); 3072 and 9216 mostly 3-10 % faster (4096 x 3072 x 3072: 43.8
-    // -> 40.9).
-    if (forced < 0 && codes_format == DVDQ_CODES_INT8 && k / 128 >= 12) v = 5;
     if (v == 5)
         return launch_w4ax_gemm_wide(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, w_zero, code_rowsum, bias,
                                      M, N, K, false, y, acc_out, stream);

@@ -424,13 +424,12 @@ int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uin
         case 6: return launch_tile<FMT, 2, 4, 1>(DVDQ_SMALL_ARGS);             \
         default: return DVDQ_ERR_UNSUPPORTED;                                  \
     }
-    // Canonical weights have no other kernel: outputs beyond the lines above take a wave per 64 x 128 tile, all of K in
-    // one wave.  (Codes and weights come in rows of K and K / 2 bytes; a slice of a weight row is half a cache line, and
+    // Canonical weights have no other kernel: outputs beyond the lines above take shape 6, a wave per 64 x 128 tile, all of K
+    // in one wave.  (Codes and weights come in rows of K and K / 2 bytes; a slice of a weight row is half a cache line, and
     // that traffic out of the L2 is the limit.  7800 x 1440 x 1440: 61.7 us with 256 x 256 tiles shared by four waves,
     // 43.9 as shape 5, 40.0 as 6; 512 x 3072 x 3072: 83.4 -> 15.5 as 3; 32760 x 1536 x 4608: 543 -> 349 as 6;
     // 32760 x 13824 x 5120: 2792 -> 2471, in the tile order below; in plain order deep
     // K with many channels lost to it, 27510 x 11552 x 7296: 3272 -> 5513, now 3319.)
-    if (w_layout == DVDQ_W_CANONICAL && shape < 0) shape = 6;
     if (codes_format == DVDQ_CODES_FP6) DVDQ_SMALL(FMT_FP6)
     if (codes_format == DVDQ_CODES_PACKED4) DVDQ_SMALL(FMT_PACKED4)
     if (w_layout == DVDQ_W_CANONICAL) DVDQ_SMALL(FMT_CANONICAL)
