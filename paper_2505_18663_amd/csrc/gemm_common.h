@@ -23,14 +23,24 @@ static __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
     return __builtin_bit_cast(uint32_t, p);
 }
 
-// 16-byte store of output the kernel never reads again, at byte `off` of the tile's buffer (output_tile below).
-// Non-temporal: with whole 128-byte lines per instruction (the staged epilogue) the output stream then bypasses the L2
-// instead of evicting code and weight panels and leaving dirty lines to flush at the kernel's end.  (For partial-line
-// stores the same hint is much slower than write-back caching.)
-static __device__ __forceinline__ void store_streaming16(__amdgpu_buffer_rsrc_t tile, uint32_t off, uint4 v) {
+// Stores of a staged chunk, output the kernel never reads again: 16 bytes per lane in each of four rows 8 apart, from byte
+// `off` of the tile's buffer (output_tile below) on; 8 lanes make 128 bytes of a row.
+// Non-temporal where rows begin at a multiple of 64 bytes (N of 32): the output stream then bypasses the L2 instead of
+// evicting code and weight panels and leaving dirty lines to flush at the kernel's end (FP6, 118800 x 768 x 1536: 121.5 us,
+// cached 170.3; 32760 x 1536 x 4608: 163.3 and 175.9).  Where they do not, the 128 bytes begin and end within a line, and
+// every part of a line becomes a write to memory of its own: cached stores, which meet in the L2 (118800 x 256 x 952: 155.1
+// us non-temporal, 59.5 cached; 32760 x 1536 x 9704: 535.8 and 476.6; int8 codes 118800 x 768 x 1160: 191.3 and 161.9).
+static __device__ __forceinline__ void store_chunk(__amdgpu_buffer_rsrc_t tile, uint32_t off, int N, const uint4 (&v)[4]) {
     typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-    const v4u vv = {v.x, v.y, v.z, v.w};
-    __builtin_amdgcn_raw_buffer_store_b128(vv, tile, (int)off, 0, 2 /* nt */);
+    if ((N & 31) == 0) {
+#pragma unroll
+        for (int pass = 0; pass < 4; ++pass)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v[pass]), tile, (int)(off + pass * 16 * N), 0, 2 /* nt */);
+    } else {
+#pragma unroll
+        for (int pass = 0; pass < 4; ++pass)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v[pass]), tile, (int)(off + pass * 16 * N), 0, 0);
+    }
 }
 
 // Buffer of the output rows from m0 on, starting at channel n0, at most bm of them: what lies past row M is past the
@@ -331,8 +341,7 @@ static __device__ __forceinline__ void epilogue_interior(typename P::vec (&acc)[
                 const int row = pass * 8 + rd_row;
                 v[pass] = *reinterpret_cast<const uint4 *>(stg + row * 128 + ((rd_piece ^ (row & 7)) << 4));
             }
-#pragma unroll
-            for (int pass = 0; pass < 4; ++pass) store_streaming16(tile, off + pass * 16 * N, v[pass]);
+            store_chunk(tile, off, N, v);
             __builtin_amdgcn_wave_barrier();   // the next chunk's LDS writes stay behind these reads
         }
     }

@@ -627,8 +627,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                     // same area stay behind these reads) and stored to memory half a chunk later.
                     if constexpr (U == 11) publish_draw();
                     if constexpr ((U & 7) == 3 && U > 8) {
-#pragma unroll
-                        for (int pass = 0; pass < 4; ++pass) store_streaming16(tile, pend_off + pass * 16 * N, pend[pass]);
+                        store_chunk(tile, pend_off, N, pend);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     if constexpr ((U & 7) == 7) {   // the chunk is staged: whole rows back, 8 lanes per 128-byte row
@@ -646,8 +645,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 });
-#pragma unroll
-                for (int pass = 0; pass < 4; ++pass) store_streaming16(tile, pend_off + pass * 16 * N, pend[pass]);   // the last chunk
+                store_chunk(tile, pend_off, N, pend);   // the last chunk
             };
             if (w_zero) {
                 if (bias) interior(std::true_type{}, std::true_type{});

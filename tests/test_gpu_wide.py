@@ -162,3 +162,23 @@ def test_default_dispatch_around_the_fp6_wide_kernel_threshold(K):
     for variant in (1, 2, WIDE_FP6):
         y = _run(c, variant)
         assert torch.equal(y.view(torch.int16), y_plain.view(torch.int16)), f"variant {variant}"
+
+
+@pytest.mark.parametrize("fp6", [False, True])
+@pytest.mark.parametrize("N", [248, 520, 1032, 1120, 1152, 772, 1161])
+def test_tiles_at_the_edges_store_their_part_and_nothing_else(N, fp6):
+    """Row pitches of 16, 64 and 128 bytes' multiples (N = 520 and 1032; 1120; 1152: cached and non-temporal stores) and
+    rows stored per element, ragged in M: each large-tile kernel against the small-output kernel, with memory of a known
+    pattern before and behind Y"""
+    M, K = 901, 512
+    c = _case(M, K, N, 4, N, fp6)
+    guard = 1 << 16
+    for extra in (dict(), dict(bias=c["bias"], w_zero=c["wz"], code_rowsum=c["rs"])):
+        y_ref = _run(c, 15, **extra)
+        for variant in (1, 3) if fp6 else (1, 2, 3, 4, 5):
+            print(f"edges N{N} fp6={fp6} variant {variant} {sorted(extra)}", flush=True)
+            buf = torch.full((M * N + 2 * guard,), 0x5A5A, dtype=torch.int16, device=DEV)
+            y = buf[guard:guard + M * N].view(M, N).view(torch.bfloat16)
+            _run(c, variant, y=y, **extra)
+            assert torch.equal(y.view(torch.int16), y_ref.view(torch.int16)), variant
+            assert bool((buf[:guard] == 0x5A5A).all()) and bool((buf[guard + M * N:] == 0x5A5A).all()), variant
