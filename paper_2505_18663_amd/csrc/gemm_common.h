@@ -138,10 +138,14 @@ static __device__ __forceinline__ void tile_origin(int t, int tiles_m, int tiles
 // Workgroup ids are dealt round-robin to the 8 XCDs, and the workgroups of one XCD work on one contiguous
 // run of tile numbers at a time.
 //   ctr != nullptr: XCD x owns tile numbers [x total / 8, (x + 1) total / 8).  Its i-th workgroup starts with the
-//     i-th of them; the others are drawn in order through one counter word (an atomic add).  (A workgroup has to
+//     i-th of them and goes on with the one its neighbour in a pair would take of the next n (n workgroups per XCD); the
+//     others are drawn in order through one counter word (an atomic add).  (A workgroup has to
 //     know its second tile when it starts.  When it drew both, the workgroups that started first took two tiles
 //     each and, with fewer than two tiles per workgroup, left none to the last ones: 732 tiles on 512 workgroups
-//     took 65.7 us instead of 52.9, 125 tiles on 128 workgroups 39 instead of 21.)  The word is zero when the kernel starts: whatever
+//     took 65.7 us instead of 52.9, 125 tiles on 128 workgroups 39 instead of 21.  When it drew the second, that draw's
+//     reply stood at the start of every launch, and where columns of tiles differ in cost and alternate, as with 343
+//     channels, some workgroups took two dear ones: 58675 x 512 x 343 95.3 -> 107.6 us, now 88.5; 9000 x 640 x 3072 35.2
+//     -> 31.1, with packed codes 9000 x 1536 x 4608 74.1 -> 64.4, 32760 x 1536 x 8960 474.9 -> 469.9.)  The word is zero when the kernel starts: whatever
 //     runs on the stream right before the GEMM clears the slot (the quantizer kernel, if that is what the
 //     library enqueued last on the stream, else a one-wave kernel the GEMM's launcher puts in front), so no
 //     launch depends on what an earlier one -- finished or not -- left behind, and nothing has to be put back
@@ -149,7 +153,7 @@ static __device__ __forceinline__ void tile_origin(int t, int tiles_m, int tiles
 //   ctr == nullptr: fixed shares, the j-th tile of workgroup b is number j * grid + (b % 8) * (grid / 8) + b / 8.
 struct TileSource {
     int total, grid, xcd, first_tile, run_lo;
-    unsigned run_len, started;   // tiles of this XCD; how many of them its workgroups start with
+    unsigned run_len, wgs, fixed;   // tiles and workgroups of this XCD; tiles the workgroups start with, two each
     unsigned *ctr;   // this XCD's counter
 
     __device__ __forceinline__ TileSource(int tiles_m, int tiles_n, unsigned *sched) {
@@ -159,12 +163,13 @@ struct TileSource {
         first_tile = xcd * (grid / 8) + blockIdx.x / 8;
         run_lo = (int)((int64_t)xcd * total / 8);
         run_len = (unsigned)((int64_t)(xcd + 1) * total / 8) - (unsigned)run_lo;
-        started = min(run_len, gridDim.x / 8);
+        wgs = gridDim.x / 8;
+        fixed = min(run_len, 2 * wgs);
         ctr = sched ? sched + xcd : nullptr;
     }
     // the tile a draw's reply stands for (drawn mode), or the workgroup's ordinal-th tile (fixed shares); -1: none left
     __device__ __forceinline__ int tile(unsigned reply, int ordinal) const {
-        if (ctr) return reply < run_len - started ? run_lo + (int)(started + reply) : -1;
+        if (ctr) return reply < run_len - fixed ? run_lo + (int)(fixed + reply) : -1;
         const int t = first_tile + ordinal * grid;
         return t < total ? t : -1;
     }
@@ -173,8 +178,9 @@ struct TileSource {
     // the workgroup's first two tiles (one lane; either mode)
     __device__ __forceinline__ void first_two(int &t0, int &t1) const {
         if (ctr) {
-            t0 = blockIdx.x / 8 < run_len ? run_lo + (int)(blockIdx.x / 8) : -1;
-            t1 = started < run_len ? tile(draw(), 1) : -1;
+            const unsigned i = blockIdx.x / 8, second = wgs + ((i ^ 1u) < wgs ? i ^ 1u : i);
+            t0 = i < run_len ? run_lo + (int)i : -1;
+            t1 = second < run_len ? run_lo + (int)second : -1;
         } else {
             t0 = tile(0u, 0);
             t1 = tile(0u, 1);

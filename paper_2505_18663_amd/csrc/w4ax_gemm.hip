@@ -110,7 +110,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
         }
         draw_pending = false;
     };
-    // the first tile follows from the workgroup's number, the second is drawn now
+    // the first two tiles follow from the workgroup's number
     if (wave == 0 && lane == 0) {
         int t0, t1;
         tiles.first_two(t0, t1);
