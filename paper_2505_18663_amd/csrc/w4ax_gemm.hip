@@ -586,12 +586,18 @@ int limited_grid(int grid) {
 //     -> 40.9);
 //   - where its tiles are stored as whole lines.  Stored per element (N no multiple of 8), a tile takes several times as
 //     long, and there is no second workgroup to multiply meanwhile: variant 2 is 4-24 % faster at K = 1536 .. 6144, and
-//     with bias and zero-points 20-53 % (5000 x 4609 with K = 3072: 147.1 -> 118.3 us, with both 234.3 -> 161.7).
+//     with bias and zero-points 20-53 % (5000 x 4609 with K = 3072: 147.1 -> 118.3 us, with both 234.3 -> 161.7);
+//   - unless one to four rounds of its tiles (one per compute unit) would end in one that is less than two fifths full:
+//     variant 2's smaller tiles spread that rest (K = 12800, 4878 x 3088, 260 tiles: 281 us, as variant 2 177; K = 5248,
+//     5960 x 8840, 840 tiles: 267 and 250; on the other side K = 1536, 15600 x 1536, 366 tiles: 48.8 and 50.0).  Over 82
+//     outputs of 117 to 864 tiles the mean time is the same within 1 % for lines from 0.3 to 0.5 of a round.
 int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout) {
     const int shape = small_gemm_shape(M, N, K, false);
     if (w_layout == DVDQ_W_CANONICAL) return kFirstSmallVariant + (shape < 0 ? kLargestSmallShape : shape);
     if (shape >= 0) return kFirstSmallVariant + shape;
-    return codes_format == DVDQ_CODES_INT8 && K / 128 >= 12 && whole_line_tiles(N) ? 5 : 2;
+    if (codes_format != DVDQ_CODES_INT8 || K / 128 < 12 || !whole_line_tiles(N)) return 2;
+    const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
+    return tiles > 256 && tiles < 1024 && last != 0 && 5 * last < 2 * 256 ? 2 : 5;
 }
 
 int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,

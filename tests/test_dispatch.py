@@ -30,6 +30,12 @@ def test_depth_of_k():
     assert dvdq.bench_gemm_choice(32760, 4608, 1536, PACKED4, NATIVE) == 2
 
 
+@pytest.mark.parametrize("tiles,variant", [(192, 5), (256, 5), (257, 2), (358, 2), (359, 5), (512, 5), (513, 2), (614, 2), (615, 5),
+                                           (768, 5), (870, 2), (871, 5), (1024, 5), (1025, 5), (4480, 5)])
+def test_a_nearly_empty_last_round_of_int8_tiles(tiles, variant):
+    assert int8(256 * tiles, 256, 3072) == variant   # one column of 256 x 256 tiles
+
+
 def test_small_outputs_and_canonical_weights():
     assert int8(2, 9216, 1536) >= 10 and fp6(128, 256, 256) >= 10
     assert dvdq.bench_gemm_choice(32760, 4608, 1440, INT8, CANONICAL) == 16
