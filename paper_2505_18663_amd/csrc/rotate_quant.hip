@@ -539,18 +539,20 @@ int launch_rotate_quant(const uint16_t *x, int64_t M, int64_t K, int log2_block,
     const dim3 block(kWave * W * rows_per_wg);
     int wgs_per_cu = 16 / (W * rows_per_wg);
     if (wgs_per_cu < 1) wgs_per_cu = 1;
-    // FP6: consecutive rows a wave takes in turn (see the kernel): 8 if the LDS for collecting them allows, and at most
-    // as many as give every resident workgroup a run.  (Whole 128-byte lines need 8 rows, but a wave takes them one
-    // after the other: with a run of 8 at any M, 128 rows of 1536 channels took 11.6 us on two workgroups, with runs
-    // of one row 4.0.  Swept over runs of 1, 2, 4, 8, M = 32 .. 32768 and 256 .. 13824 channels: the best run is 1 up to
-    // one row per resident slot (512 to 4096 rows), 2 up to four, 4 up to eight, 8 from there: 8192 x 1536 as 8 / 4 / 2 / 1:
-    // 13.8 / 9.4 / 8.6 / 9.3 us, 16384 x 1536: 16.2 / 13.9 / 14.2 / 19.0, 32768 x 1536: 26.2 / 27.0 / 28.9 / 39.5.)
+    // FP6: consecutive rows a wave takes in turn (see the kernel): 1, 2, 4 or 8, the largest run that the LDS for collecting
+    // them allows and of which there are enough for 13/16 of the resident slots (a row each).  (Whole 128-byte
+    // lines need 8 rows, but a wave takes them one after the other: with a run of 8 at any M, 128 rows of 1536 channels took
+    // 11.6 us on two workgroups, with runs of one row 4.0.  Swept over the four runs, M = 1024 .. 32760 and 256 .. 13824
+    // channels: the best run changes between 1.5 and 1.75, 3 and 3.5, 6 and 6.5 rows per slot.  1536 channels (4096 slots) as
+    // runs of 1 / 2 / 4 / 8: 6144 rows 7.0 / 7.9 / 8.5 / 13.0 us, 7168: 8.6 / 8.1 / 8.7 / 13.2, 12288: 13.0 / 10.5 / 12.4 / 14.4,
+    // 14336: 15.3 / 13.3 / 12.7 / 14.7, 24576: 29.5 / 21.4 / 19.1 / 21.8, 26624: 32.0 / 23.6 / 23.3 / 22.6, 32760: 39.1 / 28.0 /
+    // 25.8 / 25.0.)
     const int64_t wgs_resident = 256 * (int64_t)wgs_per_cu;
     int run = 1;
     if (pack4 == 3) {
         const size_t budget = (kLdsPerCu - 8192) / wgs_per_cu;
         for (run = 8; run > 1 && ((size_t)W * rows_per_wg * run * (cpw * 384 + 16) > budget ||
-                                  wgs_resident * rows_per_wg * run > M);)
+                                  13 * wgs_resident * rows_per_wg * run > 16 * M);)
             run /= 2;
     }
     const int group_rows = rows_per_wg * run;

@@ -131,7 +131,7 @@ def rand_x(rng, M, K):
 @pytest.mark.parametrize("M,K,B", [
     (1, 128, 1), (3, 128, 128), (7, 384, 32), (130, 256, 256), (33, 768, 256), (257, 1536, 256), (64, 3072, 256),
     (31, 512, 512), (6, 13824, 512), (17, 640, 8), (4, 65536, 512), (1027, 1536, 256), (40, 2560, 512),
-    (70, 13824, 512), (45, 32768, 512), (70, 8192, 256),   # rows of many units: runs of 8, 4 and 2 rows staged per wave
+    (70, 13824, 512), (45, 32768, 512), (70, 8192, 256),   # rows of many units
 ])
 def test_rotate_quant_fp6_decodes_to_the_int8_codes(M, K, B):
     rng = np.random.default_rng(M * 17 + K + B)
@@ -147,6 +147,19 @@ def test_rotate_quant_fp6_decodes_to_the_int8_codes(M, K, B):
     codes_r, scale_r, xr = oracle.rotate_quant(xb, B, 4, return_rotated=True)
     check_codes_and_scales(decoded, scale6.cpu().numpy(), codes_r, scale_r, xr, 4, f"fp6 M{M} K{K} B{B}",
                            allow_fp32_ties=B <= 8)
+
+
+@pytest.mark.parametrize("M", [831, 833, 1663, 1665, 3327, 3335])
+def test_rotate_quant_fp6_runs_of_rows(M):
+    """8960 channels are 512 resident rows: runs of 1, 2, 4 and 8 rows staged per wave begin at 832, 1664 and 3328 tokens.
+    The same codes as in the int8 container, up to a ragged last run."""
+    K, B = 8960, 256
+    x = to_bf16(rand_x(np.random.default_rng(M), M, K))
+    c6, scale6, rs6 = dvdq.rotate_quant(x, B, 4, codes_format=dvdq.CODES_FP6, want_rowsum=True)
+    codes8, scale8, rs8 = dvdq.rotate_quant(x, B, 4, want_rowsum=True)
+    torch.cuda.synchronize()
+    assert torch.equal(scale6, scale8) and torch.equal(rs6, rs8)
+    assert np.array_equal(oracle.unpack_fp6(c6.cpu().numpy(), M, K), codes8.cpu().numpy())
 
 
 def test_rotate_quant_fp6_leaves_neighbouring_memory_alone():
