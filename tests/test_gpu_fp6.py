@@ -49,7 +49,7 @@ def test_fp6_weight_prepack_holds_the_oracle_encoding():
     assert np.array_equal(native.reshape(K // 128, 512 // 32, 3072), ref)
 
 
-@pytest.mark.parametrize("schedule,variant", [(-1, -1), (0, -1), (-1, 1), (-1, 2), (0, 2)])
+@pytest.mark.parametrize("schedule,variant", [(-1, -1), (0, -1), (-1, 1), (-1, 3), (0, 3)])
 @pytest.mark.parametrize("M,N,K,use_bias", [
     (1, 1, 128, False),          # one row, one channel, one K slice
     (128, 256, 256, True),       # exactly one interior tile
@@ -70,7 +70,7 @@ def test_fp6_gemm_int32_exact(M, N, K, use_bias, schedule, variant):
     c6 = dev(oracle.pack_fp6(codes))
     assert c6.numel() == dvdq.codes_bytes(M, K, dvdq.CODES_FP6)
     dvdq.bench_set_gemm_schedule(schedule)
-    dvdq.bench_set_gemm_variant(variant)   # 1: 128 x 256 tiles, two workgroups per compute unit; 2: 256 x 256 tiles, one
+    dvdq.bench_set_gemm_variant(variant)   # 1: 128 x 256 tiles, two workgroups per compute unit; 3: the wide kernel
     try:
         y, acc = dvdq.w4ax_gemm(c6, dev(xs), w6, dev(ws), 4, dvdq.W_NATIVE_FP6, bias=bias_dev, want_acc=True,
                                 codes_format=dvdq.CODES_FP6, K=K)

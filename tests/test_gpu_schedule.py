@@ -1,6 +1,7 @@
-"""Tile scheduling of the native-layout GEMM.  The persistent workgroups either draw their tiles from
+"""Tile scheduling of the native-layout GEMM.  The persistent workgroups start with two tiles each and draw the others from
 per-stream counters in device memory (default) or take fixed equal shares (while a stream is being
-captured, or forced through the benchmark hook).  Which workgroup computes a tile must not show in
+captured, or forced through the benchmark hook).  So that sizes small enough for a test draw at all, the tests name the
+kernel and let it launch few workgroups only, and say (`_draws`) how many tiles that leaves to draw.  Which workgroup computes a tile must not show in
 the result: outputs are compared bit for bit between the two modes, over shapes with fewer tiles than
 workgroups, edge tiles, every tile variant, many launches in a row (no launch may depend on what the
 one before left in the counters), counters overwritten with garbage between launches, and launches on
@@ -19,6 +20,20 @@ def _library_defaults():
     yield
     dvdq.bench_set_gemm_schedule(-1)
     dvdq.bench_set_gemm_variant(-1)
+    dvdq.bench_set_gemm_grid_limit(0)
+
+
+TILE = {("int8", 1): (256, 256), ("int8", 2): (128, 256), ("int8", 3): (256, 256), ("int8", 4): (128, 256),
+        ("packed", 4): (256, 256), ("int8", 5): (256, 256), ("fp6", 1): (128, 256), ("fp6", 3): (256, 256)}
+
+
+def _draws(kind, variant, workgroups, M, N):
+    """The kernel forced and its grid limited; fails if the launch would leave no tile to draw."""
+    bm, bn = TILE.get((kind, variant)) or TILE["int8", variant]
+    tiles = -(-M // bm) * -(-N // bn)
+    assert workgroups % 8 == 0 and tiles > 2 * workgroups, f"{tiles} tiles on {workgroups} workgroups: nothing to draw"
+    dvdq.bench_set_gemm_variant(variant)
+    dvdq.bench_set_gemm_grid_limit(workgroups)
 
 
 def _operands(M, K, N, bits, packed, seed):
@@ -47,7 +62,7 @@ SHAPES = [
     (100, 256, 200, 8, False),       # one edge tile
     (1000, 384, 776, 6, False),      # 8 x 4 tiles: fewer than workgroups, ragged in M and N
     (3000, 512, 1030, 4, True),      # N not a multiple of 8: per-element path on every tile
-    (8192, 1024, 4096, 4, True),     # 1024 tiles: two per workgroup
+    (8192, 1024, 4096, 4, True),     # 1024 tiles: two per workgroup, none to draw
     (20000, 640, 2304, 4, False),    # 157 x 9 tiles, uneven shares, ragged M
 ]
 
@@ -66,6 +81,11 @@ def test_drawn_and_fixed_shares_give_identical_outputs(M, K, N, bits, packed):
     assert torch.equal(y_fixed.view(torch.int16), y_drawn.view(torch.int16))
     assert torch.equal(y2_fixed.view(torch.int16), y2_drawn.view(torch.int16))
     assert torch.equal(y_fixed.view(torch.int16), y2_fixed.view(torch.int16))
+    tiles = -(-M // 128) * -(-N // 256)
+    for workgroups in (8, 24, 40):      # 1, 3 and 5 workgroups per counter: pairs of them, and one without a partner
+        if tiles > 2 * workgroups:
+            _draws("int8", 2, workgroups, M, N)
+            assert torch.equal(_gemm(ops, bits, packed).view(torch.int16), y_fixed.view(torch.int16)), workgroups
 
 
 @pytest.mark.parametrize("variant", [1, 2, 3, 4])
@@ -73,7 +93,7 @@ def test_drawn_and_fixed_shares_give_identical_outputs(M, K, N, bits, packed):
 def test_every_tile_variant_agrees_between_the_two_modes(variant, packed):
     M, K, N, bits = 5000, 768, 1536, 4
     ops = _operands(M, K, N, bits, packed, seed=variant)
-    dvdq.bench_set_gemm_variant(variant)
+    _draws("packed" if packed else "int8", variant, 24, M, N)
     dvdq.bench_set_gemm_schedule(0)
     y_fixed = _gemm(ops, bits, packed)
     dvdq.bench_set_gemm_schedule(-1)
@@ -85,6 +105,8 @@ def test_every_tile_variant_agrees_between_the_two_modes(variant, packed):
 def test_many_launches_in_a_row_on_one_stream():
     """200 launches in a row on one stream, alternating between two shapes: a launch that counted on from
     where the one before stopped would skip or repeat tiles."""
+    for M, N in ((4096, 2048), (700, 520)):
+        _draws("int8", 2, 8, M, N)
     a = _operands(4096, 512, 2048, 4, True, seed=1)
     b = _operands(700, 256, 520, 6, False, seed=2)
     dvdq.bench_set_gemm_schedule(0)
@@ -103,6 +125,7 @@ def test_many_launches_in_a_row_on_one_stream():
 
 
 def test_launches_on_several_streams_do_not_share_counters():
+    _draws("int8", 2, 24, 6000, 1536)
     ops = [_operands(6000 + 512 * i, 512, 1536, 4, True, seed=10 + i) for i in range(4)]
     dvdq.bench_set_gemm_schedule(0)
     refs = [_gemm(o, 4, True) for o in ops]
@@ -137,13 +160,14 @@ def _fp6_gemm(ops, y=None, stream=None):
     return dvdq.w4ax_gemm(c6, xs, w, ws, 4, dvdq.W_NATIVE_FP6, y=y, codes_format=dvdq.CODES_FP6, K=K, stream=stream)
 
 
-@pytest.mark.parametrize("variant", [1, 2])
+@pytest.mark.parametrize("variant", [1, 3])
 def test_fp6_kernel_counters_and_streams(variant):
     """the FP6 matrix path's kernel draws tiles the same way: both tile variants, many launches in a row on
     one stream and launches on several streams at once, against fixed shares"""
     a = _fp6_operands(4100, 512, 2056, seed=3)     # 17 x 9 tiles of 256 x 256 (33 x 9 of 128 x 256), ragged
-    b = _fp6_operands(700, 256, 520, seed=4)
-    dvdq.bench_set_gemm_variant(variant)
+    b = _fp6_operands(1300, 256, 520, seed=4)
+    for M, N in ((4100, 2056), (1300, 520)):
+        _draws("fp6", variant, 8, M, N)
     dvdq.bench_set_gemm_schedule(0)
     ya_ref, yb_ref = _fp6_gemm(a), _fp6_gemm(b)
     dvdq.bench_set_gemm_schedule(-1)
@@ -173,8 +197,12 @@ def test_fp6_kernel_counters_and_streams(variant):
 def test_gemms_do_not_depend_on_what_the_tile_counters_hold(value):
     """Every counter word overwritten (as a launch that never finished, or a stray write, would leave it) before
     each of several launches: the two-wave INT8 kernel, the wide INT8 kernel, both FP6 kernels, and the fused
-    layer, whose quantizer kernel is what clears the counters."""
+    layer, whose quantizer kernel is what clears the counters.  Eight workgroups: all but their first 16 tiles are drawn."""
     s = torch.cuda.Stream()
+    for kind, variant, M, N in (("int8", 2, 4096, 2048), ("int8", 5, 2100, 1300), ("fp6", 1, 4100, 2056), ("fp6", 3, 4100, 2056),
+                                ("fp6", 1, 3000, 2056)):
+        _draws(kind, variant, 8, M, N)
+    dvdq.bench_set_gemm_variant(-1)
     i8 = _operands(4096, 512, 2048, 4, True, seed=21)
     wide = _operands(2100, 384, 1300, 4, False, seed=22)
     f6 = _fp6_operands(4100, 512, 2056, seed=23)
@@ -195,8 +223,10 @@ def test_gemms_do_not_depend_on_what_the_tile_counters_hold(value):
     with torch.cuda.stream(s):
         for rep in range(3):
             dvdq.bench_fill_tile_counters(value, stream=s)
+            dvdq.bench_set_gemm_variant(1)
             y_layer, _ = dvdq.qlinear(x, f6[2], f6[3], 256, 4, dvdq.W_NATIVE_FP6, codes_format=dvdq.CODES_FP6, stream=s)
             dvdq.bench_fill_tile_counters(value, stream=s)
+            dvdq.bench_set_gemm_variant(2)
             y = _gemm(i8, 4, True, stream=s)
             dvdq.bench_fill_tile_counters(value + rep, stream=s)
             dvdq.bench_set_gemm_variant(5)
@@ -204,7 +234,7 @@ def test_gemms_do_not_depend_on_what_the_tile_counters_hold(value):
             dvdq.bench_fill_tile_counters(value, stream=s)
             dvdq.bench_set_gemm_variant(3)
             y6w = _fp6_gemm(f6, stream=s)
-            dvdq.bench_set_gemm_variant(-1)
+            dvdq.bench_set_gemm_variant(1)
             dvdq.bench_fill_tile_counters(value ^ 5, stream=s)
             y6 = _fp6_gemm(f6, stream=s)
             s.synchronize()
@@ -217,6 +247,7 @@ def test_gemms_do_not_depend_on_what_the_tile_counters_hold(value):
 
 
 def test_a_released_stream_can_be_used_again():
+    _draws("int8", 2, 8, 3000, 1024)
     ops = _operands(3000, 256, 1024, 4, True, seed=31)
     dvdq.bench_set_gemm_schedule(0)
     ref = _gemm(ops, 4, True)
