@@ -30,9 +30,14 @@ static __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 // cached 170.3; 32760 x 1536 x 4608: 163.3 and 175.9).  Where they do not, the 128 bytes begin and end within a line, and
 // every part of a line becomes a write to memory of its own: cached stores, which meet in the L2 (118800 x 256 x 952: 155.1
 // us non-temporal, 59.5 cached; 32760 x 1536 x 9704: 535.8 and 476.6; int8 codes 118800 x 768 x 1160: 191.3 and 161.9).
+// WHICH: the kernel is compiled for one of the two, or tests N at every chunk (a branch there cost the wide INT8 kernel, whose
+// epilogue nothing hides, 1 %: 32760 x 1536 x 8960 468.3 and 463.5 us).
+enum StoreKind { STORE_BY_PITCH, STORE_STREAMING, STORE_CACHED };
+static inline bool streaming_pitch(int64_t N) { return (N & 31) == 0; }
+template <StoreKind WHICH = STORE_BY_PITCH>
 static __device__ __forceinline__ void store_chunk(__amdgpu_buffer_rsrc_t tile, uint32_t off, int N, const uint4 (&v)[4]) {
     typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-    if ((N & 31) == 0) {
+    if (WHICH == STORE_STREAMING || (WHICH == STORE_BY_PITCH && (N & 31) == 0)) {
 #pragma unroll
         for (int pass = 0; pass < 4; ++pass)
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v[pass]), tile, (int)(off + pass * 16 * N), 0, 2 /* nt */);

@@ -71,7 +71,8 @@ __device__ __forceinline__ void static_for(F &&f) {
 // inside a tile.  A kernel of its own rather than a run-time flag: with both orders in one loop the compiler copies
 // registers at the loop's edges, among them the pending reply of the tile draw, and waits for every outstanding
 // load in front of such a copy.
-template <bool FP6, bool ACROSS>
+// STORE: how tiles are stored (see store_chunk).
+template <bool FP6, bool ACROSS, StoreKind STORE>
 __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
     const uint8_t *__restrict__ codes, const float *__restrict__ x_scale, const uint8_t *__restrict__ w,
     const float *__restrict__ w_scale, const int8_t *__restrict__ w_zero, const int32_t *__restrict__ code_rowsum,
@@ -627,7 +628,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                     // same area stay behind these reads) and stored to memory half a chunk later.
                     if constexpr (U == 11) publish_draw();
                     if constexpr ((U & 7) == 3 && U > 8) {
-                        store_chunk(tile, pend_off, N, pend);
+                        store_chunk<STORE>(tile, pend_off, N, pend);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     if constexpr ((U & 7) == 7) {   // the chunk is staged: whole rows back, 8 lanes per 128-byte row
@@ -645,7 +646,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 });
-                store_chunk(tile, pend_off, N, pend);   // the last chunk
+                store_chunk<STORE>(tile, pend_off, N, pend);   // the last chunk
             };
             if (w_zero) {
                 if (bias) interior(std::true_type{}, std::true_type{});
@@ -753,7 +754,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
 
 namespace {
 
-template <bool FP6, bool ACROSS>
+template <bool FP6, bool ACROSS, StoreKind STORE>
 int launch_wide(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale, const int8_t *w_zero,
                 const int32_t *code_rowsum, const uint16_t *bias, int M, int N, int K, uint16_t *y, int32_t *acc_out,
                 hipStream_t stream) {
@@ -781,7 +782,7 @@ int launch_wide(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
     if (total < grid) grid = (total + 7) / 8 * 8;
     grid = limited_grid(grid);
     const size_t smem = (size_t)STAGES * 48 * 1024 + 3 * ((BM + BN) * 4 + BN * 2 + BM * 4 + BN) + 8 * sizeof(int);
-    auto k = w4ax_gemm_wide_kernel<FP6, ACROSS>;
+    auto k = w4ax_gemm_wide_kernel<FP6, ACROSS, STORE>;
     static std::atomic<uint64_t> configured{0};
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
     bool is_clear = false;
@@ -799,14 +800,13 @@ int launch_wide(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
 int launch_w4ax_gemm_wide(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                           const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
                           int64_t K, bool fp6, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
-    if (fp6 && K / kBK >= 3)
-        return launch_wide<true, true>(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, (int)M, (int)N, (int)K, y,
-                                       acc_out, stream);
+#define DVDQ_WIDE_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, (int)M, (int)N, (int)K, y, acc_out, stream
+    const bool streaming = streaming_pitch(N);
+    if (fp6 && K / kBK < 3) return launch_wide<true, false, STORE_BY_PITCH>(DVDQ_WIDE_ARGS);   // (not chosen by the dispatch)
     if (fp6)
-        return launch_wide<true, false>(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, (int)M, (int)N, (int)K, y,
-                                        acc_out, stream);
-    return launch_wide<false, false>(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, (int)M, (int)N, (int)K, y, acc_out,
-                                     stream);
+        return streaming ? launch_wide<true, true, STORE_STREAMING>(DVDQ_WIDE_ARGS) : launch_wide<true, true, STORE_CACHED>(DVDQ_WIDE_ARGS);
+    return streaming ? launch_wide<false, false, STORE_STREAMING>(DVDQ_WIDE_ARGS) : launch_wide<false, false, STORE_CACHED>(DVDQ_WIDE_ARGS);
+#undef DVDQ_WIDE_ARGS
 }
 
 }  // namespace dvdq
