@@ -21,7 +21,7 @@
 // in them is rounded before the end.  The prefix sums are 64-bit integers, the weights in units of 2^-43 .. 2^-47 of
 // the row's largest (FixedPoint below): a weight is exact in them unless it is more than 2^20 times smaller than the
 // largest, and then d is 0 on every grid that does not clip the largest away.  sum w^2 is held in two doubles and the
-// expression evaluated in two.  One rounding to fp64 remains (the row error is within 1.3e-16 of what
+// expression evaluated in them.  One rounding to fp64 remains (the row error is within 1.3e-16 of what
 // sums in 80 bits give).  Below 2^-40 sum w^2, where the two doubles would run out, e2 is taken from the row.
 // So the row is sorted once, its prefix sums are kept, and an evaluation costs 15 lookups instead of a pass over
 // the row with a division per weight.  A lookup is three dependent LDS reads (the cell of values the threshold falls
@@ -31,13 +31,13 @@
 // positions per lane; with one position per lane the divisions and the square root of a round, which are the same in
 // all lanes of a start, weigh twice as much), with no barrier inside the search.
 //
-// Cost.  1536 rows of 8960 weights, 100 steps, 10 rounds: 0.148 ms; a pass over the row per evaluation, one workgroup of
-// 256 threads per row, took 8.7 ms.  Bound by latencies, not by memory (62 MB) nor by vector issue: of the 103 K clocks a
-// row is in work (two rows per compute unit) 18 K are the load and its sums, 17 K the two dealing passes with the counts
-// between them (LDS atomics and barriers), 14 K the windows, 4 K the prefix sums, 46 K the search (eleven rounds of 4 K, a
-// chain of three divisions, a square root and five LDS reads), 6 K the codes.  The sums that are not rounded cost 7 K in
-// the load and 2 K in the search: with sums in fp64, 0.138 ms (8960 rows of 1536: 0.524, now 0.583) and a squared error
-// off by 1e-14, up to 1e-12 where a grid fits a row to a hundredth.
+// Cost.  1536 rows of 8960 weights, 100 steps, 10 rounds: 0.145 ms; a pass over the row per evaluation, one workgroup of
+// 256 threads per row, took 8.7 ms.  Bound by latencies and the issue of fp64 instructions, not by memory (62 MB): of the
+// 104 K clocks a row is in work (two rows per compute unit, each beside another one's phases) 10 K are the load, 25 K the two
+// dealing passes with the counts between them (LDS atomics and barriers) and the sum of squares, 13 K the windows, 4 K the
+// prefix sums, 46 K the search (eleven rounds of 4 K, a chain of three divisions, a square root and five LDS reads), 6 K the
+// codes.  That the sums are not rounded costs 7 K: with sums in fp64 0.136 ms (8960 rows of 1536: 0.517, now 0.586) and a
+// squared error off by 1e-14, up to 1e-12 where a grid fits a row to a hundredth.
 #include "dvdq_internal.h"
 #include "wave_reduce.h"
 
@@ -61,33 +61,11 @@ __device__ __forceinline__ T sum8(T v) {
 
 // A sum held in two doubles: hi + lo.
 struct TwoDoubles { double hi, lo; };
-// a + b without an error: hi = a + b rounded, lo the rest (the same bits for b + a)
-__device__ __forceinline__ TwoDoubles two_sum(double a, double b) {
-    const double s = a + b, t = s - a;
-    return {s, (a - (s - t)) + (b - t)};
-}
-// the same for |a| >= |b|
+// a + b without an error, |a| >= |b|: hi = a + b rounded, lo the rest
 __device__ __forceinline__ TwoDoubles fast_two_sum(double a, double b) {
     const double s = a + b;
     return {s, b - (s - a)};
 }
-__device__ __forceinline__ TwoDoubles operator+(TwoDoubles a, TwoDoubles b) {
-    const TwoDoubles s = two_sum(a.hi, b.hi);
-    return {s.hi, (a.lo + b.lo) + s.lo};
-}
-
-// sum over 16 neighbouring lanes, over the wave; the same in every lane
-template <int CTRL>
-__device__ __forceinline__ TwoDoubles dpp_sum(TwoDoubles v) { return v + TwoDoubles{dpp<CTRL>(v.hi), dpp<CTRL>(v.lo)}; }
-template <bool ROWS32>
-__device__ __forceinline__ TwoDoubles rows_sum(TwoDoubles v) {
-    const Both<double> hi = both_rows<ROWS32>(v.hi), lo = both_rows<ROWS32>(v.lo);
-    return TwoDoubles{hi.a, lo.a} + TwoDoubles{hi.b, lo.b};
-}
-__device__ __forceinline__ TwoDoubles sum16(TwoDoubles v) {
-    return dpp_sum<DPP_MIRROR>(dpp_sum<DPP_HALF_MIRROR>(dpp_sum<DPP_XOR2>(dpp_sum<DPP_XOR1>(v))));
-}
-__device__ __forceinline__ TwoDoubles sum64(TwoDoubles v) { return rows_sum<true>(rows_sum<false>(sum16(v))); }
 
 // Weights as multiples of `unit` = 2^e, summed in 64-bit integers.  A running sum of a few weights is kept as a double
 // near `bias` = 1.5 * 2^52 units, where neighbouring doubles are one unit apart: every addition rounds the weight added
@@ -329,7 +307,6 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
     // ---- minimum, maximum, sum and sum of squares
     float lo_f = INFINITY, hi_f = -INFINITY;
     double sw = 0.0;
-    TwoDoubles sw2 = {0.0, 0.0};
     for (int c = tid; c <= cells; c += T) first[c] = 0u;
     for_row([&] __device__(int, float2 v) {
         lo_f = fminf(lo_f, fminf(v.x, v.y));
@@ -337,8 +314,6 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
         const double a = (double)v.x, b = (double)v.y;
         sw += a;
         sw += b;
-        const TwoDoubles s1 = two_sum(sw2.hi, a * a), s2 = two_sum(s1.hi, b * b);   // (the square of a float is exact)
-        sw2 = {s2.hi, sw2.lo + (s1.lo + s2.lo)};
     });
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) {
@@ -346,24 +321,18 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
         hi_f = fmaxf(hi_f, __shfl_xor(hi_f, m, 64));
     }
     sw = wave_sum(sw);
-    sw2 = sum64(sw2);
     if (lane == 0) {
         s_a[wave] = sw;
-        s_b[wave] = sw2.hi;
-        s_d[wave] = sw2.lo;
         s_c[wave] = __builtin_bit_cast(double, make_float2(lo_f, hi_f));
     }
     __syncthreads();
-    sw = 0.0;
+    sw = wave_sum(lane < WAVES ? s_a[lane] : 0.0);
 #pragma unroll
     for (int i = 0; i < WAVES; ++i) {
-        sw += s_a[i];
         const float2 r = __builtin_bit_cast(float2, s_c[i]);
         lo_f = fminf(lo_f, r.x);
         hi_f = fmaxf(hi_f, r.y);
     }
-    const int slot = lane & 15;
-    sw2 = sum16(slot < WAVES ? TwoDoubles{s_b[slot], s_d[slot]} : TwoDoubles{0.0, 0.0});
     const double lo0 = (double)lo_f, hi0 = (double)hi_f;
     const bool constant = !(hi0 > lo0);
 
@@ -380,11 +349,26 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
         // (m - 2) / 16 + 2 of them at most and needs as many passes).  Rows whose weights crowd into few cells
         // (many equal weights, one enormous outlier) take a bitonic sort instead.
         const CellMap cell = {lo_f, (float)cells / (hi_f - lo_f), cells - 1};
+        // The sum of squares comes in two parts meanwhile: rounded to units so coarse that all K of them add up without an
+        // error (as in FixedPoint), and the rest.  (In this pass, which waits for LDS atomics: summed in two doubles in the
+        // first one it cost 2 to 4 % of the whole.)
+        const int exponent = __builtin_amdgcn_frexp_expf(fmaxf(fabsf(lo_f), fabsf(hi_f))), log2_k = 32 - __builtin_clz(K);
+        const double square_bias = ldexp(0x1.8p52, 2 * exponent + log2_k - 51);
+        double coarse = square_bias;
+        TwoDoubles sw2 = {0.0, 0.0};
         for_row([&] __device__(int, float2 v) {
             atomicAdd(&first[1 + cell(v.x)], 1u);
             atomicAdd(&first[1 + cell(v.y)], 1u);
+            for (int h = 0; h < 2; ++h) {
+                const double w = (double)(h ? v.y : v.x), q = w * w, sum = coarse + q;   // (the square of a float is exact)
+                sw2.lo += q - (sum - coarse);
+                coarse = sum;
+            }
         });
+        sw2 = {wave_sum(coarse - square_bias), wave_sum(sw2.lo)};
+        if (lane == 0) { s_b[wave] = sw2.hi; s_d[wave] = sw2.lo; }
         __syncthreads();
+        sw2 = {wave_sum(lane < WAVES ? s_b[lane] : 0.0), wave_sum(lane < WAVES ? s_d[lane] : 0.0)};
         uint32_t *mine = first + 1 + tid * (cells / T);   // this thread's consecutive cells
         int count = 0, fullest = 0;
         for (int i = 0; i < cells / T; ++i) {
@@ -440,8 +424,8 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
 
         // ---- prefix sums, one every BLK weights.  A unit is 2^-bits of the power of two above the largest weight: the
         // sums of up to BLK weights stay below 2^51 units, those of 15 prefix sums of K weights below 2^63.
-        const int bits = min(47, 59 - (32 - __builtin_clz(K)));
-        const double unit = ldexp(1.0, __builtin_amdgcn_frexp_expf(fmaxf(fabsf(lo_f), fabsf(hi_f))) - bits);
+        const int bits = min(47, 59 - log2_k);
+        const double unit = ldexp(1.0, exponent - bits);
         const FixedPoint fixed = {0x1.8p52 * unit, unit};
         int64_t total;   // all K weights
         {
@@ -595,7 +579,7 @@ int launch_bgr(const float *w, int64_t N, int64_t K, int n_steps, int max_refine
 #define DVDQ_BGR_ARGS(CELLS) \
     w, N, (int)K, CELLS, n_steps, max_refine, eps, search, w_packed, w_scale, w_zero, row_error, stream
     // A few weights per cell: 1024 .. 4096 cells.  Two rows at a time per compute unit, as workgroups of 512 threads,
-    // while their LDS allows (half of 160 KB each; longer rows with coarser prefix sums and cells): 0.148 ms against 0.201
+    // while their LDS allows (half of 160 KB each; longer rows with coarser prefix sums and cells): 0.145 ms against 0.20
     // as workgroups of 1024 for 1536 rows of 8960.  A workgroup of 1024 threads where there is no second row to put
     // beside it: with no more rows than compute units (32 rows of 8960: level at 100 steps, 46.7 us against 50.8 at 200;
     // 200 rows of 13824: 41.7 against 46.0), and from 14 K weights on.

@@ -23,29 +23,21 @@ static __device__ __forceinline__ T dpp(T v) {
     }
 }
 
-// {value of lane l, value of lane l ^ 16} in an order that both lanes agree on; likewise l ^ 32
-template <typename T>
-struct Both { T a, b; };
-template <bool ROWS32, typename T>
-static __device__ __forceinline__ Both<T> both_rows(T v) {
+// op(value of lane l, value of lane l ^ 16), the same in both; likewise l ^ 32
+template <bool ROWS32, class Op, typename T>
+static __device__ __forceinline__ T swap_rows(T v, Op op) {
     auto swap = [](uint32_t x) {
         if constexpr (ROWS32) return __builtin_amdgcn_permlane32_swap(x, x, false, false);
         else return __builtin_amdgcn_permlane16_swap(x, x, false, false);
     };
     if constexpr (sizeof(T) == 4) {
         const auto r = swap(__builtin_bit_cast(uint32_t, v));
-        return {__builtin_bit_cast(T, (uint32_t)r[0]), __builtin_bit_cast(T, (uint32_t)r[1])};
+        return op(__builtin_bit_cast(T, (uint32_t)r[0]), __builtin_bit_cast(T, (uint32_t)r[1]));
     } else {
         const uint64_t u = __builtin_bit_cast(uint64_t, v);
         const auto lo = swap((uint32_t)u), hi = swap((uint32_t)(u >> 32));
-        return {__builtin_bit_cast(T, ((uint64_t)hi[0] << 32) | lo[0]), __builtin_bit_cast(T, ((uint64_t)hi[1] << 32) | lo[1])};
+        return op(__builtin_bit_cast(T, ((uint64_t)hi[0] << 32) | lo[0]), __builtin_bit_cast(T, ((uint64_t)hi[1] << 32) | lo[1]));
     }
-}
-// op over the two, the same in both lanes
-template <bool ROWS32, class Op, typename T>
-static __device__ __forceinline__ T swap_rows(T v, Op op) {
-    const Both<T> r = both_rows<ROWS32>(v);
-    return op(r.a, r.b);
 }
 
 // sum over the wave, the same in every lane (a fixed order of additions)
