@@ -380,19 +380,21 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
 // The tile variant for a size (variants 1 and 3 below, 10 + shape: the small-output kernel).  `vectors`: how many there are of bias
 // and zero-points.
 // The wide kernel's fixed cost per tile (nothing hides its epilogue) makes it pay from six K slices on (GEMM alone,
-// 32760 x 4608 output, variants 1 and 3: 79 and 84 us at K = 512, 101 and 94 at 768, 118 and 109 at 1024, 134 and 116 at
-// 1280; 8192 x 4608: 29.4 and 28.9, 35.1 and 33.1, 40.9 and 39.6, 46.4 and 41.7; 6144 x 1536: 12.7 and 12.1, 14.0 and 13.3).
-// (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind one of these at every K from 256 to 1280.)
+// 32760 x 4608 output, variants 1 and 3: 81.0 and 78.8 us at K = 512, 96.3 and 92.1 at 768, 115 and 106 at 1024, 136 and 121
+// at 1280; 8192 x 4608: 29.6 and 29.0, 33.2 and 31.8, 38.0 and 35.8, 43.4 and 39.6; with zero-points it is level or behind up
+// to 640: 60000 x 3072 119 and 128 at 512).  (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind one of
+// these at nearly every K from 256 to 640, 3 % ahead at best in the mean of a shape.)
 // Tiles stored per element (N no multiple of 8) make that cost several times as large, above all where bias or zero-points
-// are fetched per element too: with both it does not pay at any depth (15601 x 1161, variants 1 and 3: 109.4 and 183.9 us at
-// K = 1280, 172.1 and 229.5 at 6144, 273 and 304 at 13824), with one from 96 slices on (with a bias 129.8 and 161.7 at K = 3072,
-// 211 and 221 at 9216, 250.7 and 250.5 at 12288, 271 and 266 at 13824), without from 24 (in the mean of 20 sizes 2 % slower at
-// K = 1280, 1 % faster at 3072, 9 % at 6144).
+// are fetched per element too: with both it does not pay at any depth (15601 x 1161, variants 1 and 3: 105 and 183 us at
+// K = 1280, 168 and 230 at 6144, 271 and 305 at 13824), with one from 96 slices on (with a bias 126 and 163 at K = 3072, 208 and
+// 223 at 9216, 247 and 253 at 12288, 269 and 268 at 13824; 5000 x 3074 231 and 208 at 12288), without from 48 (93.6 and 101 at
+// 3072, 134 and 131 at 6144, 176 and 162 at 9216; in the mean of 25 to 37 sizes 9 % slower at K = 1280, 6 % at 3072, 3 % faster
+// at 6144).
 int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors) {
     const int shape = small_gemm_shape(M, N, K, true);
     if (shape >= 0) return kFirstSmallVariant + shape;
     if (whole_line_tiles(N)) return K / kBK >= 6 ? 3 : 1;
-    return vectors < 2 && K / kBK >= (vectors ? 96 : 24) ? 3 : 1;
+    return vectors < 2 && K / kBK >= (vectors ? 96 : 48) ? 3 : 1;
 }
 
 int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,

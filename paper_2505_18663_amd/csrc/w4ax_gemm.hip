@@ -580,17 +580,16 @@ int limited_grid(int grid) {
 
 // The tile variant for a size (variants 2 and 5 below; 10 + shape: the small-output kernel, all that canonical weights have).
 // Variant 5 is the wide kernel of w4ax_gemm_wide.hip (int8 codes only), taken
-//   - from 12 K slices on.  Against variant 2 (GEMM alone, outputs of 144 to 2304 tiles of 256 x 256): K = 640 up to 7 %
-//     slower; 1280 level where channels are a multiple of 256, up to 7 % slower at 1160; 1536 level without zero-points, 1-6 %
-//     faster with them (15600 x 1536 x 1536: 55.6 -> 52.7 us); 3072 and 9216 mostly 3-10 % faster (4096 x 3072 x 3072: 43.8
-//     -> 40.9);
+//   - from 12 K slices on.  Against variant 2 (GEMM alone): K = 640 up to 7 % slower; 1280 level; 1536 from 4 % slower to 3 %
+//     faster (15600 x 1536 45.6 and 47.3 us, 32760 x 4608 221 and 214); 3072 8 % faster (4096 x 3072 40.0 and 37.0, 15600 x 3072
+//     135 and 125);
 //   - where its tiles are stored as whole lines.  Stored per element (N no multiple of 8), a tile takes several times as
 //     long, and there is no second workgroup to multiply meanwhile: variant 2 is 4-24 % faster at K = 1536 .. 6144, and
-//     with bias and zero-points 20-53 % (5000 x 4609 with K = 3072: 147.1 -> 118.3 us, with both 234.3 -> 161.7);
+//     with bias and zero-points 20-53 % (5000 x 4609 with K = 3072: 114 and 140 us, with both 158 and 233);
 //   - unless one to four rounds of its tiles (one per compute unit) would end in one that is less than two fifths full:
-//     variant 2's smaller tiles spread that rest (K = 12800, 4878 x 3088, 260 tiles: 281 us, as variant 2 177; K = 5248,
-//     5960 x 8840, 840 tiles: 267 and 250; on the other side K = 1536, 15600 x 1536, 366 tiles: 48.8 and 50.0).  Over 82
-//     outputs of 117 to 864 tiles the mean time is the same within 1 % for lines from 0.3 to 0.5 of a round.
+//     variant 2's smaller tiles spread that rest (K = 12800, 4878 x 3088, 260 tiles: 171 and 285 us; K = 5248, 5960 x 8840, 840
+//     tiles: 242 and 266).  Over 82 outputs of 117 to 864 tiles the mean time is the same within 1 % for lines from 0.3 to 0.5 of
+//     a round.
 int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout) {
     const int shape = small_gemm_shape(M, N, K, false);
     if (w_layout == DVDQ_W_CANONICAL) return kFirstSmallVariant + (shape < 0 ? kLargestSmallShape : shape);
