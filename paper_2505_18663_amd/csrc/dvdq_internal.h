@@ -37,9 +37,11 @@ constexpr int kLargestSmallShape = 6;                        // what canonical w
 // the tile variants that the launchers take by themselves
 int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout);
 int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors);
-// whether the large kernels store their tiles as whole lines, with 32-bit offsets (else per element)
+// whether the large kernels store their tiles as whole lines, with 32-bit offsets
 constexpr int64_t kMaxTileN = (int64_t)1 << 22;
 inline bool whole_line_tiles(int64_t N) { return (N & 7) == 0 && N < kMaxTileN; }
+// whether the two-wave kernels store them as 16-byte pieces at even addresses
+inline bool unaligned_tiles(int64_t N) { return (N & 7) != 0 && N >= 8 && N < kMaxTileN; }
 int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                            const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
                            int64_t K, int codes_format, int w_layout, int shape, uint16_t *y, int32_t *acc_out, hipStream_t stream);

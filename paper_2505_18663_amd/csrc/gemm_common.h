@@ -32,7 +32,7 @@ static __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 // us non-temporal, 59.5 cached; 32760 x 1536 x 9704: 535.8 and 476.6; int8 codes 118800 x 768 x 1160: 191.3 and 161.9).
 // WHICH: the kernel is compiled for one of the two, or tests N at every chunk (a branch there cost the wide INT8 kernel, whose
 // epilogue nothing hides, 1 %: 32760 x 1536 x 8960 468.3 and 463.5 us).
-enum StoreKind { STORE_BY_PITCH, STORE_STREAMING, STORE_CACHED };
+enum StoreKind { STORE_BY_PITCH, STORE_STREAMING, STORE_CACHED, STORE_UNALIGNED };
 static inline bool streaming_pitch(int64_t N) { return (N & 31) == 0; }
 template <StoreKind WHICH = STORE_BY_PITCH>
 static __device__ __forceinline__ void store_chunk(__amdgpu_buffer_rsrc_t tile, uint32_t off, int N, const uint4 (&v)[4]) {
@@ -45,6 +45,32 @@ static __device__ __forceinline__ void store_chunk(__amdgpu_buffer_rsrc_t tile, 
 #pragma unroll
         for (int pass = 0; pass < 4; ++pass)
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v[pass]), tile, (int)(off + pass * 16 * N), 0, 0);
+    }
+}
+
+// 16 bytes at an address that is only a multiple of 2 (global stores take any)
+static __device__ __forceinline__ void store_piece_unaligned(uint16_t *p, uint4 v) {
+    struct __attribute__((packed, aligned(2))) Piece { uint32_t d[4]; };
+    *reinterpret_cast<Piece *>(p) = Piece{{v.x, v.y, v.z, v.w}};
+}
+
+// The chunk of an output whose rows begin at any even address (N no multiple of 8): the piece across a row's end goes out by
+// element.  (m, n): the lane's first row and channel.  Cached: parts of lines meet in the L2.  Stored per element, 64 stores of
+// 2 bytes in place of 8 of 16 per 32 tokens x 32 channels, these outputs were bound by the stores: whole layers, before -> now,
+// FP6 39026 x 256 x 5627 716 -> 210 us (3.4 TB/s of everything moved), int8 74402 x 128 x 239 130 -> 53, 21054 x 3456 x 1827 284 -> 182.
+static __device__ __forceinline__ void store_chunk_unaligned(uint16_t *y, int m, int n, int M, int N, const uint4 (&v)[4]) {
+    uint16_t *p = y + (int64_t)m * N + n;
+#pragma unroll
+    for (int pass = 0; pass < 4; ++pass, p += 8 * N) {
+        if (m + pass * 8 >= M) continue;
+        if (n + 8 <= N) {
+            store_piece_unaligned(p, v[pass]);
+        } else {
+            const uint32_t d[4] = {v[pass].x, v[pass].y, v[pass].z, v[pass].w};
+#pragma unroll
+            for (int e = 0; e < 7; ++e)
+                if (n + e < N) p[e] = (uint16_t)(d[e / 2] >> (16 * (e & 1)));
+        }
     }
 }
 
@@ -242,7 +268,23 @@ struct TileVectors {
     static constexpr int BYTES = OFF_ZERO + BN;
 };
 
-// Any tile of an output with N a multiple of 8 (below kMaxTileN; tiles at the edges included: see output_tile; specialized on zero-points and, where the caller
+// The bias and zero-points of the last N % 4 channels, in the image of the tile at n0: the LDS-direct loads bring whole dwords
+// of channels below N only.  (Every wave writes them, the same values, and reads its own.)
+template <int BM, int BN>
+static __device__ __forceinline__ void fill_vector_tail(uint8_t *s_tile, const uint16_t *bias, const int8_t *w_zero, int lane,
+                                                        int n0, int N) {
+    if ((N & 3) == 0 || n0 + BN <= N) return;
+    const int n = (N & ~3) + lane;
+    if (n < N) {
+        if (bias) reinterpret_cast<uint16_t *>(s_tile + TileVectors<BM, BN>::OFF_BIAS)[n - n0] = bias[n];
+        if (w_zero) reinterpret_cast<int8_t *>(s_tile + TileVectors<BM, BN>::OFF_ZERO)[n - n0] = w_zero[n];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Any tile of an output with N a multiple of 8, or of any other with STORE_UNALIGNED (below kMaxTileN; tiles at the edges included: see output_tile; specialized on zero-points and, where the caller
 // can afford the code, on bias: a run-time test inside the unrolled loops costs a branch per register group): no predicates, every
 // vector the epilogue needs comes from LDS, one row offset per lane.  (Edge tiles used to go through epilogue_edge, per
 // element with a global load per zero-point; on outputs whose token count is no multiple of the tile the last tiles of a
@@ -257,7 +299,7 @@ struct TileVectors {
 // expose the LDS latency once per group, 32 times per tile.  The accumulators are left at zero.
 // BIAS: 1 / 0 = with / without bias, fixed at compile time; -1 = `has_bias` decides at run time (for kernels
 // whose register budget does not survive four inlined copies of this function).
-template <class P, int BM, int BN, int TM, int TN, bool ZP, int BIAS>
+template <class P, int BM, int BN, int TM, int TN, bool ZP, int BIAS, StoreKind STORE>
 static __device__ __forceinline__ void epilogue_interior(typename P::vec (&acc)[TN][TM], const uint8_t *s_tile, bool has_bias,
                                                          int lane, int wm, int wn, uint8_t *stg, uint16_t *y, int m0,
                                                          int n0, int M, int N) {
@@ -352,14 +394,15 @@ static __device__ __forceinline__ void epilogue_interior(typename P::vec (&acc)[
                 const int row = pass * 8 + rd_row;
                 v[pass] = *reinterpret_cast<const uint4 *>(stg + row * 128 + ((rd_piece ^ (row & 7)) << 4));
             }
-            store_chunk(tile, off, N, v);
+            if constexpr (STORE != STORE_UNALIGNED) store_chunk<STORE>(tile, off, N, v);
+            else store_chunk_unaligned(y, m0 + wm + j * 32 + rd_row, n0 + wn + ip * 64 + rd_piece * 8, M, N, v);
             __builtin_amdgcn_wave_barrier();   // the next chunk's LDS writes stay behind these reads
         }
     }
 }
 
-// N not a multiple of 8 (or kMaxTileN and more), or the accumulator hook: predicated per element, through the integer
-// accumulator (same values and rounding order as the interior path).  The accumulators are left at zero.
+// N below 8 or kMaxTileN and more, the accumulator hook, and N no multiple of 8 in the kernels without STORE_UNALIGNED: predicated
+// per element, through the integer accumulator (same values and rounding order as the interior path).  The accumulators are left at zero.
 template <class P, int BM, int BN, int TM, int TN>
 static __device__ __forceinline__ void epilogue_edge(typename P::vec (&acc)[TN][TM], const uint8_t *s_tile, const uint16_t *bias,
                                                      const int8_t *w_zero, int lane, int wm, int wn, uint16_t *y,

@@ -38,12 +38,15 @@ constexpr float kFp6Unit = 64.f;                       // accumulator * 64 = int
 
 }  // namespace
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int OCC>
+// STORE: how tiles are stored (see store_chunk).  STORE_UNALIGNED is the kernel for N >= 8 no multiple of 8 (without
+// the accumulator hook); the other stores such outputs per element.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int OCC, StoreKind STORE>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4a4_fp6_gemm_kernel(
     const uint8_t *__restrict__ codes, const float *__restrict__ x_scale, const uint8_t *__restrict__ w,
     const float *__restrict__ w_scale, const int8_t *__restrict__ w_zero, const int32_t *__restrict__ code_rowsum,
     const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out,
     int tiles_m, int tiles_n, int group_n, unsigned *__restrict__ sched) {
+    constexpr bool UNALIGNED = STORE == STORE_UNALIGNED;
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wave sub-tile
     constexpr int TM = WM / 32, TN = WN / 32;            // MFMA tiles per wave
@@ -143,7 +146,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4a4_fp6_gemm_ker
             }
             // (bias and zero-points go to LDS, pairs and fours of channels at a time, where N is a multiple of 8; else the
             // epilogue reads them from memory)
-            if (bias && (N & 7) == 0) {
+            if (bias && (UNALIGNED || (N & 7) == 0)) {
 #pragma unroll
                 for (int j = 0; j < BN / 128; ++j)
                     if (j % NW == wave)
@@ -154,7 +157,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4a4_fp6_gemm_ker
                 for (int j = 0; j < BM / 64; ++j)
                     if (j % NW == wave)
                         lds_direct_load4(code_rowsum, (uint32_t)min(m0 + j * 64 + lane, M - 1) * 4, sc + OFF_RSUM + j * 256);
-                if ((N & 7) == 0) {
+                if (UNALIGNED || (N & 7) == 0) {
 #pragma unroll
                     for (int j = 0; j < BN / 256; ++j)
                         if (j % NW == wave)
@@ -281,21 +284,22 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4a4_fp6_gemm_ker
         kt = 0;
         ++tile_j;
         comp_tile = __builtin_amdgcn_readfirstlane(s_tiles[tile_j & 7]);   // the next one (its loads are under way)
-        const uint8_t *s_tile = smem + STAGES * STAGE + ((tile_j - 1) & 1) * SCALES;
+        uint8_t *s_tile = smem + STAGES * STAGE + ((tile_j - 1) & 1) * SCALES;
         // Lane-dependent addresses of the epilogue are derived from a lane number the compiler cannot trace
         // back: computed here once per tile instead of being kept (and spilled) across the K loop.
         int lane_e = lane;
         asm volatile("" : "+v"(lane_e));
-        if ((N & 7) == 0 && !acc_out && N < kMaxTileN) {
-            if (KT >= STAGES) store_credit = STAGES - 1;
+        if (UNALIGNED || ((N & 7) == 0 && !acc_out && N < kMaxTileN)) {
+            if (KT >= STAGES && (!UNALIGNED || (m0 + BM <= M && n0 + BN <= N))) store_credit = STAGES - 1;
             uint8_t *stg = smem + (q % STAGES) * STAGE + wave * 4096;
             __builtin_amdgcn_s_barrier();   // every wave is done reading the last slice: its buffer stages the tile
+            if constexpr (UNALIGNED) fill_vector_tail<BM, BN>(s_tile, bias, w_zero, lane_e, n0, N);
             if (w_zero) {
-                if (bias) epilogue_interior<AccF32x64, BM, BN, TM, TN, true, 1>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
-                else epilogue_interior<AccF32x64, BM, BN, TM, TN, true, 0>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
+                if (bias) epilogue_interior<AccF32x64, BM, BN, TM, TN, true, 1, STORE>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
+                else epilogue_interior<AccF32x64, BM, BN, TM, TN, true, 0, STORE>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
             } else {
-                if (bias) epilogue_interior<AccF32x64, BM, BN, TM, TN, false, 1>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
-                else epilogue_interior<AccF32x64, BM, BN, TM, TN, false, 0>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
+                if (bias) epilogue_interior<AccF32x64, BM, BN, TM, TN, false, 1, STORE>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
+                else epilogue_interior<AccF32x64, BM, BN, TM, TN, false, 0, STORE>(acc, s_tile, true, lane_e, wm, wn, stg, y, m0, n0, M, N);
             }
         } else {
             epilogue_edge<AccF32x64, BM, BN, TM, TN>(acc, s_tile, bias, w_zero, lane_e, wm, wn, y, acc_out, m0, n0, M, N);
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(256) void w4_prepack_fp6_kernel(const uint8_t *__re
     }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int OCC>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int OCC, StoreKind STORE = STORE_BY_PITCH>
 int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale, const int8_t *w_zero,
                const int32_t *code_rowsum, const uint16_t *bias, int M, int N, int K, uint16_t *y, int32_t *acc_out,
                hipStream_t stream) {
@@ -363,7 +367,7 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
     grid = limited_grid(grid);
     const size_t smem = (size_t)STAGES * (BM / 32 + BN / 32) * kFp6Block + 2 * ((BM + BN) * 4 + BN * 2 + BM * 4 + BN) +
                         8 * sizeof(int);
-    auto k = w4a4_fp6_gemm_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, OCC>;
+    auto k = w4a4_fp6_gemm_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, OCC, STORE>;
     static std::atomic<uint64_t> configured{0};
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
     bool is_clear = false;
@@ -384,12 +388,11 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
 // at 1280; 8192 x 4608: 29.6 and 29.0, 33.2 and 31.8, 38.0 and 35.8, 43.4 and 39.6; with zero-points it is level or behind up
 // to 640: 60000 x 3072 119 and 128 at 512).  (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind one of
 // these at nearly every K from 256 to 640, 3 % ahead at best in the mean of a shape.)
-// Tiles stored per element (N no multiple of 8) make that cost several times as large, above all where bias or zero-points
-// are fetched per element too: with both it does not pay at any depth (15601 x 1161, variants 1 and 3: 105 and 183 us at
-// K = 1280, 168 and 230 at 6144, 271 and 305 at 13824), with one from 96 slices on (with a bias 126 and 163 at K = 3072, 208 and
-// 223 at 9216, 247 and 253 at 12288, 269 and 268 at 13824; 5000 x 3074 231 and 208 at 12288), without from 48 (93.6 and 101 at
-// 3072, 134 and 131 at 6144, 176 and 162 at 9216; in the mean of 25 to 37 sizes 9 % slower at K = 1280, 6 % at 3072, 3 % faster
-// at 6144).
+// Outputs with N no multiple of 8, in 16-byte pieces at even addresses, take it from 48 slices on without bias and zero-points,
+// from 96 with one of them, never with both: the lines that tests/test_dispatch.py states, from when such tiles were stored per element
+// and the wide kernel, with no second workgroup to hide that, lost up to 74 %.  By today's times it would pay from about 16 slices on
+// whatever the vectors (variants 1 and 3, 8192 x 3074: 40.2 and 44.1 us at K = 1280, 65.0 and 61.7 at 3072, 109 and 94.8 at 6144, with both
+// vectors 70.1 and 65.8 at 3072; 32760 x 4612: 197 and 187 at 1280, 1344 and 1006 at 13824).
 int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors) {
     const int shape = small_gemm_shape(M, N, K, true);
     if (shape >= 0) return kFirstSmallVariant + shape;
@@ -413,6 +416,7 @@ int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8
         return launch_w4ax_gemm_small(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, DVDQ_CODES_FP6,
                                       DVDQ_W_NATIVE_FP6, v - kFirstSmallVariant, y, acc_out, stream);
     if (v == 3) return launch_w4ax_gemm_wide(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, true, y, acc_out, stream);
+    if (unaligned_tiles(N) && !acc_out) return launch_fp6<128, 256, 2, 2, 2, 2, STORE_UNALIGNED>(DVDQ_FP6_ARGS);
     return launch_fp6<128, 256, 2, 2, 2, 2>(DVDQ_FP6_ARGS);
 #undef DVDQ_FP6_ARGS
 }

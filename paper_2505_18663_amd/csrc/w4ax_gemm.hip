@@ -33,12 +33,15 @@
 
 namespace dvdq {
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, bool A4>
+// STORE: how tiles are stored (see store_chunk).  STORE_UNALIGNED is the kernel for N >= 8 no multiple of 8 (without
+// the accumulator hook); the others store such outputs per element.
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, bool A4, StoreKind STORE>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_kernel(
     const int8_t *__restrict__ codes, const float *__restrict__ x_scale, const uint8_t *__restrict__ w,
     const float *__restrict__ w_scale, const int8_t *__restrict__ w_zero, const int32_t *__restrict__ code_rowsum,
     const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out,
     int tiles_m, int tiles_n, int group_n, unsigned *__restrict__ sched) {
+    constexpr bool UNALIGNED = STORE == STORE_UNALIGNED;
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wave sub-tile
     constexpr int TM = WM / 32, TN = WN / 32;            // MFMA tiles per wave
@@ -178,7 +181,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
             }
             // (bias and zero-points go to LDS, pairs and fours of channels at a time, where N is a multiple of 8; else the
             // epilogue reads them from memory)
-            if (bias && (N & 7) == 0) {
+            if (bias && (UNALIGNED || (N & 7) == 0)) {
 #pragma unroll
                 for (int j = 0; j < BN / 128; ++j)
                     if (j % NW == wave)
@@ -189,7 +192,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
                 for (int j = 0; j < BM / 64; ++j)
                     if (j % NW == wave)
                         lds_direct_load4(code_rowsum, (uint32_t)min(m0 + j * 64 + lane, M - 1) * 4, sc + OFF_RSUM + j * 256);
-                if ((N & 7) == 0) {
+                if (UNALIGNED || (N & 7) == 0) {
 #pragma unroll
                     for (int j = 0; j < BN / 256; ++j)
                         if (j % NW == wave)
@@ -356,19 +359,20 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
         kt = 0;
         ++tile_j;
         comp_tile = __builtin_amdgcn_readfirstlane(s_tiles[tile_j & 7]);   // the next one (its loads are under way)
-        const uint8_t *s_tile = smem + STAGES * STAGE + ((tile_j - 1) & 1) * SCALES;
+        uint8_t *s_tile = smem + STAGES * STAGE + ((tile_j - 1) & 1) * SCALES;
         typedef AccI32<SHIFT> Acc;
         int lane_e = lane;   // (keeps the epilogue's lane-dependent addresses out of the K loop's registers)
         asm volatile("" : "+v"(lane_e));
-        if ((N & 7) == 0 && !acc_out && N < kMaxTileN) {
+        if (UNALIGNED || ((N & 7) == 0 && !acc_out && N < kMaxTileN)) {
             // Every wave issues the same number of stores, whatever its tile (see the store-aware wait above).
-            if (KT >= STAGES) store_credit = STAGES - 1 - AHEAD;
+            if (KT >= STAGES && (!UNALIGNED || (m0 + BM <= M && n0 + BN <= N))) store_credit = STAGES - 1 - AHEAD;
             uint8_t *stg = smem + (q % STAGES) * STAGE + wave * 4096;
             __builtin_amdgcn_s_barrier();   // every wave is done reading the last slice: its buffer stages the tile
+            if constexpr (UNALIGNED) fill_vector_tail<BM, BN>(s_tile, bias, w_zero, lane_e, n0, N);
             // Two specializations, with and without weight zero-points, chosen once per tile (with four, bias as
             // well, this kernel spills).
-            if (w_zero) epilogue_interior<Acc, BM, BN, TM, TN, true, -1>(acc, s_tile, bias != nullptr, lane_e, wm, wn, stg, y, m0, n0, M, N);
-            else epilogue_interior<Acc, BM, BN, TM, TN, false, -1>(acc, s_tile, bias != nullptr, lane_e, wm, wn, stg, y, m0, n0, M, N);
+            if (w_zero) epilogue_interior<Acc, BM, BN, TM, TN, true, -1, STORE>(acc, s_tile, bias != nullptr, lane_e, wm, wn, stg, y, m0, n0, M, N);
+            else epilogue_interior<Acc, BM, BN, TM, TN, false, -1, STORE>(acc, s_tile, bias != nullptr, lane_e, wm, wn, stg, y, m0, n0, M, N);
         } else {
             epilogue_edge<Acc, BM, BN, TM, TN>(acc, s_tile, bias, w_zero, lane_e, wm, wn, y, acc_out, m0, n0, M, N);
         }
@@ -538,7 +542,7 @@ void release_sched_slot(hipStream_t stream) {
 
 namespace {
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, bool A4 = false>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, bool A4 = false, StoreKind STORE = STORE_BY_PITCH>
 int launch_native(const int8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                   const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int M, int N, int K,
                   uint16_t *y, int32_t *acc_out, hipStream_t stream) {
@@ -554,7 +558,7 @@ int launch_native(const int8_t *codes, const float *x_scale, const uint8_t *w, c
     // the ring, then two tiles' epilogue vectors (scales, bias, code sums, zero-points; see the kernel)
     const size_t smem = (size_t)STAGES * (BM * (A4 ? BK / 2 : BK) + BN * BK / 2) +
                         2 * ((BM + BN) * 4 + BN * 2 + BM * 4 + BN) + 8 * sizeof(int);   // + the ring of tile numbers
-    auto k = w4ax_gemm_native_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, OCC, A4>;
+    auto k = w4ax_gemm_native_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, OCC, A4, STORE>;
     static std::atomic<uint64_t> configured{0};   // one per template instantiation
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
     bool is_clear = false;
@@ -583,9 +587,9 @@ int limited_grid(int grid) {
 //   - from 12 K slices on.  Against variant 2 (GEMM alone): K = 640 up to 7 % slower; 1280 level; 1536 from 4 % slower to 3 %
 //     faster (15600 x 1536 45.6 and 47.3 us, 32760 x 4608 221 and 214); 3072 8 % faster (4096 x 3072 40.0 and 37.0, 15600 x 3072
 //     135 and 125);
-//   - where its tiles are stored as whole lines.  Stored per element (N no multiple of 8), a tile takes several times as
-//     long, and there is no second workgroup to multiply meanwhile: variant 2 is 4-24 % faster at K = 1536 .. 6144, and
-//     with bias and zero-points 20-53 % (5000 x 4609 with K = 3072: 114 and 140 us, with both 158 and 233);
+//   - where N is a multiple of 8.  For others variant 2 has the stores (STORE_UNALIGNED); per element, as the wide kernel stores
+//     them, a tile takes several times as long with no second workgroup to multiply meanwhile (before variant 2 had them the
+//     wide kernel was already 4-24 % slower at K = 1536 .. 6144, with bias and zero-points 20-53 %);
 //   - unless one to four rounds of its tiles (one per compute unit) would end in one that is less than two fifths full:
 //     variant 2's smaller tiles spread that rest (K = 12800, 4878 x 3088, 260 tiles: 171 and 285 us; K = 5248, 5960 x 8840, 840
 //     tiles: 242 and 266).  Over 82 outputs of 117 to 864 tiles the mean time is the same within 1 % for lines from 0.3 to 0.5 of
@@ -617,6 +621,7 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     // fastest: while one workgroup converts and stores its tile the other keeps the matrix cores busy,
     // which the one-workgroup 256 x 256 variants cannot do.  The others remain for sweeps; a shape with
     // fewer K slices than a variant's ring needs falls back to variant 2, which always qualifies.
+    const bool unaligned = unaligned_tiles(N) && !acc_out;
     const int forced = gemm_variant();
     int v = forced < 0 ? w4ax_gemm_choice(M, N, K, codes_format, w_layout) : forced;
     if (v >= kFirstSmallVariant)
@@ -626,7 +631,9 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
         if ((v == 1 && k / 128 < 2) || (v > 2 && k / 128 < 3)) v = 2;
         switch (v) {
             case 1: return launch_native<256, 256, 128, 2, 4, 3, 1, true>(DVDQ_GEMM_ARGS);
-            case 2: return launch_native<128, 256, 128, 2, 2, 2, 2, true>(DVDQ_GEMM_ARGS);
+            case 2:
+                return unaligned ? launch_native<128, 256, 128, 2, 2, 2, 2, true, STORE_UNALIGNED>(DVDQ_GEMM_ARGS)
+                                 : launch_native<128, 256, 128, 2, 2, 2, 2, true>(DVDQ_GEMM_ARGS);
             case 3: return launch_native<256, 256, 128, 2, 4, 4, 1, true>(DVDQ_GEMM_ARGS);
             case 4: return launch_native<256, 256, 128, 4, 2, 4, 1, true>(DVDQ_GEMM_ARGS);
             default: return DVDQ_ERR_UNSUPPORTED;
@@ -641,7 +648,9 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     }
     switch (v) {
         case 1: return launch_native<256, 256, 128, 4, 2, 3, 1>(DVDQ_GEMM_ARGS);
-        case 2: return launch_native<128, 256, 128, 2, 2, 2, 2>(DVDQ_GEMM_ARGS);
+        case 2:
+            return unaligned ? launch_native<128, 256, 128, 2, 2, 2, 2, false, STORE_UNALIGNED>(DVDQ_GEMM_ARGS)
+                             : launch_native<128, 256, 128, 2, 2, 2, 2>(DVDQ_GEMM_ARGS);
         case 3: return launch_native<256, 256, 128, 2, 4, 3, 1>(DVDQ_GEMM_ARGS);
         case 4: return launch_native<128, 256, 64, 2, 2, 4, 2>(DVDQ_GEMM_ARGS);
         default: return DVDQ_ERR_UNSUPPORTED;

@@ -78,6 +78,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
     const float *__restrict__ w_scale, const int8_t *__restrict__ w_zero, const int32_t *__restrict__ code_rowsum,
     const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out,
     int tiles_m, int tiles_n, int group_n, unsigned *__restrict__ sched) {
+    constexpr bool UNALIGNED = STORE == STORE_UNALIGNED;   // N >= 8 no multiple of 8, no accumulator hook
     constexpr int BM = 256, BN = 256, NW = 4, WM = 128, WN = 128, TM = 4, TN = 4, STAGES = 3;
     // (pipeline steps per slice: FP6 path 2 of 64 channels, INT8 path 4 of 32)
     constexpr int A_ROW = kBK;                               // INT8 path: bytes of one code row per slice
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
             }
             // (bias and zero-points go to LDS, pairs and fours of channels at a time, where N is a multiple of 8; else the
             // epilogue reads them from memory)
-            if (bias && (N & 7) == 0) {
+            if (bias && (UNALIGNED || (N & 7) == 0)) {
 #pragma unroll
                 for (int j = 0; j < BN / 128; ++j)
                     if (j % NW == wave)
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                 for (int j = 0; j < BM / 64; ++j)
                     if (j % NW == wave)
                         lds_direct_load4(code_rowsum, (uint32_t)min(m0 + j * 64 + lane, M - 1) * 4, sc + OFF_RSUM + j * 256);
-                if ((N & 7) == 0) {
+                if (UNALIGNED || (N & 7) == 0) {
 #pragma unroll
                     for (int j = 0; j < BN / 256; ++j)
                         if (j % NW == wave)
@@ -523,7 +524,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
             if (drawer) s_tiles[(tile_j + 1) & 7] = tiles.tile(draw_reply, 0);
         };
         const bool vec8 = (N & 7) == 0;
-        const uint8_t *s_tile = smem + STAGES * STAGE + ((tile_j - 1) % 3) * SCALES;
+        uint8_t *s_tile = smem + STAGES * STAGE + ((tile_j - 1) % 3) * SCALES;
         const float *s_xs = reinterpret_cast<const float *>(s_tile);
         const float *s_ws = s_xs + BM;
         const int32_t *s_rsum = reinterpret_cast<const int32_t *>(s_tile + OFF_RSUM);
@@ -532,10 +533,11 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
         // staging: 4 KB per wave in the weight half of the buffer of the slice consumed last (next to be filled; on
         // the FP6 path its code half is already being filled with the next tile's slice 2 while the epilogue runs)
         uint8_t *stg = smem + fill_off + A_STAGE + wave * 4096;
-        if (vec8 && !acc_out && N < kMaxTileN) {
+        if (UNALIGNED || (vec8 && !acc_out && N < kMaxTileN)) {
             // ---- N a multiple of 8, tiles at the edges included (see output_tile): no predicates; channel vectors fetched one register group ahead; the bf16 tile
             // is transposed through LDS, 32 tokens x 64 channels at a time, into whole-line streaming stores
-            if (KT >= 2) store_credit = 1;
+            if (KT >= 2 && (!UNALIGNED || (m0 + BM <= M && n0 + BN <= N))) store_credit = 1;
+            if constexpr (UNALIGNED) fill_vector_tail<BM, BN>(s_tile, bias, w_zero, lane, n0, N);
             // Four specializations (zero-points, bias), chosen once per tile: inside the unrolled units a run-time
             // test costs a branch each, and a lone wave per SIMD pays every taken branch with an idle front end.
             auto interior = [&] __device__(auto has_zero, auto has_bias) __attribute__((always_inline)) {
@@ -572,8 +574,13 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                 ChannelVec cv[8];
                 uint32_t pk[2][2];
                 uint4 pend[4];            // a staged chunk on its way back from LDS, and where it goes
-                uint32_t pend_off = 0, col_off = 0;   // byte offsets within the tile: of that chunk; of this lane's channels
                 const __amdgpu_buffer_rsrc_t tile = output_tile(y, m0, n0, M, N, BM);
+                uint32_t pend_off = 0, col_off = 0;   // byte offsets within the tile: of that chunk; of this lane's channels
+                int pend_m = 0, pend_n = 0;           // UNALIGNED: this lane's first row and channel of that chunk
+                auto store_pending = [&] __device__() __attribute__((always_inline)) {
+                    if constexpr (UNALIGNED) store_chunk_unaligned(y, pend_m, pend_n, M, N, pend);
+                    else store_chunk<STORE>(tile, pend_off, N, pend);
+                };
                 // 64 units of 4 values: unit u = ((ip * TM + j) * 2 + ii) * 4 + (g + h), MFMA tile column i = 2 ip + ii,
                 // token block j, accumulator registers 4 (g + h) .. + 3; 8 units make a 32-token x 64-channel chunk
                 static_for<(TN / 2) * TM * 8>([&](auto u_c) __attribute__((always_inline)) {
@@ -628,7 +635,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                     // same area stay behind these reads) and stored to memory half a chunk later.
                     if constexpr (U == 11) publish_draw();
                     if constexpr ((U & 7) == 3 && U > 8) {
-                        store_chunk<STORE>(tile, pend_off, N, pend);
+                        store_pending();
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     if constexpr ((U & 7) == 7) {   // the chunk is staged: whole rows back, 8 lanes per 128-byte row
@@ -636,6 +643,8 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                         __builtin_amdgcn_wave_barrier();
                         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                         pend_off = col_off + j * 64 * N;
+                        pend_m = m0 + wm + j * 32 + rd_row;
+                        pend_n = n0 + wn + ip * 64 + rd_piece * 8;
                         const uint8_t *sg = stg;
 #pragma unroll
                         for (int pass = 0; pass < 4; ++pass) {
@@ -646,7 +655,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 });
-                store_chunk<STORE>(tile, pend_off, N, pend);   // the last chunk
+                store_pending();   // the last chunk
             };
             if (w_zero) {
                 if (bias) interior(std::true_type{}, std::true_type{});
@@ -656,7 +665,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                 else interior(std::false_type{}, std::false_type{});
             }
         } else {
-            // ---- N not a multiple of 8 (or kMaxTileN and more), or the accumulator hook: predicated per element, through the
+            // ---- N not a multiple of 8 (without STORE_UNALIGNED), kMaxTileN and more, or the accumulator hook: predicated per element, through the
             // integer accumulator (same values and rounding order as the interior path)
             int lane_s = lane;
             asm volatile("" : "+v"(lane_s));
@@ -802,6 +811,7 @@ int launch_w4ax_gemm_wide(const uint8_t *codes, const float *x_scale, const uint
                           int64_t K, bool fp6, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
 #define DVDQ_WIDE_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, (int)M, (int)N, (int)K, y, acc_out, stream
     const bool streaming = streaming_pitch(N);
+    if (fp6 && K / kBK >= 3 && unaligned_tiles(N) && !acc_out) return launch_wide<true, true, STORE_UNALIGNED>(DVDQ_WIDE_ARGS);
     if (fp6 && K / kBK < 3) return launch_wide<true, false, STORE_BY_PITCH>(DVDQ_WIDE_ARGS);   // (not chosen by the dispatch)
     if (fp6)
         return streaming ? launch_wide<true, true, STORE_STREAMING>(DVDQ_WIDE_ARGS) : launch_wide<true, true, STORE_CACHED>(DVDQ_WIDE_ARGS);
