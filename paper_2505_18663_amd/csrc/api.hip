@@ -184,6 +184,11 @@ int dvdq_qlinear(const void *x_bf16, const uint8_t *w, const float *w_scale, con
     if (rc != DVDQ_OK) return rc;
     if (workspace_bytes < dvdq_qlinear_workspace_bytes(M, K, codes_format)) return DVDQ_ERR_WORKSPACE;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const int width = dvdq::gemm_variant() < 0 ? dvdq::qlinear_small_width(M, N, K) : -1;
+    if (width > 0)
+        return dvdq::launch_qlinear_small(static_cast<const uint16_t *>(x_bf16), log2b, act_bits, w, w_scale, w_zero,
+                                          static_cast<const uint16_t *>(bias_bf16), M, N, K, codes_format, w_layout, width,
+                                          static_cast<uint16_t *>(y_bf16), reinterpret_cast<uint8_t *>(codes), x_scale, rowsum, stream);
     rc = dvdq::launch_rotate_quant(static_cast<const uint16_t *>(x_bf16), M, K, log2b, act_bits, codes_format, 0,
                                    codes, x_scale, rowsum, stream);
     if (rc != DVDQ_OK) return rc;

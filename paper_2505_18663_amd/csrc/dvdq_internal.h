@@ -9,6 +9,8 @@
 
 namespace dvdq {
 
+constexpr size_t kLdsPerCu = 160 * 1024;
+
 // Launchers: arguments are already validated by the C-ABI layer in api.hip.
 // Each returns DVDQ_OK or DVDQ_ERR_HIP.
 int launch_rotate_quant(const uint16_t *x, int64_t M, int64_t K, int log2_block, int act_bits, int codes_format,
@@ -45,11 +47,17 @@ inline bool unaligned_tiles(int64_t N) { return (N & 7) != 0 && N >= 8 && N < kM
 int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                            const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
                            int64_t K, int codes_format, int w_layout, int shape, uint16_t *y, int32_t *acc_out, hipStream_t stream);
+// A whole layer of few tokens in one launch (w4ax_gemm_small.hip).  qlinear_small_width: -1 (two launches), or the tile width to take
+int qlinear_small_width(int64_t M, int64_t N, int64_t K);
+int launch_qlinear_small(const uint16_t *x, int log2_block, int act_bits, const uint8_t *w, const float *w_scale,
+                         const int8_t *w_zero, const uint16_t *bias, int64_t M, int64_t N, int64_t K, int codes_format,
+                         int w_layout, int width, uint16_t *y, uint8_t *codes, float *x_scale, int32_t *code_rowsum, hipStream_t stream);
 size_t w4_native_fp6_bytes(int64_t N, int64_t K);
 size_t codes_fp6_bytes(int64_t M, int64_t K);
 int launch_w4_prepack_fp6(const uint8_t *w_canonical, int64_t N, int64_t K, uint8_t *w_native, hipStream_t stream);
 
 size_t w4_native_bytes(int64_t N, int64_t K);
+int gemm_variant();            // the benchmark hook's tile variant (-1: the kernels' own choice)
 void set_gemm_variant(int v);  // benchmark sweeps only; -1 = choose by shape
 void set_gemm_schedule(int v); // benchmark only; 0 = fixed tile shares, -1 = drawn from counters where possible
 void set_gemm_grid_limit(int v); // benchmark only; 0 = persistent grids fill the chip, else at most v workgroups

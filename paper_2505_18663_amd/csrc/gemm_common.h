@@ -500,6 +500,5 @@ static __device__ __forceinline__ void epilogue_edge(typename P::vec (&acc)[TN][
 
 // Enqueues the one-wave kernel that zeroes a counter slot (sched_slot; defined in w4ax_gemm.hip).
 int clear_sched_slot(unsigned *slot, hipStream_t stream);
-int gemm_variant();   // the benchmark hook's tile variant (-1: the kernels' own choice)
 
 }  // namespace dvdq

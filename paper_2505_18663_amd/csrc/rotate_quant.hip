@@ -31,80 +31,14 @@
 // resident and stride over the rows, prefetching the next row while one is processed.
 // The 1/sqrt(B) normalization is never applied to the data: it is folded into the
 // scale and into the reciprocal the codes are taken with.
-#include "dvdq_internal.h"
+#include <type_traits>
+
+#include "rotate.h"
 #include "wave_reduce.h"
 
 namespace dvdq {
 namespace {
 
-constexpr int kWave = 64;
-constexpr int kUnit = 512;  // channels a wave handles per step (64 lanes x 8)
-constexpr size_t kLdsPerCu = 160 * 1024;
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-
-// One butterfly stage over a lane pairing with a single DPP operand, 8 values, one
-// instruction per value: v = own + sign * partner, sign = +1 in the lane whose stage bit
-// is clear and -1 in the other.  The lane with the bit set therefore holds MINUS the
-// butterfly's difference; the caller tracks that sign and folds it into the quantizer.
-// (The compiler does not fuse a DPP move into an fma, so this is inline assembly.  The
-// leading s_nop covers the 2 wait states a DPP read needs after a VALU write of the same
-// register.  PRE is put in front of that: the first stage reads registers that an MFMA may have written
-// directly, whose longer read-after-write distance the compiler does not see through inline assembly.)
-#define DVDQ_FMAC_DPP8(PRE, CTRL)                                                                              \
-    asm volatile(PRE "s_nop 1\n\t"                                                                             \
-                 "v_fmac_f32_dpp %0, %0, %8 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"              \
-                 "v_fmac_f32_dpp %1, %1, %8 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"              \
-                 "v_fmac_f32_dpp %2, %2, %8 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"              \
-                 "v_fmac_f32_dpp %3, %3, %8 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"              \
-                 "v_fmac_f32_dpp %4, %4, %8 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"              \
-                 "v_fmac_f32_dpp %5, %5, %8 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"              \
-                 "v_fmac_f32_dpp %6, %6, %8 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"              \
-                 "v_fmac_f32_dpp %7, %7, %8 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1"                  \
-                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]) \
-                 : "v"(sign))
-
-// (first of the lane-pairing stages: its values come straight from the 8-pass MFMAs, whose results a vector
-// instruction may read 12 wait states after the MFMA issued; 20 are kept)
-__device__ __forceinline__ void stage_xor1(float (&v)[8], float sign) { DVDQ_FMAC_DPP8("s_nop 15\n\ts_nop 1\n\t", "quad_perm:[1,0,3,2]"); }
-__device__ __forceinline__ void stage_xor2(float (&v)[8], float sign) { DVDQ_FMAC_DPP8("", "quad_perm:[2,3,0,1]"); }
-__device__ __forceinline__ void stage_xor8(float (&v)[8], float sign) { DVDQ_FMAC_DPP8("", "row_ror:8"); }
-
-__device__ __forceinline__ void stage_xor7(float (&v)[8], float sign) { DVDQ_FMAC_DPP8("", "row_half_mirror"); }
-
-// Maximum of a non-negative value over the wave, the same in every lane: two quad permutes and two row
-// mirrors leave each 16-lane row's maximum in all its lanes, two row broadcasts carry it on into lane 63.
-// (Inline assembly: the compiler keeps a move, two canonicalizing maxima and the maximum per step instead of one
-// maximum with a DPP operand.  s_nop 1: the 2 wait states between a vector write and a DPP read of a register.)
-__device__ __forceinline__ float wave_max(float a) {
-    asm volatile("s_nop 1\n\t"
-                 "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-                 "s_nop 1\n\t"
-                 "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-                 "s_nop 1\n\t"
-                 "v_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-                 "s_nop 1\n\t"
-                 "v_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
-                 "s_nop 1\n\t"
-                 "v_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"   // into rows 1, 3
-                 "s_nop 1\n\t"
-                 "v_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf"          // into rows 2, 3
-                 : "+v"(a));
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, a), 63));
-}
-
-// entry (r, k) of the 32 x 32 matrix that applies H to the index bits in `mask` and the
-// identity to the others, as a bf16 bit pattern (+1, -1 or 0)
-__device__ __forceinline__ uint32_t had5_bf16(int r, int k, int mask) {
-    if ((r ^ k) & ~mask & 31) return 0u;
-    return (__builtin_popcount(r & k & mask) & 1) ? 0xBF80u : 0x3F80u;
-}
 
 // CPW = units per wave.  waves_per_row (W) waves share a row; unit u of the row
 // belongs to wave (u % W) as its (u / W)-th unit.
@@ -134,29 +68,9 @@ __global__ __launch_bounds__(1024) void rotate_quant_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int row_in_wg = wave / waves_per_row;
     const int wsub = wave - row_in_wg * waves_per_row;
-    // this lane's 16-byte chunk within a unit
-    // (u5 .. u8: the lane's coordinates over the pairings 1, 2, 8, 7 = channel-index bits 5 .. 8 of its chunk)
-    const int u8 = (lane >> 2) & 1, u7 = (lane >> 3) & 1, u6 = ((lane >> 1) & 1) ^ u8, u5 = (lane & 1) ^ u8;
-    const int chunk = ((lane >> 4) & 3) | (u5 << 2) | (u6 << 3) | (u7 << 4) | (u8 << 5);
-
-    // constant MFMA operands: rows r = 8 (m / 4) + 4 h + (m % 4) of the 32 x 32 transform, m = lane % 16,
-    // columns k = 8 (lane / 16) + t.  MFMA h then yields transformed channels 4h .. 4h+3 of this lane's chunk.
-    bf16x8 tmat[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int m = lane & 15, r = 8 * (m >> 2) + 4 * h + (m & 3);
-        uint32_t w[4];
-#pragma unroll
-        for (int t = 0; t < 8; t += 2) {
-            const int k = 8 * (lane >> 4) + t;
-            w[t / 2] = had5_bf16(r, k, MASK5) | (had5_bf16(r, k + 1, MASK5) << 16);
-        }
-        tmat[h] = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
-    }
-    // butterfly signs of the lane-pairing stages (the lane with the stage's bit set takes the difference)
-    const float s1 = u5 ? -1.f : 1.f, s2 = u6 ? -1.f : 1.f, s8 = u7 ? -1.f : 1.f, s7 = u8 ? -1.f : 1.f;
-    // every stage leaves MINUS the difference in the lane whose coordinate is set
-    const float flip = (((LOG2B >= 6) & u5) ^ ((LOG2B >= 7) & u6) ^ ((LOG2B >= 8) & u7) ^ ((LOG2B >= 9) & u8)) ? -1.f : 1.f;
+    const HadamardLane had(lane, MASK5);
+    const int chunk = had.chunk;
+    const float flip = had.flip(LOG2B);
 
     // channel offsets of this lane's chunks; chunks at or past K are padding (zero in, nothing out)
     int k0[CPW];
@@ -228,32 +142,12 @@ __global__ __launch_bounds__(1024) void rotate_quant_kernel(
 #pragma unroll
         for (int c = 0; c < CPW; ++c) {
             if (!present(c)) continue;   // (its values are never read)
-            if (LOG2B == 0) {
-                const uint32_t w[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    v[c][2 * i] = __uint_as_float(w[i] << 16);
-                    v[c][2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-                }
-            } else {
-                const bf16x8 data = __builtin_bit_cast(bf16x8, raw[c]);
-                const v4f zero = {0.f, 0.f, 0.f, 0.f};
-                const v4f d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tmat[0], data, zero, 0, 0, 0);
-                const v4f d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tmat[1], data, zero, 0, 0, 0);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    v[c][i] = d0[i];
-                    v[c][4 + i] = d1[i];
-                }
-            }
+            had.low_bits(v[c], raw[c], LOG2B);
         }
 #pragma unroll
         for (int c = 0; c < CPW; ++c) {
             if (!present(c)) continue;
-            if (LOG2B >= 6) stage_xor1(v[c], s1);
-            if (LOG2B >= 7) stage_xor2(v[c], s2);
-            if (LOG2B >= 8) stage_xor8(v[c], s8);
-            if (LOG2B >= 9) stage_xor7(v[c], s7);
+            had.high_bits(v[c], LOG2B);
 #pragma unroll
             for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(v[c][i]));
         }
@@ -271,28 +165,13 @@ __global__ __launch_bounds__(1024) void rotate_quant_kernel(
         // (block-wise scaling stores values that carry a factor 2^emax, see below)
         if (row_ok && wsub == 0 && lane == 0) x_scale[row] = group_log2 ? ldexpf(scale, -emax) : scale;
 
-        const float magic = 12582912.f;  // 1.5 * 2^23: adding it rounds to integer, ties to even
+        const float magic = kRoundMagic;
         int csum = 0;                    // this lane's share of the row's code sum (padding chunks hold zeros)
         if (FMT == 2) {
-            // FP6 container: code c as the E2M3 pattern (c < 0) << 5 | |c|, a lane's 8 fields = 48 bits, made by
-            // the chip's packed f32 -> FP6 conversion.  The bytes of the group's rows are put together in LDS in
-            // channel order.
+            // FP6 container (see pack_codes_fp6): the bytes of the group's rows are put together in LDS in channel order.
             constexpr int TURN_BYTES = CPW * 384 + 16;   // + 16: the 8 turns a quarter-wave reads back sit in different banks
             uint8_t *stage = reinterpret_cast<uint8_t *>(s_pack) + wave * (run * TURN_BYTES);
             uint8_t *sp = stage + turn * TURN_BYTES;
-            // q_i = rne(v_i * r) as a float, by the same single-rounding fused multiply-add as the other
-            // containers (so that all containers carry identical codes), then the packed conversion: exact
-            // integers -7 .. 7 divided by 8 (its scale operand) are E2M3 subnormals m / 8, whose patterns
-            // sign << 5 | m are the container's fields.  One conversion takes 32 values, field 2 i from element i
-            // of its first source and field 2 i + 1 from element i of its second: four chunks of this lane at a
-            // time, chunk g's even channels in elements 4 g .. 4 g + 3 of the first source and its odd channels
-            // in those of the second, so that chunk g comes out as bits 48 g .. 48 g + 47.  The instruction
-            // reads its sources while it writes its result, so the result must not share registers with them
-            // (the early-clobber output; the compiler's own builtin does not keep them apart).
-            typedef float v16f __attribute__((ext_vector_type(16)));
-            typedef uint32_t v6u __attribute__((ext_vector_type(6)));
-            // even chunks sit 4-byte aligned in the turn's bytes and store bytes 0-3 and 4-5, odd chunks (2 mod 4)
-            // store bytes 0-1 and 2-5
             uint8_t *d = sp + chunk * 6;
             uint32_t *d_word = reinterpret_cast<uint32_t *>(d + ((chunk & 1) ? 2 : 0));
             uint16_t *d_half = reinterpret_cast<uint16_t *>(d + ((chunk & 1) ? 0 : 4));
@@ -300,10 +179,9 @@ __global__ __launch_bounds__(1024) void rotate_quant_kernel(
             float fsum = 0.f;   // code sums stay exact in fp32: at most 8 * CPW values of magnitude <= 127
 #pragma unroll
             for (int c0 = 0; c0 < CPW; c0 += 4) {
-                // (elements past the lane's last chunk are don't-cares: left undefined, they cost no instruction)
-                const v4f none = {0.f, 0.f, 0.f, 0.f};
-                v16f qa = __builtin_shufflevector(none, none, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1);
-                v16f qb = qa;
+                // q_i = rne(v_i * r) as a float, by the same single-rounding fused multiply-add as the other containers (so that
+                // all containers carry identical codes); elements past the lane's last chunk are don't-cares
+                fp6_source qa = fp6_undefined(), qb = qa;
 #pragma unroll
                 for (int g = 0; g < 4 && c0 + g < CPW; ++g) {
                     if (!present(c0 + g)) continue;
@@ -324,22 +202,15 @@ __global__ __launch_bounds__(1024) void rotate_quant_kernel(
                         for (int i = 0; i < 4; ++i) fsum += qa[4 * g + i] + qb[4 * g + i];
                     }
                 }
-                v6u pk;
-                asm volatile("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, %3\n\ts_nop 1" : "=&v"(pk) : "v"(qa), "v"(qb), "v"(8.0f));
-#pragma unroll
-                for (int g = 0; g < 4 && c0 + g < CPW; ++g) {
-                    if (!present(c0 + g)) continue;
-                    // the chunk's three 16-bit pieces h0 h1 h2: an even chunk stores (h0 h1) and h2, an odd one h0 and (h1 h2)
-                    const uint32_t w0 = pk[3 * (g / 2) + (g & 1)], w1 = pk[3 * (g / 2) + (g & 1) + 1];
-                    uint32_t h01, h12, h0, h2;
-                    if (g & 1) {   // bits 16 .. 63 of (w0, w1)
-                        h01 = __builtin_amdgcn_alignbit(w1, w0, 16); h12 = w1; h0 = w0 >> 16; h2 = w1 >> 16;
-                    } else {       // bits 0 .. 47
-                        h01 = w0; h12 = __builtin_amdgcn_alignbit(w1, w0, 16); h0 = w0; h2 = w1;
-                    }
-                    d_word[(c0 + g) * 96] = odd ? h12 : h01;
-                    d_half[(c0 + g) * 192] = (uint16_t)(odd ? h0 : h2);
-                }
+                const fp6_fields pk = pack_codes_fp6(qa, qb);
+                auto put = [&] __device__(auto g_c) __attribute__((always_inline)) {
+                    constexpr int G = decltype(g_c)::value;
+                    if (c0 + G < CPW && present(c0 + G)) store_chunk_fp6<G>(pk, odd, d_word + (c0 + G) * 96, d_half + (c0 + G) * 192);
+                };
+                put(std::integral_constant<int, 0>{});
+                put(std::integral_constant<int, 1>{});
+                put(std::integral_constant<int, 2>{});
+                put(std::integral_constant<int, 3>{});
             }
             if (code_rowsum) csum = (int)fsum;
             if (turn == run - 1 || next_base >= M) {
@@ -373,20 +244,15 @@ __global__ __launch_bounds__(1024) void rotate_quant_kernel(
                 __builtin_amdgcn_wave_barrier();   // the next run's LDS writes stay behind these reads
             }
         } else if (PACK4) {
-            // two codes per byte, in the nibble order the GEMM widens with two masks: byte b of a
-            // chunk's dword = code[b] (bits 0-3) | code[b + 4] (bits 4-7), two's complement
             uint32_t p[CPW];
 #pragma unroll
             for (int c = 0; c < CPW; ++c) {
                 p[c] = 0;
                 if (!present(c)) continue;
-                uint32_t b[8], u[4];
+                uint32_t b[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) b[i] = __float_as_uint(fmaf(v[c][i], r, magic));
-#pragma unroll
-                for (int i = 0; i < 4; ++i) u[i] = (b[i] & 0xFu) | (b[i + 4] << 4);
-                p[c] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(u[3], u[2], 0x0c0c0400u),
-                                             __builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400u), 0x05040100u);
+                p[c] = pack_codes_nibbles(b);
                 if (code_rowsum) csum = __builtin_amdgcn_sdot8((int)p[c], 0x11111111, csum, false);  // 8 signed nibbles
             }
             if (via_lds) {
@@ -448,12 +314,7 @@ __global__ __launch_bounds__(1024) void rotate_quant_kernel(
 #pragma unroll
                     for (int i = 0; i < 8; ++i) b[i] = __float_as_uint(fmaf(v[c][i], r, magic));
                 }
-                // low bytes of b[0..3] / b[4..7] -> one dword each
-                uint2 out;
-                out.x = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u),
-                                              __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
-                out.y = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[7], b[6], 0x0c0c0400u),
-                                              __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), 0x05040100u);
+                const uint2 out = pack_codes_int8(b);
                 if (row_ok && k0[c] < K) *reinterpret_cast<uint2 *>(codes + row * K + k0[c]) = out;
                 if (code_rowsum) {
                     csum = __builtin_amdgcn_sdot4((int)out.x, 0x01010101, csum, false);  // 4 signed bytes

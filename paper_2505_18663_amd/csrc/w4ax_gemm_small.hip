@@ -16,6 +16,11 @@
 //            hands them over, K any multiple of 32) take the same way, for outputs of every size.
 //   K tails, rows past M: loads past the end of a buffer descriptor return zeros (zero codes add nothing).
 //
+// A layer of very few tokens (CPW > 0) is one launch: the workgroup also quantizes its own tokens, into LDS, before it
+// multiplies, while its first weights are on their way.  Two launches in a row cost such a layer a launch's start and end, and a
+// round trip of the codes through memory, more than quantizing the same tokens in every workgroup does (qlinear_small_width).
+// It is bound by the chain load - transform - maximum - codes - slices - sum, a few waits each.
+//
 // Measured (back-to-back launches, int8 codes, before -> now): 2 x 1536 x 9216 (tokens x K x channels): 22.6 -> 4.4 us;
 // 512 x 3072 x 3072: 28.0 -> 11.2; 1 x 13824 x 5120: 104 -> 10.5; 3121 x 1152 x 1160: 27.7 -> 10.8.  Towards the upper
 // end of the range the operand traffic out of the L2s is the limit (14 to 20 TB/s), which is why the tile grows with
@@ -24,6 +29,8 @@
 #include <type_traits>
 
 #include "gemm_common.h"
+#include "rotate.h"
+#include "wave_reduce.h"
 
 namespace dvdq {
 namespace {
@@ -78,32 +85,183 @@ struct Slice {
     v4u w16[FMT == FMT_FP6 ? TN * 3 : FMT == FMT_CANONICAL ? TN * 2 : 1];
 };
 
+// The layer of few tokens: what the kernel quantizes instead of being handed codes, and where it leaves the codes, token scales
+// and code sums that the two-kernel layer would leave in the workspace.
+struct LayerInput {
+    const uint16_t *x;
+    double scale_mul;    // 1 / (sqrt(B) * qmax)
+    float recip_num;     // 1 / sqrt(B)
+    int log2_block;
+    uint32_t unit_mul;   // 2^16 / units of a row, rounded up
+    uint8_t *codes;
+    float *x_scale;
+    int32_t *code_rowsum;   // with zero-points
+};
+constexpr int kLayerTasks = 64;     // units of 512 channels that a workgroup quantizes, 8 per wave
+constexpr int kLayerPad = 128;      // LDS bytes a last part of a slice may read past the last row's codes
+constexpr int kLayerVectors = 3 * 32 * 4;   // maxima, scales and code sums of the rows
+
 constexpr int kGroupStride = 1024 + 32;   // LDS bytes of one group of 4 accumulator registers (see the reduction)
 
 // LDS bytes of one wave: its part in the reduction, or its operand slice where that is larger
-template <int FMT, int TM, int TN>
+template <int FMT, int TM, int TN, bool LAYER>
 constexpr int wave_lds() {
     const int reduction = TM * (TN > 2 ? TN / 2 : TN) * 4 * kGroupStride;
-    const int slice = FMT == FMT_FP6 ? 0 : TM * 32 * (FMT == FMT_PACKED4 ? 64 : 128) + (FMT == FMT_CANONICAL ? TN * 32 * 64 : 0);
+    const int slice = (FMT == FMT_FP6 || LAYER ? 0 : TM * 32 * (FMT == FMT_PACKED4 ? 64 : 128)) + (FMT == FMT_CANONICAL ? TN * 32 * 64 : 0);
     return reduction > slice ? reduction : slice;
 }
 
-template <int FMT, int TM, int TN, int NW>
+// LDS bytes between the rows of codes of the layer (16 more than a row, so that rows start in different banks)
+template <int FMT>
+__host__ __device__ constexpr int layer_row_bytes(int K) {
+    return (FMT == FMT_PACKED4 ? K / 2 : FMT == FMT_FP6 ? K / 8 * 6 : K) + 16;
+}
+
+// Quantizes rows m0 .. m0 + rows - 1 into LDS: a workgroup's rows x units of 512 channels are dealt to its waves, CPW units each at
+// most, kept in registers until the rows' maxima are known.  Same arithmetic, operation by operation, as rotate_quant.hip, so the
+// codes, scales and code sums are the same bits.  s_rowmax: zeros on entry, from before a barrier.  Ends with a barrier.
+// A unit is a chain of exchanges and waits; nothing but other units can stand in its gaps, so there is no branch per unit (a wave's
+// units past the workgroup's are zeros and are only not stored) and what is the same for a row is worked out once, a row per lane.
+template <int FMT, int NW, int CPW, class Meanwhile>
+__device__ __forceinline__ void quantize_rows(const LayerInput &in, int m0, int rows, int K, int wave, int lane, bool want_sum,
+                                              uint32_t *s_rowmax, float *s_scale, int *s_sum, uint8_t *s_codes, int code_stride, Meanwhile meanwhile) {
+    const int units = (K + kUnit - 1) / kUnit, tasks = rows * units, log2b = in.log2_block;
+    const HadamardLane had(lane, log2b >= 5 ? 31 : (1 << log2b) - 1);
+    int row[CPW], k0[CPW];
+    bool there[CPW];
+    uint4 raw[CPW];
+#pragma unroll
+    for (int c = 0; c < CPW; ++c) {   // (a unit past the workgroup's, channels past K: zeros)
+        const int t = wave + c * NW;
+        there[c] = t < tasks;
+        row[c] = there[c] ? (int)(((uint32_t)t * in.unit_mul) >> 16) : 0;
+        k0[c] = (t - row[c] * units) * kUnit + had.chunk * 8;
+        const __amdgpu_buffer_rsrc_t src = buffer(reinterpret_cast<const uint8_t *>(in.x + (int64_t)(m0 + row[c]) * K), there[c] ? K * 2 : 0);
+        const v4u q = __builtin_amdgcn_raw_buffer_load_b128(src, k0[c] * 2, 0, 0);
+        raw[c] = make_uint4(q[0], q[1], q[2], q[3]);
+    }
+    meanwhile();       // (loads of the caller's, requested behind these)
+    __syncthreads();   // (the maxima are zero)
+    float v[CPW][8], amax[CPW];
+    auto each_unit = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < CPW; ++c) f(v[c], raw[c]);
+    };
+    if (log2b == 0) each_unit([&](float (&u)[8], uint4 q) { had.low_bits(u, q, 0); });
+    else each_unit([&](float (&u)[8], uint4 q) { had.low_bits(u, q, 5); });
+    if (log2b >= 6) each_unit([&](float (&u)[8], uint4) { stage_xor1(u, had.s1); });
+    if (log2b >= 7) each_unit([&](float (&u)[8], uint4) { stage_xor2(u, had.s2); });
+    if (log2b >= 8) each_unit([&](float (&u)[8], uint4) { stage_xor8(u, had.s8); });
+    if (log2b >= 9) each_unit([&](float (&u)[8], uint4) { stage_xor7(u, had.s7); });
+#pragma unroll
+    for (int c = 0; c < CPW; ++c) {
+        amax[c] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) amax[c] = fmaxf(amax[c], fabsf(v[c][i]));
+    }
+    if constexpr (CPW >= 4) {
+#pragma unroll
+        for (int c = 0; c < CPW; c += 4) wave_max4(amax[c], amax[c + 1], amax[c + 2], amax[c + 3]);
+    } else {
+#pragma unroll
+        for (int c = 0; c < CPW; ++c) amax[c] = wave_max(amax[c]);
+    }
+    if (lane == 0) {   // (not negative: the order of the values is the order of their bits)
+#pragma unroll
+        for (int c = 0; c < CPW; ++c) atomicMax(s_rowmax + row[c], __float_as_uint(amax[c]));
+    }
+    __syncthreads();
+    float my_r;   // lane l: the reciprocal step of row l
+    {
+        const float a = __uint_as_float(s_rowmax[min(lane, rows - 1)]);
+        const float scale = (float)((double)a * in.scale_mul);
+        my_r = scale > 0.f ? in.recip_num / scale : 0.f;
+        if (wave == 0 && lane < rows) s_scale[lane] = scale;
+    }
+    const float flip = had.flip(log2b);
+    float r[CPW];
+#pragma unroll
+    for (int c = 0; c < CPW; ++c) r[c] = flip * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_r), row[c]));
+    int sum[CPW];
+    if constexpr (FMT == FMT_FP6) {
+        auto each = [&](auto f) __attribute__((always_inline)) {
+            f(std::integral_constant<int, 0>{});
+            if constexpr (CPW > 1) f(std::integral_constant<int, 1>{});
+            if constexpr (CPW > 2) f(std::integral_constant<int, 2>{});
+            if constexpr (CPW > 3) f(std::integral_constant<int, 3>{});
+        };
+#pragma unroll
+        for (int c0 = 0; c0 < CPW; c0 += 4) {
+            fp6_source qa = fp6_undefined(), qb = qa;
+            each([&](auto g_c) __attribute__((always_inline)) {
+                constexpr int G = decltype(g_c)::value;
+                float fsum = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    qa[4 * G + i] = fmaf(v[c0 + G][2 * i], r[c0 + G], kRoundMagic) - kRoundMagic;
+                    qb[4 * G + i] = fmaf(v[c0 + G][2 * i + 1], r[c0 + G], kRoundMagic) - kRoundMagic;
+                    fsum += qa[4 * G + i] + qb[4 * G + i];
+                }
+                sum[c0 + G] = (int)fsum;
+            });
+            const fp6_fields pk = pack_codes_fp6(qa, qb);
+            each([&](auto g_c) __attribute__((always_inline)) {
+                constexpr int G = decltype(g_c)::value;
+                const int c = c0 + G;
+                if (!there[c] || k0[c] >= K) return;
+                uint8_t *d = s_codes + row[c] * code_stride + k0[c] / 8 * 6;
+                const bool odd = had.chunk & 1;
+                store_chunk_fp6<G>(pk, odd, reinterpret_cast<uint32_t *>(d + (odd ? 2 : 0)), reinterpret_cast<uint16_t *>(d + (odd ? 0 : 4)));
+            });
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < CPW; ++c) {
+            uint32_t b[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) b[i] = __float_as_uint(fmaf(v[c][i], r[c], kRoundMagic));
+            uint8_t *to = s_codes + row[c] * code_stride;
+            const bool ok = there[c] && k0[c] < K;
+            if constexpr (FMT == FMT_PACKED4) {
+                const uint32_t p = pack_codes_nibbles(b);
+                if (ok) *reinterpret_cast<uint32_t *>(to + k0[c] / 2) = p;
+                sum[c] = __builtin_amdgcn_sdot8((int)p, 0x11111111, 0, false);
+            } else {
+                const uint2 p = pack_codes_int8(b);
+                if (ok) *reinterpret_cast<uint2 *>(to + k0[c]) = p;
+                sum[c] = __builtin_amdgcn_sdot4((int)p.y, 0x01010101, __builtin_amdgcn_sdot4((int)p.x, 0x01010101, 0, false), false);
+            }
+        }
+    }
+    if (want_sum) {
+#pragma unroll
+        for (int c = 0; c < CPW; ++c) sum[c] = wave_sum(sum[c]);
+        if (lane == 0) {
+#pragma unroll
+            for (int c = 0; c < CPW; ++c) atomicAdd(s_sum + row[c], sum[c]);
+        }
+    }
+    __syncthreads();
+}
+
+// CPW > 0, the layer: the codes are made here, from `in`, by every workgroup for its own 32 tokens, CPW units of 512 channels a wave.
+template <int FMT, int TM, int TN, int NW, int CPW>
 __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
     const uint8_t *__restrict__ codes, const float *__restrict__ x_scale, const uint8_t *__restrict__ w,
     const float *__restrict__ w_scale, const int8_t *__restrict__ w_zero, const int32_t *__restrict__ code_rowsum,
     const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out,
-    int tiles_m, int tiles_n, int m_fastest, int group) {
-    constexpr bool FP6 = FMT == FMT_FP6, CANONICAL = FMT == FMT_CANONICAL;
+    int tiles_m, int tiles_n, int m_fastest, int group, LayerInput in) {
+    constexpr bool FP6 = FMT == FMT_FP6, CANONICAL = FMT == FMT_CANONICAL, LAYER = CPW > 0;
     constexpr int BM = 32 * TM, BN = 32 * TN;
     constexpr int A_ROW = FMT == FMT_PACKED4 ? kBK / 2 : kBK;    // bytes of a code row per slice (row-major containers)
     constexpr int PHASES = TN > 2 ? 2 : 1, PN = TN / PHASES;   // the reduction takes PN columns of MFMA tiles at a time
     constexpr int NG = TM * PN * 4;                            // groups of 4 accumulator registers per phase
     constexpr int GROUP_STRIDE = kGroupStride;
-    constexpr int A_STAGE = FP6 ? 0 : BM * A_ROW, W_STAGE = CANONICAL ? BN * (kBK / 2) : 0;   // a wave's own slice in LDS
-    constexpr int WAVE_LDS = wave_lds<FMT, TM, TN>();
+    constexpr int A_STAGE = FP6 || LAYER ? 0 : BM * A_ROW, W_STAGE = CANONICAL ? BN * (kBK / 2) : 0;   // a wave's own slice in LDS
+    constexpr int WAVE_LDS = wave_lds<FMT, TM, TN, LAYER>();
     static_assert(NG * GROUP_STRIDE <= WAVE_LDS && A_STAGE + W_STAGE <= WAVE_LDS, "per-wave LDS");
     constexpr int CV = (BN + 63) / 64;                         // values per lane of a channel vector
+    static_assert(!LAYER || (TM == 1 && NW == 8), "the layer's tokens and units");
     static_assert(TM <= 2 && TN <= 4 && TN % PHASES == 0, "token vectors are one value per lane");
     typedef typename std::conditional<FP6, AccF32x64, AccI32<FMT == FMT_PACKED4 ? 8 : 4>>::type P;
     typedef typename P::vec Acc;
@@ -130,8 +288,8 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
     // The tile's token and channel vectors, one value per lane, requested before everything else and put into LDS
     // after the K loop.  (Always loaded, from some vector that exists: a branch would wait for them here.)
     const int vm = min(m0 + lane, M - 1);
-    const float v_xs = x_scale[vm];
-    const int v_rs = (w_zero ? code_rowsum : reinterpret_cast<const int32_t *>(x_scale))[vm];
+    const float v_xs = LAYER ? 0.f : x_scale[vm];
+    const int v_rs = LAYER ? 0 : (w_zero ? code_rowsum : reinterpret_cast<const int32_t *>(x_scale))[vm];
     float v_ws[CV];
     uint16_t v_bias[CV];
     int8_t v_z[CV];
@@ -155,8 +313,8 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
     typedef Slice<FMT, TM, TN> S;
     auto load = [&](S &s, int kt) __attribute__((always_inline)) {
         const bool ok = kt < KT;
-        const int a_off = kt * (FP6 ? kFp6Block : A_ROW);
-        const __amdgpu_buffer_rsrc_t ra = buffer(a_tile + (ok ? a_off : 0), ok ? a_bytes - a_off : 0);
+        const int a_off = LAYER ? 0 : kt * (FP6 ? kFp6Block : A_ROW);
+        const __amdgpu_buffer_rsrc_t ra = buffer(a_tile + (ok ? a_off : 0), ok ? a_bytes - a_off : 0);   // (LAYER: unused)
         const int64_t w_off = CANONICAL ? kt * (kBK / 2) : kt * w_slice_stride;
         const int w_bytes = CANONICAL ? min(BN, N - n0) * (K / 2) - (int)w_off : TN * (FP6 ? kFp6Block : kGroupBytes);
         const __amdgpu_buffer_rsrc_t rw = buffer(w_tile + (ok ? w_off : 0), ok ? w_bytes : 0);
@@ -167,7 +325,7 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
                 for (int c = 0; c < 3; ++c)
                     s.w16[i * 3 + c] = __builtin_amdgcn_raw_buffer_load_b128(rw, a_lane + i * kFp6Block + c * 512, 0, 0);
 #pragma unroll
-            for (int j = 0; j < TM; ++j)
+            for (int j = 0; j < (LAYER ? 0 : TM); ++j)
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
                     s.a[j * 3 + c] = __builtin_amdgcn_raw_buffer_load_b128(ra, a_lane + j * KT * kFp6Block + c * 512, 0, 0);
@@ -177,14 +335,14 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
             const int a_at = (lane % CHUNKS) * 16 < k_left ? a_lane : beyond;
             const int w_at = (lane % 4) * 32 < k_left ? (lane / 4) * (K / 2) + (lane % 4) * 16 : beyond;
 #pragma unroll
-            for (int i = 0; i < S::A_LOADS; ++i)
+            for (int i = 0; i < (LAYER ? 0 : S::A_LOADS); ++i)
                 s.a[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, a_at == beyond ? beyond : a_at + i * ROWS_PER_LOAD * row_bytes, 0, 0);
 #pragma unroll
             for (int i = 0; i < TN * 2; ++i)
                 s.w16[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, w_at == beyond ? beyond : w_at + i * 16 * (K / 2), 0, 0);
         } else {
 #pragma unroll
-            for (int i = 0; i < S::A_LOADS; ++i)
+            for (int i = 0; i < (LAYER ? 0 : S::A_LOADS); ++i)
                 s.a[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, a_lane + i * ROWS_PER_LOAD * row_bytes, 0, 0);
 #pragma unroll
             for (int i = 0; i < TN * 4; ++i)
@@ -201,13 +359,39 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
 
     uint8_t *mine = smem + wave * WAVE_LDS;
-    auto multiply = [&](const S &s) __attribute__((always_inline)) {
+    float *s_xs = reinterpret_cast<float *>(smem + NW * WAVE_LDS), *s_ws = s_xs + 64, *s_bias = s_ws + CV * 64;
+    int *s_rs = reinterpret_cast<int *>(s_bias + CV * 64), *s_z = s_rs + 64;
+    uint32_t *s_rowmax = reinterpret_cast<uint32_t *>(s_z + CV * 64);
+    float *s_scale = reinterpret_cast<float *>(s_rowmax + 32);
+    int *s_sum = reinterpret_cast<int *>(s_scale + 32);
+    uint8_t *s_codes = reinterpret_cast<uint8_t *>(s_sum + 32);
+    const int code_stride = layer_row_bytes<FMT>(K);
+    // (rows past M: some row that exists, for outputs that are never stored)
+    const uint8_t *my_codes = s_codes + min(frow, rows - 1) * code_stride;
+
+    S slice;
+    if constexpr (CPW > 0) {
+        if (tid < 32) s_rowmax[tid] = 0, s_sum[tid] = 0;
+        quantize_rows<FMT, NW, CPW>(in, m0, rows, K, wave, lane, w_zero != nullptr, s_rowmax, s_scale, s_sum, s_codes, code_stride,
+                                    [&]() __attribute__((always_inline)) { load(slice, wave); });
+    } else {
+        load(slice, wave);
+    }
+
+    auto multiply = [&](const S &s, int kt) __attribute__((always_inline)) {
         if constexpr (FP6) {
             auto half = [&](auto hc) __attribute__((always_inline)) {
                 constexpr int H = decltype(hc)::value;
                 v8i fa[TM];
 #pragma unroll
-                for (int j = 0; j < TM; ++j) fa[j] = fp6_fragment<H>(s.a[j * 3], s.a[j * 3 + 1], s.a[j * 3 + 2]);
+                for (int j = 0; j < TM; ++j) {
+                    if constexpr (LAYER) {
+                        const v4u *c = reinterpret_cast<const v4u *>(my_codes + kt * (kFp6Block / 32) + fhalf * 48);
+                        fa[j] = H == 0 ? fp6_fragment<H>(c[0], c[1], c[1]) : fp6_fragment<H>(c[1], c[1], c[2]);
+                    } else {
+                        fa[j] = fp6_fragment<H>(s.a[j * 3], s.a[j * 3 + 1], s.a[j * 3 + 2]);
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < TN; ++i) {
                     const v8i fw = fp6_fragment<H>(s.w16[i * 3], s.w16[i * 3 + 1], s.w16[i * 3 + 2]);
@@ -221,7 +405,7 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
         } else {
             // the code rows, loaded as whole lines, become fragments through this wave's own LDS (in order: no barrier)
 #pragma unroll
-            for (int i = 0; i < S::A_LOADS; ++i) {
+            for (int i = 0; i < (LAYER ? 0 : S::A_LOADS); ++i) {
                 const int row = i * ROWS_PER_LOAD + lane / CHUNKS;
                 *reinterpret_cast<v4u *>(mine + row * A_ROW + (((lane % CHUNKS) ^ swz_bk<A_ROW>(row)) << 4)) = s.a[i];
             }
@@ -245,7 +429,8 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
                 v4i ra[TM];
 #pragma unroll
                 for (int j = 0; j < TM; ++j)
-                    ra[j] = *reinterpret_cast<const v4i *>(mine + (j * 32 + frow) * A_ROW + (((ks * 2 + fhalf) ^ swz_bk<A_ROW>(frow)) << 4));
+                    ra[j] = LAYER ? *reinterpret_cast<const v4i *>(my_codes + kt * A_ROW + (ks * 2 + fhalf) * 16)
+                                  : *reinterpret_cast<const v4i *>(mine + (j * 32 + frow) * A_ROW + (((ks * 2 + fhalf) ^ swz_bk<A_ROW>(frow)) << 4));
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     v4i fa[TM];
@@ -273,10 +458,8 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
         }
     };
 
-    S slice;
-    load(slice, wave);
     for (int kt = wave; kt < KT; kt += NW) {
-        multiply(slice);
+        multiply(slice, kt);
         load(slice, kt + NW);   // (the compiler moves it up between the MFMAs; past the last slice it fetches nothing)
     }
 
@@ -284,11 +467,19 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
     // group (4 registers) by group; then a thread adds up and finishes 8 consecutive channels of one token, which are
     // the two lane halves of one group.  Groups are 1024 + 32 bytes apart so that the threads of a token, which read
     // neighbouring groups, use different banks.
-    float *s_xs = reinterpret_cast<float *>(smem + NW * WAVE_LDS), *s_ws = s_xs + 64, *s_bias = s_ws + CV * 64;
-    int *s_rs = reinterpret_cast<int *>(s_bias + CV * 64), *s_z = s_rs + 64;
     if (wave == NW - 1) {
-        s_xs[lane] = v_xs * P::edge_fold();
-        s_rs[lane] = w_zero ? v_rs : 0;
+        float xs = v_xs;
+        int rs = v_rs;
+        if constexpr (LAYER) {   // (lanes past the rows: values never used)
+            xs = s_scale[min(lane, rows - 1)];
+            rs = s_sum[min(lane, rows - 1)];
+            if (n0 == 0 && lane < rows) {
+                in.x_scale[m0 + lane] = xs;
+                if (w_zero) in.code_rowsum[m0 + lane] = rs;
+            }
+        }
+        s_xs[lane] = xs * P::edge_fold();
+        s_rs[lane] = w_zero ? rs : 0;
 #pragma unroll
         for (int i = 0; i < CV; ++i) {
             s_ws[i * 64 + lane] = v_ws[i];
@@ -362,17 +553,31 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
             }
         }
     }
+    if constexpr (LAYER) {
+        // the first column of tiles leaves the codes where the two-kernel layer does
+        if (n0 != 0) return;
+        const int pieces = (code_stride - 16) / 16;   // of a row; neighbouring threads take neighbouring rows
+        const int row = tid & 31;
+        if (row >= rows) return;
+        for (int p = tid >> 5; p < pieces; p += 2 * NW) {
+            uint8_t *to = FP6 ? in.codes + ((int64_t)(m0 / 32) * KT + p / 6) * kFp6Block + (p % 6) * 512 + row * 16
+                              : in.codes + (int64_t)(m0 + row) * (code_stride - 16) + p * 16;
+            *reinterpret_cast<uint4 *>(to) = *reinterpret_cast<const uint4 *>(s_codes + row * code_stride + p * 16);
+        }
+    }
 }
 
-template <int FMT, int TM, int TN, int NW>
+template <int FMT, int TM, int TN, int NW, int CPW = 0>
 int launch_tile(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale, const int8_t *w_zero,
                 const int32_t *code_rowsum, const uint16_t *bias, int M, int N, int K, uint16_t *y, int32_t *acc_out,
-                hipStream_t stream) {
+                hipStream_t stream, const LayerInput &in = {}) {
+    constexpr bool LAYER = CPW > 0;
     const int tiles_m = (M + 32 * TM - 1) / (32 * TM), tiles_n = (N + 32 * TN - 1) / (32 * TN);
-    const size_t smem = (size_t)NW * wave_lds<FMT, TM, TN>() + (2 + 3 * ((TN * 32 + 63) / 64)) * 256;
-    auto k = w4ax_gemm_small_kernel<FMT, TM, TN, NW>;
+    const size_t smem = (size_t)NW * wave_lds<FMT, TM, TN, LAYER>() + (2 + 3 * ((TN * 32 + 63) / 64)) * 256 +
+                        (LAYER ? kLayerVectors + min(M, 32) * layer_row_bytes<FMT>(K) + kLayerPad : 0);
+    auto k = w4ax_gemm_small_kernel<FMT, TM, TN, NW, CPW>;
     static std::atomic<uint64_t> configured{0};
-    allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
+    allow_dynamic_lds(reinterpret_cast<const void *>(k), LAYER ? kLdsPerCu : smem, configured);
     // an XCD takes a contiguous run of tiles: it should read all of the smaller operand and its share of the larger one
     const int m_fastest = FMT == FMT_INT8 || FMT == FMT_CANONICAL ? N > 2 * M : N > M;
     // Workgroups that run at the same time walk K at about the same pace, so what they share is read once into the L2
@@ -383,7 +588,7 @@ int launch_tile(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
     const int n_fast = m_fastest ? tiles_m : tiles_n, n_groups = FMT == FMT_CANONICAL ? (n_fast + 11) / 12 : 1;
     const int group = (n_fast + n_groups - 1) / n_groups;
     hipLaunchKernelGGL(k, dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * NW), smem, stream, codes, x_scale, w, w_scale, w_zero,
-                       code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, m_fastest, group);
+                       code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, m_fastest, group, in);
     return check_launch();
 }
 
@@ -438,6 +643,44 @@ int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uin
     DVDQ_SMALL(FMT_INT8)
 #undef DVDQ_SMALL
 #undef DVDQ_SMALL_ARGS
+}
+
+// Whether a whole layer takes the layer form of the kernel above, one launch: -1 (two launches), or the width of its tiles in 32
+// channels.  Every workgroup quantizes its 32 tokens, so it pays while that is little: up to 32 units of 512 channels (4 a wave), up to
+// 64 for rows of four units or more, where the quantizer alone takes longer too, and as long as all workgroups run at once (the lines
+// of small_gemm_shape).  Swept with launches in a graph, so without the host's time, M = 1 .. 4096, K = 256 .. 4096, N = 256 .. 9216, two
+// launches -> one (us, int8 codes): 1 x 256 x 1024 5.3 -> 4.2; 2 x 1536 x 9216 7.6 -> 5.6; 128 x 256 x 1024 (32 units) 5.9 -> 5.3;
+// 1 x 4096 x 9216 11.0 -> 7.3; 8 x 4096 x 1024 (64) 8.8 -> 8.3; not taken: 32 x 1024 x 1024 (64 units of 2-unit rows) 6.5 and 7.0,
+// 16 x 1536 x 1024 (48) 6.8 and 7.0, 64 x 512 x 9216 (288 tiles of 32 x 64) 7.4 and 10.6.  FP6 codes within 3 % of these ratios.  Outside
+// a graph the host's second launch, 4 us, comes on top of the two.
+int qlinear_small_width(int64_t M, int64_t N, int64_t K) {
+    const int64_t units = (K + kUnit - 1) / kUnit;
+    if ((M < 32 ? M : 32) * units > (units >= 4 ? kLayerTasks : kLayerTasks / 2)) return -1;
+    const int shape = small_gemm_shape(M, N, K, false);
+    return shape < 0 || shape > 2 ? -1 : shape == 0 ? 1 : 2;
+}
+
+int launch_qlinear_small(const uint16_t *x, int log2_block, int act_bits, const uint8_t *w, const float *w_scale,
+                         const int8_t *w_zero, const uint16_t *bias, int64_t M, int64_t N, int64_t K, int codes_format,
+                         int w_layout, int width, uint16_t *y, uint8_t *codes, float *x_scale, int32_t *code_rowsum, hipStream_t stream) {
+    const double qmax = (double)((1 << (act_bits - 1)) - 1), norm = 1.0 / sqrt((double)(1 << log2_block));
+    const int units = (int)((K + kUnit - 1) / kUnit);
+    const LayerInput in{x, norm / qmax, (float)norm, log2_block, (65536u + units - 1) / units, codes, x_scale, code_rowsum};
+    // units a wave takes: 1, 2, 4 or 8 (what the workgroup with most of them needs)
+    const int tasks = (int)(M < 32 ? M : 32) * units, per_wave = (tasks + 7) / 8;
+#define DVDQ_LAYER_CPW(FMT, TN, CPW) \
+    launch_tile<FMT, 1, TN, 8, CPW>(nullptr, nullptr, w, w_scale, w_zero, nullptr, bias, (int)M, (int)N, (int)K, y, nullptr, stream, in)
+#define DVDQ_LAYER_TN(FMT, TN)                                                                   \
+    (per_wave <= 1 ? DVDQ_LAYER_CPW(FMT, TN, 1) : per_wave <= 2 ? DVDQ_LAYER_CPW(FMT, TN, 2) \
+                                                : per_wave <= 4 ? DVDQ_LAYER_CPW(FMT, TN, 4) : DVDQ_LAYER_CPW(FMT, TN, 8))
+#define DVDQ_LAYER(FMT) return width == 1 ? DVDQ_LAYER_TN(FMT, 1) : DVDQ_LAYER_TN(FMT, 2);
+    if (codes_format == DVDQ_CODES_FP6) DVDQ_LAYER(FMT_FP6)
+    if (codes_format == DVDQ_CODES_PACKED4) DVDQ_LAYER(FMT_PACKED4)
+    if (w_layout == DVDQ_W_CANONICAL) DVDQ_LAYER(FMT_CANONICAL)
+    DVDQ_LAYER(FMT_INT8)
+#undef DVDQ_LAYER
+#undef DVDQ_LAYER_TN
+#undef DVDQ_LAYER_CPW
 }
 
 }  // namespace dvdq
