@@ -1,14 +1,18 @@
-"""Python binding of libdvdq (ctypes).  Argument marshalling only: every step of
+"""Python binding of libdvdq.  Argument marshalling only: every step of
 the quantized linear layer runs in the HIP kernels behind the C ABI declared in
 ``include/dvdq.h``.  PyTorch supplies device memory and streams, nothing else.
 
-There is no CPU fallback: if ``libdvdq.so`` has not been built
+Calls are made through ctypes; those that a model makes per layer or per step go through ``_marshal.so`` (csrc/marshal.cpp), which
+does the same checks and the call natively where every argument is the plain case, and hands anything else back.
+
+There is no CPU fallback: if ``libdvdq.so`` or ``_marshal.so`` has not been built
 (``python -m paper_2505_18663_amd.build``) importing a function works but the first
 call raises ``DvdqLibraryMissing``.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 
 import torch
@@ -33,7 +37,9 @@ EXPORTED_SYMBOLS = (
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libdvdq.so")
+_MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 _lib = None
+_marshal = None   # the native module, once the library is loaded
 
 
 class DvdqError(RuntimeError):
@@ -52,12 +58,13 @@ def library_path() -> str:
 
 def lib() -> C.CDLL:
     """Load libdvdq.so (once) and declare the C prototypes."""
-    global _lib
+    global _lib, _marshal
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
+    missing = [p for p in (_LIB_PATH, _MARSHAL_PATH) if not os.path.exists(p)]
+    if missing:
         raise DvdqLibraryMissing(
-            f"{_LIB_PATH} not found: build it with `python -m paper_2505_18663_amd.build` "
+            f"{missing[0]} not found: build it with `python -m paper_2505_18663_amd.build` "
             "(hipcc, gfx950).  There is no fallback path.")
     L = C.CDLL(_LIB_PATH)
     i64, i32, vp, sz = C.c_int64, C.c_int, C.c_void_p, C.c_size_t
@@ -116,7 +123,13 @@ def lib() -> C.CDLL:
               "dvdq_w4_native_bytes"):
         getattr(L, f).restype = sz
     L.dvdq_status_string.restype = C.c_char_p
-    _lib = L
+    spec = importlib.util.spec_from_file_location("_marshal", _MARSHAL_PATH)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    native.bind(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, *(C.cast(getattr(L, f), C.c_void_p).value for f in (
+        "dvdq_rotate_quant", "dvdq_rotate_quant_blockwise", "dvdq_w4ax_gemm", "dvdq_qlinear", "dvdq_gbs_reset", "dvdq_gbs_step",
+        "dvdq_codes_bytes", "dvdq_qlinear_workspace_bytes", "dvdq_w4_native_bytes", "dvdq_w4_native_fp6_bytes")))
+    _marshal, _lib = native, L
     return L
 
 
@@ -158,6 +171,13 @@ def _check(rc, where):
         raise DvdqError(rc, where)
 
 
+def _native(result, where):
+    """What a call of the native module gave: its outputs, or a status to raise."""
+    if type(result) is int:
+        _check(result, where)
+    return result
+
+
 # ------------------------------------------------------------------ the layer
 def _codes_spec(M: int, K: int, codes_format: int):
     """(dtype, shape) of the tensor that carries the activation codes."""
@@ -177,6 +197,9 @@ def rotate_quant(x, had_block: int, act_bits: int, codes=None, x_scale=None, str
     """x: bf16 [M, K] -> (codes int8 [M, K] or packed uint8 [M, K/2], x_scale fp32 [M]); with
     want_rowsum (or code_rowsum given) also the per-token code sums int32 [M].  See dvdq_rotate_quant."""
     L = lib()
+    r = _marshal.rotate_quant(x, had_block, act_bits, codes, x_scale, stream, codes_format, code_rowsum, want_rowsum)
+    if r is not None:
+        return _native(r, "dvdq_rotate_quant")
     _need(x, torch.bfloat16, None, "x")
     M, K = x.shape
     cdtype, cshape = _codes_spec(M, K, codes_format)
@@ -202,6 +225,9 @@ def rotate_quant_blockwise(x, had_block: int, act_bits: int, group: int, values=
     """Block-wise scaled quantizer: x bf16 [M, K] -> (values int8 [M, K], x_scale fp32 [M][, rowsum int32 [M]]).
     Feed the result to w4ax_gemm with act_bits=8.  See dvdq_rotate_quant_blockwise."""
     L = lib()
+    r = _marshal.rotate_quant_blockwise(x, had_block, act_bits, group, values, x_scale, want_rowsum, stream)
+    if r is not None:
+        return _native(r, "dvdq_rotate_quant_blockwise")
     _need(x, torch.bfloat16, None, "x")
     M, K = x.shape
     if values is None:
@@ -239,6 +265,11 @@ def w4ax_gemm(codes, x_scale, w, w_scale, act_bits: int, w_layout: int = W_CANON
     INT4 [N, K/2] (or native) -> y bf16 [M, N].  With want_acc (or acc_out given) also returns the int32
     accumulators."""
     L = lib()
+    if acc_out is None and not want_acc:
+        r = _marshal.w4ax_gemm(codes, x_scale, w, w_scale, act_bits, w_layout, bias, y, stream, codes_format, w_zero,
+                               code_rowsum, K)
+        if r is not None:
+            return _native(r, "dvdq_w4ax_gemm")
     if codes_format == CODES_FP6:
         _need(codes, torch.uint8, None, "codes")
         if K is None:
@@ -293,6 +324,9 @@ def qlinear(x, w, w_scale, had_block: int, act_bits: int, w_layout: int = W_CANO
     """The whole layer.  Returns (y bf16 [M, N], workspace uint8); the workspace holds the
     codes at offset 0 and the token scales at qlinear_scale_offset(M, K, codes_format)."""
     L = lib()
+    r = _marshal.qlinear(x, w, w_scale, had_block, act_bits, w_layout, bias, y, workspace, codes_format, w_zero, stream)
+    if r is not None:
+        return _native(r, "dvdq_qlinear")
     _need(x, torch.bfloat16, None, "x")
     M, K = x.shape
     _need(w_scale, torch.float32, None, "w_scale")
@@ -432,9 +466,14 @@ class GbsController:
         self.reset(stream=stream)
 
     def reset(self, stream=None):
-        _check(lib().dvdq_gbs_reset(_ptr(self.state), self.b_high, _stream(stream)), "dvdq_gbs_reset")
+        L = lib()
+        r = _marshal.gbs_reset(self.state, self.b_high, stream)
+        _check(L.dvdq_gbs_reset(_ptr(self.state), self.b_high, _stream(stream)) if r is None else r, "dvdq_gbs_reset")
 
     def step(self, f_t, f_prev, stream=None):
+        r = _marshal.gbs_step(f_t, f_prev, self.delta, self.b_low, self.b_high, self.state, self.workspace, stream)
+        if r is not None:
+            return _check(r, "dvdq_gbs_step")
         _need(f_t, torch.bfloat16, None, "f_t")
         _need(f_prev, torch.bfloat16, tuple(f_t.shape), "f_prev")
         _check(lib().dvdq_gbs_step(_ptr(f_t), _ptr(f_prev), f_t.numel(), self.delta, self.b_low, self.b_high,

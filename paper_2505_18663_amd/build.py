@@ -1,4 +1,4 @@
-"""Build libdvdq.so (hipcc, gfx950 only) in-tree, next to this file."""
+"""Build libdvdq.so (hipcc, gfx950 only) and the binding's native part in-tree, next to this file."""
 from __future__ import annotations
 
 import concurrent.futures as cf
@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdvdq.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 
 SOURCES = ["api.hip", "rotate_quant.hip", "w4ax_gemm.hip", "w4a4_fp6_gemm.hip", "w4ax_gemm_wide.hip", "w4ax_gemm_small.hip", "gbs.hip", "bgr.hip", "bench_kernels.hip"]
 
@@ -36,11 +37,31 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_marshal() -> None:
+    """csrc/marshal.cpp: host code only, against the headers and libraries of the torch that will load it."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    tmp = MARSHAL + f".tmp{os.getpid()}"
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-cast-function-type",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + sysconfig.get_path("include"),
+           *("-isystem" + d for d in cpp_extension.include_paths()), os.path.join(CSRC, "marshal.cpp"), "-o", tmp,
+           "-L" + torch_lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed for marshal.cpp:\n{res.stdout}\n{res.stderr}")
+    os.replace(tmp, MARSHAL)
+
+
 def build_library(verbose: bool = False) -> str:
-    """Compile every HIP source and link the shared library.  Always rebuilds."""
+    """Compile every source and link the shared libraries.  Always rebuilds."""
     os.makedirs(OBJ, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
+        marshal = ex.submit(_build_marshal)
         objs = list(ex.map(_compile, SOURCES))
+        marshal.result()
     tmp = LIB + f".tmp{os.getpid()}"
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)
