@@ -65,6 +65,7 @@ int limited_grid(int grid);
 // the stream's tile-counter slot (16 words; nullptr: fixed tile shares): for a GEMM, with whether the kernel enqueued last
 // on the stream zeroes it; for a quantizer, the words to zero, noted as zeroed unless taken back (w4ax_gemm.hip)
 unsigned *sched_slot(hipStream_t stream, bool *is_clear);
+unsigned *idle_slot(hipStream_t stream);   // words for launches that have nothing to draw (nullptr: fixed tile shares)
 unsigned *sched_slot_to_clear(hipStream_t stream);
 void sched_slot_not_cleared(hipStream_t stream);
 void release_sched_slot(hipStream_t stream);               // forget a stream's tile-counter slot (host bookkeeping only)

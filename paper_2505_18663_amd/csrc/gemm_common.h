@@ -181,11 +181,17 @@ static __device__ __forceinline__ void tile_origin(int t, int tiles_m, int tiles
 //     library enqueued last on the stream, else a one-wave kernel the GEMM's launcher puts in front), so no
 //     launch depends on what an earlier one -- finished or not -- left behind, and nothing has to be put back
 //     at the end.
+//     With at most two tiles per workgroup there is nothing to draw: such a launch is handed words that no one clears and no one
+//     counts in (idle_slot), so a GEMM called on its own has no clearing kernel in front of it, and its workgroups no atomics to wait for
+//     (with bias and zero-points, GEMM alone, us: 15600 x 768 x 1536 packed codes 32.8 -> 28.3, 20000 x 1024 x 1024 int8 37.3 -> 32.2,
+//     12000 x 3072 x 2048 FP6 54.0 -> 49.6; without the clearing kernel only, 31.0, 35.4, 52.4).  One that is captured, and that several
+//     graph instances may run at once, starts with the same two tiles.
 //   ctr == nullptr: fixed shares, the j-th tile of workgroup b is number j * grid + (b % 8) * (grid / 8) + b / 8.
 struct TileSource {
     int total, grid, xcd, first_tile, run_lo;
     unsigned run_len, wgs, fixed;   // tiles and workgroups of this XCD; tiles the workgroups start with, two each
-    unsigned *ctr;   // this XCD's counter
+    unsigned *ctr;        // this XCD's counter (nullptr: fixed shares)
+    unsigned *draw_ctr;   // the same where there is something to draw
 
     __device__ __forceinline__ TileSource(int tiles_m, int tiles_n, unsigned *sched) {
         total = tiles_m * tiles_n;
@@ -197,6 +203,7 @@ struct TileSource {
         wgs = gridDim.x / 8;
         fixed = min(run_len, 2 * wgs);
         ctr = sched ? sched + xcd : nullptr;
+        draw_ctr = run_len > fixed ? ctr : nullptr;
     }
     // the tile a draw's reply stands for (drawn mode), or the workgroup's ordinal-th tile (fixed shares); -1: none left
     __device__ __forceinline__ int tile(unsigned reply, int ordinal) const {

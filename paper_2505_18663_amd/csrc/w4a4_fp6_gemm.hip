@@ -89,7 +89,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4a4_fp6_gemm_ker
     bool draw_pending = false;
     int draw_wait = 0;   // loop tops until the pending draw's reply is older than loads already awaited
     auto draw = [&] __device__() {
-        if (wave == 0 && tiles.ctr && lane == 0) drawn = tiles.draw();
+        if (wave == 0 && tiles.draw_ctr && lane == 0) drawn = tiles.draw();
         ++draws;
         draw_pending = true;
         draw_wait = STAGES - 1;
@@ -371,8 +371,10 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
     static std::atomic<uint64_t> configured{0};
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
     bool is_clear = false;
-    // (a tile per workgroup at most: nothing to draw, no counter to clear)
-    unsigned *sched = total > grid ? sched_slot(stream, &is_clear) : nullptr;
+    // (two tiles per workgroup at most: nothing to draw, no counter to clear)
+    unsigned *sched = nullptr;
+    if (total > 2 * grid) sched = sched_slot(stream, &is_clear);
+    else if (total > grid) sched = idle_slot(stream), is_clear = true;
     if (sched && !is_clear && clear_sched_slot(sched, stream) != DVDQ_OK) return DVDQ_ERR_HIP;
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * WAVES_M * WAVES_N), smem, stream, codes, x_scale, w, w_scale,
                        w_zero, code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, group_n, sched);

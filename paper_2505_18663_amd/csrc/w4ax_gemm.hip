@@ -102,7 +102,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
     unsigned drawn = 0;      // wave 0, lane 0: reply of the draw not yet written into the ring
     bool draw_pending = false;
     auto draw = [&] __device__() {
-        if (wave == 0 && tiles.ctr && lane == 0) drawn = tiles.draw();
+        if (wave == 0 && tiles.draw_ctr && lane == 0) drawn = tiles.draw();
         ++draws;
         draw_pending = true;
     };
@@ -419,7 +419,7 @@ std::atomic<int> g_grid_limit{0}; // 0: persistent grids fill the chip; else at 
 // kernels of one stream run one after the other.  What a slot holds between launches does not matter (see
 // TileSource): it is cleared on the stream right before every kernel that counts in it.
 constexpr int kSchedSlots = 512;
-__device__ __align__(64) unsigned g_sched[kSchedSlots][16];
+__device__ __align__(64) unsigned g_sched[kSchedSlots + 1][16];   // (the last one: idle_slot)
 
 struct SchedTable {
     unsigned *base = nullptr;
@@ -438,6 +438,16 @@ __global__ void fill_sched_kernel(unsigned *p, unsigned value, int n) {
 
 }  // namespace
 
+static bool find_base(SchedTable &t) {
+    void *p = nullptr;
+    if (hipGetSymbolAddress(&p, HIP_SYMBOL(g_sched)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    t.base = static_cast<unsigned *>(p);
+    return true;
+}
+
 // The counter slot of `stream`, or nullptr (fixed shares): when the stream is being captured into a graph
 // -- the same node may later run in several graph instances at once, which must not share counters -- or
 // when all slots are taken.  *index: the slot's number.
@@ -452,14 +462,7 @@ static unsigned *slot_of_stream(hipStream_t stream, int *dev_out, int *index) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
     SchedTable &t = g_sched_table[dev];
-    if (!t.base) {
-        void *p = nullptr;
-        if (hipGetSymbolAddress(&p, HIP_SYMBOL(g_sched)) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        t.base = static_cast<unsigned *>(p);
-    }
+    if (!t.base && !find_base(t)) return nullptr;
     auto it = t.slot_of.find(reinterpret_cast<uint64_t>(stream));
     if (it == t.slot_of.end()) {
         int slot;
@@ -493,6 +496,25 @@ unsigned *sched_slot(hipStream_t stream, bool *is_clear) {
         g_sched_table[dev].clear[index] = false;
     }
     return slot;
+}
+
+// For a GEMM whose workgroups start with every tile there is: draws come back empty whatever the words hold, so all streams share
+// them.  (Not looked up for the first time while a stream is being captured.)
+unsigned *idle_slot(hipStream_t stream) {
+    if (g_schedule.load(std::memory_order_relaxed) == 0) return nullptr;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+    std::lock_guard<std::mutex> lock(g_sched_mu);
+    SchedTable &t = g_sched_table[dev];
+    if (!t.base) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        if (cap != hipStreamCaptureStatusNone || !find_base(t)) return nullptr;
+    }
+    return t.base + kSchedSlots * 16;
 }
 
 // For a quantizer about to be enqueued on `stream`: the 16 words it should zero (or nullptr), noted as zeroed by it;
@@ -562,8 +584,10 @@ int launch_native(const int8_t *codes, const float *x_scale, const uint8_t *w, c
     static std::atomic<uint64_t> configured{0};   // one per template instantiation
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
     bool is_clear = false;
-    // (a tile per workgroup at most: nothing to draw, no counter to clear)
-    unsigned *sched = total > grid ? sched_slot(stream, &is_clear) : nullptr;
+    // (two tiles per workgroup at most: nothing to draw, no counter to clear)
+    unsigned *sched = nullptr;
+    if (total > 2 * grid) sched = sched_slot(stream, &is_clear);
+    else if (total > grid) sched = idle_slot(stream), is_clear = true;
     if (sched && !is_clear && clear_sched_slot(sched, stream) != DVDQ_OK) return DVDQ_ERR_HIP;
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * WAVES_M * WAVES_N), smem, stream, codes, x_scale, w,
                        w_scale, w_zero, code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, group_n, sched);

@@ -132,7 +132,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
     unsigned drawn = 0;      // wave 0, lane 0: reply of the pending draw
     int draw_wait = 0;       // barriers until the pending draw is written into the ring (0: none pending)
     auto draw = [&] __device__() {
-        if (DRAW_IN_EPILOGUE || !tiles.ctr) return;
+        if (DRAW_IN_EPILOGUE || !tiles.draw_ctr) return;
         if (wave == 0 && lane == 0) drawn = tiles.draw();
         draw_wait = 2;
     };
@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
         comp_tile = tile_number(tile_j);   // the next one (its loads are under way)
         // INT8 path: the number of the tile after next, requested now and written into the ring in front of this
         // tile's first stores (behind them the compiler's wait for the reply would be the stores' round trip)
-        const bool drawer = DRAW_IN_EPILOGUE && tiles.ctr && comp_tile >= 0 && wave == 0 && lane == 0;
+        const bool drawer = DRAW_IN_EPILOGUE && tiles.draw_ctr && comp_tile >= 0 && wave == 0 && lane == 0;
         unsigned draw_reply = 0;
         if (drawer) draw_reply = tiles.draw();
         auto publish_draw = [&] __device__() {
@@ -795,8 +795,10 @@ int launch_wide(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
     static std::atomic<uint64_t> configured{0};
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
     bool is_clear = false;
-    // (a tile per workgroup at most: nothing to draw, no counter to clear)
-    unsigned *sched = total > grid ? sched_slot(stream, &is_clear) : nullptr;
+    // (two tiles per workgroup at most: nothing to draw, no counter to clear)
+    unsigned *sched = nullptr;
+    if (total > 2 * grid) sched = sched_slot(stream, &is_clear);
+    else if (total > grid) sched = idle_slot(stream), is_clear = true;
     if (K / kBK < 2) sched = nullptr;   // a tile draw takes two slices to come back
     if (sched && !is_clear && clear_sched_slot(sched, stream) != DVDQ_OK) return DVDQ_ERR_HIP;
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(256), smem, stream, codes, x_scale, w, w_scale, w_zero, code_rowsum,
