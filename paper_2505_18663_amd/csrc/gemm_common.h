@@ -202,7 +202,7 @@ struct TileSource {
         run_len = (unsigned)((int64_t)(xcd + 1) * total / 8) - (unsigned)run_lo;
         wgs = gridDim.x / 8;
         fixed = min(run_len, 2 * wgs);
-        ctr = sched ? sched + xcd : nullptr;
+        ctr = sched ? sched + xcd * kSchedStride : nullptr;
         draw_ctr = run_len > fixed ? ctr : nullptr;
     }
     // the tile a draw's reply stands for (drawn mode), or the workgroup's ordinal-th tile (fixed shares); -1: none left

@@ -54,8 +54,8 @@ __global__ __launch_bounds__(1024) void rotate_quant_kernel(
     int emax,          // block-wise scaling: largest power-of-two refinement of a group's step (8 - act_bits)
     int8_t *__restrict__ codes, float *__restrict__ x_scale,
     int32_t *__restrict__ code_rowsum,    // NULL, or [M]: sum of the row's codes (for weight zero-points)
-    unsigned *__restrict__ clear_words) { // NULL, or 16 words to zero: the tile counters of the GEMM that follows on the stream
-    if (clear_words && blockIdx.x == 0 && threadIdx.x < 16) clear_words[threadIdx.x] = 0u;
+    unsigned *__restrict__ clear_words) { // NULL, or the slot of tile counters to zero, for the GEMM that follows on the stream
+    if (clear_words && blockIdx.x == 0 && threadIdx.x < 8) clear_words[threadIdx.x * kSchedStride] = 0u;
     extern __shared__ float s_amax[];  // [2][rows_per_wg * waves_per_row], slots alternate per iteration
     // then [2][rows_per_wg * waves_per_row] per-wave code sums, then, 16-byte aligned,
     // [waves][CPW][64] dwords for gathering packed codes (via_lds), or [waves][rows in turn][CPW * 384 + 16] bytes for FP6

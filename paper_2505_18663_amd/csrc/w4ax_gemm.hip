@@ -415,11 +415,11 @@ std::atomic<int> g_variant{-1};   // -1: pick by shape; set by the benchmark's s
 std::atomic<int> g_schedule{-1};  // -1: tiles drawn from counters where possible; 0: fixed shares (benchmark hook)
 std::atomic<int> g_grid_limit{0}; // 0: persistent grids fill the chip; else at most this many workgroups (benchmark hook)
 
-// Tile counters of the persistent kernels: one slot of 16 words (the first 8 one per XCD; 64 bytes) per stream;
+// Tile counters of the persistent kernels: one slot per stream;
 // kernels of one stream run one after the other.  What a slot holds between launches does not matter (see
 // TileSource): it is cleared on the stream right before every kernel that counts in it.
 constexpr int kSchedSlots = 512;
-__device__ __align__(64) unsigned g_sched[kSchedSlots + 1][16];   // (the last one: idle_slot)
+__device__ __align__(64) unsigned g_sched[kSchedSlots + 1][kSchedWords];   // (the last one: idle_slot)
 
 struct SchedTable {
     unsigned *base = nullptr;
@@ -479,7 +479,7 @@ static unsigned *slot_of_stream(hipStream_t stream, int *dev_out, int *index) {
     }
     *dev_out = dev;
     *index = it->second;
-    return t.base + it->second * 16;
+    return t.base + it->second * kSchedWords;
 }
 
 // For a GEMM about to be enqueued on `stream`: its counter slot (or nullptr: fixed shares), and whether the
@@ -514,10 +514,10 @@ unsigned *idle_slot(hipStream_t stream) {
         }
         if (cap != hipStreamCaptureStatusNone || !find_base(t)) return nullptr;
     }
-    return t.base + kSchedSlots * 16;
+    return t.base + kSchedSlots * kSchedWords;
 }
 
-// For a quantizer about to be enqueued on `stream`: the 16 words it should zero (or nullptr), noted as zeroed by it;
+// For a quantizer about to be enqueued on `stream`: the slot it should zero (or nullptr), noted as zeroed by it;
 // if it could not be enqueued, the note is taken back.
 unsigned *sched_slot_to_clear(hipStream_t stream) {
     std::lock_guard<std::mutex> lock(g_sched_mu);
@@ -533,14 +533,14 @@ void sched_slot_not_cleared(hipStream_t stream) {
 }
 
 int clear_sched_slot(unsigned *slot, hipStream_t stream) {
-    hipLaunchKernelGGL(fill_sched_kernel, dim3(1), dim3(64), 0, stream, slot, 0u, 16);
+    hipLaunchKernelGGL(fill_sched_kernel, dim3(1), dim3(kSchedWords), 0, stream, slot, 0u, kSchedWords);
     return check_launch();
 }
 
 int fill_sched_slots(uint32_t value, hipStream_t stream) {
     void *p = nullptr;
     if (hipGetSymbolAddress(&p, HIP_SYMBOL(g_sched)) != hipSuccess) return DVDQ_ERR_HIP;
-    const int n = kSchedSlots * 16;
+    const int n = kSchedSlots * kSchedWords;
     hipLaunchKernelGGL(fill_sched_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, static_cast<unsigned *>(p), value, n);
     {
         std::lock_guard<std::mutex> lock(g_sched_mu);
