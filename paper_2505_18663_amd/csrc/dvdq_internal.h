@@ -30,12 +30,11 @@ int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8
 int launch_w4ax_gemm_wide(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                           const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
                           int64_t K, bool fp6, uint16_t *y, int32_t *acc_out, hipStream_t stream);
-// Small outputs, any container of codes with its native weight layout, and int8 codes with canonical weights of any
-// size (w4ax_gemm_small.hip).  small_gemm_shape: the
-// shape of tile and waves for a size, or -1 (not a small output)
+// Small outputs, any container of codes with its native weight layout, and int8 codes with canonical weights
+// (w4ax_gemm_small.hip).  small_gemm_shape: the shape of tile and waves for a size, or -1 (not a small output)
 int small_gemm_shape(int64_t M, int64_t N, int64_t K, bool fp6);
 constexpr int kSmallVariants = 7, kFirstSmallVariant = 10;   // tile variant 10 + shape stands for a shape
-constexpr int kLargestSmallShape = 6;                        // what canonical weights take beyond the small outputs
+constexpr int kCanonicalVariant = 16;                        // canonical weights beyond the small outputs (w4ax_gemm.hip)
 // the tile variants that the launchers take by themselves
 int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout);
 int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors);

@@ -33,15 +33,19 @@
 
 namespace dvdq {
 
+// Operands: int8 codes, or packed 4-bit codes, with native weights; int8 codes with canonical weights ([N, K/2] as an offline
+// quantizer hands them over, K any multiple of 32).
+enum Operands { OPS_INT8, OPS_PACKED4, OPS_CANONICAL };
+
 // STORE: how tiles are stored (see store_chunk).  STORE_UNALIGNED is the kernel for N >= 8 no multiple of 8 (without
 // the accumulator hook); the others store such outputs per element.
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, bool A4, StoreKind STORE>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, Operands OPS, StoreKind STORE>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_kernel(
     const int8_t *__restrict__ codes, const float *__restrict__ x_scale, const uint8_t *__restrict__ w,
     const float *__restrict__ w_scale, const int8_t *__restrict__ w_zero, const int32_t *__restrict__ code_rowsum,
     const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out,
     int tiles_m, int tiles_n, int group_n, unsigned *__restrict__ sched) {
-    constexpr bool UNALIGNED = STORE == STORE_UNALIGNED;
+    constexpr bool UNALIGNED = STORE == STORE_UNALIGNED, A4 = OPS == OPS_PACKED4, CANON = OPS == OPS_CANONICAL;
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wave sub-tile
     constexpr int TM = WM / 32, TN = WN / 32;            // MFMA tiles per wave
@@ -49,7 +53,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
     // widened to int8 lanes of 16 * code in registers like the weights.  A lane's 16-byte code
     // fragment then spans 32 channels, so one pipeline step covers 64 channels = 2 MFMAs per tile.
     constexpr int A_ROW = A4 ? BK / 2 : BK;              // bytes of one code row per item
-    constexpr int NT = A4 ? 2 : 1;                       // MFMAs along K per step and output tile
+    // CANON: the packed weights of a row are loaded as they are, 16 bytes = 32 channels a piece, and such a piece is a lane's weight
+    // fragment of a 64-channel step likewise; the code fragments are put into its order (see widen_canonical).
+    constexpr int NT = A4 || CANON ? 2 : 1;              // MFMAs along K per step and output tile
     constexpr int KS = BK / (32 * NT);                   // pipeline steps per item
     constexpr int A_STAGE = BM * A_ROW, W_STAGE = BN * BK / 2, STAGE = A_STAGE + W_STAGE;
     constexpr int A_DMA = A_STAGE / 1024 / NW;           // LDS-direct loads per wave per item (1 KB each)
@@ -82,7 +88,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = (wave % WAVES_M) * WM, wn = (wave / WAVES_M) * WN;
-    const int KT = K / BK;
+    const int KT = CANON ? (K + BK - 1) / BK : K / BK;
+    const int k_tail = CANON ? K - (KT - 1) * BK : BK;   // channels of the last slice (CANON: 32 .. BK)
     const int G = ((N + kNPad - 1) / kNPad) * (kNPad / kGroup);  // 32-row groups in the padded weight buffer
     const int64_t w_slice_stride = (int64_t)G * kGroupBytes;
     const int code_row_bytes = A4 ? K / 2 : K;
@@ -139,6 +146,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
     constexpr int W_PIECE = 1024 / W_GROUP * kGroupBytes + 1024 % W_GROUP;
     static_assert(W_GROUP == kGroupBytes || W_GROUP == 1024, "piece offsets are linear for whole slices or one group per piece");
     const uint32_t lane16 = lane * 16;
+    // CANON: a load of weights is 16 rows of 4 pieces, swizzled like code rows of 64 bytes
+    uint32_t w_voff[CANON ? W_DMA : 1];
+    const int w_chunk = (lane & 3) ^ swz_bk<64>(lane >> 2);
     const int8_t *a_base = codes;   // start of the tile's first code row, advanced by BK per item
     const uint8_t *w_base = w;      // start of the tile's weight image for the item
     int issue_tile = 0, issue_kt = 0;   // next item to enqueue: K slice issue_kt of this workgroup's tile issue_tile
@@ -159,7 +169,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
             int m0, n0;
             tile_origin(issue_no, tiles_m, tiles_n, group_n, BM, BN, m0, n0);
             a_base = uniform_ptr(codes + (int64_t)m0 * code_row_bytes);
-            w_base = uniform_ptr(w + (int64_t)(n0 / kGroup) * kGroupBytes);
+            w_base = uniform_ptr(CANON ? w + (int64_t)n0 * (K / 2) : w + (int64_t)(n0 / kGroup) * kGroupBytes);
+            if constexpr (CANON) {
+#pragma unroll
+                for (int i = 0; i < W_DMA; ++i)   // (rows past N re-read the last one)
+                    w_voff[i] = (uint32_t)min((wave * W_DMA + i) * 16 + (lane >> 2), N - 1 - n0) * (K / 2) + w_chunk * 16;
+            }
 #pragma unroll
             for (int i = 0; i < A_DMA; ++i) {
                 const int row = min(a_row[i], M - 1 - m0);   // rows past M re-read the last valid row
@@ -200,6 +215,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
                 }
             }
         }
+        if constexpr (CANON) {
+            // the last slice of a tile: pieces past the rows' ends re-read the last one (their weights are taken as zeros)
+            if (issue_live && issue_kt == KT - 1 && k_tail < BK) {
+#pragma unroll
+                for (int i = 0; i < A_DMA; ++i)
+                    a_voff[i] -= max(((((lane % CHUNKS) ^ swz(a_row[i])) + 1) << 4) - k_tail, 0);
+#pragma unroll
+                for (int i = 0; i < W_DMA; ++i) w_voff[i] -= max((w_chunk + 1) * 16 - k_tail / 2, 0);
+            }
+        }
         issue_sa = smem_base + buf * STAGE;
     };
     // (idx is a constant wherever this is called.  With 128-channel slices the weight pieces of a wave are one
@@ -208,6 +233,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
     auto issue_one = [&] __device__(int idx) __attribute__((always_inline)) {
         if (idx < A_DMA) {
             lds_direct_load16(a_base, a_voff[idx], issue_sa + (wave * A_DMA + idx) * 1024);
+        } else if constexpr (CANON) {
+            lds_direct_load16(w_base, w_voff[idx - A_DMA], issue_sa + A_STAGE + (wave * W_DMA + idx - A_DMA) * 1024);
         } else if (W_PIECE != 1024 || W_DMA > 4 || idx == A_DMA) {
             lds_direct_load16(w_base + (wave * W_DMA + idx - A_DMA) * W_PIECE, lane16,
                               issue_sa + A_STAGE + (wave * W_DMA + idx - A_DMA) * 1024);
@@ -225,7 +252,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
         if (issue_kt + 1 < KT) {
             a_base += A_ROW;
             // items alternate between the halves of a 128-channel slice of the native layout when BK = 64
-            w_base += (BK == 128 || (issue_kt & 1)) ? w_slice_stride - (kBK - BK) * (kGroup / 2) : (int64_t)W_GROUP;
+            w_base += CANON ? BK / 2 : (BK == 128 || (issue_kt & 1)) ? w_slice_stride - (kBK - BK) * (kGroup / 2) : (int64_t)W_GROUP;
             ++issue_kt;
         } else {   // next: slice 0 of the next tile, whose addresses issue_prepare sets (or none: stay on this slice)
             issue_kt = 0;
@@ -250,12 +277,29 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
     // Weight fragment of MFMA t of step ks: the 16 channels at 32 (NT ks + t) + 16 fhalf of the slice
     // with int8 codes; with packed codes lane half fhalf owns channels 64 ks + 32 fhalf + 16 t
     // (what its 16-byte code fragment holds), i.e. k32 step 2 ks + fhalf, k16 half t of the layout.
-    const int w_off = (wn / kGroup) * W_GROUP + frow * 8 + fhalf * (A4 ? 512 : 256);
+    // (CANON: likewise, from the piece 2 ks + fhalf of its row)
+    const int w_off = (wn / kGroup) * W_GROUP + (CANON ? frow * 64 : frow * 8 + fhalf * (A4 ? 512 : 256));
+    const int w_xor = swz_bk<64>(frow);
 
     // fragments of one step: TM code fragments (16 B) and NT x TN packed weight fragments (8 B)
-    struct Frags { v4i a[TM]; uint2 w[NT][TN]; };
+    // (CANON: NT code fragments each, and 16 bytes of weights for both MFMAs of a step)
+    struct Frags { v4i a[CANON ? NT * TM : TM]; uint2 w[NT][TN]; };
     auto load_frags = [&] __device__(Frags &f, int buf, int ks) {
         const uint8_t *sa = smem + buf * STAGE, *sw = sa + A_STAGE;
+        if constexpr (CANON) {
+#pragma unroll
+            for (int i = 0; i < TN; ++i) {
+                const uint4 p = *reinterpret_cast<const uint4 *>(sw + w_off + i * W_GROUP + (((ks * 2 + fhalf) ^ w_xor) << 4));
+                f.w[0][i] = make_uint2(p.x, p.y);
+                f.w[1][i] = make_uint2(p.z, p.w);
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+                    f.a[t * TM + j] = *reinterpret_cast<const v4i *>(sa + a_row_off[j] + (((ks * 4 + fhalf * 2 + t) ^ a_xor) << 4));
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < TM; ++j) {
             f.a[j] = *reinterpret_cast<const v4i *>(sa + a_row_off[j] + (((ks * 2 + fhalf) ^ a_xor) << 4));
@@ -276,6 +320,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
         f[2] = (int)((hi << 4) & 0xF0F0F0F0u);
         f[3] = (int)(hi & 0xF0F0F0F0u);
         return f;
+    };
+
+    // canonical nibble order (nibble i of a dword = channel i): the masks of `widen` give the even and the odd channels of 8, and
+    // the codes of 8 channels are dealt the same way (the order of channels within an MFMA is free)
+    auto deal_codes = [] __device__(v4i c) {
+        v4i r;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            r[2 * h] = (int)__builtin_amdgcn_perm((uint32_t)c[2 * h + 1], (uint32_t)c[2 * h], 0x06040200u);
+            r[2 * h + 1] = (int)__builtin_amdgcn_perm((uint32_t)c[2 * h + 1], (uint32_t)c[2 * h], 0x07050301u);
+        }
+        return r;
     };
 
     // ---- prologue: fill STAGES-1 buffers; with look-ahead also publish slice 0 and fetch its first fragments
@@ -330,12 +386,25 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
             if (ks + 1 < KS) load_frags(nxt, buf, ks + 1);
             else if (AHEAD) load_frags(nxt, (q + 1) % STAGES, 0);   // after the last item: stale but in-bounds, unused
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (CANON) {
+                if (kt == KT - 1 && (ks * 2 + 2) * 32 > k_tail) {   // a step with channels past K
+                    const bool past = (ks * 2 + fhalf) * 32 >= k_tail;
+#pragma unroll
+                    for (int i = 0; i < TN; ++i)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            cur.w[t][i].x = past ? 0u : cur.w[t][i].x;
+                            cur.w[t][i].y = past ? 0u : cur.w[t][i].y;
+                        }
+                }
+            }
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 v4i fa[TM];
 #pragma unroll
                 for (int j = 0; j < TM; ++j)
-                    fa[j] = A4 ? widen((uint32_t)cur.a[j][2 * t], (uint32_t)cur.a[j][2 * t + 1]) : cur.a[j];
+                    fa[j] = A4 ? widen((uint32_t)cur.a[j][2 * t], (uint32_t)cur.a[j][2 * t + 1])
+                               : CANON ? deal_codes(cur.a[t * TM + j]) : cur.a[j];
 #pragma unroll
                 for (int i = 0; i < TN; ++i) {
                     const v4i fw = widen(cur.w[t][i].x, cur.w[t][i].y);
@@ -564,7 +633,7 @@ void release_sched_slot(hipStream_t stream) {
 
 namespace {
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, bool A4 = false, StoreKind STORE = STORE_BY_PITCH>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, Operands OPS = OPS_INT8, StoreKind STORE = STORE_BY_PITCH>
 int launch_native(const int8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                   const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int M, int N, int K,
                   uint16_t *y, int32_t *acc_out, hipStream_t stream) {
@@ -578,9 +647,9 @@ int launch_native(const int8_t *codes, const float *x_scale, const uint8_t *w, c
     if (total < grid) grid = (total + 7) / 8 * 8;
     grid = limited_grid(grid);
     // the ring, then two tiles' epilogue vectors (scales, bias, code sums, zero-points; see the kernel)
-    const size_t smem = (size_t)STAGES * (BM * (A4 ? BK / 2 : BK) + BN * BK / 2) +
+    const size_t smem = (size_t)STAGES * (BM * (OPS == OPS_PACKED4 ? BK / 2 : BK) + BN * BK / 2) +
                         2 * ((BM + BN) * 4 + BN * 2 + BM * 4 + BN) + 8 * sizeof(int);   // + the ring of tile numbers
-    auto k = w4ax_gemm_native_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, OCC, A4, STORE>;
+    auto k = w4ax_gemm_native_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, OCC, OPS, STORE>;
     static std::atomic<uint64_t> configured{0};   // one per template instantiation
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
     bool is_clear = false;
@@ -606,7 +675,8 @@ int limited_grid(int grid) {
     return limit < 8 ? 8 : limit / 8 * 8;
 }
 
-// The tile variant for a size (variants 2 and 5 below; 10 + shape: the small-output kernel, all that canonical weights have).
+// The tile variant for a size (variants 2 and 5 below; 10 + shape: the small-output kernel; kCanonicalVariant: the two-wave kernel
+// with canonical weights).
 // Variant 5 is the wide kernel of w4ax_gemm_wide.hip (int8 codes only), taken
 //   - from 12 K slices on.  Against variant 2 (GEMM alone): K = 640 up to 7 % slower; 1280 level; 1536 from 4 % slower to 3 %
 //     faster (15600 x 1536 45.6 and 47.3 us, 32760 x 4608 221 and 214); 3072 8 % faster (4096 x 3072 40.0 and 37.0, 15600 x 3072
@@ -620,7 +690,7 @@ int limited_grid(int grid) {
 //     a round.
 int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout) {
     const int shape = small_gemm_shape(M, N, K, false);
-    if (w_layout == DVDQ_W_CANONICAL) return kFirstSmallVariant + (shape < 0 ? kLargestSmallShape : shape);
+    if (w_layout == DVDQ_W_CANONICAL) return shape < 0 ? kCanonicalVariant : kFirstSmallVariant + shape;
     if (shape >= 0) return kFirstSmallVariant + shape;
     if (codes_format != DVDQ_CODES_INT8 || K / 128 < 12 || !whole_line_tiles(N)) return 2;
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
@@ -633,8 +703,18 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     if (w_layout == DVDQ_W_CANONICAL) {
         if (codes_format != DVDQ_CODES_INT8 || w_zero) return DVDQ_ERR_UNSUPPORTED;
         const int f = gemm_variant(), v = f >= kFirstSmallVariant ? f : w4ax_gemm_choice(M, N, K, codes_format, w_layout);
-        return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, nullptr, nullptr, bias, M, N,
-                                      K, codes_format, w_layout, v - kFirstSmallVariant, y, acc_out, stream);
+        if (v != kCanonicalVariant)
+            return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, nullptr, nullptr, bias, M, N,
+                                          K, codes_format, w_layout, v - kFirstSmallVariant, y, acc_out, stream);
+        // Variant 2 with the weights as they come.  A slice of a weight row is 64 bytes, half a cache line, so twice the weight bytes
+        // leave the L2, but once per 256 channels x 128 tokens: a wave per 64 x 128 tile, its operands for itself, was bound by
+        // that traffic.  Before -> now: 7800 x 1440 x 1440 40.1 -> 27.8 us, 32760 x 1536 x 4608 342 -> 247 (1.9 POP/s), 32760 x 13824 x 5120
+        // 2708 -> 1993, 27510 x 11552 x 7296 3282 -> 2266, 32760 x 1440 x 1441 170 -> 92; 23080 x 288 x 528 (543 tiles) 19.8 and 20.5.
+        if (unaligned_tiles(N) && !acc_out)
+            return launch_native<128, 256, 128, 2, 2, 2, 2, OPS_CANONICAL, STORE_UNALIGNED>(
+                codes, x_scale, w, w_scale, nullptr, nullptr, bias, (int)M, (int)N, (int)K, y, acc_out, stream);
+        return launch_native<128, 256, 128, 2, 2, 2, 2, OPS_CANONICAL>(codes, x_scale, w, w_scale, nullptr, nullptr, bias, (int)M, (int)N,
+                                                                       (int)K, y, acc_out, stream);
     }
     const int m = (int)M, n = (int)N, k = (int)K;
 #define DVDQ_GEMM_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, m, n, k, y, acc_out, stream
@@ -654,12 +734,12 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     if (codes_format == DVDQ_CODES_PACKED4) {
         if ((v == 1 && k / 128 < 2) || (v > 2 && k / 128 < 3)) v = 2;
         switch (v) {
-            case 1: return launch_native<256, 256, 128, 2, 4, 3, 1, true>(DVDQ_GEMM_ARGS);
+            case 1: return launch_native<256, 256, 128, 2, 4, 3, 1, OPS_PACKED4>(DVDQ_GEMM_ARGS);
             case 2:
-                return unaligned ? launch_native<128, 256, 128, 2, 2, 2, 2, true, STORE_UNALIGNED>(DVDQ_GEMM_ARGS)
-                                 : launch_native<128, 256, 128, 2, 2, 2, 2, true>(DVDQ_GEMM_ARGS);
-            case 3: return launch_native<256, 256, 128, 2, 4, 4, 1, true>(DVDQ_GEMM_ARGS);
-            case 4: return launch_native<256, 256, 128, 4, 2, 4, 1, true>(DVDQ_GEMM_ARGS);
+                return unaligned ? launch_native<128, 256, 128, 2, 2, 2, 2, OPS_PACKED4, STORE_UNALIGNED>(DVDQ_GEMM_ARGS)
+                                 : launch_native<128, 256, 128, 2, 2, 2, 2, OPS_PACKED4>(DVDQ_GEMM_ARGS);
+            case 3: return launch_native<256, 256, 128, 2, 4, 4, 1, OPS_PACKED4>(DVDQ_GEMM_ARGS);
+            case 4: return launch_native<256, 256, 128, 4, 2, 4, 1, OPS_PACKED4>(DVDQ_GEMM_ARGS);
             default: return DVDQ_ERR_UNSUPPORTED;
         }
     }
@@ -673,7 +753,7 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     switch (v) {
         case 1: return launch_native<256, 256, 128, 4, 2, 3, 1>(DVDQ_GEMM_ARGS);
         case 2:
-            return unaligned ? launch_native<128, 256, 128, 2, 2, 2, 2, false, STORE_UNALIGNED>(DVDQ_GEMM_ARGS)
+            return unaligned ? launch_native<128, 256, 128, 2, 2, 2, 2, OPS_INT8, STORE_UNALIGNED>(DVDQ_GEMM_ARGS)
                              : launch_native<128, 256, 128, 2, 2, 2, 2>(DVDQ_GEMM_ARGS);
         case 3: return launch_native<256, 256, 128, 2, 4, 3, 1>(DVDQ_GEMM_ARGS);
         case 4: return launch_native<128, 256, 64, 2, 2, 4, 2>(DVDQ_GEMM_ARGS);

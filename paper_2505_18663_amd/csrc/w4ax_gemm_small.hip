@@ -12,8 +12,7 @@
 //   codes:   FP6 likewise.  The row-major containers are loaded as whole lines (rows of a slice: 128 or 64 bytes) and
 //            turned into fragments through the wave's own LDS; fetched as fragments directly, a load instruction
 //            would touch 32 lines.
-//            Canonical weights ([N, K/2] as an offline quantizer
-//            hands them over, K any multiple of 32) take the same way, for outputs of every size.
+//            Canonical weights ([N, K/2] as an offline quantizer hands them over, K any multiple of 32) take the same way.
 //   K tails, rows past M: loads past the end of a buffer descriptor return zeros (zero codes add nothing).
 //
 // A layer of very few tokens (CPW > 0) is one launch: the workgroup also quantizes its own tokens, into LDS, before it
@@ -250,7 +249,7 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
     const uint8_t *__restrict__ codes, const float *__restrict__ x_scale, const uint8_t *__restrict__ w,
     const float *__restrict__ w_scale, const int8_t *__restrict__ w_zero, const int32_t *__restrict__ code_rowsum,
     const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out,
-    int tiles_m, int tiles_n, int m_fastest, int group, LayerInput in) {
+    int tiles_m, int tiles_n, int m_fastest, LayerInput in) {
     constexpr bool FP6 = FMT == FMT_FP6, CANONICAL = FMT == FMT_CANONICAL, LAYER = CPW > 0;
     constexpr int BM = 32 * TM, BN = 32 * TN;
     constexpr int A_ROW = FMT == FMT_PACKED4 ? kBK / 2 : kBK;    // bytes of a code row per slice (row-major containers)
@@ -277,11 +276,7 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
     int tile = blockIdx.x;
     const int per_xcd = total / 8;
     if (tile < per_xcd * 8) tile = (tile % 8) * per_xcd + tile / 8;
-    // `group` tiles of one direction run fastest, then the other direction, then the groups
-    const int n_fast = m_fastest ? tiles_m : tiles_n, n_slow = m_fastest ? tiles_n : tiles_m;
-    const int grp = tile / (n_slow * group), in_grp = tile - grp * (n_slow * group);
-    const int width = min(group, n_fast - grp * group);
-    const int slow = in_grp / width, fast = grp * group + in_grp - slow * width;
+    const int n_fast = m_fastest ? tiles_m : tiles_n, slow = tile / n_fast, fast = tile - slow * n_fast;
     const int m0 = (m_fastest ? fast : slow) * BM, n0 = (m_fastest ? slow : fast) * BN;
     const int rows = min(BM, M - m0);
 
@@ -580,15 +575,8 @@ int launch_tile(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
     allow_dynamic_lds(reinterpret_cast<const void *>(k), LAYER ? kLdsPerCu : smem, configured);
     // an XCD takes a contiguous run of tiles: it should read all of the smaller operand and its share of the larger one
     const int m_fastest = FMT == FMT_INT8 || FMT == FMT_CANONICAL ? N > 2 * M : N > M;
-    // Workgroups that run at the same time walk K at about the same pace, so what they share is read once into the L2
-    // if there is not too much of it: with canonical weights, where outputs are of any size, tiles go in equal groups of
-    // at most 12 in the fast direction.  Groups of at most 6 / 12 / 24 / as wide as the output: 27510 x 11552 x 7296 (57 column
-    // tiles) 3.25 / 3.32 / 3.88 / 5.51 ms, 20000 x 9248 x 9000 2.33 / 2.28 / 2.81 ms, 32760 x 13824 x 5120 2.63 / 2.47 / 2.51 / 2.75;
-    // 118800 x 3072 x 3072 (24) 1.36 / 1.40 / 1.40 / 1.40, 7800 x 1440 x 1440 43.0 / 42.6 / 42.4 us.
-    const int n_fast = m_fastest ? tiles_m : tiles_n, n_groups = FMT == FMT_CANONICAL ? (n_fast + 11) / 12 : 1;
-    const int group = (n_fast + n_groups - 1) / n_groups;
     hipLaunchKernelGGL(k, dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * NW), smem, stream, codes, x_scale, w, w_scale, w_zero,
-                       code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, m_fastest, group, in);
+                       code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, m_fastest, in);
     return check_launch();
 }
 
@@ -628,15 +616,11 @@ int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uin
         case 3: return launch_tile<FMT, 2, 2, 4>(DVDQ_SMALL_ARGS); \
         case 4: return launch_tile<FMT, 2, 2, 2>(DVDQ_SMALL_ARGS); \
         case 5: return launch_tile<FMT, 2, 4, 2>(DVDQ_SMALL_ARGS); \
-        case 6: return launch_tile<FMT, 2, 4, 1>(DVDQ_SMALL_ARGS);             \
+        case 6: /* (sweeps only; canonical weights: w4ax_gemm.hip) */          \
+            if constexpr (FMT != FMT_CANONICAL) return launch_tile<FMT, 2, 4, 1>(DVDQ_SMALL_ARGS); \
+            else return DVDQ_ERR_UNSUPPORTED;                                  \
         default: return DVDQ_ERR_UNSUPPORTED;                                  \
     }
-    // Canonical weights have no other kernel: outputs beyond the lines above take shape 6, a wave per 64 x 128 tile, all of K
-    // in one wave.  (Codes and weights come in rows of K and K / 2 bytes; a slice of a weight row is half a cache line, and
-    // that traffic out of the L2 is the limit.  7800 x 1440 x 1440: 61.7 us with 256 x 256 tiles shared by four waves,
-    // 43.9 as shape 5, 40.0 as 6; 512 x 3072 x 3072: 83.4 -> 15.5 as 3; 32760 x 1536 x 4608: 543 -> 349 as 6;
-    // 32760 x 13824 x 5120: 2792 -> 2471, in the tile order below; in plain order deep
-    // K with many channels lost to it, 27510 x 11552 x 7296: 3272 -> 5513, now 3319.)
     if (codes_format == DVDQ_CODES_FP6) DVDQ_SMALL(FMT_FP6)
     if (codes_format == DVDQ_CODES_PACKED4) DVDQ_SMALL(FMT_PACKED4)
     if (w_layout == DVDQ_W_CANONICAL) DVDQ_SMALL(FMT_CANONICAL)
