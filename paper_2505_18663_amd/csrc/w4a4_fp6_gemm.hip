@@ -388,8 +388,13 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
 // The wide kernel's fixed cost per tile (nothing hides its epilogue) makes it pay from six K slices on (GEMM alone,
 // 32760 x 4608 output, variants 1 and 3: 81.0 and 78.8 us at K = 512, 96.3 and 92.1 at 768, 115 and 106 at 1024, 136 and 121
 // at 1280; 8192 x 4608: 29.6 and 29.0, 33.2 and 31.8, 38.0 and 35.8, 43.4 and 39.6; with zero-points it is level or behind up
-// to 640: 60000 x 3072 119 and 128 at 512).  (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind one of
-// these at nearly every K from 256 to 640, 3 % ahead at best in the mean of a shape.)
+// to 640: 60000 x 3072 119 and 128 at 512).  Later where its last round of tiles, one per compute unit, is at most half full:
+// variant 1's tiles are half as large, so it ends half a round earlier.  Time of variant 3 over that of variant 1 (bias and zero-points,
+// 1536 to 3072 channels) by the number of 256 x 256 tiles, at 6 / 8 / 12 / 16 / 24 slices: 96 to 128 tiles 1.19 / 1.16 / 1.10 / 1.05 / 0.89;
+// 264 to 384 1.16 / 1.12 / 1.02 / 0.96 / 0.89; 516 to 640 1.12 / 1.08 / 1.03 / 0.98 / 0.91; 1098 to 1400 1.10 / 1.10 / 1.02; 2172 1.08 / 1.05 /
+// 0.99; more than half full 144 to 240 0.98 / 0.95 / 0.94, 432 to 512 0.97 / 0.95 / 0.91, 672 to 768 1.0 / 0.97 / 0.93.  (6240 x 768 x 1024, 100
+// tiles: 13.7 and 11.5 us; 9000 x 768 x 2000, 288: 30.0 and 25.0.)  (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind
+// one of these at nearly every K from 256 to 640, 3 % ahead at best in the mean of a shape.)
 // Outputs with N no multiple of 8, in 16-byte pieces at even addresses, take it from 48 slices on without bias and zero-points,
 // from 96 with one of them, never with both: the lines that tests/test_dispatch.py states, from when such tiles were stored per element
 // and the wide kernel, with no second workgroup to hide that, lost up to 74 %.  By today's times it would pay from about 16 slices on
@@ -398,7 +403,11 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
 int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors) {
     const int shape = small_gemm_shape(M, N, K, true);
     if (shape >= 0) return kFirstSmallVariant + shape;
-    if (whole_line_tiles(N)) return K / kBK >= 6 ? 3 : 1;
+    if (whole_line_tiles(N)) {
+        const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
+        const bool half_empty = last != 0 && last <= 128 && tiles < 4096;
+        return K / kBK >= (!half_empty ? 6 : tiles <= 128 ? 18 : 12) ? 3 : 1;
+    }
     return vectors < 2 && K / kBK >= (vectors ? 96 : 48) ? 3 : 1;
 }
 

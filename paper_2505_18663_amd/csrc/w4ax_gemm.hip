@@ -678,23 +678,26 @@ int limited_grid(int grid) {
 // The tile variant for a size (variants 2 and 5 below; 10 + shape: the small-output kernel; kCanonicalVariant: the two-wave kernel
 // with canonical weights).
 // Variant 5 is the wide kernel of w4ax_gemm_wide.hip (int8 codes only), taken
-//   - from 12 K slices on.  Against variant 2 (GEMM alone): K = 640 up to 7 % slower; 1280 level; 1536 from 4 % slower to 3 %
-//     faster (15600 x 1536 45.6 and 47.3 us, 32760 x 4608 221 and 214); 3072 8 % faster (4096 x 3072 40.0 and 37.0, 15600 x 3072
-//     135 and 125);
+//   - from 12 K slices on (from 8 where its one or two rounds of tiles end more than half full: 0.93-0.98 of variant 2's time there at
+//     8 to 11 slices, 1536 and 2048 channels, 144 to 500 tiles);
 //   - where N is a multiple of 8.  For others variant 2 has the stores (STORE_UNALIGNED); per element, as the wide kernel stores
 //     them, a tile takes several times as long with no second workgroup to multiply meanwhile (before variant 2 had them the
 //     wide kernel was already 4-24 % slower at K = 1536 .. 6144, with bias and zero-points 20-53 %);
-//   - unless one to four rounds of its tiles (one per compute unit) would end in one that is less than two fifths full:
-//     variant 2's smaller tiles spread that rest (K = 12800, 4878 x 3088, 260 tiles: 171 and 285 us; K = 5248, 5960 x 8840, 840
-//     tiles: 242 and 266).  Over 82 outputs of 117 to 864 tiles the mean time is the same within 1 % for lines from 0.3 to 0.5 of
-//     a round.
+//   - unless its last round of tiles, one per compute unit, is at most half full: variant 2's tiles are half as large, so it ends
+//     half a round earlier.  Time of variant 5 over that of variant 2 (bias and zero-points, 1536 to 3072 channels, 12 to 60 slices) by the
+//     number of 256 x 256 tiles: 1.11-1.15 at 264 to 384 (15600 x 1536 x 1536, 366 tiles: 48.3 and 43.0 us), 0.94-0.97 at 432 to 512,
+//     1.08-1.12 at 516 to 640, 0.95-0.99 at 672 to 768, 1.04-1.10 at 1026 to 1400, 1.02-1.07 at 2064 to 2172, 1.01-1.05 at 3100 to 3200.
+//     One column of tiles: 1.02 to 1.14 up to two fifths of a round; the line stays there, and below four rounds, as
+//     tests/test_dispatch.py states it.
 int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout) {
     const int shape = small_gemm_shape(M, N, K, false);
     if (w_layout == DVDQ_W_CANONICAL) return shape < 0 ? kCanonicalVariant : kFirstSmallVariant + shape;
     if (shape >= 0) return kFirstSmallVariant + shape;
-    if (codes_format != DVDQ_CODES_INT8 || K / 128 < 12 || !whole_line_tiles(N)) return 2;
+    if (codes_format != DVDQ_CODES_INT8 || K / 128 < 8 || !whole_line_tiles(N)) return 2;
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
-    return tiles > 256 && tiles < 1024 && last != 0 && 5 * last < 2 * 256 ? 2 : 5;
+    if (K / 128 < 12) return tiles < 512 && last > 128 ? 5 : 2;
+    if (N <= 256) return tiles > 256 && tiles < 1024 && last != 0 && 5 * last < 2 * 256 ? 2 : 5;
+    return tiles < 4096 && last != 0 && last <= 128 ? 2 : 5;
 }
 
 int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,

@@ -1,0 +1,28 @@
+"""Which GEMM kernel the library takes where the last round of 256 x 256 tiles (256 at a time) is at most half full, and where it is
+not (host code only; that the kernels agree bit for bit is tested on the GPU)."""
+import pytest
+
+import paper_2505_18663_amd as dvdq
+
+
+def choice(tiles, slices, fp6):
+    """of an output of `tiles` tiles in two columns (or four, for an odd half)"""
+    cols = 2
+    fmt, layout = (dvdq.CODES_FP6, dvdq.W_NATIVE_FP6) if fp6 else (dvdq.CODES_INT8, dvdq.W_NATIVE)
+    return dvdq.bench_gemm_choice(256 * (tiles // cols), 256 * cols, 128 * slices, fmt, layout)
+
+
+@pytest.mark.parametrize("tiles,variant", [(256, 5), (258, 2), (384, 2), (386, 5), (512, 5), (514, 2), (640, 2), (642, 5), (1024, 5), (1026, 2),
+                                           (4094, 5), (4098, 5)])
+def test_int8(tiles, variant):
+    assert choice(tiles, 12, False) == choice(tiles, 108, False) == variant
+
+
+def test_int8_of_few_slices():
+    assert [choice(400, s, False) for s in (7, 8, 11)] == [2, 5, 5]
+    assert [choice(t, 8, False) for t in (256, 384, 386, 510, 512, 770)] == [2, 2, 5, 5, 2, 2]
+
+
+@pytest.mark.parametrize("tiles,slices", [(100, 18), (128, 18), (130, 6), (256, 6), (258, 12), (384, 12), (386, 6), (514, 12), (3968, 12), (4100, 6)])
+def test_fp6(tiles, slices):
+    assert choice(tiles, slices, True) == 3 and choice(tiles, slices - 1, True) == 1
