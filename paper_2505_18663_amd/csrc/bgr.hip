@@ -27,16 +27,18 @@
 // the row with a division per weight.  A lookup is three dependent LDS reads (the cell of values the threshold falls
 // in, the block of 4 .. 16 weights there, its weights and prefix sum).  The division survives only where it decides:
 // for a float that sits on a threshold to within fp64 rounding, so every weight is classified by exactly the quotient
-// and rounding of the definition.  The starts of the search are independent of each other: 8 lanes take one start (two
-// positions per lane; with one position per lane the divisions and the square root of a round, which are the same in
-// all lanes of a start, weigh twice as much), with no barrier inside the search.
+// and rounding of the definition.  The starts of the search are independent of each other: 8 lanes take one start, two
+// positions each, with no barrier inside the search.  (What a round does once per start, divisions, square root and the
+// expression of e2, all lanes of the start do, some 100 of its 300 instructions.)
 //
-// Cost.  1536 rows of 8960 weights, 100 steps, 10 rounds: 0.145 ms; a pass over the row per evaluation, one workgroup of
+// Cost.  1536 rows of 8960 weights, 100 steps, 10 rounds: 0.140 ms; a pass over the row per evaluation, one workgroup of
 // 256 threads per row, took 8.7 ms.  Bound by latencies and the issue of fp64 instructions, not by memory (62 MB): of the
 // 104 K clocks a row is in work (two rows per compute unit, each beside another one's phases) 10 K are the load, 25 K the two
 // dealing passes with the counts between them (LDS atomics and barriers) and the sum of squares, 13 K the windows, 4 K the
-// prefix sums, 46 K the search (eleven rounds of 4 K, a chain of three divisions, a square root and five LDS reads), 6 K the
-// codes.  That the sums are not rounded costs 7 K: with sums in fp64 0.136 ms (8960 rows of 1536: 0.517, now 0.586) and a
+// prefix sums, 46 K the search, 6 K the codes.  The search is eleven rounds of 4 K, bound by issue: three to four waves per SIMD,
+// some 300 instructions each.  Since those figures it got 5 to 10 % of the whole cheaper (sq / K without the division's steps,
+// weights chosen before they are converted, unsigned block numbers, 24-bit products: 8960 rows of 1536 587 -> 539 us, 13824 of
+// 256 837 -> 763, 1536 of 8960 151 -> 146).  That the sums are not rounded costs 7 K: with sums in fp64 0.136 ms for 0.145 (8960 rows of 1536: 0.517 for 0.586) and a
 // squared error off by 1e-14, up to 1e-12 where a grid fits a row to a hundredth.
 #include "dvdq_internal.h"
 #include "wave_reduce.h"
@@ -47,15 +49,15 @@ namespace dvdq {
 namespace {
 
 constexpr double kQmax = 15.0;           // INT4
-constexpr int kLanes = 8;        // lanes per start of the search
 constexpr int kCellLimit = 1024; // fullest cell that is sorted in windows (see the kernel)
 
-// Sum over 8 neighbouring lanes of an integer; every lane gets it.
-template <typename T>
-__device__ __forceinline__ T sum8(T v) {
+// Sum over 4 or 8 neighbouring lanes; every lane gets it.
+template <int LANES, typename T>
+__device__ __forceinline__ T sum_lanes(T v) {
+    static_assert(LANES == 4 || LANES == 8);
     v += dpp<DPP_XOR1>(v);
     v += dpp<DPP_XOR2>(v);
-    v += dpp<DPP_HALF_MIRROR>(v);
+    if constexpr (LANES == 8) v += dpp<DPP_HALF_MIRROR>(v);
     return v;
 }
 
@@ -108,45 +110,53 @@ struct Row {
     TwoDoubles sw2;           // sum of their squares
 };
 
-// The four sums on the grid (delta, z), by the 8 lanes of a group (j = lane % 8 takes positions j and j + 8): every
+// The four sums on the grid (delta, z), by the LANES lanes of a group (j = lane % LANES takes positions j, j + LANES, ...): every
 // lane gets all of them.
-template <int BLK>
+template <int BLK, int LANES>
 __device__ __forceinline__ Sums evaluate(const Row<BLK> &r, int j, double delta, double z) {
-    float bound[2];      // pos_j = #{w < bound}
-    int lo[2], hi[2];
+    constexpr int P = 16 / LANES;
+    float bound[P];      // pos_j = #{w < bound}
+    unsigned lo[P], hi[P];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < P; ++i) {
         // With t the threshold (j - z + 1/2) Delta and c the float nearest to it, every smaller float is below t and
         // every larger one above it by at least a quarter of a float's ulp, which the roundings of t and of a
         // quotient (fp64) cannot bridge.  So is c itself unless it equals t to within a few of those roundings:
         // then its own quotient decides.
-        const double u = (double)(j + i * kLanes) - z, t = (u + 0.5) * delta;
+        const double u = (double)(j + i * LANES) - z, t = (u + 0.5) * delta;
         const float c = (float)t;
         const double off = (double)c - t;
         bool below = off < 0.0;
         if (fabs(off) <= fabs(t) * 0x1p-48) below = rint((double)c / delta) <= u;
         bound[i] = below ? next_up(c) : c;
         const int cb = r.cell(bound[i]);
-        const int first = (int)r.cells[cb], past = (int)r.cells[cb + 1];
+        const unsigned first = r.cells[cb], past = r.cells[cb + 1];
         lo[i] = first / BLK;
-        hi[i] = max(past - 1, first) / BLK;
+        hi[i] = (past > first ? past - 1 : first) / BLK;
     }
     // the last block of each cell that starts below the bound (or the cell's first)
-    while (lo[0] < hi[0] || lo[1] < hi[1]) {
+    auto searching = [&] __device__ {
+        bool any = false;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int mid = (lo[i] + hi[i] + 1) >> 1;
+        for (int i = 0; i < P; ++i) any |= lo[i] < hi[i];
+        return any;
+    };
+    while (searching()) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const unsigned mid = (lo[i] + hi[i] + 1) >> 1;
             const bool up = r.sorted[mid * BLK] < bound[i] || lo[i] >= hi[i];
             lo[i] = up ? mid : lo[i];   // (mid = lo where the range is a single block)
             hi[i] = up ? hi[i] : mid - 1;
         }
     }
-    int64_t p[2];
-    int pos[2];
+    int64_t p = 0;              // this lane's share of the sums over the positions: of P(pos_j),
+    int moment = 0, count = 0;  // (2 (j - z) + 1) pos_j and pos_j
+    const int zi = (int)z;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < P; ++i) {
         double run = r.fixed.bias;
-        pos[i] = lo[i] * BLK;
+        int pos = (int)(lo[i] * BLK);
         const float4 *blk = reinterpret_cast<const float4 *>(r.sorted + lo[i] * BLK);
 #pragma unroll
         for (int b = 0; b < BLK / 4; ++b) {
@@ -155,18 +165,22 @@ __device__ __forceinline__ Sums evaluate(const Row<BLK> &r, int j, double delta,
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
                 const bool in = q[h] < bound[i];
-                pos[i] += in ? 1 : 0;
-                run += (double)(in ? q[h] : 0.f);
+                pos += in ? 1 : 0;
+                float w = in ? q[h] : 0.f;
+                asm("" : "+v"(w));   // (chosen as a float: the compiler would choose among the converted doubles, twice the work)
+                run += (double)w;
             }
         }
-        p[i] = r.prefix[lo[i]] + r.fixed.integer(run);
+        int64_t sum = r.prefix[lo[i]] + r.fixed.integer(run);
+        if (i == P - 1 && j == LANES - 1) { pos = 0; sum = 0; }   // (15 positions)
+        p += sum;
+        moment += __mul24(2 * (j + i * LANES - zi) + 1, pos);   // (24 bits: pos <= K, the row fits the LDS)
+        count += pos;
     }
-    if (j == kLanes - 1) { pos[1] = 0; p[1] = 0; }   // (15 positions)
-    const int zi = (int)z;
     Sums s;
-    const int64_t num = (15 - zi) * r.sum - sum8(p[0] + p[1]);
-    s.den = (double)((15 - zi) * (15 - zi) * r.K - sum8((2 * (j - zi) + 1) * pos[0] + (2 * (j + kLanes - zi) + 1) * pos[1]));
-    s.sq = (double)(15 * r.K - sum8(pos[0] + pos[1]));
+    const int64_t num = (int64_t)((uint64_t)(uint32_t)(15 - zi) * (uint64_t)r.sum) - sum_lanes<LANES>(p);
+    s.den = (double)(__mul24(__mul24(15 - zi, 15 - zi), r.K) - sum_lanes<LANES>(moment));
+    s.sq = (double)(15 * r.K - sum_lanes<LANES>(count));
     // num in two doubles: its upper and lower 32 bits are exact (and the upper ones, if any, are the larger)
     const double upper = (double)(int32_t)(num >> 32) * (0x1p32 * r.fixed.unit), lower = (double)(uint32_t)num * r.fixed.unit;
     s.num = upper + lower;
@@ -182,12 +196,12 @@ __device__ __forceinline__ Sums evaluate(const Row<BLK> &r, int j, double delta,
     // A (nearly) exact fit: the sum over the row instead, as slow as it is.
     if (!(s.e2 > 0x1p-40 * r.sw2.hi)) {
         double e2 = 0.0;
-        for (int k = j; k < r.K; k += kLanes) {
+        for (int k = j; k < r.K; k += LANES) {
             const double w = (double)r.sorted[k];
             const double d = w - delta * (clamp_d(rint(w / delta) + z, 0.0, kQmax) - z);
             e2 += d * d;
         }
-        s.e2 = sum8(e2);
+        s.e2 = sum_lanes<LANES>(e2);
     }
     return s;
 }
@@ -264,7 +278,7 @@ __device__ void bitonic_sort(float *a, int n) {
 // T threads, a prefix sum every BLK weights.  HELD > 0: the threads hold the row in registers, HELD pairs of weights
 // each (K <= 2 HELD T); 0: it is read again for every step that needs it in its own order.
 // (16 waves per compute unit in every case: one workgroup of 1024 threads or two of 512, 128 registers per lane.)
-template <int T, int BLK, int HELD>
+template <int T, int BLK, int HELD, int LANES>
 __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, int K, int cells, int n_steps, int max_refine,
                                                 double eps, int search, uint8_t *__restrict__ w_packed,
                                                 float *__restrict__ w_scale, int8_t *__restrict__ w_zero,
@@ -467,32 +481,39 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
             total = prefix[full] + fixed.integer(rest);
         }
 
-        // ---- search: 8 lanes per start, no barrier
+        // ---- search: LANES lanes per start, no barrier
         const Row<BLK> r = {row, prefix, first, cell, K, fixed, total, sw2};
-        const int j = lane & (kLanes - 1);
+        const int j = lane & (LANES - 1);
         const bool all = search == DVDQ_BGR_BEST_OF_ALL;
         const double step = (hi0 - lo0) / (double)n_steps;
         const double mean = sw / (double)K;
+        // sq / K, rounded as the division does: with r exact, the quotient before its last rounding is off by 2^-52 of an ulp
+        // at most, and a quotient of integers below 2^19 and 2^15 is no closer to the middle between two doubles than 2^-16 ulp.
+        const double per_k = 1.0 / (double)K;
+        auto over_k = [&] __device__(double sq) {
+            const double q = sq * per_k, rest = __builtin_fma(-q, (double)K, sq);
+            return __builtin_fma(rest, per_k, q);
+        };
         int best_i = 0x7FFFFFFF;
         best = INFINITY;
         best_delta = 1.0;
         best_z = 0.0;
-        for (int64_t i = (all ? 0 : 1) + tid / kLanes; i <= n_steps; i += T / kLanes) {
+        for (int64_t i = (all ? 0 : 1) + tid / LANES; i <= n_steps; i += T / LANES) {
             const double lo = lo0 + (double)i * step, hi = hi0 - (double)i * step;
             if (!(lo < hi)) break;   // the range has collapsed (from i = n_steps / 2 on)
             // clipped MinMax start
             double delta = (hi - lo) / kQmax;
             double z = clamp_d(rint(-(lo / delta)), 0.0, kQmax);
-            Sums s = evaluate(r, j, delta, z);
+            Sums s = evaluate<BLK, LANES>(r, j, delta, z);
             double e = sqrt(s.e2);
             if (all && e < best) { best = e; best_delta = delta; best_z = z; best_i = (int)i; }
             for (int round = 0; round < max_refine; ++round) {
                 if (s.den == 0.0 || e != e) break;   // (e: a NaN among the weights)
                 const double dn = s.num / s.den;
                 if (!(dn > 0.0)) break;
-                const double zn = clamp_d(rint(s.sq / (double)K - mean / dn), 0.0, kQmax);
+                const double zn = clamp_d(rint(over_k(s.sq) - mean / dn), 0.0, kQmax);
                 if (dn == delta && zn == z) break;   // a fixed point: every further round is this grid again
-                s = evaluate(r, j, dn, zn);
+                s = evaluate<BLK, LANES>(r, j, dn, zn);
                 const double en = sqrt(s.e2);
                 if (all && en < best) { best = en; best_delta = dn; best_z = zn; best_i = (int)i; }
                 const double gain = e - en;
@@ -506,7 +527,7 @@ __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, 
         }
         // ---- the smallest error, ties to the earliest start: across the wave's groups, then the waves
 #pragma unroll
-        for (int m = kLanes; m <= 32; m <<= 1) {
+        for (int m = LANES; m <= 32; m <<= 1) {
             const double oe = __shfl_xor(best, m, 64), od = __shfl_xor(best_delta, m, 64), oz = __shfl_xor(best_z, m, 64);
             const int oi = __shfl_xor(best_i, m, 64);
             if (oe < best || (oe == best && oi < best_i)) { best = oe; best_delta = od; best_z = oz; best_i = oi; }
@@ -554,10 +575,10 @@ size_t lds_bytes(int64_t K, int blk, int cells) {
     return row_floats((int)K) * sizeof(float) + (size_t)(K / blk + 1) * sizeof(int64_t) + (size_t)(cells + 1) * sizeof(uint32_t);
 }
 
-template <int T, int BLK, int HELD>
+template <int T, int BLK, int HELD, int LANES>
 int launch(const float *w, int64_t N, int K, int cells, int n_steps, int max_refine, double eps, int search,
            uint8_t *w_packed, float *w_scale, int8_t *w_zero, double *row_error, hipStream_t stream) {
-    auto k = bgr_kernel<T, BLK, HELD>;
+    auto k = bgr_kernel<T, BLK, HELD, LANES>;
     static std::atomic<uint64_t> configured{0};   // one per template instantiation
     allow_dynamic_lds(reinterpret_cast<const void *>(k), 158 * 1024, configured);
     // (a launch has fewer than 2^32 threads: more rows than that in several)
@@ -584,10 +605,10 @@ int launch_bgr(const float *w, int64_t N, int64_t K, int n_steps, int max_refine
     // beside it: with no more rows than compute units (32 rows of 8960: level at 100 steps, 46.7 us against 50.8 at 200;
     // 200 rows of 13824: 41.7 against 46.0), and from 14 K weights on.
     const int cells = K <= 2048 ? 1024 : (K <= 4096 ? 2048 : 4096);
-    if (K > 16384) return launch<1024, 16, 0>(DVDQ_BGR_ARGS(2048));
-    if (N > 256 && K <= 10240) return launch<512, 4, 10>(DVDQ_BGR_ARGS(cells));
-    if (N > 256 && K <= 14336) return launch<512, 8, 14>(DVDQ_BGR_ARGS(2048));
-    return launch<1024, 4, 8>(DVDQ_BGR_ARGS(cells));
+    if (K > 16384) return launch<1024, 16, 0, 8>(DVDQ_BGR_ARGS(2048));
+    if (N > 256 && K <= 10240) return launch<512, 4, 10, 8>(DVDQ_BGR_ARGS(cells));
+    if (N > 256 && K <= 14336) return launch<512, 8, 14, 8>(DVDQ_BGR_ARGS(2048));
+    return launch<1024, 4, 8, 8>(DVDQ_BGR_ARGS(cells));
 #undef DVDQ_BGR_ARGS
 }
 
