@@ -29,7 +29,7 @@
 // for a float that sits on a threshold to within fp64 rounding, so every weight is classified by exactly the quotient
 // and rounding of the definition.  The starts of the search are independent of each other: 8 lanes take one start, two
 // positions each, with no barrier inside the search.  (What a round does once per start, divisions, square root and the
-// expression of e2, all lanes of the start do, some 100 of its 300 instructions.)
+// expression of e2, all lanes of the start do, some 100 of its 300 instructions; launch_bgr says where 4 lanes with four positions are better.)
 //
 // Cost.  1536 rows of 8960 weights, 100 steps, 10 rounds: 0.140 ms; a pass over the row per evaluation, one workgroup of
 // 256 threads per row, took 8.7 ms.  Bound by latencies and the issue of fp64 instructions, not by memory (62 MB): of the
@@ -599,7 +599,14 @@ int launch_bgr(const float *w, int64_t N, int64_t K, int n_steps, int max_refine
                uint8_t *w_packed, float *w_scale, int8_t *w_zero, double *row_error, hipStream_t stream) {
 #define DVDQ_BGR_ARGS(CELLS) \
     w, N, (int)K, CELLS, n_steps, max_refine, eps, search, w_packed, w_scale, w_zero, row_error, stream
-    // A few weights per cell: 1024 .. 4096 cells.  Two rows at a time per compute unit, as workgroups of 512 threads,
+    // A few weights per cell: 1024 .. 4096 cells.  Bound by the issue of instructions, most of them fp64, of which a start's
+    // own (the same in all its lanes) weigh less the fewer lanes take it: rows short enough go as workgroups of 256 threads, four
+    // lanes a start, three to four at a time on a compute unit and not held in registers (100 steps, 10 rounds; as workgroups of 512
+    // with eight lanes a start -> now: 13824 rows of 256 763 -> 504 us, 8960 of 1536 539 -> 369, 3000 of 4096 212 -> 161, 520 of 6144 63.5 ->
+    // 58.9).  Longer ones leave no room for a third beside two (780 rows of 6656: level); with at most two rows per
+    // compute unit the time is one row's own, in which more threads sort (400 rows of 5120: level, of 6144 44.9 and 46.8).
+    if (N > 256 && K <= (N > 512 ? 6144 : 4608)) return launch<256, 4, 0, 4>(DVDQ_BGR_ARGS(2048));
+    // Two rows at a time per compute unit, as workgroups of 512 threads,
     // while their LDS allows (half of 160 KB each; longer rows with coarser prefix sums and cells): 0.145 ms against 0.20
     // as workgroups of 1024 for 1536 rows of 8960.  A workgroup of 1024 threads where there is no second row to put
     // beside it: with no more rows than compute units (32 rows of 8960: level at 100 steps, 46.7 us against 50.8 at 200;
