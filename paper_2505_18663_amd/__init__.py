@@ -471,13 +471,14 @@ class GbsController:
         _check(L.dvdq_gbs_reset(_ptr(self.state), self.b_high, _stream(stream)) if r is None else r, "dvdq_gbs_reset")
 
     def step(self, f_t, f_prev, stream=None):
+        L = lib()   # (a controller may come out of a pickle, in a process that has made no call yet)
         r = _marshal.gbs_step(f_t, f_prev, self.delta, self.b_low, self.b_high, self.state, self.workspace, stream)
         if r is not None:
             return _check(r, "dvdq_gbs_step")
         _need(f_t, torch.bfloat16, None, "f_t")
         _need(f_prev, torch.bfloat16, tuple(f_t.shape), "f_prev")
-        _check(lib().dvdq_gbs_step(_ptr(f_t), _ptr(f_prev), f_t.numel(), self.delta, self.b_low, self.b_high,
-                                   _ptr(self.state), _ptr(self.workspace), self.workspace.numel(), _stream(stream)),
+        _check(L.dvdq_gbs_step(_ptr(f_t), _ptr(f_prev), f_t.numel(), self.delta, self.b_low, self.b_high,
+                               _ptr(self.state), _ptr(self.workspace), self.workspace.numel(), _stream(stream)),
                "dvdq_gbs_step")
 
     def read(self):
