@@ -2,10 +2,11 @@
 the quantized linear layer runs in the HIP kernels behind the C ABI declared in
 ``include/dvdq.h``.  PyTorch supplies device memory and streams, nothing else.
 
-Calls are made through ctypes; those that a model makes per layer or per step go through ``_marshal.so`` (csrc/marshal.cpp), which
-does the same checks and the call natively where every argument is the plain case, and hands anything else back.
+Calls are made through ctypes; those that a model makes per layer or per step go through a native module (csrc/marshal.cpp), which
+does the same checks and the call natively where every argument is the plain case, and hands anything else back.  That module is
+built against one Python and one torch, and its file name says which: with any other, all calls go through ctypes.
 
-There is no CPU fallback: if ``libdvdq.so`` or ``_marshal.so`` has not been built
+There is no CPU fallback: if ``libdvdq.so`` has not been built
 (``python -m paper_2505_18663_amd.build``) importing a function works but the first
 call raises ``DvdqLibraryMissing``.
 """
@@ -14,6 +15,8 @@ from __future__ import annotations
 import ctypes as C
 import importlib.util
 import os
+import sys
+import warnings
 
 import torch
 
@@ -37,9 +40,9 @@ EXPORTED_SYMBOLS = (
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libdvdq.so")
-_MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
+_MARSHAL_PATH = os.path.join(_HERE, f"_marshal.{sys.implementation.cache_tag}.torch-{torch.__version__}.so")
 _lib = None
-_marshal = None   # the native module, once the library is loaded
+_marshal = None   # the native module (or _Handback), once the library is loaded
 
 
 class DvdqError(RuntimeError):
@@ -52,6 +55,28 @@ class DvdqLibraryMissing(RuntimeError):
     pass
 
 
+class _Handback:
+    """In the place of the native module where none is built for this Python and torch: hands every call back."""
+    @staticmethod
+    def _hand_back(*args):
+        return None
+    rotate_quant = rotate_quant_blockwise = w4ax_gemm = qlinear = gbs_reset = gbs_step = _hand_back
+
+
+def _load_marshal(L):
+    if not os.path.exists(_MARSHAL_PATH):
+        warnings.warn(f"{os.path.basename(_MARSHAL_PATH)} is not built: calls go through ctypes, at twice the host time "
+                      "(python -m paper_2505_18663_amd.build)", RuntimeWarning, stacklevel=3)
+        return _Handback
+    spec = importlib.util.spec_from_file_location("_marshal", _MARSHAL_PATH)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    native.bind(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, *(C.cast(getattr(L, f), C.c_void_p).value for f in (
+        "dvdq_rotate_quant", "dvdq_rotate_quant_blockwise", "dvdq_w4ax_gemm", "dvdq_qlinear", "dvdq_gbs_reset", "dvdq_gbs_step",
+        "dvdq_codes_bytes", "dvdq_qlinear_workspace_bytes", "dvdq_w4_native_bytes", "dvdq_w4_native_fp6_bytes")))
+    return native
+
+
 def library_path() -> str:
     return _LIB_PATH
 
@@ -61,10 +86,9 @@ def lib() -> C.CDLL:
     global _lib, _marshal
     if _lib is not None:
         return _lib
-    missing = [p for p in (_LIB_PATH, _MARSHAL_PATH) if not os.path.exists(p)]
-    if missing:
+    if not os.path.exists(_LIB_PATH):
         raise DvdqLibraryMissing(
-            f"{missing[0]} not found: build it with `python -m paper_2505_18663_amd.build` "
+            f"{_LIB_PATH} not found: build it with `python -m paper_2505_18663_amd.build` "
             "(hipcc, gfx950).  There is no fallback path.")
     L = C.CDLL(_LIB_PATH)
     i64, i32, vp, sz = C.c_int64, C.c_int, C.c_void_p, C.c_size_t
@@ -123,13 +147,7 @@ def lib() -> C.CDLL:
               "dvdq_w4_native_bytes"):
         getattr(L, f).restype = sz
     L.dvdq_status_string.restype = C.c_char_p
-    spec = importlib.util.spec_from_file_location("_marshal", _MARSHAL_PATH)
-    native = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(native)
-    native.bind(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, *(C.cast(getattr(L, f), C.c_void_p).value for f in (
-        "dvdq_rotate_quant", "dvdq_rotate_quant_blockwise", "dvdq_w4ax_gemm", "dvdq_qlinear", "dvdq_gbs_reset", "dvdq_gbs_step",
-        "dvdq_codes_bytes", "dvdq_qlinear_workspace_bytes", "dvdq_w4_native_bytes", "dvdq_w4_native_fp6_bytes")))
-    _marshal, _lib = native, L
+    _marshal, _lib = _load_marshal(L), L
     return L
 
 

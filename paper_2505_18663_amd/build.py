@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import concurrent.futures as cf
 import os
+import shutil
 import subprocess
 import sys
 
@@ -10,7 +11,6 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdvdq.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")
 
 SOURCES = ["api.hip", "rotate_quant.hip", "w4ax_gemm.hip", "w4a4_fp6_gemm.hip", "w4ax_gemm_wide.hip", "w4ax_gemm_small.hip", "gbs.hip", "bgr.hip", "bench_kernels.hip"]
 
@@ -38,21 +38,30 @@ def _compile(src: str) -> str:
 
 
 def _build_marshal() -> None:
-    """csrc/marshal.cpp: host code only, against the headers and libraries of the torch that will load it."""
+    """csrc/marshal.cpp: host code only, against the headers and libraries of the Python and torch that will load it (the binding
+    does without where they, or a host compiler, are not installed)."""
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension
-    tmp = MARSHAL + f".tmp{os.getpid()}"
+
+    from . import _MARSHAL_PATH
+    cxx = os.environ.get("CXX", "g++")
+    headers = [os.path.join(sysconfig.get_path("include"), "Python.h"),
+               *(os.path.join(cpp_extension.include_paths()[0], "torch", "csrc", h) for h in ("Exceptions.h", "autograd/python_variable.h"))]
+    if shutil.which(cxx) is None or not all(map(os.path.exists, headers)):
+        print(f"no {cxx} or no headers of this Python and torch: {os.path.basename(_MARSHAL_PATH)} not built, calls go through ctypes")
+        return
+    tmp = _MARSHAL_PATH + f".tmp{os.getpid()}"
     torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-cast-function-type",
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-cast-function-type",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + sysconfig.get_path("include"),
            *("-isystem" + d for d in cpp_extension.include_paths()), os.path.join(CSRC, "marshal.cpp"), "-o", tmp,
            "-L" + torch_lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"{cmd[0]} failed for marshal.cpp:\n{res.stdout}\n{res.stderr}")
-    os.replace(tmp, MARSHAL)
+    os.replace(tmp, _MARSHAL_PATH)
 
 
 def build_library(verbose: bool = False) -> str:

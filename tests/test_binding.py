@@ -26,3 +26,29 @@ except Exception as e:
     print(type(e).__name__, e)
 """)
     assert out == "TypeError f_t: expected a CUDA/HIP tensor"
+
+
+def test_the_native_module_is_the_one_built_for_this_python_and_torch():
+    out = in_a_fresh_process("import os; dvdq.lib(); print(os.path.basename(dvdq._marshal.__file__))")
+    import torch
+    assert out == f"_marshal.{sys.implementation.cache_tag}.torch-{torch.__version__}.so"
+
+
+def test_without_a_native_module_calls_go_through_ctypes():
+    """Another torch than the one at hand when the native module was built: no such file."""
+    out = in_a_fresh_process("""
+import warnings
+torch.__version__ = "0.0.0"
+import importlib; importlib.reload(dvdq)
+with warnings.catch_warnings(record=True) as w:
+    warnings.simplefilter("always")
+    print(dvdq.version() >= 100, [x.category.__name__ for x in w])
+assert not hasattr(dvdq._marshal, "bind")
+for f in (lambda x: dvdq.rotate_quant(x, 128, 8), lambda x: dvdq.rotate_quant_blockwise(x, 128, 4, 128), lambda x: dvdq.qlinear(x, x, x, 128, 8),
+          lambda x: dvdq.w4ax_gemm(x, x, x, x, 8), lambda x: dvdq.GbsController.step(type("C", (), dict(delta=0., b_low=4, b_high=8, state=x, workspace=x))(), x, x)):
+    try:
+        f(torch.zeros(8, 128))
+    except TypeError as e:
+        print(e)
+""")
+    assert out.splitlines() == ["True ['RuntimeWarning']"] + [f"{n}: expected a CUDA/HIP tensor" for n in ("x", "x", "x", "codes", "f_t")]

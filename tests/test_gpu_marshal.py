@@ -16,6 +16,7 @@ M, K, N = 70, 512, 264
 def both(monkeypatch):
     """call(f) -> (f() through the native module, f() without it)"""
     dvdq.lib()
+    assert dvdq._marshal.__file__ == dvdq._MARSHAL_PATH   # (else both would go through ctypes)
     refuse = types.SimpleNamespace(**{f: lambda *a: None for f in ("qlinear", "rotate_quant", "rotate_quant_blockwise", "w4ax_gemm",
                                                                   "gbs_reset", "gbs_step")})
     native = dvdq._marshal
