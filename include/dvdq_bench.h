@@ -49,6 +49,11 @@ int dvdq_bench_set_gemm_variant(int variant);
  * how many there are of bias and zero-points.  Sizes below 1: minus a dvdq_status code. */
 int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors);
 
+/* How dvdq_qlinear runs a layer with its arguments at these addresses (host only: nothing is read there): 0 = as two launches,
+ * 1 or 2 = as one, with tiles of 32 or 64 channels.  Sizes below 1: minus a dvdq_status code. */
+int dvdq_bench_qlinear_choice(const void *x_bf16, const void *y_bf16, const void *workspace, size_t workspace_bytes, int64_t M,
+                              int64_t N, int64_t K);
+
 /* How the native-layout GEMM's persistent workgroups get their tiles: 0 = fixed equal shares,
  * -1 = the library's own choice (tiles drawn from per-stream counters, fixed shares while a
  * stream is being captured).  Results are identical either way.  Process-wide (an atomic that every

@@ -184,7 +184,7 @@ int dvdq_qlinear(const void *x_bf16, const uint8_t *w, const float *w_scale, con
     if (rc != DVDQ_OK) return rc;
     if (workspace_bytes < dvdq_qlinear_workspace_bytes(M, K, codes_format)) return DVDQ_ERR_WORKSPACE;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const int width = dvdq::gemm_variant() < 0 ? dvdq::qlinear_small_width(M, N, K) : -1;
+    const int width = dvdq::gemm_variant() < 0 ? dvdq::qlinear_choice(x_bf16, y_bf16, workspace, workspace_bytes, M, N, K) : 0;
     if (width > 0)
         return dvdq::launch_qlinear_small(static_cast<const uint16_t *>(x_bf16), log2b, act_bits, w, w_scale, w_zero,
                                           static_cast<const uint16_t *>(bias_bf16), M, N, K, codes_format, w_layout, width,

@@ -179,6 +179,12 @@ int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, in
     return dvdq::w4ax_gemm_choice(M, N, K, codes_format, w_layout);
 }
 
+int dvdq_bench_qlinear_choice(const void *x_bf16, const void *y_bf16, const void *workspace, size_t workspace_bytes, int64_t M, int64_t N,
+                              int64_t K) {
+    if (M < 1 || N < 1 || K < 32) return -DVDQ_ERR_SHAPE;
+    return dvdq::qlinear_choice(x_bf16, y_bf16, workspace, workspace_bytes, M, N, K);
+}
+
 int dvdq_bench_set_gemm_schedule(int schedule) {
     if (schedule < -1 || schedule > 0) return DVDQ_ERR_UNSUPPORTED;
     dvdq::set_gemm_schedule(schedule);

@@ -46,8 +46,8 @@ inline bool unaligned_tiles(int64_t N) { return (N & 7) != 0 && N >= 8 && N < kM
 int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
                            const int8_t *w_zero, const int32_t *code_rowsum, const uint16_t *bias, int64_t M, int64_t N,
                            int64_t K, int codes_format, int w_layout, int shape, uint16_t *y, int32_t *acc_out, hipStream_t stream);
-// A whole layer of few tokens in one launch (w4ax_gemm_small.hip).  qlinear_small_width: -1 (two launches), or the tile width to take
-int qlinear_small_width(int64_t M, int64_t N, int64_t K);
+// A whole layer of few tokens in one launch (w4ax_gemm_small.hip).  qlinear_choice: 0 (two launches), or the tile width to take
+int qlinear_choice(const void *x, const void *y, const void *workspace, size_t workspace_bytes, int64_t M, int64_t N, int64_t K);
 int launch_qlinear_small(const uint16_t *x, int log2_block, int act_bits, const uint8_t *w, const float *w_scale,
                          const int8_t *w_zero, const uint16_t *bias, int64_t M, int64_t N, int64_t K, int codes_format,
                          int w_layout, int width, uint16_t *y, uint8_t *codes, float *x_scale, int32_t *code_rowsum, hipStream_t stream);

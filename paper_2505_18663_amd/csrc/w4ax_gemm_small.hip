@@ -17,7 +17,7 @@
 //
 // A layer of very few tokens (CPW > 0) is one launch: the workgroup also quantizes its own tokens, into LDS, before it
 // multiplies, while its first weights are on their way.  Two launches in a row cost such a layer a launch's start and end, and a
-// round trip of the codes through memory, more than quantizing the same tokens in every workgroup does (qlinear_small_width).
+// round trip of the codes through memory, more than quantizing the same tokens in every workgroup does (qlinear_choice).
 // It is bound by the chain load - transform - maximum - codes - slices - sum, a few waits each.
 //
 // Measured (back-to-back launches, int8 codes, before -> now): 2 x 1536 x 9216 (tokens x K x channels): 22.6 -> 4.4 us;
@@ -648,19 +648,24 @@ int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uin
 #undef DVDQ_SMALL_ARGS
 }
 
-// Whether a whole layer takes the layer form of the kernel above, one launch: -1 (two launches), or the width of its tiles in 32
-// channels.  Every workgroup quantizes its 32 tokens, so it pays while that is little: up to 32 units of 512 channels (4 a wave), up to
+// Whether a whole layer takes the layer form of the kernel above, one launch: 0 (two launches), or the width of its tiles in 32
+// channels.  Not where y or the workspace lies over x, against the rule of dvdq.h: one workgroup stores its part of y and the codes
+// while others still read their tokens, where of two launches the first has read all of x before the second stores.  Every workgroup quantizes its 32 tokens, so it pays while that is little: up to 32 units of 512 channels (4 a wave), up to
 // 64 for rows of four units or more, where the quantizer alone takes longer too, and as long as all workgroups run at once (the lines
 // of small_gemm_shape).  Swept with launches in a graph, so without the host's time, M = 1 .. 4096, K = 256 .. 4096, N = 256 .. 9216, two
 // launches -> one (us, int8 codes): 1 x 256 x 1024 5.3 -> 4.2; 2 x 1536 x 9216 7.6 -> 5.6; 128 x 256 x 1024 (32 units) 5.9 -> 5.3;
 // 1 x 4096 x 9216 11.0 -> 7.3; 8 x 4096 x 1024 (64) 8.8 -> 8.3; not taken: 32 x 1024 x 1024 (64 units of 2-unit rows) 6.5 and 7.0,
 // 16 x 1536 x 1024 (48) 6.8 and 7.0, 64 x 512 x 9216 (288 tiles of 32 x 64) 7.4 and 10.6.  FP6 codes within 3 % of these ratios.  Outside
 // a graph the host's second launch, 4 us, comes on top of the two.
-int qlinear_small_width(int64_t M, int64_t N, int64_t K) {
+int qlinear_choice(const void *x, const void *y, const void *workspace, size_t workspace_bytes, int64_t M, int64_t N, int64_t K) {
     const int64_t units = (K + kUnit - 1) / kUnit;
-    if ((M < 32 ? M : 32) * units > (units >= 4 ? kLayerTasks : kLayerTasks / 2)) return -1;
+    if ((M < 32 ? M : 32) * units > (units >= 4 ? kLayerTasks : kLayerTasks / 2)) return 0;
     const int shape = small_gemm_shape(M, N, K, false);
-    return shape < 0 || shape > 2 ? -1 : shape == 0 ? 1 : 2;
+    if (shape < 0 || shape > 2) return 0;
+    const uintptr_t at = reinterpret_cast<uintptr_t>(x), end = at + 2 * (uintptr_t)(M * K);
+    auto over_x = [&](const void *p, size_t bytes) { return at < reinterpret_cast<uintptr_t>(p) + bytes && reinterpret_cast<uintptr_t>(p) < end; };
+    if (over_x(y, 2 * (size_t)(M * N)) || over_x(workspace, workspace_bytes)) return 0;
+    return shape == 0 ? 1 : 2;
 }
 
 int launch_qlinear_small(const uint16_t *x, int log2_block, int act_bits, const uint8_t *w, const float *w_scale,
