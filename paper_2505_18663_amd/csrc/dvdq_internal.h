@@ -63,8 +63,12 @@ void set_gemm_grid_limit(int v); // benchmark only; 0 = persistent grids fill th
 int limited_grid(int grid);
 // A slot of tile counters: a word per XCD, each in a 64-byte line of its own.  Atomics on one line are served one after the other,
 // whatever words they name: with the eight in one line the 256 workgroups that start together waited 3200 clocks (median; at
-// most 6000 to 8000) for their first reply, apart 1200 (2100), and 1650 against 760 later on.  (Whole layers: 32760 x 1536 x 4608 packed codes 241 -> 229
-// us, FP6 167 -> 165; 60000 x 512 x 1024 FP6 67.1 -> 63.8.)
+// most 6000 to 8000) for their first reply, apart 1200 (2100), and 1650 against 760 later on.  Time apart over time in one line, launches that
+// draw, K 128 to 6000: two-wave kernels 0.96 in the mean with packed codes, 0.93 with int8, 0.89 with FP6, at most 1.04.
+// The wide kernels keep their eight in one line (words 0 to 7 of the slot).  Replies that come one after the other keep the epilogues of
+// their lone workgroups apart; a line each, they fall into step, and how dear that is differs from card to card: FP6 0.99 in the mean
+// (0.95 to 1.01) on two, on a third up to 1.19 (35129 x 1280 x 2648 102 -> 119 us, 32760 x 1536 x 4608 152 -> 163, 18973 x 1024 x 3216
+// 61.8 -> 69.8, its layer 75.1 -> 85.4).
 constexpr int kSchedStride = 16, kSchedWords = 8 * kSchedStride;
 // the stream's tile-counter slot (nullptr: fixed tile shares): for a GEMM, with whether the kernel enqueued last
 // on the stream zeroes it; for a quantizer, the words to zero, noted as zeroed unless taken back (w4ax_gemm.hip)

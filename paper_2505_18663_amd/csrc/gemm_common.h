@@ -193,7 +193,8 @@ struct TileSource {
     unsigned *ctr;        // this XCD's counter (nullptr: fixed shares)
     unsigned *draw_ctr;   // the same where there is something to draw
 
-    __device__ __forceinline__ TileSource(int tiles_m, int tiles_n, unsigned *sched) {
+    // stride: words between the XCDs' counters
+    __device__ __forceinline__ TileSource(int tiles_m, int tiles_n, unsigned *sched, int stride = kSchedStride) {
         total = tiles_m * tiles_n;
         grid = gridDim.x;   // a multiple of 8
         xcd = blockIdx.x % 8;
@@ -202,7 +203,7 @@ struct TileSource {
         run_len = (unsigned)((int64_t)(xcd + 1) * total / 8) - (unsigned)run_lo;
         wgs = gridDim.x / 8;
         fixed = min(run_len, 2 * wgs);
-        ctr = sched ? sched + xcd * kSchedStride : nullptr;
+        ctr = sched ? sched + xcd * stride : nullptr;
         draw_ctr = run_len > fixed ? ctr : nullptr;
     }
     // the tile a draw's reply stands for (drawn mode), or the workgroup's ordinal-th tile (fixed shares); -1: none left

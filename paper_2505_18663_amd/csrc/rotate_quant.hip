@@ -55,7 +55,8 @@ __global__ __launch_bounds__(1024) void rotate_quant_kernel(
     int8_t *__restrict__ codes, float *__restrict__ x_scale,
     int32_t *__restrict__ code_rowsum,    // NULL, or [M]: sum of the row's codes (for weight zero-points)
     unsigned *__restrict__ clear_words) { // NULL, or the slot of tile counters to zero, for the GEMM that follows on the stream
-    if (clear_words && blockIdx.x == 0 && threadIdx.x < 8) clear_words[threadIdx.x * kSchedStride] = 0u;
+    // (the counters as they lie a line apart, and in one line)
+    if (clear_words && blockIdx.x == 0 && threadIdx.x < 16) clear_words[threadIdx.x < 8 ? threadIdx.x * kSchedStride : threadIdx.x - 8] = 0u;
     extern __shared__ float s_amax[];  // [2][rows_per_wg * waves_per_row], slots alternate per iteration
     // then [2][rows_per_wg * waves_per_row] per-wave code sums, then, 16-byte aligned,
     // [waves][CPW][64] dwords for gathering packed codes (via_lds), or [waves][rows in turn][CPW * 384 + 16] bytes for FP6

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
 
     // ---- tiles: persistent workgroups, per-XCD runs of tile numbers drawn through counters (sched) or dealt
     // in fixed shares (sched == nullptr); numbers travel through an 8-entry ring in LDS.  See w4ax_gemm.hip.
-    const TileSource tiles(tiles_m, tiles_n, sched);
+    const TileSource tiles(tiles_m, tiles_n, sched, 1);   // (counters in one line: see kSchedStride)
     typedef volatile __attribute__((address_space(3))) int lds_int;
     lds_int *s_tiles = (lds_int *)DVDQ_LDS(smem + STAGES * STAGE + 3 * SCALES);
     // Fixed shares (no counters): the ordinal-th tile of this workgroup follows from its number alone, which

@@ -262,3 +262,25 @@ def test_a_released_stream_can_be_used_again():
             assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
             dvdq.release_stream(s)
             dvdq.release_stream(s)   # unknown by now: no-op
+
+
+@pytest.mark.parametrize("fmt,variant", [("int8", 5), ("fp6", 3), ("fp6", 1)])
+@pytest.mark.parametrize("N", [2048, 2056, 2088]) 
+def test_the_layers_quantizer_clears_the_counters_its_gemm_draws_from(fmt, variant, N):
+    """Both kinds: the wide kernels' counters lie in one line, the others' a line apart."""
+    M, K = 4100, 512
+    _draws(fmt, variant, 8, M, N)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N)
+    x = torch.randn((M, K), device=DEV, generator=g).to(torch.bfloat16)
+    packed = torch.randint(0, 256, (N, K // 2), device=DEV, dtype=torch.uint8, generator=g)
+    w, layout, codes = ((dvdq.w4_prepack_fp6(packed), dvdq.W_NATIVE_FP6, dvdq.CODES_FP6) if fmt == "fp6"
+                        else (dvdq.w4_prepack(packed), dvdq.W_NATIVE, dvdq.CODES_INT8))
+    ws = torch.rand((N,), device=DEV, generator=g) + 0.1
+    layer = lambda: dvdq.qlinear(x, w, ws, 256, 4, layout, codes_format=codes)[0]
+    dvdq.bench_set_gemm_schedule(0)
+    ref = layer()
+    dvdq.bench_set_gemm_schedule(-1)
+    for value in (1, 0xFFFFFFFF):
+        dvdq.bench_fill_tile_counters(value)
+        assert torch.equal(layer().view(torch.int16), ref.view(torch.int16))
