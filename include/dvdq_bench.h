@@ -46,7 +46,8 @@ int dvdq_bench_mfma_fp6(int iters, int data, int32_t *sink, double *ops_out, voi
 int dvdq_bench_set_gemm_variant(int variant);
 
 /* The tile variant the library takes by itself for a product (numbers as above; host only, no GPU needed).  `vectors`:
- * how many there are of bias and zero-points.  Sizes below 1: minus a dvdq_status code. */
+ * how many there are of bias and zero-points.  After dvdq_bench_set_gemm_schedule(0): what a launch under stream capture takes.
+ * Sizes below 1: minus a dvdq_status code. */
 int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors);
 
 /* How dvdq_qlinear runs a layer with its arguments at these addresses (host only: nothing is read there): 0 = as two launches,

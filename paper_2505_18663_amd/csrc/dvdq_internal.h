@@ -35,9 +35,11 @@ int launch_w4ax_gemm_wide(const uint8_t *codes, const float *x_scale, const uint
 int small_gemm_shape(int64_t M, int64_t N, int64_t K, bool fp6);
 constexpr int kSmallVariants = 7, kFirstSmallVariant = 10;   // tile variant 10 + shape stands for a shape
 constexpr int kCanonicalVariant = 16;                        // canonical weights beyond the small outputs (w4ax_gemm.hip)
-// the tile variants that the launchers take by themselves
-int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout);
-int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors);
+// the tile variants that the launchers take by themselves, where tiles are drawn from counters and where they are fixed shares
+int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, bool drawn);
+int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors, bool drawn);
+bool tiles_drawn(hipStream_t stream);   // false: the stream is being captured
+bool drawing_enabled();                 // the benchmark hook
 // whether the large kernels store their tiles as whole lines, with 32-bit offsets
 constexpr int64_t kMaxTileN = (int64_t)1 << 22;
 inline bool whole_line_tiles(int64_t N) { return (N & 7) == 0 && N < kMaxTileN; }

@@ -389,7 +389,8 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
 // 32760 x 4608 output, variants 1 and 3: 81.0 and 78.8 us at K = 512, 96.3 and 92.1 at 768, 115 and 106 at 1024, 136 and 121
 // at 1280; 8192 x 4608: 29.6 and 29.0, 33.2 and 31.8, 38.0 and 35.8, 43.4 and 39.6; with zero-points it is level or behind up
 // to 640: 60000 x 3072 119 and 128 at 512).  Later where its last round of tiles, one per compute unit, is at most half full:
-// variant 1's tiles are half as large, so it ends half a round earlier.  Time of variant 3 over that of variant 1 (bias and zero-points,
+// variant 1's tiles are half as large, so it ends half a round earlier, if the rest is spread over the chip (drawn tiles; fixed shares,
+// see w4ax_gemm_choice, from two rounds on: 1.00 to 1.13 of variant 3's time at 6 to 11 slices).  Drawn: time of variant 3 over that of variant 1 (bias and zero-points,
 // 1536 to 3072 channels) by the number of 256 x 256 tiles, at 6 / 8 / 12 / 16 / 24 slices: 96 to 128 tiles 1.19 / 1.16 / 1.10 / 1.05 / 0.89;
 // 264 to 384 1.16 / 1.12 / 1.02 / 0.96 / 0.89; 516 to 640 1.12 / 1.08 / 1.03 / 0.98 / 0.91; 1098 to 1400 1.10 / 1.10 / 1.02; 2172 1.08 / 1.05 /
 // 0.99; more than half full 144 to 240 0.98 / 0.95 / 0.94, 432 to 512 0.97 / 0.95 / 0.91, 672 to 768 1.0 / 0.97 / 0.93.  (6240 x 768 x 1024, 100
@@ -400,12 +401,12 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
 // and the wide kernel, with no second workgroup to hide that, lost up to 74 %.  By today's times it would pay from about 16 slices on
 // whatever the vectors (variants 1 and 3, 8192 x 3074: 40.2 and 44.1 us at K = 1280, 65.0 and 61.7 at 3072, 109 and 94.8 at 6144, with both
 // vectors 70.1 and 65.8 at 3072; 32760 x 4612: 197 and 187 at 1280, 1344 and 1006 at 13824).
-int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors) {
+int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors, bool drawn) {
     const int shape = small_gemm_shape(M, N, K, true);
     if (shape >= 0) return kFirstSmallVariant + shape;
     if (whole_line_tiles(N)) {
         const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
-        const bool half_empty = last != 0 && last <= 128 && tiles < 4096;
+        const bool half_empty = last != 0 && last <= 128 && tiles < (drawn ? 4096 : 512);
         return K / kBK >= (!half_empty ? 6 : tiles <= 128 ? 18 : 12) ? 3 : 1;
     }
     return vectors < 2 && K / kBK >= (vectors ? 96 : 48) ? 3 : 1;
@@ -421,8 +422,11 @@ int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8
     //   3: the wide kernel of w4ax_gemm_wide.hip: one 4-wave workgroup, 256 x 256 tiles, 128 x 128 wave tiles with
     //      the accumulators in AGPRs: a third fewer LDS fragment bytes per MFMA, but a larger fixed cost per tile.
     int v = gemm_variant();
-    if (v != 1 && v != 3 && (v < kFirstSmallVariant || v >= kFirstSmallVariant + kSmallVariants))
-        v = w4a4_fp6_gemm_choice(M, N, K, (bias != nullptr) + (w_zero != nullptr));
+    if (v != 1 && v != 3 && (v < kFirstSmallVariant || v >= kFirstSmallVariant + kSmallVariants)) {
+        const int vectors = (bias != nullptr) + (w_zero != nullptr), fixed = w4a4_fp6_gemm_choice(M, N, K, vectors, false);
+        v = w4a4_fp6_gemm_choice(M, N, K, vectors, true);
+        if (fixed != v && !tiles_drawn(stream)) v = fixed;
+    }
     if (v >= kFirstSmallVariant)
         return launch_w4ax_gemm_small(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, DVDQ_CODES_FP6,
                                       DVDQ_W_NATIVE_FP6, v - kFirstSmallVariant, y, acc_out, stream);

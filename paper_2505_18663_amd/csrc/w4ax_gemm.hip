@@ -517,17 +517,23 @@ static bool find_base(SchedTable &t) {
     return true;
 }
 
+bool drawing_enabled() { return g_schedule.load(std::memory_order_relaxed) != 0; }
+
+bool tiles_drawn(hipStream_t stream) {
+    if (!drawing_enabled()) return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cap == hipStreamCaptureStatusNone;
+}
+
 // The counter slot of `stream`, or nullptr (fixed shares): when the stream is being captured into a graph
 // -- the same node may later run in several graph instances at once, which must not share counters -- or
 // when all slots are taken.  *index: the slot's number.
 static unsigned *slot_of_stream(hipStream_t stream, int *dev_out, int *index) {
-    if (g_schedule.load(std::memory_order_relaxed) == 0) return nullptr;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    if (cap != hipStreamCaptureStatusNone) return nullptr;
+    if (!tiles_drawn(stream)) return nullptr;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
     SchedTable &t = g_sched_table[dev];
@@ -684,12 +690,15 @@ int limited_grid(int grid) {
 //     them, a tile takes several times as long with no second workgroup to multiply meanwhile (before variant 2 had them the
 //     wide kernel was already 4-24 % slower at K = 1536 .. 6144, with bias and zero-points 20-53 %);
 //   - unless its last round of tiles, one per compute unit, is at most half full: variant 2's tiles are half as large, so it ends
-//     half a round earlier.  Time of variant 5 over that of variant 2 (bias and zero-points, 1536 to 3072 channels, 12 to 60 slices) by the
+//     half a round earlier, if the rest is spread over the chip, as drawn tiles are.  Fixed shares (a stream under capture) deal it to the
+//     first XCDs, compute units with two tiles each beyond the first 16 tiles (32 of variant 2's): variant 2 has 0.84 to 0.95 of variant 5's time
+//     there below two rounds and, from two to five, at 16 and fewer (14897 x 1536 x 2200, 531 tiles: 69.1 and 78.3 us), else 1.00 to 1.09 up to
+//     fifteen rounds (41486 x 4480 x 1704, 1141 tiles: 325 and 306).  Drawn: time of variant 5 over that of variant 2 (bias and zero-points, 1536 to 3072 channels, 12 to 60 slices) by the
 //     number of 256 x 256 tiles: 1.11-1.15 at 264 to 384 (15600 x 1536 x 1536, 366 tiles: 48.3 and 43.0 us), 0.94-0.97 at 432 to 512,
 //     1.08-1.12 at 516 to 640, 0.95-0.99 at 672 to 768, 1.04-1.10 at 1026 to 1400, 1.02-1.07 at 2064 to 2172, 1.01-1.05 at 3100 to 3200.
 //     One column of tiles: 1.02 to 1.14 up to two fifths of a round; the line stays there, and below four rounds, as
 //     tests/test_dispatch.py states it.
-int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout) {
+int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, bool drawn) {
     const int shape = small_gemm_shape(M, N, K, false);
     if (w_layout == DVDQ_W_CANONICAL) return shape < 0 ? kCanonicalVariant : kFirstSmallVariant + shape;
     if (shape >= 0) return kFirstSmallVariant + shape;
@@ -697,7 +706,8 @@ int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_la
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
     if (K / 128 < 12) return tiles < 512 && last > 128 ? 5 : 2;
     if (N <= 256) return tiles > 256 && tiles < 1024 && last != 0 && 5 * last < 2 * 256 ? 2 : 5;
-    return tiles < 4096 && last != 0 && last <= 128 ? 2 : 5;
+    const int64_t most = drawn ? (tiles < 4096 ? 128 : 0) : tiles < 512 ? 128 : tiles < 1536 ? 16 : 0;
+    return last != 0 && last <= most ? 2 : 5;
 }
 
 int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale,
@@ -705,7 +715,7 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
                      int64_t K, int codes_format, int w_layout, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
     if (w_layout == DVDQ_W_CANONICAL) {
         if (codes_format != DVDQ_CODES_INT8 || w_zero) return DVDQ_ERR_UNSUPPORTED;
-        const int f = gemm_variant(), v = f >= kFirstSmallVariant ? f : w4ax_gemm_choice(M, N, K, codes_format, w_layout);
+        const int f = gemm_variant(), v = f >= kFirstSmallVariant ? f : w4ax_gemm_choice(M, N, K, codes_format, w_layout, true);
         if (v != kCanonicalVariant)
             return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, nullptr, nullptr, bias, M, N,
                                           K, codes_format, w_layout, v - kFirstSmallVariant, y, acc_out, stream);
@@ -730,7 +740,12 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     // fewer K slices than a variant's ring needs falls back to variant 2, which always qualifies.
     const bool unaligned = unaligned_tiles(N) && !acc_out;
     const int forced = gemm_variant();
-    int v = forced < 0 ? w4ax_gemm_choice(M, N, K, codes_format, w_layout) : forced;
+    int v = forced;
+    if (forced < 0) {
+        v = w4ax_gemm_choice(M, N, K, codes_format, w_layout, true);
+        const int fixed = w4ax_gemm_choice(M, N, K, codes_format, w_layout, false);
+        if (fixed != v && !tiles_drawn(stream)) v = fixed;
+    }
     if (v >= kFirstSmallVariant)
         return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, w_zero, code_rowsum,
                                       bias, M, N, K, codes_format, w_layout, v - kFirstSmallVariant, y, acc_out, stream);

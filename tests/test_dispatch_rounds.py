@@ -26,3 +26,22 @@ def test_int8_of_few_slices():
 @pytest.mark.parametrize("tiles,slices", [(100, 18), (128, 18), (130, 6), (256, 6), (258, 12), (384, 12), (386, 6), (514, 12), (3968, 12), (4100, 6)])
 def test_fp6(tiles, slices):
     assert choice(tiles, slices, True) == 3 and choice(tiles, slices - 1, True) == 1
+
+
+@pytest.fixture
+def fixed_shares():
+    """as under stream capture, where the tiles of a launch are fixed shares"""
+    dvdq.bench_set_gemm_schedule(0)
+    yield
+    dvdq.bench_set_gemm_schedule(-1)
+
+
+@pytest.mark.parametrize("tiles,variant", [(256, 5), (258, 2), (384, 2), (386, 5), (512, 5), (514, 2), (528, 2), (530, 5), (640, 5), (1026, 2),
+                                           (1296, 2), (1538, 5), (4098, 5)])
+def test_int8_with_fixed_shares(fixed_shares, tiles, variant):
+    """The rest of a later round is not spread over the chip: half a round is gained below two rounds, then for 16 tiles at most."""
+    assert choice(tiles, 12, False) == choice(tiles, 108, False) == variant
+
+
+def test_fp6_with_fixed_shares(fixed_shares):
+    assert [choice(t, 6, True) for t in (128, 258, 384, 514, 640, 1026, 3968)] == [1, 1, 1, 3, 3, 3, 3]
