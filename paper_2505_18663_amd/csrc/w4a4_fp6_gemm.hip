@@ -390,11 +390,19 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
 // at 1280; 8192 x 4608: 29.6 and 29.0, 33.2 and 31.8, 38.0 and 35.8, 43.4 and 39.6; with zero-points it is level or behind up
 // to 640: 60000 x 3072 119 and 128 at 512).  Later where its last round of tiles, one per compute unit, is at most half full:
 // variant 1's tiles are half as large, so it ends half a round earlier, if the rest is spread over the chip (drawn tiles; fixed shares,
-// see w4ax_gemm_choice, from two rounds on: 1.00 to 1.13 of variant 3's time at 6 to 11 slices).  Drawn: time of variant 3 over that of variant 1 (bias and zero-points,
-// 1536 to 3072 channels) by the number of 256 x 256 tiles, at 6 / 8 / 12 / 16 / 24 slices: 96 to 128 tiles 1.19 / 1.16 / 1.10 / 1.05 / 0.89;
-// 264 to 384 1.16 / 1.12 / 1.02 / 0.96 / 0.89; 516 to 640 1.12 / 1.08 / 1.03 / 0.98 / 0.91; 1098 to 1400 1.10 / 1.10 / 1.02; 2172 1.08 / 1.05 /
-// 0.99; more than half full 144 to 240 0.98 / 0.95 / 0.94, 432 to 512 0.97 / 0.95 / 0.91, 672 to 768 1.0 / 0.97 / 0.93.  (6240 x 768 x 1024, 100
-// tiles: 13.7 and 11.5 us; 9000 x 768 x 2000, 288: 30.0 and 25.0.)  (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind
+// see w4ax_gemm_choice, from two rounds on: 1.00 to 1.13 of variant 3's time at 6 to 11 slices).  What that is worth differs by the epilogue,
+// the part of a tile that nothing hides in variant 3.  Drawn, time of variant 1 over that of variant 3 in the mean (and at most) by the number
+// of 256 x 256 tiles, at 6-7 / 8-9 / 10-11 / 12-13 / 14-15 slices:
+//   92 to 128    no vectors 0.93 (0.97) / 0.95 (0.98) / 0.99 (1.05) / 1.07 (1.15) / 1.06 (1.20); one 0.88 (0.92) / 0.92 (1.07) / 0.96 (1.10) /
+//                0.98 (1.15) / 1.02 (1.14); both 0.85 / 0.88 / 0.94 (1.05) / 0.96 (1.08) / 1.00 (1.09)
+//   257 to 384   none 0.97 (0.99) / 1.02 (1.05) / 1.05 / 1.08 / 1.11; one 0.94 (0.96) / 1.00 (1.02) / 1.01 (1.07) / 1.07 / 1.08; both 0.91 / 0.93 (0.97) /
+//                0.97 (1.00) / 1.02 (1.05) / 1.05
+//   513 to 1408  none 0.95 (0.97) / 0.99 (1.05) / 1.02 (1.06) / 1.04 / 1.02; one 0.94 (1.01) / 0.97 (1.02) / 0.98 (1.03) / 1.01 (1.08) / 1.03; both 0.90 / 0.94
+//                (0.99) / 0.96 (1.00) / 0.97 (1.02) / 0.99 (1.06)
+//                (cached stores, N no multiple of 32, 0.93 at 6 to 11 slices whatever the vectors, at most 1.03)
+//   from 1537    6 to 9 slices 0.99 to 1.07, later up to 1.18
+// (6240 x 768 x 1024, 100 tiles: 11.5 and 13.7 us; 2816 x 2176 x 2560 without vectors, 110: 19.1 and 16.3.)  More than half full: 1.00 to 1.03
+// at 6 slices, 1.06 to 1.10 at 12.  (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind
 // one of these at nearly every K from 256 to 640, 3 % ahead at best in the mean of a shape.)
 // Outputs with N no multiple of 8, in 16-byte pieces at even addresses, take it from 48 slices on without bias and zero-points,
 // from 96 with one of them, never with both: the lines that tests/test_dispatch.py states, from when such tiles were stored per element
@@ -406,8 +414,9 @@ int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors, bool draw
     if (shape >= 0) return kFirstSmallVariant + shape;
     if (whole_line_tiles(N)) {
         const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
-        const bool half_empty = last != 0 && last <= 128 && tiles < (drawn ? 4096 : 512);
-        return K / kBK >= (!half_empty ? 6 : tiles <= 128 ? 18 : 12) ? 3 : 1;
+        const bool half_empty = last != 0 && last <= 128 && tiles < (drawn ? 1536 : 512);
+        const int from = !half_empty ? 6 : tiles <= 128 ? (vectors ? 12 : 10) : tiles > 512 && !streaming_pitch(N) ? 12 : 8 + 2 * vectors;
+        return K / kBK >= from ? 3 : 1;
     }
     return vectors < 2 && K / kBK >= (vectors ? 96 : 48) ? 3 : 1;
 }

@@ -5,11 +5,11 @@ import pytest
 import paper_2505_18663_amd as dvdq
 
 
-def choice(tiles, slices, fp6):
+def choice(tiles, slices, fp6, vectors=0):
     """of an output of `tiles` tiles in two columns (or four, for an odd half)"""
     cols = 2
     fmt, layout = (dvdq.CODES_FP6, dvdq.W_NATIVE_FP6) if fp6 else (dvdq.CODES_INT8, dvdq.W_NATIVE)
-    return dvdq.bench_gemm_choice(256 * (tiles // cols), 256 * cols, 128 * slices, fmt, layout)
+    return dvdq.bench_gemm_choice(256 * (tiles // cols), 256 * cols, 128 * slices, fmt, layout, vectors)
 
 
 @pytest.mark.parametrize("tiles,variant", [(256, 5), (258, 2), (384, 2), (386, 5), (512, 5), (514, 2), (640, 2), (642, 5), (1024, 5), (1026, 2),
@@ -23,9 +23,19 @@ def test_int8_of_few_slices():
     assert [choice(t, 8, False) for t in (256, 384, 386, 510, 512, 770)] == [2, 2, 5, 5, 2, 2]
 
 
-@pytest.mark.parametrize("tiles,slices", [(100, 18), (128, 18), (130, 6), (256, 6), (258, 12), (384, 12), (386, 6), (514, 12), (3968, 12), (4100, 6)])
+@pytest.mark.parametrize("tiles,slices", [(100, (10, 12, 12)), (128, (10, 12, 12)), (130, (6, 6, 6)), (256, (6, 6, 6)), (258, (8, 10, 12)),
+                                          (384, (8, 10, 12)), (386, (6, 6, 6)), (514, (8, 10, 12)), (1408, (8, 10, 12)), (1538, (6, 6, 6)), (3968, (6, 6, 6))])
 def test_fp6(tiles, slices):
-    assert choice(tiles, slices, True) == 3 and choice(tiles, slices - 1, True) == 1
+    """The first depth, in slices, at which the wide kernel is taken, by the number of vectors (bias, zero-points)."""
+    for vectors, s in enumerate(slices):
+        assert choice(tiles, s, True, vectors) == 3 and choice(tiles, s - 1, True, vectors) == 1
+
+
+def test_fp6_with_cached_stores():
+    """N no multiple of 32, more than two rounds of tiles: 12 slices whatever the vectors."""
+    fp6 = lambda m, slices, v: dvdq.bench_gemm_choice(256 * m, 264, 128 * slices, dvdq.CODES_FP6, dvdq.W_NATIVE_FP6, v)
+    assert [[fp6(260, s, v) for s in (11, 12)] for v in range(3)] == [[1, 3]] * 3
+    assert [[fp6(130, s, v) for s in (7, 8, 9, 10)] for v in range(2)] == [[1, 3, 3, 3], [1, 1, 1, 3]]
 
 
 @pytest.fixture
