@@ -41,7 +41,7 @@ int dvdq_bench_mfma_fp6(int iters, int data, int32_t *sink, double *ops_out, voi
  * (INT8 matrix path: 1..5, see the dispatch tables in w4ax_gemm.hip, one per code container; shapes too
  * shallow in K for a variant's ring fall back to variant 2.  FP6 matrix path: 1 and 3, see w4a4_fp6_gemm.hip,
  * other values mean its own choice; either path: 10..16 force a shape of the small-output kernel, see
- * w4ax_gemm_small.hip); -1 restores the library's own choice.  Process-wide (an atomic
+ * w4ax_gemm_small.hip; canonical weights: 10..15 and 17 do, 16 is the two-wave kernel); -1 restores the library's own choice.  Process-wide (an atomic
  * that every launch reads once), meant for benchmarking only. */
 int dvdq_bench_set_gemm_variant(int variant);
 

@@ -34,7 +34,8 @@ int launch_w4ax_gemm_wide(const uint8_t *codes, const float *x_scale, const uint
 // (w4ax_gemm_small.hip).  small_gemm_shape: the shape of tile and waves for a size, or -1 (not a small output)
 int small_gemm_shape(int64_t M, int64_t N, int64_t K, bool fp6);
 constexpr int kSmallVariants = 7, kFirstSmallVariant = 10;   // tile variant 10 + shape stands for a shape
-constexpr int kCanonicalVariant = 16;                        // canonical weights beyond the small outputs (w4ax_gemm.hip)
+// canonical weights beyond the small outputs (w4ax_gemm.hip): the two-wave kernel; the small kernel's shape 6
+constexpr int kCanonicalVariant = 16, kCanonicalShape6Variant = 17;
 // the tile variants that the launchers take by themselves, where tiles are drawn from counters and where they are fixed shares
 int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, bool drawn);
 int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors, bool drawn);

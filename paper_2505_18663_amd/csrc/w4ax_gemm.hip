@@ -682,7 +682,7 @@ int limited_grid(int grid) {
 }
 
 // The tile variant for a size (variants 2 and 5 below; 10 + shape: the small-output kernel; kCanonicalVariant: the two-wave kernel
-// with canonical weights).
+// with canonical weights, kCanonicalShape6Variant: the small-output kernel beyond its outputs, a wave per 64 x 128 tile).
 // Variant 5 is the wide kernel of w4ax_gemm_wide.hip (int8 codes only), taken
 //   - from 12 K slices on (from 8 where its one or two rounds of tiles end more than half full: 0.93-0.98 of variant 2's time there at
 //     8 to 11 slices, 1536 and 2048 channels, 144 to 500 tiles);
@@ -700,7 +700,11 @@ int limited_grid(int grid) {
 //     tests/test_dispatch.py states it.
 int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, bool drawn) {
     const int shape = small_gemm_shape(M, N, K, false);
-    if (w_layout == DVDQ_W_CANONICAL) return shape < 0 ? kCanonicalVariant : kFirstSmallVariant + shape;
+    if (w_layout == DVDQ_W_CANONICAL && shape < 0) {
+        // a second round of the two-wave kernel's tiles where the waves, eight per compute unit, take one
+        const bool one_round = ((M + 63) / 64) * ((N + 127) / 128) <= 2048;
+        return one_round && ((M + 127) / 128) * ((N + 255) / 256) > 512 ? kCanonicalShape6Variant : kCanonicalVariant;
+    }
     if (shape >= 0) return kFirstSmallVariant + shape;
     if (codes_format != DVDQ_CODES_INT8 || K / 128 < 8 || !whole_line_tiles(N)) return 2;
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
@@ -717,12 +721,14 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
         if (codes_format != DVDQ_CODES_INT8 || w_zero) return DVDQ_ERR_UNSUPPORTED;
         const int f = gemm_variant(), v = f >= kFirstSmallVariant ? f : w4ax_gemm_choice(M, N, K, codes_format, w_layout, true);
         if (v != kCanonicalVariant)
-            return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, nullptr, nullptr, bias, M, N,
-                                          K, codes_format, w_layout, v - kFirstSmallVariant, y, acc_out, stream);
+            return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, nullptr, nullptr, bias, M, N, K,
+                                          codes_format, w_layout, v == kCanonicalShape6Variant ? 6 : v - kFirstSmallVariant, y, acc_out, stream);
         // Variant 2 with the weights as they come.  A slice of a weight row is 64 bytes, half a cache line, so twice the weight bytes
         // leave the L2, but once per 256 channels x 128 tokens: a wave per 64 x 128 tile, its operands for itself, was bound by
         // that traffic.  Before -> now: 7800 x 1440 x 1440 40.1 -> 27.8 us, 32760 x 1536 x 4608 342 -> 247 (1.9 POP/s), 32760 x 13824 x 5120
-        // 2708 -> 1993, 27510 x 11552 x 7296 3282 -> 2266, 32760 x 1440 x 1441 170 -> 92; 23080 x 288 x 528 (543 tiles) 19.8 and 20.5.
+        // 2708 -> 1993, 27510 x 11552 x 7296 3282 -> 2266, 32760 x 1440 x 1441 170 -> 92.  The waves keep what they take in one round
+        // (eight per compute unit, 2048) and variant 2 in two: a wave per tile 0.81 to 0.98 of its time there (22528 x 96 x 592 15.1 and 12.2 us,
+        // 5910 x 160 x 2680 18.5 and 15.6, 16734 x 1120 x 792 36.0 and 33.1), from 2050 waves on 1.01 to 1.4 (12021 x 64 x 1328 15.7 and 15.9).
         if (unaligned_tiles(N) && !acc_out)
             return launch_native<128, 256, 128, 2, 2, 2, 2, OPS_CANONICAL, STORE_UNALIGNED>(
                 codes, x_scale, w, w_scale, nullptr, nullptr, bias, (int)M, (int)N, (int)K, y, acc_out, stream);

@@ -635,9 +635,7 @@ int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uin
         case 3: return launch_tile<FMT, 2, 2, 4>(DVDQ_SMALL_ARGS); \
         case 4: return launch_tile<FMT, 2, 2, 2>(DVDQ_SMALL_ARGS); \
         case 5: return launch_tile<FMT, 2, 4, 2>(DVDQ_SMALL_ARGS); \
-        case 6: /* (sweeps only; canonical weights: w4ax_gemm.hip) */          \
-            if constexpr (FMT != FMT_CANONICAL) return launch_tile<FMT, 2, 4, 1>(DVDQ_SMALL_ARGS); \
-            else return DVDQ_ERR_UNSUPPORTED;                                  \
+        case 6: return launch_tile<FMT, 2, 4, 1>(DVDQ_SMALL_ARGS); /* (sweeps, and canonical weights: w4ax_gemm_choice) */ \
         default: return DVDQ_ERR_UNSUPPORTED;                                  \
     }
     if (codes_format == DVDQ_CODES_FP6) DVDQ_SMALL(FMT_FP6)

@@ -55,3 +55,11 @@ def test_int8_with_fixed_shares(fixed_shares, tiles, variant):
 
 def test_fp6_with_fixed_shares(fixed_shares):
     assert [choice(t, 6, True) for t in (128, 258, 384, 514, 640, 1026, 3968)] == [1, 1, 1, 3, 3, 3, 3]
+
+
+@pytest.mark.parametrize("M,N,variant", [(22528, 592, 17), (32768, 520, 16), (65536, 256, 16), (65600, 128, 17), (130944, 128, 17), (131200, 128, 16),
+                                         (33024, 512, 16), (21760, 640, 16), (21888, 640, 17), (26112, 640, 17), (26240, 640, 16), (23080, 528, 17)])
+def test_canonical_weights_beyond_the_small_outputs(M, N, variant):
+    """17: more than 512 tiles of 128 x 256, at most 2048 of 64 x 128."""
+    for K in (32, 1440):
+        assert dvdq.bench_gemm_choice(M, N, K, dvdq.CODES_INT8, dvdq.W_CANONICAL) == variant
