@@ -50,6 +50,10 @@ int dvdq_bench_set_gemm_variant(int variant);
  * Sizes below 1: minus a dvdq_status code. */
 int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors);
 
+/* Threads per workgroup with which dvdq_bgr_quantize takes the rows: 256, 512 or 1024 (host only).  Sizes below 1 (2 weights, 0
+ * rounds): minus a dvdq_status code. */
+int dvdq_bench_bgr_choice(int64_t N, int64_t K, int n_steps, int max_refine);
+
 /* How dvdq_qlinear runs a layer with its arguments at these addresses (host only: nothing is read there): 0 = as two launches,
  * 1 or 2 = as one, with tiles of 32 or 64 channels.  Sizes below 1: minus a dvdq_status code. */
 int dvdq_bench_qlinear_choice(const void *x_bf16, const void *y_bf16, const void *workspace, size_t workspace_bytes, int64_t M,

@@ -595,27 +595,38 @@ int launch(const float *w, int64_t N, int K, int cells, int n_steps, int max_ref
 
 }  // namespace
 
+// Threads per workgroup for N rows of K weights: 256 (short rows), 512 or 1024.
+// Bound by the issue of instructions, most of them fp64, of which a start's own (the same in all its lanes) weigh less the fewer lanes
+// take it: rows short enough go as workgroups of 256 threads, four lanes a start, three to four at a time on a compute unit and not
+// held in registers (100 steps, 10 rounds; as workgroups of 512 with eight lanes a start -> now: 13824 rows of 256 763 -> 504 us, 8960 of
+// 1536 539 -> 369, 3000 of 4096 212 -> 161, 520 of 6144 63.5 -> 58.9).  Longer ones leave no room for a third beside two (780 rows of 6656:
+// level).  Beyond 5376 weights three instead of four are resident, and the sorting, in which fewer threads take longer, needs many starts to
+// outweigh: time over that of 512 threads at 4 to 50 steps up to 1.10 (1019 rows of 5604, 20 steps, 66.8 -> 73.6 us; up to 5376 weights at
+// most 0.96), at 100 and more 0.76 to 1.00.
+// With at most two rows per compute unit the time is one row's own, and the same holds for shorter rows, a start's rounds being shorter
+// with eight lanes: at 3 to 20 steps 0.92 to 1.33 (454 rows of 2798, 10 steps, 16.5 -> 18.0 us; 413 of 4318, 6 steps, 32.8 -> 40.4), at 50 and
+// 64 up to 1.17 (the starts, 24 and 31, still fill few waves), at 80 0.89 to 1.00 up to 2048 weights and 0.96 to 1.02 beyond, at 100 and more
+// 0.80 to 0.96 with three rounds and 0.85 to 1.03 with fewer.
+// 512 threads, two rows at a time per compute unit, while their LDS allows (half of 160 KB each; longer rows with coarser prefix sums
+// and cells): 0.145 ms against 0.20 as workgroups of 1024 for 1536 rows of 8960.  1024 where there is no second row to put
+// beside it: with no more rows than compute units (32 rows of 8960: level at 100 steps, 46.7 us against 50.8 at 200;
+// 200 rows of 13824: 41.7 against 46.0), and from 14 K weights on.
+int bgr_choice(int64_t N, int64_t K, int n_steps, int max_refine) {
+    if (N > 512 ? K <= 5376 || (K <= 6144 && n_steps >= 100)
+                : N > 256 && (K <= 2048 ? n_steps >= 80 : K <= 4608 && n_steps >= 100 && max_refine >= 3))
+        return 256;
+    return N > 256 && K <= 14336 ? 512 : 1024;
+}
+
 int launch_bgr(const float *w, int64_t N, int64_t K, int n_steps, int max_refine, double eps, int search,
                uint8_t *w_packed, float *w_scale, int8_t *w_zero, double *row_error, hipStream_t stream) {
 #define DVDQ_BGR_ARGS(CELLS) \
     w, N, (int)K, CELLS, n_steps, max_refine, eps, search, w_packed, w_scale, w_zero, row_error, stream
-    // A few weights per cell: 1024 .. 4096 cells.  Bound by the issue of instructions, most of them fp64, of which a start's
-    // own (the same in all its lanes) weigh less the fewer lanes take it: rows short enough go as workgroups of 256 threads, four
-    // lanes a start, three to four at a time on a compute unit and not held in registers (100 steps, 10 rounds; as workgroups of 512
-    // with eight lanes a start -> now: 13824 rows of 256 763 -> 504 us, 8960 of 1536 539 -> 369, 3000 of 4096 212 -> 161, 520 of 6144 63.5 ->
-    // 58.9).  Longer ones leave no room for a third beside two (780 rows of 6656: level); with at most two rows per
-    // compute unit the time is one row's own, in which more threads sort (400 rows of 5120: level, of 6144 44.9 and 46.8).
-    if (N > 256 && K <= (N > 512 ? 6144 : 4608)) return launch<256, 4, 0, 4>(DVDQ_BGR_ARGS(2048));
-    // Two rows at a time per compute unit, as workgroups of 512 threads,
-    // while their LDS allows (half of 160 KB each; longer rows with coarser prefix sums and cells): 0.145 ms against 0.20
-    // as workgroups of 1024 for 1536 rows of 8960.  A workgroup of 1024 threads where there is no second row to put
-    // beside it: with no more rows than compute units (32 rows of 8960: level at 100 steps, 46.7 us against 50.8 at 200;
-    // 200 rows of 13824: 41.7 against 46.0), and from 14 K weights on.
-    const int cells = K <= 2048 ? 1024 : (K <= 4096 ? 2048 : 4096);
-    if (K > 16384) return launch<1024, 16, 0, 8>(DVDQ_BGR_ARGS(2048));
-    if (N > 256 && K <= 10240) return launch<512, 4, 10, 8>(DVDQ_BGR_ARGS(cells));
-    if (N > 256 && K <= 14336) return launch<512, 8, 14, 8>(DVDQ_BGR_ARGS(2048));
-    return launch<1024, 4, 8, 8>(DVDQ_BGR_ARGS(cells));
+    // (a few weights per cell: 1024 .. 4096 cells)
+    const int threads = bgr_choice(N, K, n_steps, max_refine), cells = K <= 2048 ? 1024 : (K <= 4096 ? 2048 : 4096);
+    if (threads == 256) return launch<256, 4, 0, 4>(DVDQ_BGR_ARGS(2048));
+    if (threads == 512) return K <= 10240 ? launch<512, 4, 10, 8>(DVDQ_BGR_ARGS(cells)) : launch<512, 8, 14, 8>(DVDQ_BGR_ARGS(2048));
+    return K > 16384 ? launch<1024, 16, 0, 8>(DVDQ_BGR_ARGS(2048)) : launch<1024, 4, 8, 8>(DVDQ_BGR_ARGS(cells));
 #undef DVDQ_BGR_ARGS
 }
 

@@ -63,3 +63,16 @@ def test_canonical_weights_beyond_the_small_outputs(M, N, variant):
     """17: more than 512 tiles of 128 x 256, at most 2048 of 64 x 128."""
     for K in (32, 1440):
         assert dvdq.bench_gemm_choice(M, N, K, dvdq.CODES_INT8, dvdq.W_CANONICAL) == variant
+
+
+@pytest.mark.parametrize("K,n_steps,max_refine,threads", [(256, 50, 10, 512), (256, 80, 0, 256), (2048, 80, 0, 256), (2050, 80, 10, 512), (2050, 100, 3, 256),
+                                                          (2050, 100, 2, 512), (4608, 100, 10, 256), (4610, 100, 10, 512), (4096, 20, 10, 512)])
+def test_offline_quantizer_with_at_most_two_rows_per_compute_unit(K, n_steps, max_refine, threads):
+    """The time is one row's own: workgroups of 256 threads only with starts enough to outweigh their sorting."""
+    assert dvdq.bench_bgr_choice(257, K, n_steps, max_refine) == dvdq.bench_bgr_choice(512, K, n_steps, max_refine) == threads
+
+
+def test_offline_quantizer_with_more_rows():
+    assert [dvdq.bench_bgr_choice(513, K, s, 0) for K, s in ((5376, 3), (5378, 99), (5378, 100), (6144, 100), (6146, 100), (14336, 100), (14338, 100))] == [
+        256, 512, 256, 256, 512, 512, 1024]
+    assert dvdq.bench_bgr_choice(256, 256, 100, 10) == 1024
