@@ -41,20 +41,34 @@ def _check(fmt, M, K, N, had_block, bits, zero, bias, x=None):
     assert bool((workspace[-256:] == 0x5A).all())
 
 
-# one token, a full and a part tile of 32 tokens, rows of one unit to many, units that do not divide among the waves, both tile
-# widths, odd channel counts
+# one token, a full and a part tile of 32 tokens, rows of one unit to many, units that do not divide among the waves, odd channel
+# counts; tiles of 32 and 64 channels (width 1 and 2) with 1, 2, 4 and 8 units a wave each
 @pytest.mark.parametrize("fmt", list(FORMATS))
-@pytest.mark.parametrize("M,K,N,had_block", [(1, 128, 8, 128), (1, 32768, 33, 512), (2, 1536, 9216, 256), (5, 6144, 1161, 32), (32, 1024, 64, 64),
-                                             (33, 640, 255, 128), (128, 256, 256, 256), (300, 512, 96, 512), (8000, 384, 32, 1),
-                                             (21, 1408, 5000, 8)])
-def test_equals_two_calls(fmt, M, K, N, had_block):
+@pytest.mark.parametrize("M,K,N,had_block,width,units", [
+    (1, 128, 8, 128, 1, 1), (12, 512, 264, 256, 1, 2), (9, 896, 1161, 128, 1, 4), (128, 256, 256, 256, 1, 4), (300, 512, 96, 512, 1, 4),
+    (8000, 384, 32, 1, 1, 4), (1, 32768, 33, 512, 1, 8), (5, 6144, 1161, 32, 1, 8),
+    (2, 1536, 9216, 256, 2, 1), (12, 512, 9216, 64, 2, 2), (3, 2432, 9001, 128, 2, 2), (32, 512, 9216, 512, 2, 4), (41, 384, 6000, 8, 2, 4),
+    (8, 4096, 9216, 256, 2, 8), (12, 2176, 8200, 2, 2, 8)])
+def test_equals_two_calls(fmt, M, K, N, had_block, width, units):
+    assert dvdq.bench_qlinear_choice(M, N, K) == width
+    per_wave = -(-min(M, 32) * -(-K // 512) // 8)   # of the workgroup with most of them; the kernel has forms for 1, 2, 4 and 8
+    assert min(u for u in (1, 2, 4, 8) if u >= per_wave) == units
     for zero, bias in ((False, False), (True, True)):
         if not (zero and fmt == "canonical"):   # (canonical weights carry no zero-points)
             _check(fmt, M, K, N, had_block, 4 if fmt in ("packed4", "fp6") else 6, zero, bias)
 
 
-@pytest.mark.parametrize("M,K,N,had_block", [(3, 32, 40, 32), (31, 672, 70, 16), (1, 1440, 1440, 32), (9, 3104, 513, 2)])
+@pytest.mark.parametrize("fmt", list(FORMATS))
+@pytest.mark.parametrize("M,K,N,had_block", [(32, 1024, 64, 64), (33, 640, 255, 128), (21, 1408, 5000, 8), (64, 512, 9216, 256)])
+def test_just_past_the_line(fmt, M, K, N, had_block):
+    """Two launches: more units than a workgroup takes, or more tiles than run at once."""
+    assert dvdq.bench_qlinear_choice(M, N, K) == 0
+    _check(fmt, M, K, N, had_block, 4 if fmt in ("packed4", "fp6") else 6, fmt != "canonical", True)
+
+
+@pytest.mark.parametrize("M,K,N,had_block", [(3, 32, 40, 32), (15, 672, 70, 16), (1, 1440, 1440, 32), (9, 3104, 513, 2), (20, 480, 8300, 32), (2, 2080, 9001, 16)])
 def test_canonical_part_slices(M, K, N, had_block):
+    assert dvdq.bench_qlinear_choice(M, N, K) > 0
     _check("canonical", M, K, N, had_block, 8, False, True)
 
 

@@ -18,3 +18,11 @@ def test_one_launch_only_where_nothing_it_stores_lies_over_x(M, N, K):
         assert dvdq.bench_qlinear_choice(M, N, K, X, y, WS, 4096) == width, hex(y)
     for ws, over in ((X, True), (end - 256, True), (X - 4096 + 256, True), (end, False), (X - 4096, False)):
         assert (dvdq.bench_qlinear_choice(M, N, K, X, Y, ws, 4096) == 0) == over, hex(ws)
+
+
+@pytest.mark.parametrize("M,N,K,width", [(1, 64, 32768, 1), (1, 64, 65536, 0), (32, 64, 512, 1), (33, 64, 512, 1), (32, 64, 520, 0), (16, 64, 1024, 1), (17, 64, 1024, 0),
+                                         (10, 64, 1536, 1), (11, 64, 1536, 0), (16, 64, 2048, 1), (17, 64, 2048, 0), (1, 8192, 512, 1), (1, 8193, 512, 2),
+                                         (1, 16384, 512, 2), (1, 16385, 512, 0), (8192, 32, 512, 1), (8193, 32, 512, 0)])
+def test_lines(M, N, K, width):
+    """32 units of 512 channels per 32 tokens, 64 for rows of four units and more; as long as all workgroups run at once."""
+    assert dvdq.bench_qlinear_choice(M, N, K) == width
