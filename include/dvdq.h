@@ -16,12 +16,12 @@
  * Conventions shared by every entry point
  *   - Every data pointer is a DEVICE pointer owned by the caller.  The library
  *     never allocates or frees device memory.  Its only state: the measurement hooks
- *     of dvdq_bench.h, the scratch array of dvdq_qlinear_static, and a fixed 32 KB array
+ *     of dvdq_bench.h, the scratch array of dvdq_qlinear_static, and a fixed 257 KB array
  *     of device memory per GPU (part of the loaded code object) that the GEMM kernels
- *     use as tile counters, 64 bytes per stream.  No launch depends on what an earlier
+ *     use as tile counters, 512 bytes per stream.  No launch depends on what an earlier
  *     one left in its counters: they are zeroed on the stream right before every GEMM
  *     that counts in them (by the quantizer kernel when that is what the library enqueued
- *     last on the stream, as in dvdq_qlinear; else by a one-wave kernel in front of the
+ *     last on the stream, as in dvdq_qlinear; else by a small kernel in front of the
  *     GEMM), so a launch that never finished or a stray write cannot make a later GEMM
  *     skip tiles.  Calls on one stream from several host threads must be ordered by the
  *     caller, as for any stream.  Kernels of one stream run one after the

@@ -29,17 +29,17 @@
 // for a float that sits on a threshold to within fp64 rounding, so every weight is classified by exactly the quotient
 // and rounding of the definition.  The starts of the search are independent of each other: 8 lanes take one start, two
 // positions each, with no barrier inside the search.  (What a round does once per start, divisions, square root and the
-// expression of e2, all lanes of the start do, some 100 of its 300 instructions; launch_bgr says where 4 lanes with four positions are better.)
+// expression of e2, all lanes of the start do, some 100 of its 300 instructions; bgr_choice says where 4 lanes with four positions are better.)
 //
 // Cost.  1536 rows of 8960 weights, 100 steps, 10 rounds: 0.140 ms; a pass over the row per evaluation, one workgroup of
 // 256 threads per row, took 8.7 ms.  Bound by latencies and the issue of fp64 instructions, not by memory (62 MB): of the
 // 104 K clocks a row is in work (two rows per compute unit, each beside another one's phases) 10 K are the load, 25 K the two
 // dealing passes with the counts between them (LDS atomics and barriers) and the sum of squares, 13 K the windows, 4 K the
 // prefix sums, 46 K the search, 6 K the codes.  The search is eleven rounds of 4 K, bound by issue: three to four waves per SIMD,
-// some 300 instructions each.  Since those figures it got 5 to 10 % of the whole cheaper (sq / K without the division's steps,
-// weights chosen before they are converted, unsigned block numbers, 24-bit products: 8960 rows of 1536 587 -> 539 us, 13824 of
-// 256 837 -> 763, 1536 of 8960 151 -> 146).  That the sums are not rounded costs 7 K: with sums in fp64 0.136 ms for 0.145 (8960 rows of 1536: 0.517 for 0.586) and a
-// squared error off by 1e-14, up to 1e-12 where a grid fits a row to a hundredth.
+// some 300 instructions each.  (The clocks are from when the row took 0.145 ms; since then the search got 4 to 9 % of the whole cheaper:
+// sq / K without the division's steps, weights chosen before they are converted, unsigned block numbers, 24-bit products: 8960 rows of 1536
+// 587 -> 539 us, 13824 of 256 837 -> 763, 1536 of 8960 146 -> 140.)  That the sums are not rounded costs 7 K: with sums in fp64 0.136 ms for
+// 0.145 (8960 rows of 1536: 0.517 for 0.586) and a squared error off by 1e-14, up to 1e-12 where a grid fits a row to a hundredth.
 #include "dvdq_internal.h"
 #include "wave_reduce.h"
 
@@ -277,7 +277,8 @@ __device__ void bitonic_sort(float *a, int n) {
 
 // T threads, a prefix sum every BLK weights.  HELD > 0: the threads hold the row in registers, HELD pairs of weights
 // each (K <= 2 HELD T); 0: it is read again for every step that needs it in its own order.
-// (16 waves per compute unit in every case: one workgroup of 1024 threads or two of 512, 128 registers per lane.)
+// (128 registers per lane at most: 16 waves per compute unit, one workgroup of 1024 threads, two of 512, or as many of 256, up to four, as
+// their LDS lets be resident.)
 template <int T, int BLK, int HELD, int LANES>
 __global__ __launch_bounds__(T, 4) void bgr_kernel(const float *__restrict__ w, int K, int cells, int n_steps, int max_refine,
                                                 double eps, int search, uint8_t *__restrict__ w_packed,

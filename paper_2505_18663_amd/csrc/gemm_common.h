@@ -178,7 +178,7 @@ static __device__ __forceinline__ void tile_origin(int t, int tiles_m, int tiles
 //     channels, some workgroups took two dear ones: 58675 x 512 x 343 95.3 -> 107.6 us, now 88.5; 9000 x 640 x 3072 35.2
 //     -> 31.1, with packed codes 9000 x 1536 x 4608 74.1 -> 64.4, 32760 x 1536 x 8960 474.9 -> 469.9.)  The word is zero when the kernel starts: whatever
 //     runs on the stream right before the GEMM clears the slot (the quantizer kernel, if that is what the
-//     library enqueued last on the stream, else a one-wave kernel the GEMM's launcher puts in front), so no
+//     library enqueued last on the stream, else a small kernel the GEMM's launcher puts in front), so no
 //     launch depends on what an earlier one -- finished or not -- left behind, and nothing has to be put back
 //     at the end.
 //     With at most two tiles per workgroup there is nothing to draw: such a launch is handed words that no one clears and no one
@@ -506,7 +506,7 @@ static __device__ __forceinline__ void epilogue_edge(typename P::vec (&acc)[TN][
     }
 }
 
-// Enqueues the one-wave kernel that zeroes a counter slot (sched_slot; defined in w4ax_gemm.hip).
+// Enqueues the kernel that zeroes a counter slot (sched_slot; defined in w4ax_gemm.hip).
 int clear_sched_slot(unsigned *slot, hipStream_t stream);
 
 }  // namespace dvdq

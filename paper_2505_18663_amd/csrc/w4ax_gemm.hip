@@ -54,7 +54,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
     // fragment then spans 32 channels, so one pipeline step covers 64 channels = 2 MFMAs per tile.
     constexpr int A_ROW = A4 ? BK / 2 : BK;              // bytes of one code row per item
     // CANON: the packed weights of a row are loaded as they are, 16 bytes = 32 channels a piece, and such a piece is a lane's weight
-    // fragment of a 64-channel step likewise; the code fragments are put into its order (see widen_canonical).
+    // fragment of a 64-channel step likewise; the code fragments are put into its order (see deal_codes).
     constexpr int NT = A4 || CANON ? 2 : 1;              // MFMAs along K per step and output tile
     constexpr int KS = BK / (32 * NT);                   // pipeline steps per item
     constexpr int A_STAGE = BM * A_ROW, W_STAGE = BN * BK / 2, STAGE = A_STAGE + W_STAGE;
@@ -194,8 +194,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
                 else
                     lds_direct_load4(w_scale, (uint32_t)min(n0 + (j - BM / 64) * 64 + lane, N - 1) * 4, sc + j * 256);
             }
-            // (bias and zero-points go to LDS, pairs and fours of channels at a time, where N is a multiple of 8; else the
-            // epilogue reads them from memory)
+            // (bias and zero-points go to LDS, pairs and fours of channels at a time, where N is a multiple of 8 or, with STORE_UNALIGNED,
+            // any other; the last N % 4 channels follow in front of the epilogue, see fill_vector_tail.  Elsewhere the epilogue reads them
+            // from memory)
             if (bias && (UNALIGNED || (N & 7) == 0)) {
 #pragma unroll
                 for (int j = 0; j < BN / 128; ++j)
@@ -684,8 +685,9 @@ int limited_grid(int grid) {
 // The tile variant for a size (variants 2 and 5 below; 10 + shape: the small-output kernel; kCanonicalVariant: the two-wave kernel
 // with canonical weights, kCanonicalShape6Variant: the small-output kernel beyond its outputs, a wave per 64 x 128 tile).
 // Variant 5 is the wide kernel of w4ax_gemm_wide.hip (int8 codes only), taken
-//   - from 12 K slices on (from 8 where its one or two rounds of tiles end more than half full: 0.93-0.98 of variant 2's time there at
-//     8 to 11 slices, 1536 and 2048 channels, 144 to 500 tiles);
+//   - from 12 K slices on (from 8 where its one or two rounds of tiles end more than half full but not full: 0.94 to 1.06 of variant 2's
+//     time there at 8 to 11 slices, 0.98 in the mean of 61 outputs of 129 to 511 tiles; with 256 or 512 tiles 0.94 to 1.12, 1.01 in the
+//     mean of 16, and 1.03 to 1.07 in one column of tiles);
 //   - where N is a multiple of 8.  For others variant 2 has the stores (STORE_UNALIGNED); per element, as the wide kernel stores
 //     them, a tile takes several times as long with no second workgroup to multiply meanwhile (before variant 2 had them the
 //     wide kernel was already 4-24 % slower at K = 1536 .. 6144, with bias and zero-points 20-53 %);

@@ -21,10 +21,10 @@
 // It is bound by the chain load - transform - maximum - codes - slices - sum, a few waits each.
 //
 // Measured (back-to-back launches, int8 codes, before -> now): 2 x 1536 x 9216 (tokens x K x channels): 22.6 -> 4.4 us;
-// 512 x 3072 x 3072: 28.0 -> 11.2; 1 x 13824 x 5120: 104 -> 10.5; 3121 x 1152 x 1160: 27.7 -> 10.8.  Towards the upper
+// 512 x 3072 x 3072: 28.0 -> 10.5; 1 x 13824 x 5120: 104 -> 10.5; 3121 x 1152 x 1160: 27.7 -> 10.1.  Towards the upper
 // end of the range the operand traffic out of the L2s is the limit (14 to 20 TB/s), which is why the tile grows with
-// the output.  A second slice in flight per wave costs registers and
-// resident waves: 10 % slower at 512 x 3072 x 3072, at best 5 % faster (1560 x 3072 x 3072).
+// the output.  A second slice in flight per wave was 10 % slower at 512 x 3072 x 3072, at best 5 % faster (1560 x 3072 x 3072); why is not
+// known: the shapes of 64 x 64 use 124 to 158 registers, and LDS, not registers, sets how many of their waves are resident.
 #include <type_traits>
 
 #include "gemm_common.h"
@@ -102,14 +102,14 @@ constexpr int kLayerVectors = 3 * 32 * 4;   // maxima, scales and code sums of t
 
 constexpr int kGroupStride = 1024 + 32;   // LDS bytes of one group of 4 accumulator registers (see the reduction)
 
-// LDS bytes of one wave: its part in the reduction, or its operand slice where that is larger
 // columns of MFMA tiles that the reduction takes at a time
-template <int TN, int NW>
+template <int TN>
 constexpr int phase_columns() { return TN == 4 ? 2 : TN; }
 
-template <int FMT, int TM, int TN, bool LAYER, int NW>
+// LDS bytes of one wave: its part in the reduction, or its operand slice where that is larger
+template <int FMT, int TM, int TN, bool LAYER>
 constexpr int wave_lds() {
-    const int reduction = TM * phase_columns<TN, NW>() * 4 * kGroupStride;
+    const int reduction = TM * phase_columns<TN>() * 4 * kGroupStride;
     const int slice = (FMT == FMT_FP6 || LAYER ? 0 : TM * 32 * (FMT == FMT_PACKED4 ? 64 : 128)) + (FMT == FMT_CANONICAL ? TN * 32 * 64 : 0);
     return reduction > slice ? reduction : slice;
 }
@@ -257,11 +257,11 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
     constexpr bool FP6 = FMT == FMT_FP6, CANONICAL = FMT == FMT_CANONICAL, LAYER = CPW > 0;
     constexpr int BM = 32 * TM, BN = 32 * TN;
     constexpr int A_ROW = FMT == FMT_PACKED4 ? kBK / 2 : kBK;    // bytes of a code row per slice (row-major containers)
-    constexpr int PN = phase_columns<TN, NW>(), PHASES = TN / PN;   // the reduction takes PN columns of MFMA tiles at a time
+    constexpr int PN = phase_columns<TN>(), PHASES = TN / PN;   // the reduction takes PN columns of MFMA tiles at a time
     constexpr int NG = TM * PN * 4;                            // groups of 4 accumulator registers per phase
     constexpr int GROUP_STRIDE = kGroupStride;
     constexpr int A_STAGE = FP6 || LAYER ? 0 : BM * A_ROW, W_STAGE = CANONICAL ? BN * (kBK / 2) : 0;   // a wave's own slice in LDS
-    constexpr int WAVE_LDS = wave_lds<FMT, TM, TN, LAYER, NW>();
+    constexpr int WAVE_LDS = wave_lds<FMT, TM, TN, LAYER>();
     static_assert(NG * GROUP_STRIDE <= WAVE_LDS && A_STAGE + W_STAGE <= WAVE_LDS, "per-wave LDS");
     constexpr int CV = (BN + 63) / 64;                         // values per lane of a channel vector
     static_assert(!LAYER || (TM == 1 && NW == 8), "the layer's tokens and units");
@@ -315,6 +315,8 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
         const int a_off = LAYER ? 0 : kt * (FP6 ? kFp6Block : A_ROW);
         const __amdgpu_buffer_rsrc_t ra = buffer(a_tile + (ok ? a_off : 0), ok ? a_bytes - a_off : 0);   // (LAYER: unused)
         const int64_t w_off = CANONICAL ? kt * (kBK / 2) : kt * w_slice_stride;
+        // (G is a multiple of 8: the minimum is TN.  With the constant in its place the same loads come out in another order: 3121 x 1152 x 1160
+        // packed codes 9.7 -> 9.8 us, 512 x 3072 x 3072 int8 10.4 -> 10.6, 300 x 3072 x 3072 7.4 -> 7.2)
         const int w_bytes = CANONICAL ? min(BN, N - n0) * (K / 2) - (int)w_off : min(TN, G - n0 / kGroup) * (FP6 ? kFp6Block : kGroupBytes);
         const __amdgpu_buffer_rsrc_t rw = buffer(w_tile + (ok ? w_off : 0), ok ? w_bytes : 0);
         if constexpr (FP6) {
@@ -587,7 +589,7 @@ int launch_tile(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
                 hipStream_t stream, const LayerInput &in = {}) {
     constexpr bool LAYER = CPW > 0;
     const int tiles_m = (M + 32 * TM - 1) / (32 * TM), tiles_n = (N + 32 * TN - 1) / (32 * TN);
-    const size_t smem = (size_t)NW * wave_lds<FMT, TM, TN, LAYER, NW>() + (2 + 3 * ((TN * 32 + 63) / 64)) * 256 +
+    const size_t smem = (size_t)NW * wave_lds<FMT, TM, TN, LAYER>() + (2 + 3 * ((TN * 32 + 63) / 64)) * 256 +
                         (LAYER ? kLayerVectors + min(M, 32) * layer_row_bytes<FMT>(K) + kLayerPad : 0);
     auto k = w4ax_gemm_small_kernel<FMT, TM, TN, NW, CPW>;
     static std::atomic<uint64_t> configured{0};

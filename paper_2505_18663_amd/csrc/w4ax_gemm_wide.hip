@@ -220,8 +220,9 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                 else
                     lds_direct_load4(w_scale, (uint32_t)min(n0 + (j - BM / 64) * 64 + lane, N - 1) * 4, sc + j * 256);
             }
-            // (bias and zero-points go to LDS, pairs and fours of channels at a time, where N is a multiple of 8; else the
-            // epilogue reads them from memory)
+            // (bias and zero-points go to LDS, pairs and fours of channels at a time, where N is a multiple of 8 or, with STORE_UNALIGNED,
+            // any other; the last N % 4 channels follow in front of the epilogue, see fill_vector_tail.  Elsewhere the epilogue reads them
+            // from memory)
             if (bias && (UNALIGNED || (N & 7) == 0)) {
 #pragma unroll
                 for (int j = 0; j < BN / 128; ++j)

@@ -19,7 +19,8 @@ def fp6(M, N, K, vectors=0):
 
 @pytest.mark.parametrize("vectors", [0, 1, 2])
 @pytest.mark.parametrize("M,N,K", [(15601, 1161, 1280), (5000, 4609, 3072), (8192, 3074, 6144), (32760, 4612, 13824)])
-def test_outputs_stored_per_element_stay_with_the_kernel_that_hides_it(M, N, K, vectors):
+def test_channel_counts_that_are_no_multiple_of_8(M, N, K, vectors):
+    """INT8: the two-wave kernel.  FP6: the wide one from depths that are from when such tiles were stored per element."""
     assert int8(M, N, K, vectors) == 2
     assert fp6(M, N, K, vectors) == (3 if K >= (6144, 12288, 1 << 30)[vectors] else 1)
 
