@@ -176,7 +176,7 @@ int dvdq_bench_set_gemm_variant(int variant) {
 int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors) {
     if (M < 1 || N < 1 || K < 32) return -DVDQ_ERR_SHAPE;
     if (w_layout == DVDQ_W_NATIVE_FP6) return dvdq::w4a4_fp6_gemm_choice(M, N, K, vectors, dvdq::drawing_enabled());
-    return dvdq::w4ax_gemm_choice(M, N, K, codes_format, w_layout, dvdq::drawing_enabled());
+    return dvdq::w4ax_gemm_choice(M, N, K, codes_format, w_layout, vectors, dvdq::drawing_enabled());
 }
 
 int dvdq_bench_bgr_choice(int64_t N, int64_t K, int n_steps, int max_refine) {

@@ -37,7 +37,7 @@ constexpr int kSmallVariants = 7, kFirstSmallVariant = 10;   // tile variant 10 
 // canonical weights beyond the small outputs (w4ax_gemm.hip): the two-wave kernel; the small kernel's shape 6
 constexpr int kCanonicalVariant = 16, kCanonicalShape6Variant = 17;
 // the tile variants that the launchers take by themselves, where tiles are drawn from counters and where they are fixed shares
-int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, bool drawn);
+int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors, bool drawn);
 int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors, bool drawn);
 bool tiles_drawn(hipStream_t stream);   // false: the stream is being captured
 bool drawing_enabled();                 // the benchmark hook

@@ -682,12 +682,12 @@ int limited_grid(int grid) {
     return limit < 8 ? 8 : limit / 8 * 8;
 }
 
-// The tile variant for a size (variants 2 and 5 below; 10 + shape: the small-output kernel; kCanonicalVariant: the two-wave kernel
+// The tile variant for a size and the number of vectors, bias and zero-points (variants 2 and 5 below; 10 + shape: the small-output kernel; kCanonicalVariant: the two-wave kernel
 // with canonical weights, kCanonicalShape6Variant: the small-output kernel beyond its outputs, a wave per 64 x 128 tile).
 // Variant 5 is the wide kernel of w4ax_gemm_wide.hip (int8 codes only), taken
-//   - from 12 K slices on (from 8 where its one or two rounds of tiles end more than half full but not full: 0.94 to 1.06 of variant 2's
-//     time there at 8 to 11 slices, 0.98 in the mean of 61 outputs of 129 to 511 tiles; with 256 or 512 tiles 0.94 to 1.12, 1.01 in the
-//     mean of 16, and 1.03 to 1.07 in one column of tiles);
+//   - from 12 K slices on (from 8 with both vectors, bias and zero-points, where its one or two rounds of tiles end more than half full but
+//     not full: 0.97 of variant 2's time there in the mean of 61 outputs of 129 to 511 tiles at 8 to 11 slices, 0.93 to 1.04; with one
+//     vector 1.00, up to 1.19, with none 1.01, up to 1.07; with 256 or 512 tiles 1.01 in the mean of 16, and 1.03 to 1.07 in one column);
 //   - where N is a multiple of 8.  For others variant 2 has the stores (STORE_UNALIGNED); per element, as the wide kernel stores
 //     them, a tile takes several times as long with no second workgroup to multiply meanwhile (before variant 2 had them the
 //     wide kernel was already 4-24 % slower at K = 1536 .. 6144, with bias and zero-points 20-53 %);
@@ -700,7 +700,7 @@ int limited_grid(int grid) {
 //     1.08-1.12 at 516 to 640, 0.95-0.99 at 672 to 768, 1.04-1.10 at 1026 to 1400, 1.02-1.07 at 2064 to 2172, 1.01-1.05 at 3100 to 3200.
 //     One column of tiles: 1.02 to 1.14 up to two fifths of a round; the line stays there, and below four rounds, as
 //     tests/test_dispatch.py states it.
-int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, bool drawn) {
+int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors, bool drawn) {
     const int shape = small_gemm_shape(M, N, K, false);
     if (w_layout == DVDQ_W_CANONICAL && shape < 0) {
         // a second round of the two-wave kernel's tiles where the waves, eight per compute unit, take one
@@ -710,7 +710,7 @@ int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_la
     if (shape >= 0) return kFirstSmallVariant + shape;
     if (codes_format != DVDQ_CODES_INT8 || K / 128 < 8 || !whole_line_tiles(N)) return 2;
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
-    if (K / 128 < 12) return tiles < 512 && last > 128 ? 5 : 2;
+    if (K / 128 < 12) return vectors == 2 && tiles < 512 && last > 128 ? 5 : 2;
     if (N <= 256) return tiles > 256 && tiles < 1024 && last != 0 && 5 * last < 2 * 256 ? 2 : 5;
     const int64_t most = drawn ? (tiles < 4096 ? 128 : 0) : tiles < 512 ? 128 : tiles < 1536 ? 16 : 0;
     return last != 0 && last <= most ? 2 : 5;
@@ -721,7 +721,7 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
                      int64_t K, int codes_format, int w_layout, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
     if (w_layout == DVDQ_W_CANONICAL) {
         if (codes_format != DVDQ_CODES_INT8 || w_zero) return DVDQ_ERR_UNSUPPORTED;
-        const int f = gemm_variant(), v = f >= kFirstSmallVariant ? f : w4ax_gemm_choice(M, N, K, codes_format, w_layout, true);
+        const int f = gemm_variant(), v = f >= kFirstSmallVariant ? f : w4ax_gemm_choice(M, N, K, codes_format, w_layout, bias != nullptr, true);
         if (v != kCanonicalVariant)
             return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, nullptr, nullptr, bias, M, N, K,
                                           codes_format, w_layout, v == kCanonicalShape6Variant ? 6 : v - kFirstSmallVariant, y, acc_out, stream);
@@ -750,8 +750,9 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     const int forced = gemm_variant();
     int v = forced;
     if (forced < 0) {
-        v = w4ax_gemm_choice(M, N, K, codes_format, w_layout, true);
-        const int fixed = w4ax_gemm_choice(M, N, K, codes_format, w_layout, false);
+        const int vectors = (bias != nullptr) + (w_zero != nullptr);
+        v = w4ax_gemm_choice(M, N, K, codes_format, w_layout, vectors, true);
+        const int fixed = w4ax_gemm_choice(M, N, K, codes_format, w_layout, vectors, false);
         if (fixed != v && !tiles_drawn(stream)) v = fixed;
     }
     if (v >= kFirstSmallVariant)

@@ -19,8 +19,10 @@ def test_int8(tiles, variant):
 
 
 def test_int8_of_few_slices():
-    assert [choice(400, s, False) for s in (7, 8, 11)] == [2, 5, 5]
-    assert [choice(t, 8, False) for t in (256, 384, 386, 510, 512, 770)] == [2, 2, 5, 5, 2, 2]
+    """Eight to eleven: the wide kernel with bias and zero-points only, in one or two rounds that end more than half full."""
+    assert [choice(400, s, False, 2) for s in (7, 8, 11)] == [2, 5, 5]
+    assert [choice(t, 8, False, 2) for t in (256, 384, 386, 510, 512, 770)] == [2, 2, 5, 5, 2, 2]
+    assert [choice(400, s, False, v) for s in (8, 11) for v in (0, 1)] == [2] * 4
 
 
 @pytest.mark.parametrize("tiles,slices", [(100, (10, 12, 12)), (128, (10, 12, 12)), (130, (6, 6, 6)), (256, (6, 6, 6)), (258, (8, 10, 12)),
