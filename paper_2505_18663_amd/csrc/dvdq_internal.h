@@ -10,6 +10,7 @@
 namespace dvdq {
 
 constexpr size_t kLdsPerCu = 160 * 1024;
+constexpr int kCusPerXcd = 32;
 
 // Launchers: arguments are already validated by the C-ABI layer in api.hip.
 // Each returns DVDQ_OK or DVDQ_ERR_HIP.

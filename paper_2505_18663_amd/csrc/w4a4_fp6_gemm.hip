@@ -375,7 +375,7 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
     // (two tiles per workgroup at most: nothing to draw, no counter to clear)
     unsigned *sched = nullptr;
     if (total > 2 * grid) sched = sched_slot(stream, &is_clear);
-    else if (total > grid) sched = idle_slot(stream), is_clear = true;
+    else if (total > grid + kCusPerXcd) sched = idle_slot(stream), is_clear = true;
     if (sched && !is_clear && clear_sched_slot(sched, stream) != DVDQ_OK) return DVDQ_ERR_HIP;
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * WAVES_M * WAVES_N), smem, stream, codes, x_scale, w, w_scale,
                        w_zero, code_rowsum, bias, M, N, K, y, acc_out, tiles_m, tiles_n, group_n, sched);

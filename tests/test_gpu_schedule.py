@@ -284,3 +284,30 @@ def test_the_layers_quantizer_clears_the_counters_its_gemm_draws_from(fmt, varia
     for value in (1, 0xFFFFFFFF):
         dvdq.bench_fill_tile_counters(value)
         assert torch.equal(layer().view(torch.int16), ref.view(torch.int16))
+
+
+@pytest.mark.parametrize("kind,variant", [("int8", 2), ("packed", 2), ("int8", 5), ("fp6", 1), ("fp6", 3)])
+@pytest.mark.parametrize("more", [1, 31, 32, 33, 64])
+def test_at_most_two_tiles_per_workgroup(kind, variant, more):
+    """64 workgroups with 65 to 128 tiles: none to draw; up to 32 more tiles than workgroups are fixed shares, beyond that the second
+    tiles are crosswise.  Whatever the counters hold, in a graph and outside."""
+    bm = TILE.get((kind, variant), (128, 256))[0]
+    M, K, N = (64 + more) * bm - 5, 256, 248
+    operands = _fp6_operands(M, K, N, seed=more) if kind == "fp6" else _operands(M, K, N, 4, kind == "packed", seed=more)
+    gemm = (lambda y=None: _fp6_gemm(operands, y=y)) if kind == "fp6" else (lambda y=None: _gemm(operands, 4, kind == "packed", y=y))
+    dvdq.bench_set_gemm_variant(13)   # the small-output kernel
+    ref = gemm()
+    dvdq.bench_set_gemm_variant(variant)
+    dvdq.bench_set_gemm_grid_limit(64)
+    y = torch.zeros_like(ref)
+    for value in (0, 0xFFFFFFFF):
+        dvdq.bench_fill_tile_counters(value)
+        gemm(y.zero_())
+        assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gemm(y)
+    for _ in range(3):
+        y.zero_()
+        graph.replay()
+        assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
