@@ -38,10 +38,10 @@ int dvdq_bench_mfma_i8(int iters, int data, int32_t *sink, double *ops_out, void
 int dvdq_bench_mfma_fp6(int iters, int data, int32_t *sink, double *ops_out, void *hip_stream);
 
 /* Tile-configuration sweeps: force the native-layout GEMMs to use tile variant `variant`
- * (INT8 matrix path: 1..5, see the dispatch tables in w4ax_gemm.hip, one per code container; shapes too
- * shallow in K for a variant's ring fall back to variant 2.  FP6 matrix path: 1 and 3, see w4a4_fp6_gemm.hip,
+ * (INT8 matrix path: 1..6, see the dispatch tables in w4ax_gemm.hip, one per code container; shapes too
+ * shallow in K for a variant's ring fall back to variant 2.  FP6 matrix path: 1, 3 and 6, see w4a4_fp6_gemm.hip,
  * other values mean its own choice; either path: 10..16 force a shape of the small-output kernel, see
- * w4ax_gemm_small.hip; canonical weights: 10..15 and 17 do, 16 is the two-wave kernel); -1 restores the library's own choice.  Process-wide (an atomic
+ * w4ax_gemm_small.hip; canonical weights: 10..15 and 17 do, 16 is the two-wave kernel, 6 the same with 128 x 128 tiles); -1 restores the library's own choice.  Process-wide (an atomic
  * that every launch reads once), meant for benchmarking only. */
 int dvdq_bench_set_gemm_variant(int variant);
 
@@ -49,6 +49,9 @@ int dvdq_bench_set_gemm_variant(int variant);
  * how many there are of bias and zero-points.  After dvdq_bench_set_gemm_schedule(0): what a launch under stream capture takes.
  * Sizes below 1: minus a dvdq_status code. */
 int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors);
+
+/* Where that is a two-wave kernel (2, FP6 1, canonical weights 16): 1 if it takes tiles of 128 x 128 (variant 6), 0 if 128 x 256. */
+int dvdq_bench_narrow_tiles(int64_t M, int64_t N, int64_t K);
 
 /* Threads per workgroup with which dvdq_bgr_quantize takes the rows: 256, 512 or 1024 (host only).  Sizes below 1 (2 weights, 0
  * rounds): minus a dvdq_status code. */

@@ -179,6 +179,11 @@ int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, in
     return dvdq::w4ax_gemm_choice(M, N, K, codes_format, w_layout, vectors, dvdq::drawing_enabled());
 }
 
+int dvdq_bench_narrow_tiles(int64_t M, int64_t N, int64_t K) {
+    if (M < 1 || N < 1 || K < 32) return -DVDQ_ERR_SHAPE;
+    return dvdq::narrow_tiles(M, N, K);
+}
+
 int dvdq_bench_bgr_choice(int64_t N, int64_t K, int n_steps, int max_refine) {
     if (N < 1 || K < 2 || n_steps < 1 || max_refine < 0) return -DVDQ_ERR_SHAPE;
     return dvdq::bgr_choice(N, K, n_steps, max_refine);

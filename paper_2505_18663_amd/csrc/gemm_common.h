@@ -276,7 +276,7 @@ struct AccF32x64 {
 template <int BM, int BN>
 struct TileVectors {
     static constexpr int OFF_BIAS = (BM + BN) * 4, OFF_RSUM = OFF_BIAS + BN * 2, OFF_ZERO = OFF_RSUM + BM * 4;
-    static constexpr int BYTES = OFF_ZERO + BN;
+    static constexpr int BYTES = OFF_ZERO + (BN < 256 ? 256 : BN);   // (zero-points come 256 at a time)
 };
 
 // The bias and zero-points of the last N % 4 channels, in the image of the tile at n0: the LDS-direct loads bring whole dwords

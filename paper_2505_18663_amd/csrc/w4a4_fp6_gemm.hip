@@ -160,7 +160,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4a4_fp6_gemm_ker
                         lds_direct_load4(code_rowsum, (uint32_t)min(m0 + j * 64 + lane, M - 1) * 4, sc + OFF_RSUM + j * 256);
                 if (UNALIGNED || (N & 7) == 0) {
 #pragma unroll
-                    for (int j = 0; j < BN / 256; ++j)
+                    for (int j = 0; j < (BN + 255) / 256; ++j)
                         if (j % NW == wave)
                             lds_direct_load4(w_zero, (uint32_t)min(n0 / 4 + j * 64 + lane, N / 4 - 1) * 4, sc + OFF_ZERO + j * 256);
                 }
@@ -366,7 +366,7 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
     int grid = 256 * OCC;
     if (total < grid) grid = (total + 7) / 8 * 8;
     grid = limited_grid(grid);
-    const size_t smem = (size_t)STAGES * (BM / 32 + BN / 32) * kFp6Block + 2 * ((BM + BN) * 4 + BN * 2 + BM * 4 + BN) +
+    const size_t smem = (size_t)STAGES * (BM / 32 + BN / 32) * kFp6Block + 2 * TileVectors<BM, BN>::BYTES +
                         8 * sizeof(int);
     auto k = w4a4_fp6_gemm_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, OCC, STORE>;
     static std::atomic<uint64_t> configured{0};
@@ -429,19 +429,24 @@ int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8
     // Outputs of few tiles go to w4ax_gemm_small.hip (small_gemm_shape).  Tile variants of the others:
     //   1: two independent 4-wave workgroups per compute unit, 128 x 256 tiles, two buffers: while one
     //      converts and stores a tile the other multiplies;
+    //   6: the same with 128 x 128 tiles and three workgroups per compute unit, taken in place of 1 by narrow_tiles;
     //   3: the wide kernel of w4ax_gemm_wide.hip: one 4-wave workgroup, 256 x 256 tiles, 128 x 128 wave tiles with
     //      the accumulators in AGPRs: a third fewer LDS fragment bytes per MFMA, but a larger fixed cost per tile.
     int v = gemm_variant();
-    if (v != 1 && v != 3 && (v < kFirstSmallVariant || v >= kFirstSmallVariant + kSmallVariants)) {
+    if (v != 1 && v != 3 && v != 6 && (v < kFirstSmallVariant || v >= kFirstSmallVariant + kSmallVariants)) {
         const int vectors = (bias != nullptr) + (w_zero != nullptr), fixed = w4a4_fp6_gemm_choice(M, N, K, vectors, false);
         v = w4a4_fp6_gemm_choice(M, N, K, vectors, true);
         if (fixed != v && !tiles_drawn(stream)) v = fixed;
+        if (v == 1 && narrow_tiles(M, N, K)) v = 6;
     }
     if (v >= kFirstSmallVariant)
         return launch_w4ax_gemm_small(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, DVDQ_CODES_FP6,
                                       DVDQ_W_NATIVE_FP6, v - kFirstSmallVariant, y, acc_out, stream);
     if (v == 3) return launch_w4ax_gemm_wide(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, true, y, acc_out, stream);
-    if (unaligned_tiles(N) && !acc_out) return launch_fp6<128, 256, 2, 2, 2, 2, STORE_UNALIGNED>(DVDQ_FP6_ARGS);
+    const bool unaligned = unaligned_tiles(N) && !acc_out;
+    if (v == 6)
+        return unaligned ? launch_fp6<128, 128, 2, 2, 2, 3, STORE_UNALIGNED>(DVDQ_FP6_ARGS) : launch_fp6<128, 128, 2, 2, 2, 3>(DVDQ_FP6_ARGS);
+    if (unaligned) return launch_fp6<128, 256, 2, 2, 2, 2, STORE_UNALIGNED>(DVDQ_FP6_ARGS);
     return launch_fp6<128, 256, 2, 2, 2, 2>(DVDQ_FP6_ARGS);
 #undef DVDQ_FP6_ARGS
 }

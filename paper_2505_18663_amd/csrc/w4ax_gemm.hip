@@ -210,7 +210,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC) void w4ax_gemm_native_
                         lds_direct_load4(code_rowsum, (uint32_t)min(m0 + j * 64 + lane, M - 1) * 4, sc + OFF_RSUM + j * 256);
                 if (UNALIGNED || (N & 7) == 0) {
 #pragma unroll
-                    for (int j = 0; j < BN / 256; ++j)
+                    for (int j = 0; j < (BN + 255) / 256; ++j)
                         if (j % NW == wave)
                             lds_direct_load4(w_zero, (uint32_t)min(n0 / 4 + j * 64 + lane, N / 4 - 1) * 4, sc + OFF_ZERO + j * 256);
                 }
@@ -655,7 +655,7 @@ int launch_native(const int8_t *codes, const float *x_scale, const uint8_t *w, c
     grid = limited_grid(grid);
     // the ring, then two tiles' epilogue vectors (scales, bias, code sums, zero-points; see the kernel)
     const size_t smem = (size_t)STAGES * (BM * (OPS == OPS_PACKED4 ? BK / 2 : BK) + BN * BK / 2) +
-                        2 * ((BM + BN) * 4 + BN * 2 + BM * 4 + BN) + 8 * sizeof(int);   // + the ring of tile numbers
+                        2 * TileVectors<BM, BN>::BYTES + 8 * sizeof(int);   // + the ring of tile numbers
     auto k = w4ax_gemm_native_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, OCC, OPS, STORE>;
     static std::atomic<uint64_t> configured{0};   // one per template instantiation
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
@@ -721,8 +721,8 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
                      int64_t K, int codes_format, int w_layout, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
     if (w_layout == DVDQ_W_CANONICAL) {
         if (codes_format != DVDQ_CODES_INT8 || w_zero) return DVDQ_ERR_UNSUPPORTED;
-        const int f = gemm_variant(), v = f >= kFirstSmallVariant ? f : w4ax_gemm_choice(M, N, K, codes_format, w_layout, bias != nullptr, true);
-        if (v != kCanonicalVariant)
+        const int f = gemm_variant(), v = f >= kFirstSmallVariant || f == 6 ? f : w4ax_gemm_choice(M, N, K, codes_format, w_layout, bias != nullptr, true);
+        if (v != kCanonicalVariant && v != 6)
             return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, nullptr, nullptr, bias, M, N, K,
                                           codes_format, w_layout, v == kCanonicalShape6Variant ? 6 : v - kFirstSmallVariant, y, acc_out, stream);
         // Variant 2 with the weights as they come.  A slice of a weight row is 64 bytes, half a cache line, so twice the weight bytes
@@ -731,11 +731,14 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
         // 2708 -> 1993, 27510 x 11552 x 7296 3282 -> 2266, 32760 x 1440 x 1441 170 -> 92.  The waves keep what they take in one round
         // (eight per compute unit, 2048) and variant 2 in two: a wave per tile 0.81 to 0.98 of its time there (22528 x 96 x 592 15.1 and 12.2 us,
         // 5910 x 160 x 2680 18.5 and 15.6, 16734 x 1120 x 792 36.0 and 33.1), from 2050 waves on 1.01 to 1.4 (12021 x 64 x 1328 15.7 and 15.9).
-        if (unaligned_tiles(N) && !acc_out)
-            return launch_native<128, 256, 128, 2, 2, 2, 2, OPS_CANONICAL, STORE_UNALIGNED>(
-                codes, x_scale, w, w_scale, nullptr, nullptr, bias, (int)M, (int)N, (int)K, y, acc_out, stream);
-        return launch_native<128, 256, 128, 2, 2, 2, 2, OPS_CANONICAL>(codes, x_scale, w, w_scale, nullptr, nullptr, bias, (int)M, (int)N,
-                                                                       (int)K, y, acc_out, stream);
+#define DVDQ_CANONICAL_ARGS codes, x_scale, w, w_scale, nullptr, nullptr, bias, (int)M, (int)N, (int)K, y, acc_out, stream
+        const bool unaligned = unaligned_tiles(N) && !acc_out;
+        if (v == 6 || (f < 0 && narrow_tiles(M, N, K)))
+            return unaligned ? launch_native<128, 128, 128, 2, 2, 2, 3, OPS_CANONICAL, STORE_UNALIGNED>(DVDQ_CANONICAL_ARGS)
+                             : launch_native<128, 128, 128, 2, 2, 2, 3, OPS_CANONICAL>(DVDQ_CANONICAL_ARGS);
+        return unaligned ? launch_native<128, 256, 128, 2, 2, 2, 2, OPS_CANONICAL, STORE_UNALIGNED>(DVDQ_CANONICAL_ARGS)
+                         : launch_native<128, 256, 128, 2, 2, 2, 2, OPS_CANONICAL>(DVDQ_CANONICAL_ARGS);
+#undef DVDQ_CANONICAL_ARGS
     }
     const int m = (int)M, n = (int)N, k = (int)K;
 #define DVDQ_GEMM_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, m, n, k, y, acc_out, stream
@@ -744,7 +747,8 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
     // each owning a 128 x 256 tile (64 x 128 per wave) with K slices of 128 through two buffers.  In
     // interleaved sweeps over the DiT shapes (K = 1536 ... 13824) it was fastest or within 1 % of the
     // fastest: while one workgroup converts and stores its tile the other keeps the matrix cores busy,
-    // which the one-workgroup 256 x 256 variants cannot do.  The others remain for sweeps; a shape with
+    // which the one-workgroup 256 x 256 variants cannot do.  Variant 6 is the same with 128 x 128 tiles (64 x 64 per wave) and three
+    // workgroups per compute unit, taken in place of variant 2 by narrow_tiles.  The others remain for sweeps; a shape with
     // fewer K slices than a variant's ring needs falls back to variant 2, which always qualifies.
     const bool unaligned = unaligned_tiles(N) && !acc_out;
     const int forced = gemm_variant();
@@ -754,12 +758,13 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
         v = w4ax_gemm_choice(M, N, K, codes_format, w_layout, vectors, true);
         const int fixed = w4ax_gemm_choice(M, N, K, codes_format, w_layout, vectors, false);
         if (fixed != v && !tiles_drawn(stream)) v = fixed;
+        if (v == 2 && narrow_tiles(M, N, K)) v = 6;
     }
     if (v >= kFirstSmallVariant)
         return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, w_zero, code_rowsum,
                                       bias, M, N, K, codes_format, w_layout, v - kFirstSmallVariant, y, acc_out, stream);
     if (codes_format == DVDQ_CODES_PACKED4) {
-        if ((v == 1 && k / 128 < 2) || (v > 2 && k / 128 < 3)) v = 2;
+        if ((v == 1 && k / 128 < 2) || (v > 2 && v < 6 && k / 128 < 3)) v = 2;
         switch (v) {
             case 1: return launch_native<256, 256, 128, 2, 4, 3, 1, OPS_PACKED4>(DVDQ_GEMM_ARGS);
             case 2:
@@ -767,6 +772,9 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
                                  : launch_native<128, 256, 128, 2, 2, 2, 2, OPS_PACKED4>(DVDQ_GEMM_ARGS);
             case 3: return launch_native<256, 256, 128, 2, 4, 4, 1, OPS_PACKED4>(DVDQ_GEMM_ARGS);
             case 4: return launch_native<256, 256, 128, 4, 2, 4, 1, OPS_PACKED4>(DVDQ_GEMM_ARGS);
+            case 6:
+                return unaligned ? launch_native<128, 128, 128, 2, 2, 2, 3, OPS_PACKED4, STORE_UNALIGNED>(DVDQ_GEMM_ARGS)
+                                 : launch_native<128, 128, 128, 2, 2, 2, 3, OPS_PACKED4>(DVDQ_GEMM_ARGS);
             default: return DVDQ_ERR_UNSUPPORTED;
         }
     }
@@ -774,7 +782,7 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
         return launch_w4ax_gemm_wide(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, w_zero, code_rowsum, bias,
                                      M, N, K, false, y, acc_out, stream);
     {
-        const int bk = v == 4 ? 64 : 128, stages = v == 2 ? 2 : (v == 4 ? 4 : 3);
+        const int bk = v == 4 ? 64 : 128, stages = v == 2 || v == 6 ? 2 : (v == 4 ? 4 : 3);
         if (k / bk < stages - 1) v = 2;
     }
     switch (v) {
@@ -784,6 +792,9 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
                              : launch_native<128, 256, 128, 2, 2, 2, 2>(DVDQ_GEMM_ARGS);
         case 3: return launch_native<256, 256, 128, 2, 4, 3, 1>(DVDQ_GEMM_ARGS);
         case 4: return launch_native<128, 256, 64, 2, 2, 4, 2>(DVDQ_GEMM_ARGS);
+        case 6:
+            return unaligned ? launch_native<128, 128, 128, 2, 2, 2, 3, OPS_INT8, STORE_UNALIGNED>(DVDQ_GEMM_ARGS)
+                             : launch_native<128, 128, 128, 2, 2, 2, 3>(DVDQ_GEMM_ARGS);
         default: return DVDQ_ERR_UNSUPPORTED;
     }
 #undef DVDQ_GEMM_ARGS
