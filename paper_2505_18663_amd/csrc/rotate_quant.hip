@@ -399,7 +399,13 @@ int launch_rotate_quant(const uint16_t *x, int64_t M, int64_t K, int log2_block,
     const int wg_waves = W >= 8 ? 16 : 8;
     const int rows_per_wg = W >= wg_waves ? 1 : wg_waves / W;
     const dim3 block(kWave * W * rows_per_wg);
-    int wgs_per_cu = 16 / (W * rows_per_wg);
+    // 24 waves for int8 and packed codes where a wave has few units or few rows: with one row loading while one is worked on, a slot's
+    // rows are as many round trips to memory (16 -> 24 waves, us: 15600 x 1536 int8 15.2 -> 15.0, block-wise 18.2 -> 16.9, 2000 x 5120 9.6 -> 8.6,
+    // 4096 x 3072 10.2 -> 9.6, 20000 x 1152 packed 14.5 -> 13.5, 100000 x 512 33.5 -> 29.5, 100000 x 256 int8 25.3 -> 21.6).  With three units and
+    // more than 8 rows a slot it is level, up to 5 % slower (118800 x 3072 201 -> 213); four units or more leave no registers for 24
+    // (8000 x 3584 block-wise 21.1 -> 23.2); 32 are behind 24 nearly everywhere, and behind 16 for most.
+    const int resident = pack4 != 3 && (cpw <= 2 || (cpw == 3 && M * W <= 8 * 256 * 16)) ? 24 : 16;
+    int wgs_per_cu = resident / (W * rows_per_wg);
     if (wgs_per_cu < 1) wgs_per_cu = 1;
     // FP6: consecutive rows a wave takes in turn (see the kernel): 1, 2, 4 or 8, the largest run that the LDS for collecting
     // them allows and of which there are enough for 13/16 of the resident slots (a row each).  (Whole 128-byte
