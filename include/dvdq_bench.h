@@ -40,7 +40,7 @@ int dvdq_bench_mfma_fp6(int iters, int data, int32_t *sink, double *ops_out, voi
 /* Tile-configuration sweeps: force the native-layout GEMMs to use tile variant `variant`
  * (INT8 matrix path: 1..6, see the dispatch tables in w4ax_gemm.hip, one per code container; shapes too
  * shallow in K for a variant's ring fall back to variant 2.  FP6 matrix path: 1, 3 and 6, see w4a4_fp6_gemm.hip,
- * other values mean its own choice; either path: 10..16 force a shape of the small-output kernel, see
+ * other values mean its own choice; either path: 10..17 force a shape of the small-output kernel, see
  * w4ax_gemm_small.hip; canonical weights: 10..15 and 17 do, 16 is the two-wave kernel, 6 the same with 128 x 128 tiles); -1 restores the library's own choice.  Process-wide (an atomic
  * that every launch reads once), meant for benchmarking only. */
 int dvdq_bench_set_gemm_variant(int variant);

@@ -34,7 +34,7 @@ int launch_w4ax_gemm_wide(const uint8_t *codes, const float *x_scale, const uint
 // Small outputs, any container of codes with its native weight layout, and int8 codes with canonical weights
 // (w4ax_gemm_small.hip).  small_gemm_shape: the shape of tile and waves for a size, or -1 (not a small output)
 int small_gemm_shape(int64_t M, int64_t N, int64_t K, bool fp6);
-constexpr int kSmallVariants = 7, kFirstSmallVariant = 10;   // tile variant 10 + shape stands for a shape
+constexpr int kSmallVariants = 8, kFirstSmallVariant = 10;   // tile variant 10 + shape stands for a shape
 // canonical weights beyond the small outputs (w4ax_gemm.hip): the two-wave kernel; the small kernel's shape 6
 constexpr int kCanonicalVariant = 16, kCanonicalShape6Variant = 17;
 // the tile variants that the launchers take by themselves, where tiles are drawn from counters and where they are fixed shares

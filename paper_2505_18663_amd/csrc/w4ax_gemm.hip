@@ -715,6 +715,7 @@ int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_la
         const bool pays = codes_format == DVDQ_CODES_INT8 ? slices < 20 || tiles > 384 : slices < 6 || (slices < 12 && tiles > 320);
         if (w_layout != DVDQ_W_CANONICAL && tiles <= 512 && pays) return 2;
     }
+    if (shape == 7 && w_layout == DVDQ_W_CANONICAL) return kFirstSmallVariant + 3;   // (variant 17 is another thing there)
     if (shape >= 0) return kFirstSmallVariant + shape;
     if (codes_format != DVDQ_CODES_INT8 || K / 128 < 8 || !whole_line_tiles(N)) return 2;
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;

@@ -21,10 +21,10 @@
 // It is bound by the chain load - transform - maximum - codes - slices - sum, a few waits each.
 //
 // Measured (back-to-back launches, int8 codes, before -> now): 2 x 1536 x 9216 (tokens x K x channels): 22.6 -> 4.4 us;
-// 512 x 3072 x 3072: 28.0 -> 10.5; 1 x 13824 x 5120: 104 -> 10.5; 3121 x 1152 x 1160: 27.7 -> 10.1.  Towards the upper
+// 512 x 3072 x 3072: 28.0 -> 10.7; 1 x 13824 x 5120: 104 -> 10.5; 3121 x 1152 x 1160: 27.7 -> 9.8.  Towards the upper
 // end of the range the operand traffic out of the L2s is the limit (14 to 20 TB/s), which is why the tile grows with
-// the output.  A second slice in flight per wave was 10 % slower at 512 x 3072 x 3072, at best 5 % faster (1560 x 3072 x 3072); why is not
-// known: the shapes of 64 x 64 use 124 to 158 registers, and LDS, not registers, sets how many of their waves are resident.
+// the output.  A second slice in flight pays where a compute unit has one workgroup (64 x 96, from 18 slices on); with two, as the 64 x 64
+// shapes have, their operands come at the L2s' rate either way (level at 512 x 3072 x 3072 and 3121 x 1152 x 1160).
 #include <type_traits>
 
 #include "gemm_common.h"
@@ -248,8 +248,9 @@ __device__ __forceinline__ void quantize_rows(const LayerInput &in, int m0, int 
 }
 
 // CPW > 0, the layer: the codes are made here, from `in`, by every workgroup for its own 32 tokens, CPW units of 512 channels a wave.
-template <int FMT, int TM, int TN, int NW, int CPW>
-__global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
+// DEPTH: slices a wave has in flight.  2, in shapes with one workgroup per compute unit (and so 512 registers a lane).
+template <int FMT, int TM, int TN, int NW, int CPW, int DEPTH>
+__global__ __launch_bounds__(64 * NW, DEPTH == 2 ? 1 : 2) void w4ax_gemm_small_kernel(
     const uint8_t *__restrict__ codes, const float *__restrict__ x_scale, const uint8_t *__restrict__ w,
     const float *__restrict__ w_scale, const int8_t *__restrict__ w_zero, const int32_t *__restrict__ code_rowsum,
     const uint16_t *__restrict__ bias, int M, int N, int K, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out,
@@ -370,13 +371,14 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
     // (rows past M: some row that exists, for outputs that are never stored)
     const uint8_t *my_codes = s_codes + min(frow, rows - 1) * code_stride;
 
-    S slice;
+    S slice, behind;
     if constexpr (CPW > 0) {
         if (tid < 32) s_rowmax[tid] = 0, s_sum[tid] = 0;
         quantize_rows<FMT, NW, CPW>(in, m0, rows, K, wave, lane, w_zero != nullptr, s_rowmax, s_scale, s_sum, s_codes, code_stride,
                                     [&]() __attribute__((always_inline)) { load(slice, wave); });
     } else {
         load(slice, wave);
+        if constexpr (DEPTH == 2) load(behind, wave + NW);
     }
 
     auto multiply = [&](const S &s, int kt) __attribute__((always_inline)) {
@@ -459,9 +461,24 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
         }
     };
 
-    for (int kt = wave; kt < KT; kt += NW) {
-        multiply(slice, kt);
-        load(slice, kt + NW);   // (the compiler moves it up between the MFMAs; past the last slice it fetches nothing)
+    if constexpr (DEPTH == 2) {
+        // (pairs in one basic block: with a way out between the two the compiler waits for all loads in front of the second, which
+        // is why a second slice in flight was 10 % slower at 512 x 3072 x 3072 once)
+        int kt = wave;
+        for (; kt + NW < KT; kt += 2 * NW) {
+            multiply(slice, kt);
+            load(slice, kt + 2 * NW);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(behind, kt + NW);
+            load(behind, kt + 3 * NW);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (kt < KT) multiply(slice, kt);
+    } else {
+        for (int kt = wave; kt < KT; kt += NW) {
+            multiply(slice, kt);
+            load(slice, kt + NW);   // (the compiler moves it up between the MFMAs; past the last slice it fetches nothing)
+        }
     }
 
     // ---- reduction over the waves' shares of K and epilogue.  Every wave puts its accumulators into its part of LDS,
@@ -506,52 +523,36 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
                         Q{t[g * 4], t[g * 4 + 1], t[g * 4 + 2], t[g * 4 + 3]};
                 }
         __syncthreads();
-        // (unrolled, so that the reads of a thread's pieces run beside each other, and what is not there -- zero-points, bias -- is
-        // branched around: 2800 of the kernel's 16500 clocks went to these sums at 300 x 3072 x 3072; 512 x 3072 x 3072 int8 11.6 -> 10.5 us,
-        // 512 x 1536 x 3072 8.6 -> 7.4)
+        // (unrolled, so that the reads of a thread's pieces run beside each other: 2800 of the kernel's 16500 clocks went to these sums at
+        // 300 x 3072 x 3072; 512 x 3072 x 3072 int8 11.6 -> 10.5 us, 512 x 1536 x 3072 8.6 -> 7.4.  With several pieces a thread, what is not there --
+        // zero-points, bias -- is chosen once: a branch in each piece keeps the reads apart (1560 x 1536 x 1536 packed 10.0 -> 9.4, 3121 x 1152 x
+        // 1160 10.3 -> 9.8).  With one, and with canonical weights, it is branched around: there the copies of the code cost 1 to 2 %)
         constexpr int ITEMS = (BM * PIECES + 64 * NW - 1) / (64 * NW);
-#pragma unroll
-        for (int item = 0; item < ITEMS; ++item) {
-            const int it = tid + item * 64 * NW;
-            const int p = it % PIECES, r = it / PIECES;
-            const int c = (ph * PIECES + p) * 8;   // the piece's first channel within the tile
-            if ((BM * PIECES % (64 * NW) != 0 && it >= BM * PIECES) || r >= rows || n0 + c >= N) continue;
+        constexpr bool SAME_CHANNELS = 64 * NW % PIECES == 0;   // of all of a thread's pieces
+        typedef typename std::conditional<FP6, v4f_t, v4i>::type Q;
+        auto row_of = [&](int it) { return it / PIECES; };
+        auto channel_of = [&](int it) { return (ph * PIECES + it % PIECES) * 8; };   // a piece's first channel within the tile
+        auto exists = [&](int it) {
+            return (BM * PIECES % (64 * NW) == 0 || it < BM * PIECES) && row_of(it) < rows && n0 + channel_of(it) < N;
+        };
+        auto sum_shares = [&](int it, Q &lo, Q &hi) __attribute__((always_inline)) {
+            const int p = it % PIECES, r = row_of(it);
             const uint8_t *q = smem + (((p >> 2) * TM + (r >> 5)) * 4 + (p & 3)) * GROUP_STRIDE + (r & 31) * 16;
-            typedef typename std::conditional<FP6, v4f_t, v4i>::type Q;
-            Q lo = *reinterpret_cast<const Q *>(q), hi = *reinterpret_cast<const Q *>(q + 512);
+            lo = *reinterpret_cast<const Q *>(q);
+            hi = *reinterpret_cast<const Q *>(q + 512);
 #pragma unroll
             for (int u = 1; u < NW; ++u) {
                 lo += *reinterpret_cast<const Q *>(q + u * WAVE_LDS);
                 hi += *reinterpret_cast<const Q *>(q + u * WAVE_LDS + 512);
             }
-            const float xs = s_xs[r];
-            v4f_t ws[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) ws[h] = *reinterpret_cast<const v4f_t *>(s_ws + c + h * 4);
-            int a[8];
-            float o[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) a[e] = P::integer(e < 4 ? lo[e] : hi[e - 4]);
-            if (w_zero) {
-                const int rs = s_rs[r];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const v4i z = *reinterpret_cast<const v4i *>(s_z + c + h * 4);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) a[h * 4 + e] = P::unzero(a[h * 4 + e], z[e], rs);
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (float)a[e] * xs * ws[e / 4][e % 4];
-            if (has_bias) {
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const v4f_t bb = *reinterpret_cast<const v4f_t *>(s_bias + c + h * 4);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[h * 4 + e] += bb[e];
-                }
-            }
-            const int64_t at = (int64_t)(m0 + r) * N + n0 + c;
+        };
+        auto read8 = [](auto (&v)[2], const auto *from) __attribute__((always_inline)) {
+            v[0] = *reinterpret_cast<const std::remove_reference_t<decltype(v[0])> *>(from);
+            v[1] = *reinterpret_cast<const std::remove_reference_t<decltype(v[1])> *>(from + 4);
+        };
+        auto store = [&](int it, const float (&o)[8], const int (&a)[8]) __attribute__((always_inline)) {
+            const int c = channel_of(it);
+            const int64_t at = (int64_t)(m0 + row_of(it)) * N + n0 + c;
             // (16 bytes at any even address: rows of an output with N no multiple of 8 begin anywhere.  Stored per element such
             // rows cost the layer 385 x 2304 x 4436 1.3 of 14.6 us)
             if (n0 + c + 8 <= N) {
@@ -566,6 +567,80 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     if (n0 + c + e < N) acc_out[at + e] = P::sum(a[e]);
+            }
+        };
+        if constexpr (ITEMS == 1 || CANONICAL) {
+#pragma unroll
+            for (int item = 0; item < ITEMS; ++item) {
+                const int it = tid + item * 64 * NW;
+                if (!exists(it)) continue;
+                Q lo, hi;
+                sum_shares(it, lo, hi);
+                const int r = row_of(it), c = channel_of(it);
+                const float xs = s_xs[r];
+                v4f_t ws[2], bb[2];
+                read8(ws, s_ws + c);
+                int a[8];
+                float o[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) a[e] = P::integer(e < 4 ? lo[e] : hi[e - 4]);
+                if (w_zero) {
+                    const int rs = s_rs[r];
+                    v4i z[2];
+                    read8(z, s_z + c);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) a[e] = P::unzero(a[e], z[e / 4][e % 4], rs);
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (float)a[e] * xs * ws[e / 4][e % 4];
+                if (has_bias) {
+                    read8(bb, s_bias + c);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o[e] += bb[e / 4][e % 4];
+                }
+                store(it, o, a);
+            }
+        } else {
+            auto finish = [&](auto zp, auto with_bias) __attribute__((always_inline)) {
+                constexpr bool ZP = decltype(zp)::value, BIAS = decltype(with_bias)::value;
+                struct Channels { v4f_t ws[2], bias[2]; v4i z[2]; } ch[SAME_CHANNELS ? 1 : ITEMS];
+                Q lo[ITEMS], hi[ITEMS];
+                float xs[ITEMS];
+                int rs[ITEMS];
+#pragma unroll
+                for (int item = 0; item < ITEMS; ++item) {   // (rows past M and channels past N: sums that are not stored)
+                    const int it = min(tid + item * 64 * NW, BM * PIECES - 1);
+                    sum_shares(it, lo[item], hi[item]);
+                    xs[item] = s_xs[row_of(it)];
+                    if constexpr (ZP) rs[item] = s_rs[row_of(it)];
+                    if (item == 0 || !SAME_CHANNELS) {
+                        read8(ch[item].ws, s_ws + channel_of(it));
+                        if constexpr (BIAS) read8(ch[item].bias, s_bias + channel_of(it));
+                        if constexpr (ZP) read8(ch[item].z, s_z + channel_of(it));
+                    }
+                }
+#pragma unroll
+                for (int item = 0; item < ITEMS; ++item) {
+                    const int it = tid + item * 64 * NW;
+                    const Channels &h = ch[SAME_CHANNELS ? 0 : item];
+                    int a[8];
+                    float o[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        a[e] = P::integer(e < 4 ? lo[item][e] : hi[item][e - 4]);
+                        if constexpr (ZP) a[e] = P::unzero(a[e], h.z[e / 4][e % 4], rs[item]);
+                        o[e] = (float)a[e] * xs[item] * h.ws[e / 4][e % 4];
+                        if constexpr (BIAS) o[e] += h.bias[e / 4][e % 4];
+                    }
+                    if (exists(it)) store(it, o, a);
+                }
+            };
+            if (w_zero) {
+                if (has_bias) finish(std::true_type{}, std::true_type{});
+                else finish(std::true_type{}, std::false_type{});
+            } else {
+                if (has_bias) finish(std::false_type{}, std::true_type{});
+                else finish(std::false_type{}, std::false_type{});
             }
         }
     }
@@ -583,7 +658,7 @@ __global__ __launch_bounds__(64 * NW, 2) void w4ax_gemm_small_kernel(
     }
 }
 
-template <int FMT, int TM, int TN, int NW, int CPW = 0>
+template <int FMT, int TM, int TN, int NW, int CPW = 0, int DEPTH = 1>
 int launch_tile(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale, const int8_t *w_zero,
                 const int32_t *code_rowsum, const uint16_t *bias, int M, int N, int K, uint16_t *y, int32_t *acc_out,
                 hipStream_t stream, const LayerInput &in = {}) {
@@ -591,7 +666,7 @@ int launch_tile(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
     const int tiles_m = (M + 32 * TM - 1) / (32 * TM), tiles_n = (N + 32 * TN - 1) / (32 * TN);
     const size_t smem = (size_t)NW * wave_lds<FMT, TM, TN, LAYER>() + (2 + 3 * ((TN * 32 + 63) / 64)) * 256 +
                         (LAYER ? kLayerVectors + min(M, 32) * layer_row_bytes<FMT>(K) + kLayerPad : 0);
-    auto k = w4ax_gemm_small_kernel<FMT, TM, TN, NW, CPW>;
+    auto k = w4ax_gemm_small_kernel<FMT, TM, TN, NW, CPW, DEPTH>;
     static std::atomic<uint64_t> configured{0};
     allow_dynamic_lds(reinterpret_cast<const void *>(k), LAYER ? kLdsPerCu : smem, configured);
     // an XCD takes a contiguous run of tiles: it should read all of the smaller operand and its share of the larger one
@@ -609,7 +684,7 @@ int launch_tile(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
 // sweep over M = 1 .. 16384, N = 256 .. 9216, K = 256 .. 9216, int8 and FP6 codes (all shapes timed at each point): this
 // rule is within 2.6 % of the best shape in the geometric mean, and the same lines are best for both containers.  On
 // the lines (int8 codes): 1024 x 1024 x 256 (tokens x K x channels, 256 tiles of 32 x 32) 4.6 us as shape 0, 4.8 as 1;
-// 512 x 3072 x 3072 (384 tiles of 64 x 64) 11.8 as 3, 14.7 as 4; 1024 x 3072 x 3072 (768) 18.7 and 16.9;
+// 512 x 3072 x 3072 (384 tiles of 64 x 64) 11.8 as 3, 10.7 as 7, 14.7 as 4; 1024 x 3072 x 3072 (768) 18.7 and 16.9;
 // 2048 x 3072 x 3072 (768 tiles of 64 x 128) 29.0 as 5, 31.1 with large tiles; 3072 x 3072 x 3072 (1152) 45.5 and 40.0.
 // FP6 codes halve the large tiles' time per slice, not the operand traffic of the small ones: there the large tiles
 // win as soon as 96 of them (256 x 256) are at work: 1536 x 3072 x 3072 (72) 20.4 as 5 and 24.0, 2048 x 3072 x 3072 (96)
@@ -619,6 +694,10 @@ int small_gemm_shape(int64_t M, int64_t N, int64_t K, bool fp6) {
     if (tiles(32, 32) <= 256) return 0;
     // (deep K: eight waves; 1 x 9216 x 9216: 14.8 -> 11.0 us, at 3072 channels equal)
     if (tiles(32, 64) <= 256) return K / kBK >= 48 ? 2 : 1;
+    // (one workgroup per compute unit with the same outputs each, where of the 64 x 64 tiles some compute units have two and some one: by the
+    // number of slices up to 11 / 12 to 17 / 18 to 23 / more 0.94 to 1.08 / 0.97 to 1.01 / 0.94 to 0.97 / 0.85 to 0.89 of shape 3's time, int8,
+    // packed and FP6 codes; 512 x 3072 x 3072 int8 12.0 -> 10.7 us, FP6 9.9 -> 8.8)
+    if (tiles(64, 64) > 256 && tiles(64, 96) <= 256 && K / kBK >= 18) return 7;
     if (tiles(64, 64) <= 512) return 3;
     if (tiles(64, 64) <= 1024) return 4;
     if (tiles(64, 128) <= 1024 && !(fp6 && tiles(256, 256) >= 96)) return 5;
@@ -630,6 +709,9 @@ int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uin
                            int64_t K, int codes_format, int w_layout, int shape, uint16_t *y, int32_t *acc_out, hipStream_t stream) {
 #define DVDQ_SMALL_ARGS codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, (int)M, (int)N, (int)K, y, acc_out, stream
 #define DVDQ_SMALL(FMT) /* {tile M / 32, tile N / 32, waves} */                \
+    if constexpr (FMT != FMT_CANONICAL) { /* (two slices in flight) */         \
+        if (shape == 7) return launch_tile<FMT, 2, 3, 4, 0, 2>(DVDQ_SMALL_ARGS); \
+    }                                                                          \
     switch (shape) {                                                           \
         case 0: return launch_tile<FMT, 1, 1, 8>(DVDQ_SMALL_ARGS); \
         case 1: return launch_tile<FMT, 1, 2, 4>(DVDQ_SMALL_ARGS); \
@@ -640,9 +722,9 @@ int launch_w4ax_gemm_small(const uint8_t *codes, const float *x_scale, const uin
         case 6: return launch_tile<FMT, 2, 4, 1>(DVDQ_SMALL_ARGS); /* (sweeps, and canonical weights: w4ax_gemm_choice) */ \
         default: return DVDQ_ERR_UNSUPPORTED;                                  \
     }
-    if (codes_format == DVDQ_CODES_FP6) DVDQ_SMALL(FMT_FP6)
-    if (codes_format == DVDQ_CODES_PACKED4) DVDQ_SMALL(FMT_PACKED4)
-    if (w_layout == DVDQ_W_CANONICAL) DVDQ_SMALL(FMT_CANONICAL)
+    if (codes_format == DVDQ_CODES_FP6) { DVDQ_SMALL(FMT_FP6) }
+    if (codes_format == DVDQ_CODES_PACKED4) { DVDQ_SMALL(FMT_PACKED4) }
+    if (w_layout == DVDQ_W_CANONICAL) { DVDQ_SMALL(FMT_CANONICAL) }
     DVDQ_SMALL(FMT_INT8)
 #undef DVDQ_SMALL
 #undef DVDQ_SMALL_ARGS
