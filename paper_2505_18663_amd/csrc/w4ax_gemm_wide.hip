@@ -22,8 +22,8 @@
 // behind the last step of slice q the first half of slice q+3); the barrier of iteration q publishes slice
 // q+1 and frees buffer q % 3 for slice q+3.  Everything else -- LDS-direct loads
 // with hand-kept vmcnt, persistent workgroups drawing tiles per XCD, tile scales staged in LDS, whole-line
-// epilogue through the ring buffer that was consumed last -- follows w4ax_gemm.hip.  The epilogue stages 4 KB
-// per wave in the weight half of that buffer; on the FP6 path (tiles of three slices or more) its code half is
+// epilogue through the ring buffer that was consumed last -- follows w4ax_gemm.hip.  The epilogue stages its chunks
+// in that buffer; on the FP6 path (tiles of three slices or more) in its weight half, while its code half is
 // filled meanwhile with the first half of the next tile's slice 2, so that the loads cross a tile boundary in the
 // same order as inside a tile and a tile's first step issues six loads, not twelve, behind the stores of the
 // tile before (measured per tile on K = 1536: 970 of 27300 clocks less on 32 workgroups, 1280 of 28600 on the
@@ -64,6 +64,8 @@ __device__ __forceinline__ void static_for(F &&f) {
 
 #include "wide_acc.inc"
 
+// LDS of a workgroup: the ring, the tiles' vectors and tile numbers (laid out in the kernel)
+constexpr int wide_lds_bytes(bool across) { return 3 * 48 * 1024 + (across ? 2 * 3840 + 8192 : 3 * 3840) + 8 * 4; }
 
 }  // namespace
 
@@ -94,7 +96,12 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
     static_assert(STAGE == 48 * 1024 && DMA == 12, "ring geometry");
     static_assert(DMA + STORES < 64 && (STAGES - 1) * DMA + 8 < 64, "vmcnt is 6 bits");
     static_assert(FP6 || !ACROSS, "the INT8 path issues a slice's loads in one piece");
-    static_assert(NW * 4096 <= W_STAGE, "the epilogue stages 4 KB per wave in the weight half of one ring buffer");
+    constexpr float kUnit = FP6 ? kFp6Unit : 1.f / (float)(1 << SHIFT);   // accumulator * kUnit = integer sum
+    // LDS behind the ring: the vectors of the tiles at work (see issue_prepare), ACROSS: one wave's staging, the ring of tile numbers
+    constexpr int VECTOR_SETS = ACROSS ? 2 : 3, STAGING = 8192, OFF_STAGING = STAGES * STAGE + VECTOR_SETS * SCALES;
+    constexpr int OFF_TILES = OFF_STAGING + (ACROSS ? STAGING : 0), LDS_BYTES = OFF_TILES + 8 * 4;
+    static_assert(LDS_BYTES == wide_lds_bytes(ACROSS) && LDS_BYTES <= kLdsPerCu, "LDS");
+    static_assert((ACROSS ? 3 * STAGING <= W_STAGE : NW * STAGING <= STAGE) && OFF_STAGING % 256 == 0 && STAGE % 256 == 0, "staging");
 
     extern __shared__ __align__(16) uint8_t smem[];
     const uint32_t smem_base = lds_address(smem);
@@ -112,7 +119,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
     // in fixed shares (sched == nullptr); numbers travel through an 8-entry ring in LDS.  See w4ax_gemm.hip.
     const TileSource tiles(tiles_m, tiles_n, sched, 1);   // (counters in one line: see kSchedStride)
     typedef volatile __attribute__((address_space(3))) int lds_int;
-    lds_int *s_tiles = (lds_int *)DVDQ_LDS(smem + STAGES * STAGE + 3 * SCALES);
+    lds_int *s_tiles = (lds_int *)DVDQ_LDS(smem + OFF_TILES);
     // Fixed shares (no counters): the ordinal-th tile of this workgroup follows from its number alone, which
     // every wave computes for itself.  Drawn tiles (K / 128 >= 2), two protocols:
     // FP6 path: the number drawn while slice `draw_kt` of tile n is issued belongs to tile n + 2; wave 0 writes it
@@ -210,8 +217,9 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
             }
             // the tile's epilogue vectors: token scales, channel scales, bias, code sums, zero-points.  Three tiles
             // deep: loads run two slices ahead, so with one slice per tile the tile after next is issued before
-            // this tile's epilogue has read its own
-            const uint32_t sc = smem_base + STAGES * STAGE + (issue_tile % 3) * SCALES;
+            // this tile's epilogue has read its own (ACROSS, three slices or more: two, the tile after next is issued behind the
+            // next tile's first barrier at the earliest)
+            const uint32_t sc = smem_base + STAGES * STAGE + (issue_tile % VECTOR_SETS) * SCALES;
 #pragma unroll
             for (int j = 0; j < (BM + BN) / 64; ++j) {
                 if (j % NW != wave) continue;
@@ -525,15 +533,16 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
             if (drawer) s_tiles[(tile_j + 1) & 7] = tiles.tile(draw_reply, 0);
         };
         const bool vec8 = (N & 7) == 0;
-        uint8_t *s_tile = smem + STAGES * STAGE + ((tile_j - 1) % 3) * SCALES;
+        uint8_t *s_tile = smem + STAGES * STAGE + ((tile_j - 1) % VECTOR_SETS) * SCALES;
         const float *s_xs = reinterpret_cast<const float *>(s_tile);
         const float *s_ws = s_xs + BM;
         const int32_t *s_rsum = reinterpret_cast<const int32_t *>(s_tile + OFF_RSUM);
         // sum q (c - z) = acc - z * rs with a 24-bit multiply (ranges: C ABI)
         auto unzero = [] __device__(int a, int z, int rs) { return a - __mul24(z, rs); };
-        // staging: 4 KB per wave in the weight half of the buffer of the slice consumed last (next to be filled; on
-        // the FP6 path its code half is already being filled with the next tile's slice 2 while the epilogue runs)
-        uint8_t *stg = smem + fill_off + A_STAGE + wave * 4096;
+        // staging: 8 KB per wave in the buffer of the slice consumed last (next to be filled).  ACROSS: its code half is already
+        // being filled with the next tile's slice 2 while the epilogue runs, the weight half holds three waves' and the fourth has
+        // 8 KB behind the vectors.  (Without zero-points 4 KB are in use.)
+        const uint32_t stg = !ACROSS ? fill_off + wave * STAGING : wave < 3 ? fill_off + A_STAGE + wave * STAGING : OFF_STAGING;
         if (UNALIGNED || (vec8 && !acc_out && N < kMaxTileN)) {
             // ---- N a multiple of 8, tiles at the edges included (see output_tile): no predicates; channel vectors fetched one register group ahead; the bf16 tile
             // is transposed through LDS, 32 tokens x 64 channels at a time, into whole-line streaming stores
@@ -541,34 +550,24 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
             if constexpr (UNALIGNED) fill_vector_tail<BM, BN>(s_tile, bias, w_zero, lane, n0, N);
             // Four specializations (zero-points, bias), chosen once per tile: inside the unrolled units a run-time
             // test costs a branch each, and a lone wave per SIMD pays every taken branch with an idle front end.
-            auto interior = [&] __device__(auto has_zero, auto has_bias) __attribute__((always_inline)) {
+            auto interior = [&] __device__(auto has_bias) __attribute__((always_inline)) {
                 // (scale, then add the bias, each rounded: a fused multiply-add would differ from the per-element path in the last bit)
 #pragma clang fp contract(off)
-                constexpr bool ZP = decltype(has_zero)::value, BIAS = decltype(has_bias)::value;
+                constexpr bool BIAS = decltype(has_bias)::value;
                 int lane_e = lane;   // (keeps the epilogue's lane-dependent addresses out of the K loop's registers)
                 asm volatile("" : "+v"(lane_e));
                 const int frow = lane_e & 31, fhalf = lane_e >> 5;
                 const float *ws_l = s_ws + wn + fhalf * 4;
                 const uint32_t *bias_l = reinterpret_cast<const uint32_t *>(s_tile + OFF_BIAS) + (wn + fhalf * 4) / 2;
-                const uint32_t *zero_l = reinterpret_cast<const uint32_t *>(s_tile + OFF_ZERO) + (wn + fhalf * 4) / 4;
-                // token scale folded with the accumulator's power-of-two unit (exact); with zero-points the
-                // integer accumulator is formed first
-                float xs_l[TM];
-                int rsum[TM];
+                float xs_l[TM];   // token scale folded with the accumulator's power-of-two unit (exact)
 #pragma unroll
-                for (int j = 0; j < TM; ++j) {
-                    const float xs = s_xs[wm + j * 32 + frow];
-                    if constexpr (FP6) xs_l[j] = ZP ? xs : xs * kFp6Unit;
-                    else xs_l[j] = xs * (1.f / (float)(1 << SHIFT));
-                    rsum[j] = ZP ? s_rsum[wm + j * 32 + frow] : 0;
-                }
+                for (int j = 0; j < TM; ++j) xs_l[j] = s_xs[wm + j * 32 + frow] * kUnit;
                 const int rd_row = lane_e >> 3, rd_piece = lane_e & 7;
-                struct ChannelVec { float4 ws; uint2 bb; uint32_t zq; };
+                struct ChannelVec { float4 ws; uint2 bb; };
                 auto fetch = [&] __device__(ChannelVec &cv, int i, int g) {
                     const int c = i * 32 + g * 8;
                     cv.ws = *reinterpret_cast<const float4 *>(ws_l + c);
                     if constexpr (BIAS) cv.bb = *reinterpret_cast<const uint2 *>(bias_l + c / 2);
-                    if constexpr (ZP) cv.zq = zero_l[c / 4];
                 };
                 // The 8 channel vectors of a pair of MFMA tile columns serve all TM token blocks: fetched once per pair
                 // into registers (the operand fragments' registers are free here), not once per unit.
@@ -597,14 +596,8 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                     float o[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        if constexpr (ZP) {
-                            const int z = (int)(int8_t)(c.zq >> (8 * e));
-                            if constexpr (FP6) o[e] = (float)unzero((int)(__int_as_float(raw[e]) * kFp6Unit), z, rsum[j]) * xs_l[j];
-                            else o[e] = (float)unzero(raw[e], z * (1 << SHIFT), rsum[j]) * xs_l[j];
-                        } else {
-                            if constexpr (FP6) o[e] = __int_as_float(raw[e]) * xs_l[j];
-                            else o[e] = (float)raw[e] * xs_l[j];
-                        }
+                        if constexpr (FP6) o[e] = __int_as_float(raw[e]) * xs_l[j];
+                        else o[e] = (float)raw[e] * xs_l[j];
                     }
                     o[0] *= c.ws.x;
                     o[1] *= c.ws.y;
@@ -628,7 +621,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                             pk[1][d] = sw[1];
                         }
                         const int piece = ii * 4 + g + fhalf;   // 16-byte piece of the 64-channel row
-                        *reinterpret_cast<uint4 *>(stg + frow * 128 + ((piece ^ (frow & 7)) << 4)) =
+                        *reinterpret_cast<uint4 *>(smem + stg + frow * 128 + ((piece ^ (frow & 7)) << 4)) =
                             make_uint4(pk[0][0], pk[0][1], pk[1][0], pk[1][1]);
                     }
                     // A staged chunk is read back right away (its LDS round trip then runs under the next chunk's
@@ -646,7 +639,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                         pend_off = col_off + j * 64 * N;
                         pend_m = m0 + wm + j * 32 + rd_row;
                         pend_n = n0 + wn + ip * 64 + rd_piece * 8;
-                        const uint8_t *sg = stg;
+                        const uint8_t *sg = smem + stg;
 #pragma unroll
                         for (int pass = 0; pass < 4; ++pass) {
                             const int row = pass * 8 + rd_row;
@@ -658,12 +651,134 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                 });
                 store_pending();   // the last chunk
             };
+            auto interior_zp = [&] __device__(auto has_bias) __attribute__((always_inline)) {
+                // (scale, then add the bias, each rounded: a fused multiply-add would differ from the per-element path in the last bit)
+#pragma clang fp contract(off)
+                constexpr bool BIAS = decltype(has_bias)::value;
+                int lane_e = lane;   // (keeps the epilogue's lane-dependent addresses out of the K loop's registers)
+                asm volatile("" : "+v"(lane_e));
+                const int frow = lane_e & 31, fhalf = lane_e >> 5;
+                // With zero-points the tile is transposed before it is converted, not after: a lane then has the same 8 channels for all its
+                // tokens of a pair of MFMA tile columns, whose step sizes, biases and zero-points it unpacks once, and the accumulators go
+                // to LDS as they are, without a read into vector registers or an exchange of lane halves: 10 vector instructions per
+                // four values with FP6 codes, and both vectors, where it were 27.  Twice the bytes through LDS are what it costs: without zero-points
+                // it is level (with a bias) or 2 to 3 % slower.  GEMM alone, us: FP6 32760 x 1536 x 4608 152.6 -> 141.7, without bias
+                // 146.5 -> 138.5, 60000 x 3072 x 3072 300.4 -> 288, 20000 x 1536 x 3080 85.3 -> 80.6; int8 32760 x 1536 x 8960 464 -> 459.
+                // A chunk of 32 tokens x 64 channels is staged as the accumulators hold it, 32 bits a value: 256 bytes a token, 16-byte
+                // pieces, piece index xor-ed with the token's lower four bits.  Write: four registers (4 channels of token
+                // frow) at piece 8 ii + 2 g + fhalf; 16 lanes fill 16 different pieces.  Read: the two pieces of the 8 channels
+                // rd_piece of token rd_row + 8 pass; 8 lanes of one token and 8 of the next, whose pieces differ in the lowest bit.
+                const uint32_t at_w = stg + frow * 256 + ((fhalf ^ (frow & 15)) << 4);
+                const int rd_row = lane_e >> 3, rd_piece = lane_e & 7;
+                const uint32_t at_r = stg + rd_row * 256 + (((rd_piece * 2) ^ rd_row) << 4);
+                uint32_t w_at[8], r_at[4];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) w_at[u] = smem_base + (at_w ^ (u * 32));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) r_at[u] = at_r ^ ((u >> 1) * 128 + (u & 1) * 16);
+                // registers 4 (U % 4) .. + 3 of MFMA tile (2 ip + U / 4, j) of chunk C = ip TM + j
+                auto stage = [&] __device__(auto c_c, auto u_c) __attribute__((always_inline)) {
+                    constexpr int C = decltype(c_c)::value, U = decltype(u_c)::value;
+                    write_acc4<(2 * (C / TM) + U / 4) * TM + C % TM, U % 4>(w_at[U]);
+                };
+                v4i raw[2][4][2];   // by chunk parity, pass, half of the 8 channels
+                auto fetch_pass = [&] __device__(v4i (&r)[2], int pass) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        r[h] = *reinterpret_cast<const v4i *>(smem + r_at[(pass & 1) * 2 + h] + pass * 2048);
+                };
+                // this lane's channels: 8 of a pair of MFMA tile columns, the same for all its tokens
+                struct ChannelVec { float4 ws[2]; uint4 bb; uint2 zq; };
+                auto fetch_channels = [&] __device__(ChannelVec &v, int ip) __attribute__((always_inline)) {
+                    const int c = wn + ip * 64 + rd_piece * 8;
+                    v.ws[0] = *reinterpret_cast<const float4 *>(s_ws + c);
+                    v.ws[1] = *reinterpret_cast<const float4 *>(s_ws + c + 4);
+                    if constexpr (BIAS) v.bb = *reinterpret_cast<const uint4 *>(s_tile + OFF_BIAS + c * 2);
+                    v.zq = *reinterpret_cast<const uint2 *>(s_tile + OFF_ZERO + c);
+                };
+                static_for<8>([&](auto u_c) __attribute__((always_inline)) { stage(I<0>{}, u_c); });
+                static_for<4>([&](auto p_c) __attribute__((always_inline)) { fetch_pass(raw[0][decltype(p_c)::value], decltype(p_c)::value); });
+                ChannelVec next;
+                fetch_channels(next, 0);
+                // token scale folded with the accumulator's power-of-two unit (exact); code sums in that unit as well
+                // (FP6: fp32, exact: the sums are below 2^24)
+                float xs_l[TM][4], rs_f[TM][4];
+                int rs_i[TM][4];
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) {
+                        const int m = wm + j * 32 + p * 8 + rd_row;
+                        xs_l[j][p] = s_xs[m] * kUnit;
+                        rs_i[j][p] = s_rsum[m];
+                        rs_f[j][p] = (float)rs_i[j][p] * (1.f / kFp6Unit);
+                    }
+                const __amdgpu_buffer_rsrc_t tile = output_tile(y, m0, n0, M, N, BM);
+                uint4 out[2][4];                      // a finished chunk, stored half a chunk later
+                uint32_t pend_off = 0, col_off = 0;   // byte offsets within the tile: of that chunk; of this lane's channels
+                int pend_m = 0, pend_n = 0;           // UNALIGNED: this lane's first row and channel of that chunk
+                auto store_pending = [&] __device__(const uint4 (&v)[4]) __attribute__((always_inline)) {
+                    if constexpr (UNALIGNED) store_chunk_unaligned(y, pend_m, pend_n, M, N, v);
+                    else store_chunk<STORE>(tile, pend_off, N, v);
+                };
+                float ws[8], bias_f[8], nz_f[8];
+                int nz_i[8];
+                constexpr int CHUNKS = TN / 2 * TM;
+                // Eight units a chunk: unit U = 2 pass + half finishes 4 values a lane; the first two stage the next chunk (a wave's
+                // LDS instructions execute in order: behind the reads of this one), the next four read it back, so that the LDS
+                // round trip runs under this chunk's arithmetic.
+                static_for<CHUNKS * 8>([&](auto u_c) __attribute__((always_inline)) {
+                    constexpr int C = decltype(u_c)::value / 8, U = decltype(u_c)::value % 8, j = C % TM, ip = C / TM, pass = U / 2, h = U & 1;
+                    if constexpr (U == 0 && j == 0) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            ws[e] = e < 4 ? (&next.ws[0].x)[e & 3] : (&next.ws[1].x)[e & 3];
+                            if constexpr (BIAS) {
+                                const uint32_t b = (&next.bb.x)[e / 2];
+                                bias_f[e] = __uint_as_float(e & 1 ? b & 0xFFFF0000u : b << 16);
+                            }
+                            const int z = (int)(int8_t)((e < 4 ? next.zq.x : next.zq.y) >> (8 * (e & 3)));
+                            nz_f[e] = -(float)z;
+                            nz_i[e] = -z * (1 << SHIFT);
+                        }
+                        col_off = n0 + wn + ip * 64 + rd_piece * 8 < N ? ((wm + rd_row) * N + wn + ip * 64 + rd_piece * 8) * 2 : kPastTile;
+                    }
+                    if constexpr (U == 6 && j == TM - 1 && C + 1 < CHUNKS) fetch_channels(next, ip + 1);
+                    const v4i r = raw[C & 1][pass][h];
+                    float o[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        // sum q (c - z) = acc - z * rs: exact in a 24-bit multiply and in an fp32 fma alike (ranges: C ABI)
+                        float v;
+                        if constexpr (FP6) v = __builtin_fmaf(nz_f[h * 4 + e], rs_f[j][pass], __int_as_float(r[e]));
+                        else v = (float)(r[e] + __mul24(nz_i[h * 4 + e], rs_i[j][pass]));
+                        o[e] = v * xs_l[j][pass] * ws[h * 4 + e];
+                        if constexpr (BIAS) o[e] += bias_f[h * 4 + e];
+                    }
+                    uint4 &d = out[C & 1][pass];
+                    (h ? d.z : d.x) = pack_bf16x2(o[0], o[1]);
+                    (h ? d.w : d.y) = pack_bf16x2(o[2], o[3]);
+                    if constexpr (C + 1 < CHUNKS) {
+                        if constexpr (U < 2) static_for<4>([&](auto v_c) __attribute__((always_inline)) { stage(I<C + 1>{}, I<U * 4 + decltype(v_c)::value>{}); });
+                        else if constexpr (U < 6) fetch_pass(raw[(C + 1) & 1][U - 2], U - 2);
+                    }
+                    if constexpr (C == 1 && U == 3) publish_draw();
+                    if constexpr (C > 0 && U == 3) store_pending(out[(C - 1) & 1]);
+                    if constexpr (U == 7) {
+                        pend_off = col_off + j * 64 * N;
+                        pend_m = m0 + wm + j * 32 + rd_row;
+                        pend_n = n0 + wn + ip * 64 + rd_piece * 8;
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                store_pending(out[(CHUNKS - 1) & 1]);   // the last chunk
+            };
             if (w_zero) {
-                if (bias) interior(std::true_type{}, std::true_type{});
-                else interior(std::true_type{}, std::false_type{});
+                if (bias) interior_zp(std::true_type{});
+                else interior_zp(std::false_type{});
             } else {
-                if (bias) interior(std::false_type{}, std::true_type{});
-                else interior(std::false_type{}, std::false_type{});
+                if (bias) interior(std::true_type{});
+                else interior(std::false_type{});
             }
         } else {
             // ---- N not a multiple of 8 (without STORE_UNALIGNED), kMaxTileN and more, or the accumulator hook: predicated per element, through the
@@ -768,7 +883,7 @@ template <bool FP6, bool ACROSS, StoreKind STORE>
 int launch_wide(const uint8_t *codes, const float *x_scale, const uint8_t *w, const float *w_scale, const int8_t *w_zero,
                 const int32_t *code_rowsum, const uint16_t *bias, int M, int N, int K, uint16_t *y, int32_t *acc_out,
                 hipStream_t stream) {
-    constexpr int BM = 256, BN = 256, STAGES = 3;
+    constexpr int BM = 256, BN = 256;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     // Column tiles per L2 sharing group (the 32 workgroups of an XCD then work on about 32 / group_n token panels
     // x group_n channel panels at a time, so a width near 6 pulls the fewest panels through the XCD's L2).
@@ -791,7 +906,7 @@ int launch_wide(const uint8_t *codes, const float *x_scale, const uint8_t *w, co
     int grid = 256;
     if (total < grid) grid = (total + 7) / 8 * 8;
     grid = limited_grid(grid);
-    const size_t smem = (size_t)STAGES * 48 * 1024 + 3 * ((BM + BN) * 4 + BN * 2 + BM * 4 + BN) + 8 * sizeof(int);
+    const size_t smem = wide_lds_bytes(ACROSS);
     auto k = w4ax_gemm_wide_kernel<FP6, ACROSS, STORE>;
     static std::atomic<uint64_t> configured{0};
     allow_dynamic_lds(reinterpret_cast<const void *>(k), smem, configured);
