@@ -382,14 +382,14 @@ int launch_rotate_quant(const uint16_t *x, int64_t M, int64_t K, int log2_block,
     const int units = (int)((K + kUnit - 1) / kUnit);
     // Waves per row: at most 4 units (32 fp32 values per lane) in registers per wave, never 3 waves, whole waves
     // per SIMD beyond 4, at most 16.  Workgroups of 8 waves, of 16 once a row takes 8 (two such rows then share a
-    // workgroup and its barrier), 16 waves resident per compute unit (256 of them), every workgroup striding over
+    // workgroup and its barrier), 16 or 24 waves resident per compute unit (256 of them), every workgroup striding over
     // the rows.  Swept with the kernel timed where the layer runs it, between two GEMMs, over units per wave
     // (3 .. 8) and workgroups of 8 and 16 waves, rows of 2048 .. 16384 channels, both containers: rows of 4, 8 and
     // 16 units are 6-17 % faster as one, two and four waves of 4 units than in waves of 3 or fewer; 12 units are
     // 4 % slower as three waves of 4 than as four of 3; a 13824-channel row (27 units) takes 225 us per launch as
     // eight waves of 3-4 units in 16-wave workgroups, 238 in 8-wave workgroups, 252 as twelve waves of 2-3 units
-    // (an earlier state of this rule, chosen from launches timed back to back).  Resident waves (8 .. 28) and
-    // smaller workgroups stay within 2 % of this on the video-DiT shapes.
+    // (an earlier state of this rule, chosen from launches timed back to back).  Smaller workgroups stay within 2 % of
+    // this on the video-DiT shapes.
     int W = (units + 3) / 4;
     if (W == 3) W = 4;
     if (W > 4) W = (W + 3) / 4 * 4;   // whole waves per SIMD
