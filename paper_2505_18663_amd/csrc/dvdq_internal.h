@@ -49,12 +49,13 @@ bool drawing_enabled();                 // the benchmark hook
 // 2500 large tiles that these kernels take (int8, packed and FP6 codes, 2 to 48 slices, drawn and captured) small tiles have 0.84 to 0.87 of the
 // time there in the mean, at most 1.10: below one round 0.67 to 0.88 (7800 x 1536 x 1440 int8 23.8 -> 21.9 us, packed 23.1 -> 20.0, 90678 x 896
 // x 640 75.1 -> 63.0, FP6 2048 x 768 x 3072 10.6 -> 8.9, canonical 6200 x 1440 x 1440 24.2 -> 22.4), from 1.02 rounds on 0.75 to 0.96.  Where they
-// take a round more: 0.86 to 1.13.  Not in a second round that is at most half full of large tiles and more than two thirds full of
-// small ones, from 20 slices on: 1.01 to 1.04 there (int8 to canonical), up to 1.10, 0.90 to 0.99 with fewer slices.
+// take a round more: 0.86 to 1.13.  Not in a last round that is at most half full of large tiles and more than two thirds full of
+// small ones, from 20 slices on in the second round (1.01 to 1.04 there, int8 to canonical, up to 1.10; 0.90 to 0.99 with fewer slices) and
+// from 48 on later (20912 x 13568 x 1664 int8 571 and 583 us; 0.88 to 1.00 with fewer).
 inline bool narrow_tiles(int64_t M, int64_t N, int64_t K) {
     const int64_t rows = (M + 127) / 128, large = rows * ((N + 255) / 256), small = rows * ((N + 127) / 128);
     if ((small + 767) / 768 > (large + 511) / 512) return false;
-    return !(K / 128 >= 20 && large > 512 && large <= 768 && (small - 1) % 768 >= 512);
+    return !(large > 512 && (large - 1) % 512 < 256 && (small - 1) % 768 >= 512 && K / 128 >= (large <= 1024 ? 20 : 48));
 }
 // whether the large kernels store their tiles as whole lines, with 32-bit offsets
 constexpr int64_t kMaxTileN = (int64_t)1 << 22;

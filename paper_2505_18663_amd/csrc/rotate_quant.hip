@@ -404,7 +404,10 @@ int launch_rotate_quant(const uint16_t *x, int64_t M, int64_t K, int log2_block,
     // 4096 x 3072 10.2 -> 9.6, 20000 x 1152 packed 14.5 -> 13.5, 100000 x 512 33.5 -> 29.5, 100000 x 256 int8 25.3 -> 21.6).  With three units and
     // more than 8 rows a slot it is level, up to 5 % slower (118800 x 3072 201 -> 213); four units or more leave no registers for 24
     // (8000 x 3584 block-wise 21.1 -> 23.2); 32 are behind 24 nearly everywhere, and behind 16 for most.
-    const int resident = pack4 != 3 && (cpw <= 2 || (cpw == 3 && M * W <= 8 * 256 * 16)) ? 24 : 16;
+    // Below a row for each of the 24 waves' slots the second row that some of 16 waves take costs less than the additional workgroups
+    // (5000 x 512 4.5 -> 4.9, 6000 x 640 packed 4.9 -> 5.2).
+    const bool many = cpw <= 2 || (cpw == 3 && M * W <= 8 * 256 * 16);
+    const int resident = pack4 != 3 && many && M * W >= 256 * 24 ? 24 : 16;
     int wgs_per_cu = resident / (W * rows_per_wg);
     if (wgs_per_cu < 1) wgs_per_cu = 1;
     // FP6: consecutive rows a wave takes in turn (see the kernel): 1, 2, 4 or 8, the largest run that the LDS for collecting

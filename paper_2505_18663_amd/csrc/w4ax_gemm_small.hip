@@ -524,9 +524,10 @@ __global__ __launch_bounds__(64 * NW, DEPTH == 2 ? 1 : 2) void w4ax_gemm_small_k
                 }
         __syncthreads();
         // (unrolled, so that the reads of a thread's pieces run beside each other: 2800 of the kernel's 16500 clocks went to these sums at
-        // 300 x 3072 x 3072; 512 x 3072 x 3072 int8 11.6 -> 10.5 us, 512 x 1536 x 3072 8.6 -> 7.4.  With several pieces a thread, what is not there --
+        // 300 x 3072 x 3072; 512 x 3072 x 3072 int8 11.6 -> 10.5 us, 512 x 1536 x 3072 8.6 -> 7.4.  With more than two pieces a thread, what is not there --
         // zero-points, bias -- is chosen once: a branch in each piece keeps the reads apart (1560 x 1536 x 1536 packed 10.0 -> 9.4, 3121 x 1152 x
-        // 1160 10.3 -> 9.8).  With one, and with canonical weights, it is branched around: there the copies of the code cost 1 to 2 %)
+        // 1160 10.3 -> 9.8).  With two at most, with canonical weights and with FP6 codes it is branched around: there the copies of the code
+        // cost up to 4 %: 700 x 1536 x 2304 int8 8.4 and 8.7)
         constexpr int ITEMS = (BM * PIECES + 64 * NW - 1) / (64 * NW);
         constexpr bool SAME_CHANNELS = 64 * NW % PIECES == 0;   // of all of a thread's pieces
         typedef typename std::conditional<FP6, v4f_t, v4i>::type Q;
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(64 * NW, DEPTH == 2 ? 1 : 2) void w4ax_gemm_small_k
                     if (n0 + c + e < N) acc_out[at + e] = P::sum(a[e]);
             }
         };
-        if constexpr (ITEMS == 1 || CANONICAL) {
+        if constexpr (ITEMS <= 2 || CANONICAL || (FP6 && DEPTH == 1)) {
 #pragma unroll
             for (int item = 0; item < ITEMS; ++item) {
                 const int it = tid + item * 64 * NW;

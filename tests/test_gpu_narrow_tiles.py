@@ -58,7 +58,8 @@ def test_narrow_tiles(fmt, M, K, N):
 @pytest.mark.parametrize("M,N,K,narrow", [(7800, 1440, 1440, True), (15600, 1536, 1536, True), (32760, 1536, 1536, False), (128 * 64, 1536, 1536, True),
                                           (128 * 64 + 1, 1536, 1536, False), (128 * 86, 1536, 1536, True), (128 * 128, 1536, 1536, True),
                                           (128 * 128 + 1, 1536, 1536, False), (128 * 86, 1536, 2560, True), (128 * 107, 1536, 2560, False),
-                                          (128 * 107, 1536, 2432, True), (90678, 640, 896, True), (118800, 640, 1536, False)])   # (the last: 7 rounds for 6)
+                                          (128 * 107, 1536, 2432, True), (20912, 1664, 13568, False), (20912, 1664, 128 * 47, True), (90678, 640, 896, True), (118800, 640, 1536, False)])   # (the last: 7 rounds for 6)
 def test_where_they_are_taken(M, N, K, narrow):
-    """A round of 768 small tiles for one of 512 large ones; a second round of up to half large and over two thirds small ones below 20 slices."""
+    """A round of 768 small tiles for one of 512 large ones; a last round of up to half large and over two thirds small ones below 20 slices
+    in the second, below 48 later."""
     assert dvdq.bench_narrow_tiles(M, N, K) == narrow
