@@ -57,6 +57,27 @@ inline bool narrow_tiles(int64_t M, int64_t N, int64_t K) {
     if ((small + 767) / 768 > (large + 511) / 512) return false;
     return !(large > 512 && (large - 1) % 512 < 256 && (small - 1) % 768 >= 512 && K / 128 >= (large <= 1024 ? 20 : 48));
 }
+// 128 x 128 tiles (narrow_tiles takes them for all of these) for outputs of the largest of the small shapes, a wave or two per 64 x 128 tile.
+// Both run in one round, so what counts is the fullest compute unit: two large tiles against three small ones, 256 rows to 192, up to 768 small
+// tiles, against four beyond, and there are fewer bytes to read with the large ones.  Whole layers, large over small by the number of
+// slices, in the mean (worst), N a multiple of 8 / any other N (tiles that are stored unaligned):
+//   up to 768   int8    below 10: 0.95 to 0.98 (1.07), from 10 on 0.99 to 1.08 (1.13)  /  0.98 to 1.07 (1.14)
+//               packed  below 6: 0.96 to 0.97 (1.06), 6 and 7 from 321 large tiles on 0.98, from 8 on 0.99 to 1.01 (1.07)  /  0.98 to 1.03 (1.07)
+//               FP6     below 6: 0.93 to 0.96 (1.06), from 6 on 0.99 to 1.03 (1.10)  /  below 4: 0.95 to 0.98 (1.05), from 4 on 0.99 to 1.04 (1.12)
+//   beyond      int8    0.90 to 0.98 (1.06)                                       /  one slice 0.99 (1.05), then 0.94 to 0.99 (1.07)
+//               packed  below 10: 0.92 to 0.97 (1.05), 10 and 11 0.99 (1.05)      /  below 6: 0.95 to 0.98 (1.04), from 6 on 0.99 to 1.01 (1.07)
+// 3000 outputs of int8 codes, 2600 packed, 3500 FP6 (5000 x 1536 x 1536 int8 19.4 -> 16.8 us the GEMM alone; with small tiles as before: 263 x
+// 2304 x 13637 int8 23.6 us the layer, 25.2 with large ones, 615 x 1024 x 6561 FP6, two GEMMs, 24.3 and 27.2, 676 x 5376 x 8696 int8 45.3 and 51.0).
+inline bool narrow_for_small_outputs(int64_t M, int64_t N, int64_t K, int codes_format) {
+    const int64_t columns = (N + 127) / 128, large = ((M + 127) / 128) * columns, slices = K / 128;
+    const bool beyond = ((M + 63) / 64) * columns > 768, aligned = (N & 7) == 0;
+    if (large > 512) return false;   // (more than two on a compute unit)
+    switch (codes_format) {
+        case DVDQ_CODES_INT8: return beyond ? aligned || slices > 1 : aligned && slices < 10;
+        case DVDQ_CODES_PACKED4: return slices < (beyond ? (aligned ? 10 : 6) : aligned ? (large > 320 ? 8 : 6) : 0);
+        default: return slices < (aligned ? 6 : 4);
+    }
+}
 // whether the large kernels store their tiles as whole lines, with 32-bit offsets
 constexpr int64_t kMaxTileN = (int64_t)1 << 22;
 inline bool whole_line_tiles(int64_t N) { return (N & 7) == 0 && N < kMaxTileN; }

@@ -413,9 +413,7 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
 // vectors 70.1 and 65.8 at 3072; 32760 x 4612: 197 and 187 at 1280, 1344 and 1006 at 13824).
 int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors, bool drawn) {
     const int shape = small_gemm_shape(M, N, K, true);
-    // (against the largest of the small shapes 128 x 128 tiles have 0.88 to 0.96 of its time up to eleven slices, 1.05 to 1.19 beyond: 2048 x 768 x
-    // 3072 10.8 -> 8.9 us)
-    if (shape == 5 && K / kBK < 12 && ((M + 127) / 128) * ((N + 127) / 128) <= 512) return 1;
+    if (shape == 5 && narrow_for_small_outputs(M, N, K, DVDQ_CODES_FP6)) return 1;
     if (shape >= 0) return kFirstSmallVariant + shape;
     if (whole_line_tiles(N)) {
         const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;

@@ -707,14 +707,7 @@ int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_la
         const bool one_round = ((M + 63) / 64) * ((N + 127) / 128) <= 2048;
         return one_round && ((M + 127) / 128) * ((N + 255) / 256) > 512 ? kCanonicalShape6Variant : kCanonicalVariant;
     }
-    // (the largest of the small shapes, a wave or two per 64 x 128 tile, against 128 x 128 tiles (narrow_tiles) by their number: int8 0.82 to 0.99
-    // of its time below 20 slices and 0.93 from 385 tiles on; packed codes, half the operand bytes, 0.87 to 0.96 below six slices, 0.91 to 0.98
-    // up to eleven from 321 tiles on; else 0.98 to 1.17.  5000 x 1536 x 1536 int8 19.4 -> 16.8 us, 1291 x 384 x 5128 11.9 -> 10.8)
-    if (shape == 5) {
-        const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), slices = K / 128;
-        const bool pays = codes_format == DVDQ_CODES_INT8 ? slices < 20 || tiles > 384 : slices < 6 || (slices < 12 && tiles > 320);
-        if (w_layout != DVDQ_W_CANONICAL && tiles <= 512 && pays) return 2;
-    }
+    if (shape == 5 && w_layout != DVDQ_W_CANONICAL && narrow_for_small_outputs(M, N, K, codes_format)) return 2;
     if (shape == 7 && w_layout == DVDQ_W_CANONICAL) return kFirstSmallVariant + 3;   // (variant 17 is another thing there)
     if (shape >= 0) return kFirstSmallVariant + shape;
     if (codes_format != DVDQ_CODES_INT8 || K / 128 < 8 || !whole_line_tiles(N)) return 2;

@@ -42,3 +42,32 @@ def test_small_outputs_and_canonical_weights():
     assert dvdq.bench_gemm_choice(32760, 4608, 1440, INT8, CANONICAL) == 16
     assert dvdq.bench_gemm_choice(1, 64, 32, INT8, CANONICAL) == 10
     assert dvdq.bench_gemm_choice(0, 64, 128, INT8, NATIVE) == -2
+
+
+@pytest.mark.parametrize("codes,M,N,slices,tiles", [
+    # up to 768 tiles of 64 x 128 (shape 5): by depth and by N; 263 x 13568: 318 of 128 x 128, 530 of 64 x 128
+    ("int8", 263, 13568, 9, 128), ("int8", 263, 13568, 10, 64), ("int8", 263, 13568, 18, 64), ("int8", 263, 13569, 1, 64), ("int8", 263, 13569, 5, 64),
+    ("packed4", 263, 13568, 5, 128), ("packed4", 263, 13568, 6, 64), ("packed4", 263, 13569, 2, 64), ("packed4", 385, 10240, 7, 64), ("packed4", 385, 10368, 7, 128),
+    ("packed4", 385, 10368, 8, 64), ("fp6", 615, 6560, 5, 128), ("fp6", 615, 6560, 6, 64), ("fp6", 615, 6561, 3, 128), ("fp6", 615, 6561, 4, 64),
+    # beyond; 768 and 770 of 64 x 128
+    ("int8", 768, 8192, 9, 128), ("int8", 768, 8192, 40, 64), ("int8", 5 * 128, 77 * 128, 40, 128), ("int8", 5 * 128, 77 * 128 - 1, 40, 128),
+    ("int8", 5 * 128, 77 * 128 - 1, 1, 64), ("int8", 768, 8191, 5, 64), ("packed4", 5 * 128, 77 * 128, 9, 128), ("packed4", 5 * 128, 77 * 128, 10, 64),
+    ("packed4", 5 * 128, 77 * 128 - 1, 5, 128), ("packed4", 5 * 128, 77 * 128 - 1, 6, 64),
+    # more than 512 of 128 x 128, and the largest FP6 takes (95 of 256 x 256)
+    ("int8", 65 * 64, 15 * 128, 3, 128), ("int8", 63 * 64 + 1, 16 * 128, 3, 128), ("int8", 1, 128 * 1024, 3, 64), ("int8", 1, 128 * 512, 3, 32), ("fp6", 5 * 256, 19 * 256, 3, 128)])
+def test_128_x_128_tiles_for_small_outputs(codes, M, N, slices, tiles):
+    """The two-wave kernel with these tiles against the largest shape of the small-output kernel."""
+    fmt, layout, two_wave = {"int8": (INT8, NATIVE, 2), "packed4": (PACKED4, NATIVE, 2), "fp6": (FP6, NATIVE_FP6, 1)}[codes]
+    K = 128 * slices
+    choice = dvdq.bench_gemm_choice(M, N, K, fmt, layout)
+    assert choice == two_wave if tiles == 128 else choice >= 10
+    assert tiles != 64 or choice == 15
+    assert tiles != 128 or dvdq.bench_narrow_tiles(M, N, K)
+    if codes == "int8" and tiles < 128:
+        assert dvdq.bench_gemm_choice(M, N, K, INT8, CANONICAL) == choice
+
+
+@pytest.mark.parametrize("M,N", [(263, 13568), (768, 8192), (5 * 128, 77 * 128)])
+def test_canonical_weights_stay_with_64_x_128_tiles(M, N):
+    for slices in (1, 9, 40):
+        assert dvdq.bench_gemm_choice(M, N, 128 * slices, INT8, CANONICAL) == 15
