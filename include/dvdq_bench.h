@@ -50,8 +50,9 @@ int dvdq_bench_set_gemm_variant(int variant);
  * Sizes below 1: minus a dvdq_status code. */
 int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors);
 
-/* Where that is a two-wave kernel (2, FP6 1, canonical weights 16): 1 if it takes tiles of 128 x 128 (variant 6), 0 if 128 x 256. */
-int dvdq_bench_narrow_tiles(int64_t M, int64_t N, int64_t K);
+/* Where that is a two-wave kernel (2, FP6 1, canonical weights 16): 1 if it takes tiles of 128 x 128 (variant 6), 0 if 128 x 256.
+ * drawn: the launch draws its tiles from counters; 0: fixed shares, as under stream capture.  Sizes below 1 (K below 32): minus a dvdq_status code. */
+int dvdq_bench_narrow_tiles(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int drawn);
 
 /* Threads per workgroup with which dvdq_bgr_quantize takes the rows: 256, 512 or 1024 (host only).  Sizes below 1 (2 weights, 0
  * rounds): minus a dvdq_status code. */

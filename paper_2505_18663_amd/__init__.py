@@ -136,7 +136,7 @@ def lib() -> C.CDLL:
     L.dvdq_bench_set_gemm_grid_limit.restype = i32
     L.dvdq_bench_gemm_choice.argtypes = [i64, i64, i64, i32, i32, i32]
     L.dvdq_bench_gemm_choice.restype = i32
-    L.dvdq_bench_narrow_tiles.argtypes = [i64, i64, i64]
+    L.dvdq_bench_narrow_tiles.argtypes = [i64, i64, i64, i32, i32, i32]
     L.dvdq_bench_narrow_tiles.restype = i32
     L.dvdq_bench_bgr_choice.argtypes = [i64, i64, i32, i32]
     L.dvdq_bench_bgr_choice.restype = i32
@@ -542,9 +542,9 @@ def bench_gemm_choice(M: int, N: int, K: int, codes_format: int, w_layout: int, 
     return lib().dvdq_bench_gemm_choice(M, N, K, codes_format, w_layout, int(vectors))
 
 
-def bench_narrow_tiles(M: int, N: int, K: int) -> bool:
-    """Whether the two-wave kernels take 128 x 128 tiles for a product (host only)."""
-    return lib().dvdq_bench_narrow_tiles(M, N, K) == 1
+def bench_narrow_tiles(M: int, N: int, K: int, codes_format: int = CODES_INT8, w_layout: int = W_NATIVE, drawn: bool = False) -> bool:
+    """Whether the two-wave kernels take 128 x 128 tiles for a product, drawn from counters or in fixed shares (host only)."""
+    return lib().dvdq_bench_narrow_tiles(M, N, K, codes_format, w_layout, int(drawn)) == 1
 
 
 def bench_bgr_choice(N: int, K: int, n_steps: int = 100, max_refine: int = 10) -> int:

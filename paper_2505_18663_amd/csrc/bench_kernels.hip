@@ -179,9 +179,9 @@ int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, in
     return dvdq::w4ax_gemm_choice(M, N, K, codes_format, w_layout, vectors, dvdq::drawing_enabled());
 }
 
-int dvdq_bench_narrow_tiles(int64_t M, int64_t N, int64_t K) {
+int dvdq_bench_narrow_tiles(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int drawn) {
     if (M < 1 || N < 1 || K < 32) return -DVDQ_ERR_SHAPE;
-    return dvdq::narrow_tiles(M, N, K);
+    return dvdq::narrow_tiles(M, N, K, codes_format, w_layout, drawn != 0);
 }
 
 int dvdq_bench_bgr_choice(int64_t N, int64_t K, int n_steps, int max_refine) {

@@ -52,10 +52,36 @@ bool drawing_enabled();                 // the benchmark hook
 // take a round more: 0.86 to 1.13.  Not in a last round that is at most half full of large tiles and more than two thirds full of
 // small ones, from 20 slices on in the second round (1.01 to 1.04 there, int8 to canonical, up to 1.10; 0.90 to 0.99 with fewer slices) and
 // from 48 on later (20912 x 13568 x 1664 int8 571 and 583 us; 0.88 to 1.00 with fewer).
-inline bool narrow_tiles(int64_t M, int64_t N, int64_t K) {
-    const int64_t rows = (M + 127) / 128, large = rows * ((N + 255) / 256), small = rows * ((N + 127) / 128);
+// Canonical weights, half a cache line of a weight row per slice, have less to gain and lose more by code rows that are read again for each
+// column of tiles.  Whole layers, small over large, 4700 outputs, the cases that keep large tiles: one round, up to 256 channels from 24
+// slices on 1.03 (1.10 at most), up to 512 in 577 small tiles and more from 48 on 1.02 (1.06); two rounds, up to 256 channels from 12 on 1.02
+// (1.10), up to 384 from 36 on 1.01 (1.08); three and more, up to 384 channels from 26 on 1.02 (1.08) unless less than a quarter of the
+// last small round is there, else a last large round that is nearly empty, next to half a small one from 24 on 1.01 (1.10) or, drawn, next to one
+// three quarters full 1.03 (1.11; 0.94 with fixed shares, which deal a nearly empty round of large tiles to one XCD).  The rest 0.95 in the mean, 88 of 3500
+// above 1.03 (96274 x 4704 x 320 472 us with small, 436 with large tiles, 54984 x 7584 x 301 479 and 445).  int8 codes have the last of these from 36 slices on, 1.02
+// (1.04: 10020 x 4992 x 3352 194 and 187).
+inline bool narrow_tiles(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, bool drawn) {
+    const int64_t rows = (M + 127) / 128, columns = (N + 127) / 128, large = rows * ((N + 255) / 256), small = rows * columns, slices = K / 128;
     if ((small + 767) / 768 > (large + 511) / 512) return false;
-    return !(large > 512 && (large - 1) % 512 < 256 && (small - 1) % 768 >= 512 && K / 128 >= (large <= 1024 ? 20 : 48));
+    const int64_t last_large = (large - 1) % 512, last_small = (small - 1) % 768;
+    if (w_layout == DVDQ_W_CANONICAL) {
+        if (large <= 512) {
+            if (slices >= (columns <= 2 ? 24 : 48) && columns <= (small > 576 ? 4 : 2)) return false;
+        } else if (large <= 1024) {
+            if (columns <= 3 && slices >= (columns <= 2 ? 12 : 36)) return false;
+        } else {
+            if (columns <= 3 && slices >= 26 && last_small >= 192) return false;
+            if (last_small >= 576 ? drawn && last_large < 192 && slices >= 20 : last_small >= 384 && last_large < 64 && slices >= 24) return false;
+        }
+    } else if (codes_format == DVDQ_CODES_INT8) {
+        if (drawn && large > 1024 && last_large < 128 && last_small >= 576 && slices >= 36) return false;
+    }
+    return !(large > 512 && last_large < 256 && last_small >= 512 && slices >= (large <= 1024 ? 20 : 48));
+}
+// (asked of the stream only where the answer depends on it)
+inline bool narrow_tiles(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, hipStream_t stream) {
+    const bool if_drawn = narrow_tiles(M, N, K, codes_format, w_layout, true), if_fixed = narrow_tiles(M, N, K, codes_format, w_layout, false);
+    return if_drawn == if_fixed || tiles_drawn(stream) ? if_drawn : if_fixed;
 }
 // 128 x 128 tiles (narrow_tiles takes them for all of these) for outputs of the largest of the small shapes, a wave or two per 64 x 128 tile.
 // Both run in one round, so what counts is the fullest compute unit: two large tiles against three small ones, 256 rows to 192, up to 768 small

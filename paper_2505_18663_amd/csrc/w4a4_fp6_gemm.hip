@@ -439,7 +439,7 @@ int launch_w4a4_fp6_gemm(const uint8_t *codes, const float *x_scale, const uint8
         const int vectors = (bias != nullptr) + (w_zero != nullptr), fixed = w4a4_fp6_gemm_choice(M, N, K, vectors, false);
         v = w4a4_fp6_gemm_choice(M, N, K, vectors, true);
         if (fixed != v && !tiles_drawn(stream)) v = fixed;
-        if (v == 1 && narrow_tiles(M, N, K)) v = 6;
+        if (v == 1 && narrow_tiles(M, N, K, DVDQ_CODES_FP6, DVDQ_W_NATIVE_FP6, stream)) v = 6;
     }
     if (v >= kFirstSmallVariant)
         return launch_w4ax_gemm_small(codes, x_scale, w, w_scale, w_zero, code_rowsum, bias, M, N, K, DVDQ_CODES_FP6,

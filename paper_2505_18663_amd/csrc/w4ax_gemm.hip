@@ -735,7 +735,7 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
         // 5910 x 160 x 2680 18.5 and 15.6, 16734 x 1120 x 792 36.0 and 33.1), from 2050 waves on 1.01 to 1.4 (12021 x 64 x 1328 15.7 and 15.9).
 #define DVDQ_CANONICAL_ARGS codes, x_scale, w, w_scale, nullptr, nullptr, bias, (int)M, (int)N, (int)K, y, acc_out, stream
         const bool unaligned = unaligned_tiles(N) && !acc_out;
-        if (v == 6 || (f < 0 && narrow_tiles(M, N, K)))
+        if (v == 6 || (f < 0 && narrow_tiles(M, N, K, codes_format, w_layout, stream)))
             return unaligned ? launch_native<128, 128, 128, 2, 2, 2, 3, OPS_CANONICAL, STORE_UNALIGNED>(DVDQ_CANONICAL_ARGS)
                              : launch_native<128, 128, 128, 2, 2, 2, 3, OPS_CANONICAL>(DVDQ_CANONICAL_ARGS);
         return unaligned ? launch_native<128, 256, 128, 2, 2, 2, 2, OPS_CANONICAL, STORE_UNALIGNED>(DVDQ_CANONICAL_ARGS)
@@ -760,7 +760,7 @@ int launch_w4ax_gemm(const int8_t *codes, const float *x_scale, const uint8_t *w
         v = w4ax_gemm_choice(M, N, K, codes_format, w_layout, vectors, true);
         const int fixed = w4ax_gemm_choice(M, N, K, codes_format, w_layout, vectors, false);
         if (fixed != v && !tiles_drawn(stream)) v = fixed;
-        if (v == 2 && narrow_tiles(M, N, K)) v = 6;
+        if (v == 2 && narrow_tiles(M, N, K, codes_format, w_layout, stream)) v = 6;
     }
     if (v >= kFirstSmallVariant)
         return launch_w4ax_gemm_small(reinterpret_cast<const uint8_t *>(codes), x_scale, w, w_scale, w_zero, code_rowsum,

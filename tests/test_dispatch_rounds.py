@@ -67,6 +67,29 @@ def test_canonical_weights_beyond_the_small_outputs(M, N, variant):
         assert dvdq.bench_gemm_choice(M, N, K, dvdq.CODES_INT8, dvdq.W_CANONICAL) == variant
 
 
+def narrow(M, N, slices, canonical=True, drawn=True):
+    return dvdq.bench_narrow_tiles(M, N, 128 * slices, dvdq.CODES_INT8, dvdq.W_CANONICAL if canonical else dvdq.W_NATIVE, drawn)
+
+
+# one round (288 rows of 128: 576 small tiles in two columns), two, three
+@pytest.mark.parametrize("rows,N,first", [(300, 256, 24), (150, 500, 48), (144, 500, None), (200, 384, 48), (130, 640, None),
+                                          (600, 250, 12), (400, 384, 36), (300, 512, None), (600, 320, 26), (514, 384, None), (580, 384, 26)])
+@pytest.mark.parametrize("drawn", [True, False])
+def test_canonical_weights_keep_128_x_256_tiles_from(rows, N, first, drawn):
+    """The first depth, in slices, from which few columns keep the larger tiles; none up to 100 where tiles are few or columns many."""
+    taken = [narrow(128 * rows, N, s, drawn=drawn) for s in range(1, 101)]
+    assert taken == [first is None or s < first for s in range(1, 101)]
+
+
+@pytest.mark.parametrize("M,N,canonical,drawn,first", [
+    (128 * 115, 2304, True, True, 24), (128 * 58, 4992, True, True, 20), (128 * 58, 4992, True, False, 48), (128 * 52, 5000, True, True, 24), (128 * 52, 5000, True, False, 24),
+    (128 * 60, 4800, True, True, 20), (128 * 79, 3352, False, True, 36), (128 * 79, 3352, False, False, 48), (128 * 84, 3352, False, True, 48)])
+def test_a_nearly_empty_third_round_of_128_x_256_tiles(M, N, canonical, drawn, first):
+    """The first depth from which it is preferred to a third round of 128 x 128 tiles that is half or three quarters full."""
+    taken = [narrow(M, N, s, canonical, drawn) for s in range(1, 101)]
+    assert taken == [s < first for s in range(1, 101)]
+
+
 @pytest.mark.parametrize("K,n_steps,max_refine,threads", [(256, 50, 10, 512), (256, 80, 0, 256), (2048, 80, 0, 256), (2050, 80, 10, 512), (2050, 100, 3, 256),
                                                           (2050, 100, 2, 512), (4608, 100, 10, 256), (4610, 100, 10, 512), (4096, 20, 10, 512)])
 def test_offline_quantizer_with_at_most_two_rows_per_compute_unit(K, n_steps, max_refine, threads):
