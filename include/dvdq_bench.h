@@ -54,6 +54,9 @@ int dvdq_bench_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, in
  * drawn: the launch draws its tiles from counters; 0: fixed shares, as under stream capture.  Sizes below 1 (K below 32): minus a dvdq_status code. */
 int dvdq_bench_narrow_tiles(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int drawn);
 
+/* Waves per compute unit with which dvdq_rotate_quant takes the rows, 16 or 24 (host only).  Sizes below 1: minus a dvdq_status code. */
+int dvdq_bench_quantizer_waves(int64_t M, int64_t K, int codes_format);
+
 /* Threads per workgroup with which dvdq_bgr_quantize takes the rows: 256, 512 or 1024 (host only).  Sizes below 1 (2 weights, 0
  * rounds): minus a dvdq_status code. */
 int dvdq_bench_bgr_choice(int64_t N, int64_t K, int n_steps, int max_refine);

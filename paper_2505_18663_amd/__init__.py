@@ -35,7 +35,7 @@ EXPORTED_SYMBOLS = (
     "dvdq_rotate_quant", "dvdq_rotate_quant_blockwise", "dvdq_w4ax_gemm", "dvdq_qlinear", "dvdq_qlinear_workspace_bytes",
     "dvdq_qlinear_scale_offset", "dvdq_qlinear_rowsum_offset", "dvdq_qlinear_static", "dvdq_static_workspace_bytes", "dvdq_w4_prepack", "dvdq_w4_native_bytes", "dvdq_w4_prepack_fp6",
     "dvdq_w4_native_fp6_bytes", "dvdq_codes_bytes", "dvdq_status_string",
-    "dvdq_version", "dvdq_gbs_workspace_bytes", "dvdq_gbs_reset", "dvdq_gbs_step", "dvdq_bgr_quantize", "dvdq_bench_copy", "dvdq_bench_mfma_i8", "dvdq_bench_mfma_fp6", "dvdq_bench_set_gemm_variant", "dvdq_bench_set_gemm_schedule", "dvdq_bench_fill_tile_counters", "dvdq_bench_set_gemm_grid_limit", "dvdq_bench_set_gbs_wait", "dvdq_bench_gemm_choice", "dvdq_bench_narrow_tiles", "dvdq_bench_qlinear_choice", "dvdq_bench_bgr_choice", "dvdq_release_stream",
+    "dvdq_version", "dvdq_gbs_workspace_bytes", "dvdq_gbs_reset", "dvdq_gbs_step", "dvdq_bgr_quantize", "dvdq_bench_copy", "dvdq_bench_mfma_i8", "dvdq_bench_mfma_fp6", "dvdq_bench_set_gemm_variant", "dvdq_bench_set_gemm_schedule", "dvdq_bench_fill_tile_counters", "dvdq_bench_set_gemm_grid_limit", "dvdq_bench_set_gbs_wait", "dvdq_bench_gemm_choice", "dvdq_bench_narrow_tiles", "dvdq_bench_quantizer_waves", "dvdq_bench_qlinear_choice", "dvdq_bench_bgr_choice", "dvdq_release_stream",
 )
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -138,6 +138,8 @@ def lib() -> C.CDLL:
     L.dvdq_bench_gemm_choice.restype = i32
     L.dvdq_bench_narrow_tiles.argtypes = [i64, i64, i64, i32, i32, i32]
     L.dvdq_bench_narrow_tiles.restype = i32
+    L.dvdq_bench_quantizer_waves.argtypes = [i64, i64, i32]
+    L.dvdq_bench_quantizer_waves.restype = i32
     L.dvdq_bench_bgr_choice.argtypes = [i64, i64, i32, i32]
     L.dvdq_bench_bgr_choice.restype = i32
     L.dvdq_bench_qlinear_choice.argtypes = [vp, vp, vp, sz, i64, i64, i64]
@@ -545,6 +547,11 @@ def bench_gemm_choice(M: int, N: int, K: int, codes_format: int, w_layout: int, 
 def bench_narrow_tiles(M: int, N: int, K: int, codes_format: int = CODES_INT8, w_layout: int = W_NATIVE, drawn: bool = False) -> bool:
     """Whether the two-wave kernels take 128 x 128 tiles for a product, drawn from counters or in fixed shares (host only)."""
     return lib().dvdq_bench_narrow_tiles(M, N, K, codes_format, w_layout, int(drawn)) == 1
+
+
+def bench_quantizer_waves(M: int, K: int, codes_format: int) -> int:
+    """Waves per compute unit with which rotate_quant takes the rows.  Needs no GPU."""
+    return lib().dvdq_bench_quantizer_waves(M, K, codes_format)
 
 
 def bench_bgr_choice(N: int, K: int, n_steps: int = 100, max_refine: int = 10) -> int:

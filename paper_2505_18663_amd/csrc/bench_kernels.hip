@@ -184,6 +184,11 @@ int dvdq_bench_narrow_tiles(int64_t M, int64_t N, int64_t K, int codes_format, i
     return dvdq::narrow_tiles(M, N, K, codes_format, w_layout, drawn != 0);
 }
 
+int dvdq_bench_quantizer_waves(int64_t M, int64_t K, int codes_format) {
+    if (M < 1 || K < 1) return -DVDQ_ERR_SHAPE;
+    return dvdq::quantizer_waves(M, K, codes_format);
+}
+
 int dvdq_bench_bgr_choice(int64_t N, int64_t K, int n_steps, int max_refine) {
     if (N < 1 || K < 2 || n_steps < 1 || max_refine < 0) return -DVDQ_ERR_SHAPE;
     return dvdq::bgr_choice(N, K, n_steps, max_refine);

@@ -42,6 +42,8 @@ int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_la
 int w4a4_fp6_gemm_choice(int64_t M, int64_t N, int64_t K, int vectors, bool drawn);
 bool tiles_drawn(hipStream_t stream);   // false: the stream is being captured
 bool drawing_enabled();                 // the benchmark hook
+// waves of the row quantizer that are resident on a compute unit (rotate_quant.hip)
+int quantizer_waves(int64_t M, int64_t K, int codes_format);
 // The tiles of the two-wave kernels: 128 x 128, three workgroups per compute unit (true), or 128 x 256, two (false).  The larger tile
 // moves a quarter fewer operand bytes per product and has a round of 512 tiles done in some 26 us where 768 small ones take 21 (12 slices,
 // bias and zero-points): 7 % less per output.  What decides is the last round, in which compute units hold one large tile or two, one

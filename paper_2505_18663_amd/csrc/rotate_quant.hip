@@ -372,15 +372,42 @@ int launch_cpw(int cpw, dim3 grid, dim3 block, size_t smem, hipStream_t stream, 
     return check_launch();
 }
 
+// Waves of a row and units of 512 channels of a wave (the reasons: launch_rotate_quant)
+struct RowWaves {
+    int waves, units;
+    explicit RowWaves(int64_t K) {
+        const int all = (int)((K + kUnit - 1) / kUnit);
+        waves = (all + 3) / 4;
+        if (waves == 3) waves = 4;
+        if (waves > 4) waves = (waves + 3) / 4 * 4;   // whole waves per SIMD
+        if (waves > 16) waves = 16;
+        units = (all + waves - 1) / waves;
+    }
+};
+
 }  // namespace
+
+// 24 waves for int8 and packed codes where a wave has few units or few rows: with one row loading while one is worked on, a slot's
+// rows are as many round trips to memory (16 -> 24 waves, us: 15600 x 1536 int8 15.2 -> 15.0, block-wise 18.2 -> 16.9, 2000 x 5120 9.6 -> 8.6,
+// 4096 x 3072 10.2 -> 9.6, 20000 x 1152 packed 14.5 -> 13.5, 100000 x 512 33.5 -> 29.5, 100000 x 256 int8 25.3 -> 21.6).  With three units and
+// more than 8 rows a slot it is level, up to 5 % slower (118800 x 3072 201 -> 213); four units or more leave no registers for 24
+// (8000 x 3584 block-wise 21.1 -> 23.2); 32 are behind 24 nearly everywhere, and behind 16 for most.
+// Where some of the 24 waves' slots have one row and some two, the second row that some of 16 waves take costs less than the additional workgroups:
+// layers of 1 unit 1.01 times the time with 24 up to one and a half rows a slot, up to 1.05 (6172 x 384 x 118 9.3 and 9.7 us), of 2 units up to
+// a twelfth more than one (6192 x 896 x 112 11.7 and 12.2), 0.98 of 3 units from one on; below one row a slot 5000 x 512 4.5 and 4.9, 6000 x 640 packed 4.9 and 5.2.
+int quantizer_waves(int64_t M, int64_t K, int codes_format) {
+    const RowWaves row(K);
+    const int64_t rows = M * row.waves;
+    const bool many = row.units <= 2 || (row.units == 3 && rows <= 8 * 256 * 16);
+    return codes_format != DVDQ_CODES_FP6 && many && rows >= 256 * (row.units == 1 ? 36 : row.units == 2 ? 26 : 24) ? 24 : 16;
+}
 
 int launch_rotate_quant(const uint16_t *x, int64_t M, int64_t K, int log2_block, int act_bits, int codes_format,
                         int group_log2, int8_t *codes, float *x_scale, int32_t *code_rowsum, hipStream_t stream) {
     const int emax = group_log2 ? 8 - act_bits : 0;
     // 0: int8; 1 / 2: packed nibbles stored per lane / gathered through LDS; 3: FP6 container
     const int pack4 = codes_format == DVDQ_CODES_FP6 ? 3 : (codes_format != DVDQ_CODES_PACKED4 ? 0 : ((K % 32) == 0 ? 2 : 1));
-    const int units = (int)((K + kUnit - 1) / kUnit);
-    // Waves per row: at most 4 units (32 fp32 values per lane) in registers per wave, never 3 waves, whole waves
+    // Waves per row (RowWaves): at most 4 units (32 fp32 values per lane) in registers per wave, never 3 waves, whole waves
     // per SIMD beyond 4, at most 16.  Workgroups of 8 waves, of 16 once a row takes 8 (two such rows then share a
     // workgroup and its barrier), 16 or 24 waves resident per compute unit (256 of them), every workgroup striding over
     // the rows.  Swept with the kernel timed where the layer runs it, between two GEMMs, over units per wave
@@ -390,24 +417,13 @@ int launch_rotate_quant(const uint16_t *x, int64_t M, int64_t K, int log2_block,
     // eight waves of 3-4 units in 16-wave workgroups, 238 in 8-wave workgroups, 252 as twelve waves of 2-3 units
     // (an earlier state of this rule, chosen from launches timed back to back).  Smaller workgroups stay within 2 % of
     // this on the video-DiT shapes.
-    int W = (units + 3) / 4;
-    if (W == 3) W = 4;
-    if (W > 4) W = (W + 3) / 4 * 4;   // whole waves per SIMD
-    if (W > 16) W = 16;
-    const int cpw = (units + W - 1) / W;
+    const RowWaves row(K);
+    const int W = row.waves, cpw = row.units;
     if (cpw > 8) return DVDQ_ERR_UNSUPPORTED;
     const int wg_waves = W >= 8 ? 16 : 8;
     const int rows_per_wg = W >= wg_waves ? 1 : wg_waves / W;
     const dim3 block(kWave * W * rows_per_wg);
-    // 24 waves for int8 and packed codes where a wave has few units or few rows: with one row loading while one is worked on, a slot's
-    // rows are as many round trips to memory (16 -> 24 waves, us: 15600 x 1536 int8 15.2 -> 15.0, block-wise 18.2 -> 16.9, 2000 x 5120 9.6 -> 8.6,
-    // 4096 x 3072 10.2 -> 9.6, 20000 x 1152 packed 14.5 -> 13.5, 100000 x 512 33.5 -> 29.5, 100000 x 256 int8 25.3 -> 21.6).  With three units and
-    // more than 8 rows a slot it is level, up to 5 % slower (118800 x 3072 201 -> 213); four units or more leave no registers for 24
-    // (8000 x 3584 block-wise 21.1 -> 23.2); 32 are behind 24 nearly everywhere, and behind 16 for most.
-    // Below a row for each of the 24 waves' slots the second row that some of 16 waves take costs less than the additional workgroups
-    // (5000 x 512 4.5 -> 4.9, 6000 x 640 packed 4.9 -> 5.2).
-    const bool many = cpw <= 2 || (cpw == 3 && M * W <= 8 * 256 * 16);
-    const int resident = pack4 != 3 && many && M * W >= 256 * 24 ? 24 : 16;
+    const int resident = quantizer_waves(M, K, codes_format);
     int wgs_per_cu = resident / (W * rows_per_wg);
     if (wgs_per_cu < 1) wgs_per_cu = 1;
     // FP6: consecutive rows a wave takes in turn (see the kernel): 1, 2, 4 or 8, the largest run that the LDS for collecting

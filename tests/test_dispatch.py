@@ -71,3 +71,18 @@ def test_128_x_128_tiles_for_small_outputs(codes, M, N, slices, tiles):
 def test_canonical_weights_stay_with_64_x_128_tiles(M, N):
     for slices in (1, 9, 40):
         assert dvdq.bench_gemm_choice(M, N, 128 * slices, INT8, CANONICAL) == 15
+
+
+# units of 512 channels a wave: 1 in rows of up to 512, 2 up to 1024, 3 up to 1536 or, in four waves, 6144 (12 units), 4 up to 2048
+@pytest.mark.parametrize("K,waves_per_row,first,last", [(128, 1, 9216, None), (512, 1, 9216, None), (544, 1, 6656, None), (1024, 1, 6656, None), (1536, 1, 6144, 32768),
+                                                       (6144, 4, 6144, 32768), (2048, 1, None, None), (5120, 4, 6144, 32768), (4096, 2, None, None)])
+@pytest.mark.parametrize("codes_format", [INT8, PACKED4, FP6])
+def test_resident_waves_of_the_quantizer(K, waves_per_row, first, last, codes_format):
+    """24 from a number of rows per slot on, up to 8 rows a slot of 16 with three units; FP6 codes 16."""
+    waves = lambda rows: dvdq.bench_quantizer_waves(rows, K, codes_format)
+    if first is None or codes_format == FP6:
+        assert {waves(m) for m in (1, 1600, 6144, 9216, 118800)} == {16}
+        return
+    assert [waves(first // waves_per_row - 1), waves(first // waves_per_row)] == [16, 24]
+    assert waves(118800) == (24 if last is None else 16)
+    assert last is None or [waves(last // waves_per_row), waves(last // waves_per_row + 1)] == [24, 16]
