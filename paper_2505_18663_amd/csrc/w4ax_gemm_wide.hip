@@ -700,8 +700,9 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                 static_for<4>([&](auto p_c) __attribute__((always_inline)) { fetch_pass(raw[0][decltype(p_c)::value], decltype(p_c)::value); });
                 ChannelVec next;
                 fetch_channels(next, 0);
-                // token scale folded with the accumulator's power-of-two unit (exact); code sums in that unit as well
-                // (FP6: fp32, exact: the sums are below 2^24)
+                // The accumulator's power-of-two unit is folded into the token scales (INT8: 1/16) or the step sizes (FP6: 64; a token's scale, which
+                // comes from the data, may be anything up to 2^126), exact as long as the products stay normal numbers.  FP6: code sums in that
+                // unit as well, in fp32 (exact: they are below 2^24)
                 float xs_l[TM][4], rs_f[TM][4];
                 int rs_i[TM][4];
 #pragma unroll
@@ -709,7 +710,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
 #pragma unroll
                     for (int p = 0; p < 4; ++p) {
                         const int m = wm + j * 32 + p * 8 + rd_row;
-                        xs_l[j][p] = s_xs[m] * kUnit;
+                        xs_l[j][p] = FP6 ? s_xs[m] : s_xs[m] * kUnit;
                         rs_i[j][p] = s_rsum[m];
                         rs_f[j][p] = (float)rs_i[j][p] * (1.f / kFp6Unit);
                     }
@@ -733,6 +734,7 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
                             ws[e] = e < 4 ? (&next.ws[0].x)[e & 3] : (&next.ws[1].x)[e & 3];
+                            if constexpr (FP6) ws[e] *= kUnit;
                             if constexpr (BIAS) {
                                 const uint32_t b = (&next.bb.x)[e / 2];
                                 bias_f[e] = __uint_as_float(e & 1 ? b & 0xFFFF0000u : b << 16);

@@ -107,6 +107,22 @@ def test_wide_kernel_bias_and_zero_points(fp6):
             assert np.array_equal(acc.cpu().numpy().astype(np.int64), acc_or)
 
 
+@pytest.mark.parametrize("N", [520, 1030])
+def test_fp6_zero_points_and_the_largest_token_scales(N):
+    """Token scales beyond 2^122 next to ordinary ones: 64 times such a scale, the unit of the accumulators, is no finite number, while
+    sum * scale is one (sums of two products and their zero-points are below 2^5)."""
+    c = _case(300, 384, N, 4, N, True)
+    codes = np.sign(c["codes"]) * (np.arange(384) < 2).astype(np.int8)
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    c.update(c_dev=put(oracle.pack_fp6(codes)), rs=put(codes.astype(np.int32).sum(axis=1).astype(np.int32)), ws=c["ws"] * 2.0 ** -20)
+    c["xs"][::3] = 2.0 ** 122 + 2.0 ** 121 * c["xs"][::3].clamp(max=1.0)
+    zero = dict(w_zero=c["wz"], code_rowsum=c["rs"])
+    for extra in (zero, dict(bias=c["bias"], **zero)):
+        y_ref, y = _run(c, 1, **extra), _run(c, WIDE_FP6, **extra)
+        assert bool(torch.isfinite(y_ref).all())
+        assert torch.equal(y.view(torch.int16), y_ref.view(torch.int16))
+
+
 @pytest.mark.parametrize("fp6", [False, True])
 def test_wide_kernel_many_launches_in_a_row(fp6):
     """a launch must not count on from where the one before stopped: two shapes alternate on one stream, eight workgroups
