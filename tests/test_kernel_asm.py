@@ -10,6 +10,9 @@ would otherwise take care of; each is checked on the generated code:
 * no basic block of the K loops of the kernels the default dispatch takes may hold a wait for ALL outstanding
   vector memory operations: the compiler puts one in front of any copy of a pending atomic's reply (the tile
   draw), and inside the loop that undoes the load pipeline (it has: twice the time per slice).
+
+The accumulators of the wide kernels are AGPRs that only inline assembly names.  To the compiler they are free: short of
+vector registers it spills into them, silently and with wrong results (it has, at 256 VGPRs, without a count of spills).
 """
 import os
 import re
@@ -35,8 +38,8 @@ def _flags():
 
 
 @pytest.fixture(scope="module")
-def kernels():
-    """{kernel symbol: list of instruction lines and labels} of every GEMM kernel in SOURCES"""
+def listings():
+    """{kernel symbol: its assembly} of every GEMM kernel in SOURCES"""
     out = {}
     with tempfile.TemporaryDirectory() as tmp:
         procs = []
@@ -53,17 +56,26 @@ def kernels():
                 m = re.match(r"(\S+):", part)
                 if not m or "gemm" not in m.group(1) or "prepack" in m.group(1):
                     continue
-                lines = []
-                for line in part.split("\n")[1:]:
-                    t = line.strip()
-                    if not t or t.startswith(";"):
-                        continue
-                    if re.match(r"\.LBB\d+_\d+:", t):
-                        lines.append(t.split(":")[0] + ":")
-                    elif not t.startswith("."):
-                        lines.append(t.split(";")[0].strip())
-                out[m.group(1)] = lines
+                out[m.group(1)] = part
     assert len(out) >= 10, sorted(out)
+    return out
+
+
+@pytest.fixture(scope="module")
+def kernels(listings):
+    """{kernel symbol: list of instruction lines and labels}"""
+    out = {}
+    for name, part in listings.items():
+        lines = []
+        for line in part.split("\n")[1:]:
+            t = line.strip()
+            if not t or t.startswith(";"):
+                continue
+            if re.match(r"\.LBB\d+_\d+:", t):
+                lines.append(t.split(":")[0] + ":")
+            elif not t.startswith("."):
+                lines.append(t.split(";")[0].strip())
+        out[name] = lines
     return out
 
 
@@ -154,3 +166,20 @@ def test_no_wait_for_all_memory_operations_inside_the_k_loops(kernels):
             assert not bad, f"{name}: {bad[0][:12]}"
         elif bad:
             print(f"{name}: {len(bad)} block(s) with MFMAs and a full vmcnt wait")
+
+
+def test_only_inline_assembly_touches_the_accumulators_of_the_wide_kernels(listings):
+    wide = {name: part for name, part in listings.items() if "w4ax_gemm_wide_kernel" in name}
+    assert len(wide) == 6
+    for name, part in wide.items():
+        inside, seen = False, 0
+        for line in part.split("\n")[1:]:
+            if "#ASMSTART" in line or "#ASMEND" in line:
+                inside = "#ASMSTART" in line
+                continue
+            t = line.split(";")[0].strip()
+            if t.startswith(".") or not re.search(r"accvgpr|\ba\d+\b|\ba\[", t):
+                continue
+            assert inside, f"{name}: {t}"
+            seen += 1
+        assert seen > 256, name
