@@ -62,6 +62,8 @@ def test_random_gemm_cases(seed):
         try:
             y, acc = dvdq.w4ax_gemm(cd, dev(xs), w_native, dev(ws), bits, lay, want_acc=True, **kw)
             y2 = dvdq.w4ax_gemm(cd, dev(xs), w_native, dev(ws), bits, lay, **kw)
+            dvdq.bench_set_gemm_variant(6)
+            y6 = dvdq.w4ax_gemm(cd, dev(xs), w_native, dev(ws), bits, lay, **kw)
             torch.cuda.synchronize()
         finally:
             dvdq.bench_set_gemm_variant(-1)
@@ -72,6 +74,7 @@ def test_random_gemm_cases(seed):
         assert np.array_equal(acc.cpu().numpy().astype(np.int64), acc_ref), label
         check_y(bits_of(y), y_ref, label, bias)
         assert torch.equal(y, y2), label + ": epilogue paths differ"
+        assert torch.equal(y, y6), label + ": 128 x 128 tiles differ"
 
 
 @pytest.mark.parametrize("seed", [21, 22])

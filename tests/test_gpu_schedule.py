@@ -24,7 +24,8 @@ def _library_defaults():
 
 
 TILE = {("int8", 1): (256, 256), ("int8", 2): (128, 256), ("int8", 3): (256, 256), ("int8", 4): (128, 256),
-        ("packed", 4): (256, 256), ("int8", 5): (256, 256), ("fp6", 1): (128, 256), ("fp6", 3): (256, 256)}
+        ("packed", 4): (256, 256), ("int8", 5): (256, 256), ("fp6", 1): (128, 256), ("fp6", 3): (256, 256),
+        ("int8", 6): (128, 128), ("fp6", 6): (128, 128)}
 
 
 def _draws(kind, variant, workgroups, M, N):
@@ -88,7 +89,7 @@ def test_drawn_and_fixed_shares_give_identical_outputs(M, K, N, bits, packed):
             assert torch.equal(_gemm(ops, bits, packed).view(torch.int16), y_fixed.view(torch.int16)), workgroups
 
 
-@pytest.mark.parametrize("variant", [1, 2, 3, 4])
+@pytest.mark.parametrize("variant", [1, 2, 3, 4, 6])
 @pytest.mark.parametrize("packed", [False, True])
 def test_every_tile_variant_agrees_between_the_two_modes(variant, packed):
     M, K, N, bits = 5000, 768, 1536, 4
@@ -160,9 +161,9 @@ def _fp6_gemm(ops, y=None, stream=None):
     return dvdq.w4ax_gemm(c6, xs, w, ws, 4, dvdq.W_NATIVE_FP6, y=y, codes_format=dvdq.CODES_FP6, K=K, stream=stream)
 
 
-@pytest.mark.parametrize("variant", [1, 3])
+@pytest.mark.parametrize("variant", [1, 3, 6])
 def test_fp6_kernel_counters_and_streams(variant):
-    """the FP6 matrix path's kernel draws tiles the same way: both tile variants, many launches in a row on
+    """the FP6 matrix path's kernel draws tiles the same way: each tile variant, many launches in a row on
     one stream and launches on several streams at once, against fixed shares"""
     a = _fp6_operands(4100, 512, 2056, seed=3)     # 17 x 9 tiles of 256 x 256 (33 x 9 of 128 x 256), ragged
     b = _fp6_operands(1300, 256, 520, seed=4)
@@ -264,7 +265,7 @@ def test_a_released_stream_can_be_used_again():
             dvdq.release_stream(s)   # unknown by now: no-op
 
 
-@pytest.mark.parametrize("fmt,variant", [("int8", 5), ("fp6", 3), ("fp6", 1)])
+@pytest.mark.parametrize("fmt,variant", [("int8", 5), ("fp6", 3), ("fp6", 1), ("int8", 6), ("fp6", 6)])
 @pytest.mark.parametrize("N", [2048, 2056, 2088]) 
 def test_the_layers_quantizer_clears_the_counters_its_gemm_draws_from(fmt, variant, N):
     """Both kinds: the wide kernels' counters lie in one line, the others' a line apart."""
@@ -286,13 +287,13 @@ def test_the_layers_quantizer_clears_the_counters_its_gemm_draws_from(fmt, varia
         assert torch.equal(layer().view(torch.int16), ref.view(torch.int16))
 
 
-@pytest.mark.parametrize("kind,variant", [("int8", 2), ("packed", 2), ("int8", 5), ("fp6", 1), ("fp6", 3)])
+@pytest.mark.parametrize("kind,variant", [("int8", 2), ("packed", 2), ("int8", 5), ("fp6", 1), ("fp6", 3), ("int8", 6), ("packed", 6), ("fp6", 6)])
 @pytest.mark.parametrize("more", [1, 31, 32, 33, 64])
 def test_at_most_two_tiles_per_workgroup(kind, variant, more):
     """64 workgroups with 65 to 128 tiles: none to draw; up to 32 more tiles than workgroups are fixed shares, beyond that the second
     tiles are crosswise.  Whatever the counters hold, in a graph and outside."""
     bm = TILE.get((kind, variant), (128, 256))[0]
-    M, K, N = (64 + more) * bm - 5, 256, 248
+    M, K, N = (64 + more) * bm - 5, 256, 120 if variant == 6 else 248   # (one column of tiles)
     operands = _fp6_operands(M, K, N, seed=more) if kind == "fp6" else _operands(M, K, N, 4, kind == "packed", seed=more)
     gemm = (lambda y=None: _fp6_gemm(operands, y=y)) if kind == "fp6" else (lambda y=None: _gemm(operands, 4, kind == "packed", y=y))
     dvdq.bench_set_gemm_variant(13)   # the small-output kernel

@@ -47,4 +47,25 @@ def test_where_it_is_taken(M, N, slices, variant):
     """One round of 64 x 96 tiles for more than one of 64 x 64, from 18 slices on; canonical weights keep the 64 x 64 tiles."""
     for fmt, layout in ((dvdq.CODES_INT8, dvdq.W_NATIVE), (dvdq.CODES_PACKED4, dvdq.W_NATIVE), (dvdq.CODES_FP6, dvdq.W_NATIVE_FP6)):
         assert dvdq.bench_gemm_choice(M, N, 128 * slices, fmt, layout) == variant
-    assert dvdq.bench_gemm_choice(M, N, 128 * slices, dvdq.CODES_INT8, dvdq.W_CANONICAL) in (11, 12, 13)
+    assert dvdq.bench_gemm_choice(M, N, 128 * slices, dvdq.CODES_INT8, dvdq.W_CANONICAL) == 13
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", [(512, 2304, 3072), (256, 2336, 4160)])
+def test_canonical_weights_where_others_take_it(M, K, N):
+    """The library's choice against the shape with 64 x 64 tiles and the shape with 64 x 128, which 17 stands for with canonical weights."""
+    assert dvdq.bench_gemm_choice(M, N, 2304, dvdq.CODES_INT8, dvdq.W_NATIVE) == 17
+    g = torch.Generator(device="cuda").manual_seed(N)
+    x = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
+    packed = torch.randint(0, 256, (N, K // 2), generator=g, device="cuda", dtype=torch.uint8)
+    ws = torch.rand((N,), generator=g, device="cuda") + 0.5
+    codes, scale = dvdq.rotate_quant(x, 32, 8)[:2]
+    out = []
+    try:
+        for variant in (-1, 13, 17):
+            dvdq.bench_set_gemm_variant(variant)
+            out.append(dvdq.w4ax_gemm(codes, scale, packed, ws, 8, dvdq.W_CANONICAL, want_acc=True, K=K))
+    finally:
+        dvdq.bench_set_gemm_variant(-1)
+    for y, acc in out[1:]:
+        assert torch.equal(acc, out[0][1]) and torch.equal(y.view(torch.int16), out[0][0].view(torch.int16))

@@ -163,6 +163,33 @@ def test_wide_kernel_with_few_workgroups_walking_many_tiles(K, fp6):
     dvdq.bench_set_gemm_grid_limit(0)
 
 
+@pytest.mark.parametrize("fp6", [False, True])
+@pytest.mark.parametrize("K,N", [(128, 1160), (256, 1152), (384, 1160), (384, 1152), (384, 1190), (640, 1160), (1536, 1152)])
+def test_zero_points_with_few_workgroups_walking_many_tiles(K, N, fp6):
+    """As above with zero-points: tiles staged before they are converted, 8 KB a wave, in the buffer that the next tile's loads go to
+    next or, its code half, are landing in (FP6 from three slices on, K = 384 with the two sets of vectors in closest turn); draws published
+    within the first chunks.  Rows of a multiple of 64 and of 16 bytes and, FP6, at any even address."""
+    M = 5000
+    c = _case(M, K, N, 4, 900 + K + N, fp6)
+    wide, two_wave = (WIDE_FP6, 1) if fp6 else (WIDE_INT8, 2)
+    rows = np.r_[0:8, 2556:2564, M - 8:M]
+    want = oracle.int_gemm(c["codes"][rows], c["wc"]) - c["codes"][rows].astype(np.int64).sum(axis=1)[:, None] * c["wz"].cpu().numpy().astype(np.int64)[None, :]
+    guard = 1 << 16
+    for extra in (dict(w_zero=c["wz"], code_rowsum=c["rs"]), dict(bias=c["bias"], w_zero=c["wz"], code_rowsum=c["rs"])):
+        dvdq.bench_set_gemm_grid_limit(0)
+        y_ref, acc = _run(c, two_wave, want_acc=True, **extra)
+        assert np.array_equal(acc.cpu().numpy()[rows].astype(np.int64), want)
+        for limit in (8, 24):
+            dvdq.bench_set_gemm_grid_limit(limit)
+            for schedule in (0, -1):
+                print(f"wide zero-points K{K} N{N} fp6={fp6} workgroups {limit} schedule {schedule}", flush=True)
+                buf = torch.full((M * N + 2 * guard,), 0x5A5A, dtype=torch.int16, device=DEV)
+                y = buf[guard:guard + M * N].view(M, N).view(torch.bfloat16)
+                _run(c, wide, schedule, y=y, **extra)
+                assert torch.equal(y.view(torch.int16), y_ref.view(torch.int16)), (limit, schedule, sorted(extra))
+                assert bool((buf[:guard] == 0x5A5A).all()) and bool((buf[guard + M * N:] == 0x5A5A).all())
+
+
 @pytest.mark.parametrize("K", [640, 768])
 def test_default_dispatch_around_the_fp6_wide_kernel_threshold(K):
     """512 tiles of 256 x 256 (two rounds of them on the chip): below six K slices the library takes the two-wave FP6
