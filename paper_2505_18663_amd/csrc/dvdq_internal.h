@@ -45,13 +45,14 @@ bool drawing_enabled();                 // the benchmark hook
 // waves of the row quantizer that are resident on a compute unit (rotate_quant.hip)
 int quantizer_waves(int64_t M, int64_t K, int codes_format);
 // The tiles of the two-wave kernels: 128 x 128, three workgroups per compute unit (true), or 128 x 256, two (false).  The larger tile
-// moves a quarter fewer operand bytes per product and has a round of 512 tiles done in some 26 us where 768 small ones take 21 (12 slices,
+// moves a third fewer operand bytes per product with int8 codes, a quarter fewer with packed and FP6 ones, and has a round of 512 tiles done in some 26 us where 768 small ones take 21 (12 slices,
 // bias and zero-points): 7 % less per output.  What decides is the last round, in which compute units hold one large tile or two, one
 // small tile, two or three, at 14, 26 and 9, 14.5, 21 us.  So: small tiles unless they take a round more.  Over 5450 outputs of 100 to
 // 2500 large tiles that these kernels take (int8, packed and FP6 codes, 2 to 48 slices, drawn and captured) small tiles have 0.84 to 0.87 of the
 // time there in the mean, at most 1.10: below one round 0.67 to 0.88 (7800 x 1536 x 1440 int8 23.8 -> 21.9 us, packed 23.1 -> 20.0, 90678 x 896
 // x 640 75.1 -> 63.0, FP6 2048 x 768 x 3072 10.6 -> 8.9, canonical 6200 x 1440 x 1440 24.2 -> 22.4), from 1.02 rounds on 0.75 to 0.96.  Where they
-// take a round more: 0.86 to 1.13.  Not in a last round that is at most half full of large tiles and more than two thirds full of
+// take a round more: 0.86 to 1.13 there, two for one 1.04 to 1.2 (FP6 1.06 to 1.4), three for two 0.98 to 1.05 (FP6 1.05 to 1.17), from four for three on
+// below six slices 0.91 to 0.95, six to eleven 0.94 to 1.00, beyond 0.97 to 1.07 (drawn; the GEMM alone); the line does not follow these.  Not in a last round that is at most half full of large tiles and more than two thirds full of
 // small ones, from 20 slices on in the second round (1.01 to 1.04 there, int8 to canonical, up to 1.10; 0.90 to 0.99 with fewer slices) and
 // from 48 on later (20912 x 13568 x 1664 int8 571 and 583 us; 0.88 to 1.00 with fewer).
 // Canonical weights, half a cache line of a weight row per slice, have less to gain and lose more by code rows that are read again for each

@@ -402,8 +402,8 @@ int launch_fp6(const uint8_t *codes, const float *x_scale, const uint8_t *w, con
 //                (0.99) / 0.96 (1.00) / 0.97 (1.02) / 0.99 (1.06)
 //                (cached stores, N no multiple of 32, 0.93 at 6 to 11 slices whatever the vectors, at most 1.03)
 //   from 1537    6 to 9 slices 0.99 to 1.07, later up to 1.18
-// (With zero-points the wide kernel's time has since gone down by 8 % at 12 slices, 4 % at 24; and variant 1 stands for variant 6 as well, which
-// narrow_tiles takes where it is faster: the lines have stayed between them.)  (6240 x 768 x 1024, 100 tiles: 11.5 and 13.7 us; 2816 x 2176 x 2560 without vectors, 110: 19.1 and 16.3.)  More than half full: 1.00 to 1.03
+// (These are times from before variant 6, which narrow_tiles takes in the place of variant 1, and from before the wide kernel transposed tiles with
+// zero-points first, 8 % off its time at 12 slices, 4 % at 24: neither has been drawn into the lines.)  (6240 x 768 x 1024, 100 tiles: 11.5 and 13.7 us; 2816 x 2176 x 2560 without vectors, 110: 19.1 and 16.3.)  More than half full: 1.00 to 1.03
 // at 6 slices, 1.06 to 1.10 at 12.  (One 8-wave workgroup with 256 x 256 tiles, three buffers, lay behind
 // one of these at nearly every K from 256 to 640, 3 % ahead at best in the mean of a shape.)
 // Outputs with N no multiple of 8, in 16-byte pieces at even addresses, take it from 48 slices on without bias and zero-points,

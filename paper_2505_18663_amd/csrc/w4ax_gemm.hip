@@ -700,6 +700,10 @@ int limited_grid(int grid) {
 //     1.08-1.12 at 516 to 640, 0.95-0.99 at 672 to 768, 1.04-1.10 at 1026 to 1400, 1.02-1.07 at 2064 to 2172, 1.01-1.05 at 3100 to 3200.
 //     One column of tiles: 1.02 to 1.14 up to two fifths of a round; the line stays there, and below four rounds, as
 //     tests/test_dispatch.py states it.
+// The lines between 2 and 5 are from before variant 2 had 128 x 128 tiles (narrow_tiles).  Where variant 5 is
+// taken and those take no more rounds of 768 than it of 256, they have 0.91 of its time in the mean of 383 outputs of one round (1.03 at most), 0.89 of 59 of two
+// (1.01), 0.91 of 25 of three (the GEMM alone, drawn, 8 to 47 slices, with the wide kernel of before it transposed tiles with zero-points first, which
+// takes 1 to 2 % off): a line there would pay (25805 x 2560 x 320: 37.1 and 30.8 us).
 int w4ax_gemm_choice(int64_t M, int64_t N, int64_t K, int codes_format, int w_layout, int vectors, bool drawn) {
     const int shape = small_gemm_shape(M, N, K, false);
     if (w_layout == DVDQ_W_CANONICAL && shape < 0) {

@@ -316,8 +316,9 @@ __global__ __launch_bounds__(64 * NW, DEPTH == 2 ? 1 : 2) void w4ax_gemm_small_k
         const int a_off = LAYER ? 0 : kt * (FP6 ? kFp6Block : A_ROW);
         const __amdgpu_buffer_rsrc_t ra = buffer(a_tile + (ok ? a_off : 0), ok ? a_bytes - a_off : 0);   // (LAYER: unused)
         const int64_t w_off = CANONICAL ? kt * (kBK / 2) : kt * w_slice_stride;
-        // (G is a multiple of 8: the minimum is TN.  With the constant in its place the same loads come out in another order: 3121 x 1152 x 1160
-        // packed codes 9.7 -> 9.8 us, 512 x 3072 x 3072 int8 10.4 -> 10.6, 300 x 3072 x 3072 7.4 -> 7.2)
+        // (G is a multiple of 8: the minimum is TN but for TN = 3, whose last tile has one or two groups left, and whose reads past them the
+        // descriptor's end turns into zeros.  With the constant in its place, where it is TN, the same loads come out in another order: 3121 x 1152 x
+        // 1160 packed codes 9.7 -> 9.8 us, 512 x 3072 x 3072 int8 10.4 -> 10.6, 300 x 3072 x 3072 7.4 -> 7.2)
         const int w_bytes = CANONICAL ? min(BN, N - n0) * (K / 2) - (int)w_off : min(TN, G - n0 / kGroup) * (FP6 ? kFp6Block : kGroupBytes);
         const __amdgpu_buffer_rsrc_t rw = buffer(w_tile + (ok ? w_off : 0), ok ? w_bytes : 0);
         if constexpr (FP6) {
@@ -526,7 +527,7 @@ __global__ __launch_bounds__(64 * NW, DEPTH == 2 ? 1 : 2) void w4ax_gemm_small_k
         // (unrolled, so that the reads of a thread's pieces run beside each other: 2800 of the kernel's 16500 clocks went to these sums at
         // 300 x 3072 x 3072; 512 x 3072 x 3072 int8 11.6 -> 10.5 us, 512 x 1536 x 3072 8.6 -> 7.4.  With more than two pieces a thread, what is not there --
         // zero-points, bias -- is chosen once: a branch in each piece keeps the reads apart (1560 x 1536 x 1536 packed 10.0 -> 9.4, 3121 x 1152 x
-        // 1160 10.3 -> 9.8).  With two at most, with canonical weights and with FP6 codes it is branched around: there the copies of the code
+        // 1160 10.3 -> 9.8 the GEMM; 2300 whole layers 0.98 of their time in the mean, with zero-points 0.97 to 0.99, without 0.98 to 1.00).  With two at most, with canonical weights and with FP6 codes it is branched around: there the copies of the code
         // cost up to 4 %: 700 x 1536 x 2304 int8 8.4 and 8.7)
         constexpr int ITEMS = (BM * PIECES + 64 * NW - 1) / (64 * NW);
         constexpr bool SAME_CHANNELS = 64 * NW % PIECES == 0;   // of all of a thread's pieces

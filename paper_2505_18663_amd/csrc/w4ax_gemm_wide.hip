@@ -750,7 +750,8 @@ __global__ __launch_bounds__(256, 1) void w4ax_gemm_wide_kernel(
                     float o[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        // sum q (c - z) = acc - z * rs: exact in a 24-bit multiply and in an fp32 fma alike (ranges: C ABI)
+                        // sum q (c - z) = acc - z * rs: exact in 32-bit integers (ranges: C ABI); the fp32 fma rounds once, as the conversion of
+                        // the integer does (the sum may need 25 bits), so both have the bits of the per-element path
                         float v;
                         if constexpr (FP6) v = __builtin_fmaf(nz_f[h * 4 + e], rs_f[j][pass], __int_as_float(r[e]));
                         else v = (float)(r[e] + __mul24(nz_i[h * 4 + e], rs_i[j][pass]));
